@@ -656,7 +656,7 @@ static const char* const kKernelNames[KID_COUNT] = {
     "transpose_w", "encode_bf16", "encode_f32", "gather_rows", "slot_count", "slot_emit", "seg_reduce",
     "seg_combine", "wgrad_bf16", "wgrad_f32", "wgrad_reduce", "flush_meta",
     "flush_rows", "unique_small", "gather_heavy", "pseudo_target", "pseudo_loss", "chunk_ids",
-    "pseudo_miss", "mlp_to_bf16", "encode_bf16_wide", "wgrad_bf16_wide"};
+    "pseudo_miss", "mlp_to_bf16", "encode_bf16_wide", "wgrad_bf16_wide", "rank_small"};
 
 int gram_kernel_count(void) { return KID_COUNT; }
 

@@ -68,7 +68,7 @@ enum KernelId {
     KID_SLOT_COUNT, KID_SLOT_EMIT, KID_SEG_REDUCE, KID_SEG_COMBINE, KID_WGRAD_BF16, KID_WGRAD_F32,
     KID_WGRAD_REDUCE, KID_FLUSH_META, KID_FLUSH_ROWS, KID_UNIQUE_SMALL,
     KID_GATHER_HEAVY, KID_PSEUDO_TARGET, KID_PSEUDO_LOSS, KID_CHUNK_IDS, KID_PSEUDO_MISS, KID_MLP_TO_BF16,
-    KID_ENCODE_BF16_WIDE, KID_WGRAD_BF16_WIDE, KID_COUNT
+    KID_ENCODE_BF16_WIDE, KID_WGRAD_BF16_WIDE, KID_RANK_SMALL, KID_COUNT
 };
 
 static_assert(KID_COUNT <= 64, "the profiling mask has 64 bits");
@@ -206,7 +206,7 @@ int radix_sort_pairs(Ctx* c, const int* keys_in, const int* vals_in, int n_host,
                      int64_t n_max, bool check_range, int fix_key, hipStream_t s);
 void unique_from_sorted(Ctx* c, int n, int* uniq, int* inverse, int* counts, int* u_out, hipStream_t s,
                         bool prospect = false, int first_step = 0);
-// One-launch dedup for small batches; returns false if n is too large for it.
+// Dedup of small batches in one or two launches; returns false if n is too large for it.
 bool unique_small(Ctx* c, const int* ids, int n, int fix_key, int* uniq, int* inverse, int* counts,
                   int* u_out, hipStream_t s, bool prospect = false, int first_step = 0);
 

@@ -7,7 +7,7 @@
 // compaction.  Each 64-lane wave owns a contiguous chunk of keys; ranks inside
 // a wave come from ballot-based digit matching, ranks across blocks from a
 // per-block digit table that one wave per digit prefix-sums.  Small batches
-// take a one-launch variant that keeps everything in LDS (k_unique_small).
+// are ranked by counting comparisons instead (k_rank_small).
 // All counters are integer (LDS atomics are order independent), so the result
 // is exact.
 #include "gram_internal.h"
@@ -19,7 +19,6 @@ namespace gram {
 // space is compiled to flat, system-coherent accesses, each followed by a wait for every
 // outstanding memory operation of the wave (its scattered global stores included).
 typedef __attribute__((address_space(3))) int lds_i32;
-typedef __attribute__((address_space(3))) unsigned long long lds_u64;
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 __device__ __forceinline__ int wave_id() { return threadIdx.x >> 6; }
@@ -513,35 +512,32 @@ __global__ void k_unique_empty(int* u_ws, int* u_out, int* offsets)
     }
 }
 
-// ---- small batches: the whole dedup in one block ------------------------------------
+// ---- small batches: ranks by comparison ----------------------------------------------
 //
-// Up to kSmallMaxN positions: keys and positions live in LDS, the radix passes
-// (8-bit digits, 16 waves), the head-flag scan and the compaction all run in one launch
-// of 1024 threads.  A step of the paper-shaped KT and news batches moves a few
-// microseconds of HBM traffic, so its cost is the number of launches - and, inside this
-// one block, the number of instructions its 16 waves issue on one CU:
-//  * the lanes of a wave that hold the same digit find each other through a per-wave table
-//    of 64-bit lane masks in LDS (one atomic OR and one read per round; the first lane of a
-//    group clears the entry again) instead of one ballot per digit bit;
-//  * positions are 16-bit, which makes room for that table;
-//  * `inverse` is assembled in LDS and written in position order, because a CU retires
-//    scattered 4-byte stores at about one lane per clock.
+// Up to kSmallMaxN positions (12,000: 28 us against 32 to 35 us for the radix sort; 16,384: 34 against 32 to
+// 36).  The sorted place of a position is the number of positions whose
+// (id, position) pair is smaller, and that number is counted outright: every position against every
+// other, two VALU instructions per pair.  n^2 comparisons spread over the whole chip are cheaper at
+// these sizes than sorting on one CU (a radix sort in the LDS of one block: 21 us at n = 6,400 with 14
+// key bits, 28 us at n = 7,040 with 17; here 14.7 us for both) and than a radix sort over many blocks (8
+// launches, about 36 us).  What bounds k_rank_small is the VALU: 4.7 of its 10 us at n = 6,400 are
+// comparisons, the rest is the launch and the loads of the IDs.  Two launches:
+//   k_rank_small  kRankP positions per block, 1024 threads: thread (p, slice) compares position p
+//                 with the 16-byte groups slice, slice + S, ... of all IDs, which the block holds in
+//                 LDS; the counts of the slices are added and (id, position) goes to its place;
+//   k_emit_small  head flags of the sorted IDs, their scan, and everything that is known per
+//                 position and per unique item; every block works out the flags of all rows and
+//                 writes its own 1024 rows and items.
+// Batches of at most kFusedMaxN positions do both in one block and one launch (3.9 us at n = 64, where the
+// LDS radix sort took 7.3; at 512 the two launches take as long as the one).
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallWaves = kSmallThreads / kWave;
-constexpr int kSmallMaxN = 8192;
-constexpr int kSmallBits = 8;
-constexpr int kSmallBins = 1 << kSmallBits;
-constexpr int kSmallRounds = kSmallMaxN / kSmallWaves / kWave;   // rounds of 64 keys per wave, at most
-// LDS, in ints: keys x2 | positions x2 (16-bit) | per-wave digit counts | per-wave peer masks (64-bit) | wave sums
-constexpr int kSmallOffV = 2 * kSmallMaxN;
-constexpr int kSmallOffCnt = kSmallOffV + kSmallMaxN;
-constexpr int kSmallOffPeer = kSmallOffCnt + kSmallWaves * kSmallBins;
-constexpr int kSmallOffSum = kSmallOffPeer + 2 * kSmallWaves * kSmallBins;
-constexpr size_t kSmallLds = (size_t)(kSmallOffSum + 2 * kSmallWaves) * sizeof(int);
-static_assert(2 * kSmallWaves * kSmallBins >= kSmallMaxN, "the peer table doubles as the segment-start list");
+constexpr int kSmallMaxN = 12288;
+constexpr int kFusedMaxN = 512;
+constexpr int kRankP = 32;
 
 // Exclusive scan of one value per thread over the 1024-thread block.
-__device__ __forceinline__ int block1024_excl_scan(int v, int* total, int* wsum /*[2*kSmallWaves]*/)
+__device__ __forceinline__ int block1024_excl_scan(int v, int* total, int* wsum /*[kSmallWaves]*/)
 {
     const int incl = wave_incl_scan(v);
     if (lane_id() == kWave - 1) wsum[wave_id()] = incl;
@@ -558,233 +554,202 @@ __device__ __forceinline__ int block1024_excl_scan(int v, int* total, int* wsum 
     return base + incl - v;
 }
 
-__global__ __launch_bounds__(kSmallThreads) void k_unique_small(
-    const int* __restrict__ ids, int n, int key_bits, int vocab_n, int fix_key, int* __restrict__ err,
-    int* __restrict__ sorted_keys, int* __restrict__ perm, int* __restrict__ uniq,
+// IDs of the batch into LDS (checked; a multiple of 4 entries, the rest larger than any ID).
+__device__ __forceinline__ void load_small_ids(const int* __restrict__ ids, int n, int vocab_n, int fix_key,
+                                               int* __restrict__ err, bool report, int* keys)
+{
+    const int n4 = (n + 3) & ~3;
+    bool bad = false;
+    for (int i0 = 0; i0 < n4; i0 += 8 * kSmallThreads) {
+        int k[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int i = i0 + u * kSmallThreads + threadIdx.x;
+            k[u] = i < n ? ids[i] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int i = i0 + u * kSmallThreads + threadIdx.x;
+            if (i >= n4) break;
+            if (i >= n) k[u] = 0x7fffffff;
+            else if (k[u] < 0 || k[u] >= vocab_n) { bad = true; k[u] = fix_key; }
+            keys[i] = k[u];
+        }
+    }
+    if (report && bad) atomicOr(err, kErrBitRange);
+}
+
+// Rank of position p0 + (tid % P) of the n keys in LDS, P = 1 << log2p positions per block; valid in
+// threads tid < P.  red: kSmallThreads ints of LDS.  Contains barriers.
+__device__ __forceinline__ int rank_by_comparison(const int* keys, int n, int p0, int log2p, int* red)
+{
+    const int tid = threadIdx.x, P = 1 << log2p, S = kSmallThreads >> log2p;
+    const int p = p0 + (tid & (P - 1)), slice = tid >> log2p;
+    const int groups = (n + 3) >> 2, own = p >> 2;
+    const int key = keys[p < n ? p : n - 1];
+    const int4* k4 = reinterpret_cast<const int4*>(keys);
+    int cnt = 0;
+    // an equal ID counts if its position is smaller: groups before the position's own are compared
+    // with key + 1 (IDs are below 2^31 - 1), later ones with key
+#pragma unroll 4
+    for (int g = slice; g < groups; g += S) {
+        const int4 q = k4[g];
+        const int t = key + (g < own ? 1 : 0);
+        cnt += (q.x < t ? 1 : 0) + (q.y < t ? 1 : 0) + (q.z < t ? 1 : 0) + (q.w < t ? 1 : 0);
+    }
+    red[tid] = cnt;
+    __syncthreads();
+    int rank = 0;
+    if (tid < P) {
+#pragma unroll 8
+        for (int s = 0; s < S; ++s) rank += red[(s << log2p) + tid];
+        for (int q = own << 2; q < p && q < n; ++q) rank += keys[q] == key ? 1 : 0;
+    }
+    return rank;
+}
+
+__global__ __launch_bounds__(kSmallThreads) void k_rank_small(const int* __restrict__ ids, int n, int vocab_n,
+                                                              int fix_key, int* __restrict__ err,
+                                                              int* __restrict__ sorted_keys, int* __restrict__ perm)
+{
+    extern __shared__ __attribute__((aligned(16))) int lds[];
+    __shared__ int red[kSmallThreads];
+    constexpr int kLog2P = 5;
+    static_assert(1 << kLog2P == kRankP, "positions per block");
+    load_small_ids(ids, n, vocab_n, fix_key, err, blockIdx.x == 0, lds);
+    __syncthreads();
+    const int p0 = blockIdx.x * kRankP;
+    const int rank = rank_by_comparison(lds, n, p0, kLog2P, red);
+    const int p = p0 + (int)threadIdx.x;
+    if ((int)threadIdx.x < kRankP && p < n && (unsigned)rank < (unsigned)n) {   // rank < n always holds;
+        sorted_keys[rank] = lds[p];                                             // the test keeps a logic error
+        perm[rank] = p;                                                         // from becoming a stray store
+    }
+}
+
+// R sorted rows per thread (n <= 1024 R).  FUSED: the ranks are worked out here too (one block).
+template <int R, bool FUSED>
+__global__ __launch_bounds__(kSmallThreads) void k_emit_small(
+    const int* __restrict__ ids, int n, int log2p, int vocab_n, int fix_key, int* __restrict__ err,
+    const int* __restrict__ sorted_keys, int* __restrict__ perm, int* __restrict__ uniq,
     int* __restrict__ inverse, int* __restrict__ counts, int* __restrict__ offsets,
     int* __restrict__ seg_of_row, int* __restrict__ uniq_ws, int* __restrict__ u_ws,
     int* __restrict__ u_out, const int* __restrict__ slot_of, int* __restrict__ seg_slot,
     int* __restrict__ scal, int first_step, int cap_total)
 {
-    extern __shared__ __attribute__((aligned(16))) int lds[];
-    // keys of order `o` at KBUF(o), positions at VBUF(o)
-#define KBUF(o) (lds + (o) * kSmallMaxN)
-#define VBUF(o) (reinterpret_cast<uint16_t*>(lds + kSmallOffV) + (o) * kSmallMaxN)
-    int* cnt_all = lds + kSmallOffCnt;                   // [kSmallWaves][kSmallBins]
-    unsigned long long* peer_all = reinterpret_cast<unsigned long long*>(lds + kSmallOffPeer);
-    int* wsum = lds + kSmallOffSum;
-    const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
-
-    bool bad = false;
-    for (int i = tid; i < n; i += kSmallThreads) {
-        int k = ids[i];
-        if (k < 0 || k >= vocab_n) { bad = true; k = fix_key; }
-        KBUF(0)[i] = k;
-        VBUF(0)[i] = (uint16_t)i;
+    constexpr int NR = kSmallThreads * R;
+    // sorted IDs | segment of every row (16-bit) | first row of every segment (16-bit)
+    extern __shared__ __attribute__((aligned(16))) int sk[];
+    __shared__ int wsum[kSmallWaves];
+    uint16_t* lseg = reinterpret_cast<uint16_t*>(sk + NR);
+    uint16_t* loff = lseg + NR;
+    const int tid = threadIdx.x;
+    const int r0 = tid * R;
+    const int row = blockIdx.x * kSmallThreads + tid;       // the row and the item this thread writes
+    int key[R], posn = 0;
+    if constexpr (FUSED) {
+        static_assert(R == 1, "one row per thread");
+        __shared__ __attribute__((aligned(16))) int kin[kFusedMaxN];
+        __shared__ int red[kSmallThreads], pos_of[kFusedMaxN];
+        load_small_ids(ids, n, vocab_n, fix_key, err, true, kin);
+        __syncthreads();
+        const int rank = rank_by_comparison(kin, n, 0, log2p, red);
+        if (tid < n && (unsigned)rank < (unsigned)n) {
+            sk[rank] = kin[tid];
+            pos_of[rank] = tid;
+        }
+        __syncthreads();
+        key[0] = tid < n ? sk[tid] : 0;
+        if (tid < n) {
+            posn = pos_of[tid];
+            perm[tid] = posn;
+        }
+    } else {
+        if (r0 + R <= n) {
+#pragma unroll
+            for (int i = 0; i < R / 4; ++i) {
+                const int4 k = *reinterpret_cast<const int4*>(sorted_keys + r0 + 4 * i);
+                key[4 * i] = k.x; key[4 * i + 1] = k.y; key[4 * i + 2] = k.z; key[4 * i + 3] = k.w;
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < R; ++i) key[i] = r0 + i < n ? sorted_keys[r0 + i] : 0;
+        }
+        if (row < n) posn = perm[row];
+#pragma unroll
+        for (int i = 0; i < R / 4; ++i)
+            *reinterpret_cast<int4*>(sk + r0 + 4 * i) = make_int4(key[4 * i], key[4 * i + 1], key[4 * i + 2], key[4 * i + 3]);
+        __syncthreads();
     }
-    if (bad) atomicOr(err, kErrBitRange);
-    for (int b = tid; b < kSmallWaves * kSmallBins; b += kSmallThreads) peer_all[b] = 0ull;
-    __syncthreads();
-
-    // wave w owns the contiguous chunk [w * cw, (w + 1) * cw) of the current order
-    const int cw = ((n + kSmallWaves - 1) / kSmallWaves + kWave - 1) / kWave * kWave;
-    const int cbeg = wave * cw;
-    const int cend = cbeg + cw < n ? cbeg + cw : n;
-    volatile lds_i32* cnt = (volatile lds_i32*)(cnt_all + wave * kSmallBins);
-    volatile lds_u64* peer = (volatile lds_u64*)(peer_all + wave * kSmallBins);
-    const unsigned long long lt_mask = (1ull << lane) - 1ull;
-    int cur = 0;
-    for (int shift = 0; shift < key_bits; shift += kSmallBits) {
-        for (int b = lane; b < kSmallBins; b += kWave) cnt[b] = 0;
-        __syncthreads();
-        // the keys (and, for the second walk, positions) of all of the wave's rounds are read from
-        // LDS up front: a round is a chain of dependent LDS operations, and the reads of the next
-        // round would otherwise wait behind it
-        int kr[kSmallRounds];
-#pragma unroll
-        for (int r = 0; r < kSmallRounds; ++r) {
-            const int i = cbeg + r * kWave + lane;
-            kr[r] = i < cend ? KBUF(cur)[i] : 0;
-        }
-#pragma unroll
-        for (int r = 0; r < kSmallRounds; ++r) {
-            if (cbeg + r * kWave >= cend) break;             // wave-uniform
-            const bool valid = cbeg + r * kWave + lane < cend;
-            const int dg = valid ? (kr[r] >> shift) & (kSmallBins - 1) : -1;
-            // the digit of the round's first key is counted once for all lanes that hold it:
-            // padding and very popular items would otherwise pile up on one LDS counter
-            const int d0 = __builtin_amdgcn_readfirstlane(dg);
-            const unsigned long long m0 = __ballot(dg == d0);
-            if (lane == 0) atomicAdd(&cnt_all[wave * kSmallBins + d0], (int)__popcll(m0));
-            else if (valid && dg != d0) atomicAdd(&cnt_all[wave * kSmallBins + dg], 1);
-        }
-        __syncthreads();
-        {   // exclusive scan in (digit, wave) order; thread t owns digit t / 4, waves 4 (t % 4) .. + 3
-            const int dg = tid >> 2, w0 = (tid & 3) * 4;
-            int v[4], sum = 0;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                v[i] = cnt_all[(w0 + i) * kSmallBins + dg];
-                sum += v[i];
-            }
-            int total;
-            int run = block1024_excl_scan(sum, &total, wsum);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                cnt_all[(w0 + i) * kSmallBins + dg] = run;
-                run += v[i];
-            }
-        }
-        __syncthreads();
-        int vr[kSmallRounds];
-#pragma unroll
-        for (int r = 0; r < kSmallRounds; ++r) {
-            const int i = cbeg + r * kWave + lane;
-            vr[r] = i < cend ? VBUF(cur)[i] : 0;
-        }
-#pragma unroll
-        for (int r = 0; r < kSmallRounds; ++r) {
-            if (cbeg + r * kWave >= cend) break;             // wave-uniform
-            const bool valid = cbeg + r * kWave + lane < cend;
-            const int k = kr[r];
-            const int v = vr[r];
-            const int dg = (k >> shift) & (kSmallBins - 1);
-            // Lanes holding the digit of the round's first key know their group from one ballot
-            // (padding and very popular items fill most of a round); the others meet through the
-            // mask table.  LDS operations of one wave execute in program order: every lane's OR
-            // lands before the reads below, and every lane has read before a group's first lane
-            // writes.
-            const int d0 = __builtin_amdgcn_readfirstlane(dg);
-            const unsigned long long m0 = __ballot(valid && dg == d0);
-            const bool in0 = valid && dg == d0;
-            if (valid && !in0) atomicOr(&peer_all[wave * kSmallBins + dg], 1ull << lane);
-            __builtin_amdgcn_wave_barrier();
-            unsigned long long peers = 0ull;
-            int pos = 0;
-            if (valid) {
-                peers = in0 ? m0 : peer[dg];
-                pos = cnt[dg];
-            }
-            const int below = __popcll(peers & lt_mask);
-            pos += below;
-            __builtin_amdgcn_wave_barrier();
-            if (valid && below == 0) {
-                cnt[dg] = pos + __popcll(peers);
-                if (!in0) peer[dg] = 0ull;
-            }
-            __builtin_amdgcn_wave_barrier();
-            if (valid && (unsigned)pos < (unsigned)n) {
-                KBUF(cur ^ 1)[pos] = k;
-                VBUF(cur ^ 1)[pos] = (uint16_t)v;
-            }
-        }
-        __syncthreads();
-        cur ^= 1;
-    }
-
-    // head flags and their scan: thread t owns the 8 sorted rows 8 t .. 8 t + 7 and leaves each
-    // row's segment index in LDS; the outputs are then written with consecutive threads on
-    // consecutive rows / positions, so that the stores of a wave coalesce
-    const int* sk = KBUF(cur);
-    const uint16_t* sv = VBUF(cur);
-    int* lseg = KBUF(cur ^ 1);                               // free after the last pass: segment of every sorted row
-    int* loff = reinterpret_cast<int*>(peer_all);            // first sorted row of every segment
-    uint16_t* linv = VBUF(cur ^ 1);                          // segment of every position
-    const int r0 = tid * 8;
-    // the thread's 8 keys and positions as 16-byte LDS reads (rows 8 t .. 8 t + 7 one by one
-    // would hit the same banks in every lane)
-    int key[8];
-    uint16_t posn[8];
-    {
-        const int4 k0 = *reinterpret_cast<const int4*>(sk + r0);
-        const int4 k1 = *reinterpret_cast<const int4*>(sk + r0 + 4);
-        key[0] = k0.x; key[1] = k0.y; key[2] = k0.z; key[3] = k0.w;
-        key[4] = k1.x; key[5] = k1.y; key[6] = k1.z; key[7] = k1.w;
-        const uint4 p4 = *reinterpret_cast<const uint4*>(sv + r0);
-        posn[0] = (uint16_t)p4.x; posn[1] = (uint16_t)(p4.x >> 16); posn[2] = (uint16_t)p4.y; posn[3] = (uint16_t)(p4.y >> 16);
-        posn[4] = (uint16_t)p4.z; posn[5] = (uint16_t)(p4.z >> 16); posn[6] = (uint16_t)p4.w; posn[7] = (uint16_t)(p4.w >> 16);
-    }
+    const int u_base = (slot_of && !first_step) ? scal[kSUTotal] : 0;    // a flush leaves the old count behind
     const int prev = r0 > 0 && r0 < n ? sk[r0 - 1] : -1;
-    bool f[8];
+    bool f[R];
     int sum = 0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < R; ++i) {
         const int r = r0 + i;
         f[i] = r < n && (r == 0 || key[i] != (i ? key[i - 1] : prev));
         sum += f[i] ? 1 : 0;
     }
     int total;
     int run = block1024_excl_scan(sum, &total, wsum);
-    int seg8[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int r = r0 + i;
+    for (int i = 0; i < R; ++i) {
         run += f[i] ? 1 : 0;
-        seg8[i] = run - 1;
-        if (r < n) {
-            linv[posn[i]] = (uint16_t)(run - 1);
-            if (f[i]) loff[run - 1] = r;
-        }
+        lseg[r0 + i] = (uint16_t)(run - 1);
+        if (f[i]) loff[run - 1] = (uint16_t)(r0 + i);
     }
-    if (r0 < n) {       // rows past n inside the last thread's 8 are never read back
-        *reinterpret_cast<int4*>(lseg + r0) = make_int4(seg8[0], seg8[1], seg8[2], seg8[3]);
-        *reinterpret_cast<int4*>(lseg + r0 + 4) = make_int4(seg8[4], seg8[5], seg8[6], seg8[7]);
+    __syncthreads();
+    if (row < n) {
+        const int seg = lseg[row];
+        seg_of_row[row] = seg;
+        inverse[posn] = seg;
     }
-    if (tid == 0) {
+    if (row < total) {
+        const int r = loff[row];
+        const int k = sk[r];
+        uniq[row] = k;
+        uniq_ws[row] = k;
+        offsets[row] = r;
+        counts[row] = (row + 1 < total ? (int)loff[row + 1] : n) - r;
+    }
+    if (blockIdx.x == 0 && tid == 0) {
         *u_ws = total;
         if (u_out) *u_out = total;
         offsets[total] = n;
     }
-    __syncthreads();
-    for (int r = tid; r < n; r += kSmallThreads) {
-        sorted_keys[r] = sk[r];
-        perm[r] = sv[r];
-        seg_of_row[r] = lseg[r];
-        inverse[r] = linv[r];
-    }
-    for (int j = tid; j < total; j += kSmallThreads) {
-        const int r = loff[j];
-        const int key = sk[r];
-        uniq[j] = key;
-        uniq_ws[j] = key;
-        offsets[j] = r;
-        counts[j] = (j + 1 < total ? loff[j + 1] : n) - r;
-    }
-    // the buffer rows the items would get from the next gram_grad_accumulate (see k_heads_emit):
-    // thread t looks up items 8 t .. 8 t + 7, one scan ranks the items new to the window
-    if (slot_of) {
-        const int j0 = tid * 8;
-        int old[8], fresh = 0;
+    // the buffer rows the items would get from the next gram_grad_accumulate (see k_heads_emit).  In
+    // the first step of a window the buffer holds nothing: item j gets row j.  Later thread t looks up
+    // items R t .. R t + R - 1, one scan ranks the items new to the window.
+    if (!slot_of) return;
+    int nt = total;
+    if (first_step) {
+        if (row < total) seg_slot[row] = row < cap_total ? (row | kSlotNew) : -1;
+    } else {
+        int old[R], fresh = 0;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            old[i] = 0;
-            if (j0 + i < total) {
-                // in the first step of a window the buffer holds nothing: every item is new
-                old[i] = first_step ? -1 : slot_of[sk[loff[j0 + i]]];
-                fresh += old[i] < 0 ? 1 : 0;
-            }
-        }
+        for (int i = 0; i < R; ++i) old[i] = r0 + i < total ? slot_of[sk[loff[r0 + i]]] : 0;
+#pragma unroll
+        for (int i = 0; i < R; ++i) fresh += old[i] < 0 ? 1 : 0;
         int total_fresh;
-        const int u_base = first_step ? 0 : scal[kSUTotal];    // a flush leaves the old count behind
         int next_slot = u_base + block1024_excl_scan(fresh, &total_fresh, wsum);
+        nt = u_base + total_fresh;
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-            if (j0 + i < total) {
-                int code = old[i];
-                if (code < 0) {
-                    const int slot = next_slot++;
-                    code = slot < cap_total ? (slot | kSlotNew) : -1;
-                }
-                seg_slot[j0 + i] = code;
+        for (int i = 0; i < R; ++i) {
+            int code = old[i];
+            if (code < 0) {
+                const int slot = next_slot++;
+                code = slot < cap_total ? (slot | kSlotNew) : -1;
             }
-        if (tid == 0) {
-            const int nt = u_base + total_fresh;
-            scal[kSUNext] = nt < cap_total ? nt : cap_total;
-            scal[kSLongCount] = 0;
+            // (each block writes the codes of its own items)
+            if (r0 + i < total && (unsigned)(r0 + i - (int)blockIdx.x * kSmallThreads) < (unsigned)kSmallThreads)
+                seg_slot[r0 + i] = code;
         }
     }
-#undef KBUF
-#undef VBUF
+    if (blockIdx.x == 0 && tid == 0) {
+        scal[kSUNext] = nt < cap_total ? nt : cap_total;
+        scal[kSLongCount] = 0;
+    }
 }
 
 // prospect: also work out the buffer rows the items would get (slot-table contexts only);
@@ -805,17 +770,40 @@ void unique_from_sorted(Ctx* c, int n, int* uniq, int* inverse, int* counts, int
            c->seg_slot, c->scal, first_step, (int)c->cap_total);
 }
 
+template <int R, bool FUSED>
+static void launch_emit_small(Ctx* c, const int* ids, int n, int log2p, int fix_key, int* uniq, int* inverse,
+                              int* counts, int* u_out, hipStream_t s, bool prospect, int first_step)
+{
+    constexpr size_t lds = (size_t)kSmallThreads * R * 8;
+    constexpr auto kern = k_emit_small<R, FUSED>;
+    ensure_dynamic_lds<kern>((int)lds);
+    const unsigned blocks = (unsigned)((n + kSmallThreads - 1) / kSmallThreads);
+    launch_smem(c, KID_UNIQUE_SMALL, kern, dim3(blocks), dim3(kSmallThreads), lds, s, ids, n, log2p, c->cfg.vocab_n,
+                fix_key, c->scal + kSErr, c->sorted_keys, c->perm, uniq, inverse, counts, c->offsets, c->seg_of_row,
+                c->uniq_ws, c->scal + kSU, u_out, prospect ? c->slot_of : nullptr, c->seg_slot, c->scal, first_step,
+                (int)c->cap_total);
+}
+
 bool unique_small(Ctx* c, const int* ids, int n, int fix_key, int* uniq, int* inverse, int* counts,
                   int* u_out, hipStream_t s, bool prospect, int first_step)
 {
     if (n <= 0 || n > kSmallMaxN) return false;
-    ensure_dynamic_lds<k_unique_small>((int)kSmallLds);
     c->sorted_keys = c->keys[0];
     c->perm = c->vals[0];
-    launch_smem(c, KID_UNIQUE_SMALL, k_unique_small, dim3(1), dim3(kSmallThreads), kSmallLds, s, ids, n,
-                c->key_bits, c->cfg.vocab_n, fix_key, c->scal + kSErr, c->sorted_keys, c->perm, uniq, inverse,
-                counts, c->offsets, c->seg_of_row, c->uniq_ws, c->scal + kSU, u_out,
-                prospect ? c->slot_of : nullptr, c->seg_slot, c->scal, first_step, (int)c->cap_total);
+    if (n <= kFusedMaxN) {
+        int log2p = 6;
+        while ((1 << log2p) < n) ++log2p;
+        launch_emit_small<1, true>(c, ids, n, log2p, fix_key, uniq, inverse, counts, u_out, s, prospect, first_step);
+        return true;
+    }
+    const size_t lds = (size_t)((n + 3) & ~3) * sizeof(int);
+    ensure_dynamic_lds<k_rank_small>(kSmallMaxN * (int)sizeof(int));
+    launch_smem(c, KID_RANK_SMALL, k_rank_small, dim3((unsigned)((n + kRankP - 1) / kRankP)), dim3(kSmallThreads), lds, s,
+                ids, n, c->cfg.vocab_n, fix_key, c->scal + kSErr, c->sorted_keys, c->perm);
+    if (n <= 8 * kSmallThreads)
+        launch_emit_small<8, false>(c, ids, n, 0, fix_key, uniq, inverse, counts, u_out, s, prospect, first_step);
+    else
+        launch_emit_small<kSmallMaxN / kSmallThreads, false>(c, ids, n, 0, fix_key, uniq, inverse, counts, u_out, s, prospect, first_step);
     return true;
 }
 

@@ -1,0 +1,86 @@
+"""The dedup's ways of doing its work (ranks by comparison in one or two launches, larger batches
+otherwise) against numpy, at the batch sizes where they change over, over a window of three steps so
+that items already in the buffer and new ones meet in a batch.  Whole numbers: bit-exact."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _batch(rng, m, n, kind):
+    if kind == "few":                       # a handful of items: long runs, every slice sees equal IDs
+        ids = rng.choice(np.array([0, 1, n // 2, n - 1]), size=m)
+    elif kind == "distinct_first":          # ascending, then all equal
+        ids = np.minimum(np.arange(m), n - 1)
+    else:                                   # popular items, padding, the largest ID
+        ids = np.minimum((rng.pareto(0.7, size=m) * 3).astype(np.int64), n - 1)
+        ids[rng.random(m) < 0.2] = 0
+        ids[::97] = n - 1
+    return ids.astype(np.int32)
+
+
+def check_dedup_window(m, n, kind, steps=3, m_last=None):
+    import torch
+    from paper_2204_04179_amd import gram
+    rng = np.random.default_rng(m * 31 + n)
+    d = 4
+    g = gram.Gram(gram.make_config(n, 8, d, m, steps, 0, 0, gram.F32))
+    cap = min(m, n)
+    seen, total = [], np.zeros(n, np.int64)
+    for k in range(steps):
+        mk = m_last if (m_last and k == steps - 1) else m
+        ids = _batch(rng, mk, n, kind)
+        dev = torch.from_numpy(ids).cuda()
+        uniq = torch.full((cap,), -7, dtype=torch.int32, device="cuda")
+        counts = torch.full((cap,), -7, dtype=torch.int32, device="cuda")
+        inverse = torch.full((mk,), -7, dtype=torch.int32, device="cuda")
+        U = g.unique(dev, uniq, inverse, counts, want_host_u=True)
+        ru, ri, rc = np.unique(ids, return_inverse=True, return_counts=True)
+        assert U == ru.size
+        np.testing.assert_array_equal(uniq.cpu().numpy()[:U], ru)
+        np.testing.assert_array_equal(counts.cpu().numpy()[:U], rc)
+        np.testing.assert_array_equal(inverse.cpu().numpy(), ri.reshape(-1))
+        assert bool((uniq[U:] == -7).all()) and bool((counts[U:] == -7).all())
+        # every gradient row is the same whole number: sums are exact and tell lost or doubled rows apart
+        dH = torch.full((mk, d), float(k + 1), device="cuda")
+        g.grad_accumulate(dH, mk, k)
+        total += np.bincount(ids, minlength=n) * (k + 1)
+        seen.append(ids)
+    rows = min(steps * m, n)
+    ut = torch.empty(rows, dtype=torch.int32, device="cuda")
+    ct = torch.empty(rows, dtype=torch.int32, device="cuda")
+    Gt = torch.empty((rows, d), device="cuda")
+    T = g.flush(ut, ct, Gt, want_host_u=True)
+    ru, rc = np.unique(np.concatenate(seen), return_counts=True)
+    assert T == ru.size
+    np.testing.assert_array_equal(ut.cpu().numpy()[:T], ru)
+    np.testing.assert_array_equal(ct.cpu().numpy()[:T], rc)
+    want = total[ru].astype(np.float64)
+    want[ru == 0] = 0
+    np.testing.assert_array_equal(Gt.cpu().numpy()[:T].astype(np.float64), np.repeat(want[:, None], d, 1))
+    g.close()
+
+
+@pytest.mark.parametrize("kind", ["popular", "few", "distinct_first"])
+@pytest.mark.parametrize("m", [1, 3, 511, 512, 513, 1024, 1025, 8191, 8192, 8193, 12287, 12288, 12289])
+def test_small_batches(m, kind):
+    check_dedup_window(m, 5001, kind)
+
+
+@pytest.mark.parametrize("m", [700, 9000])
+def test_largest_ids_of_the_type(m):
+    """IDs up to 2^31 - 2 through the call that needs no context (nothing is sized by the vocabulary)."""
+    import torch
+    from paper_2204_04179_amd import gram
+    n = 2**31 - 1
+    rng = np.random.default_rng(m)
+    ids = rng.choice(np.array([0, 1, 2**30, n - 2, n - 1], np.int64), size=m).astype(np.int32)
+    dev = torch.from_numpy(ids).cuda()
+    uniq, counts, inverse = (torch.empty(m, dtype=torch.int32, device="cuda") for _ in range(3))
+    u, err = (torch.zeros(1, dtype=torch.int32, device="cuda") for _ in range(2))
+    gram.unique_static(dev, n, 0, uniq, inverse, counts, u, err)
+    ru, ri, rc = np.unique(ids, return_inverse=True, return_counts=True)
+    assert int(u) == ru.size and int(err) == 0
+    np.testing.assert_array_equal(uniq.cpu().numpy()[:ru.size], ru)
+    np.testing.assert_array_equal(counts.cpu().numpy()[:ru.size], rc)
+    np.testing.assert_array_equal(inverse.cpu().numpy(), ri.reshape(-1))
