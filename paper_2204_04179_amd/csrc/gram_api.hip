@@ -110,6 +110,11 @@ int64_t layout(Ctx* c, const gram_config& cfg, const Derived& dv, char* base)
     int* table = (int*)take(table_elems_for(dv.n_sort_max) * 4);
     int* gtot = (int*)take((1 << kMaxDigitBits) * 4);
     int* tile_sums = (int*)take(dv.tiles_scan * 3 * 4);     // three figures per scan tile
+    const int64_t count_words = count_table_words(cfg.vocab_n, cfg.max_positions);
+    const int64_t count_ids = count_words ? align_up(cfg.vocab_n, 128) : 0;
+    uint32_t* cnt_table = (uint32_t*)take(count_words * 4);
+    uint2* id_info = (uint2*)take(count_ids * 8);
+    int* id_tiles = (int*)take(count_ids / 128 * 3 * 4);
     int* offsets = (int*)take((dv.cap_u + 2) * 4);
     int* seg_of_row = (int*)take(cfg.max_positions * 4);
     int* uniq_ws = (int*)take(dv.cap_u * 4);
@@ -144,6 +149,7 @@ int64_t layout(Ctx* c, const gram_config& cfg, const Derived& dv, char* base)
     if (c && base) {
         c->scal = scal; c->keys[0] = keys0; c->keys[1] = keys1; c->vals[0] = vals0; c->vals[1] = vals1;
         c->table = table; c->gtot = gtot; c->tile_sums = tile_sums; c->offsets = offsets;
+        c->cnt_table = count_words ? cnt_table : nullptr; c->id_info = id_info; c->id_tiles = id_tiles;
         c->seg_of_row = seg_of_row; c->uniq_ws = uniq_ws; c->seg_slot = seg_slot;
         c->long_list = long_list; c->slot_of = slot_of; c->id_of_slot = dense ? nullptr : id_of_slot;
         c->cnt_of_slot = cnt_of_slot; c->cnt64 = cnt64; c->dense_sums = dense_sums; c->G = G; c->E_ws = E_ws; c->loss_part = loss_part; c->chunk_ids = chunk_ids; c->seg_first = seg_first;
@@ -344,7 +350,8 @@ int gram_unique(gram_ctx* ctx, const int32_t* ids, int64_t m, int32_t* uniq, int
         // slot-table contexts: the dedup kernels also work out the buffer rows of the items
         const bool prospect = !c->dense;
         const int first_step = (c->steps_done == 0 && !c->window_imported) ? 1 : 0;
-        if (!unique_small(c, ids, (int)m, fix, uniq, inverse, counts, u_dev, s, prospect, first_step)) {
+        if (!unique_small(c, ids, (int)m, fix, uniq, inverse, counts, u_dev, s, prospect, first_step) &&
+            !unique_by_count(c, ids, (int)m, fix, uniq, inverse, counts, u_dev, s, prospect, first_step)) {
             const int r = radix_sort_pairs(c, ids, nullptr, (int)m, nullptr, m, true, fix, s);
             c->sorted_keys = c->keys[r];
             c->perm = c->vals[r];
@@ -656,7 +663,8 @@ static const char* const kKernelNames[KID_COUNT] = {
     "transpose_w", "encode_bf16", "encode_f32", "gather_rows", "slot_count", "slot_emit", "seg_reduce",
     "seg_combine", "wgrad_bf16", "wgrad_f32", "wgrad_reduce", "flush_meta",
     "flush_rows", "unique_small", "gather_heavy", "pseudo_target", "pseudo_loss", "chunk_ids",
-    "pseudo_miss", "mlp_to_bf16", "encode_bf16_wide", "wgrad_bf16_wide", "rank_small"};
+    "pseudo_miss", "mlp_to_bf16", "encode_bf16_wide", "wgrad_bf16_wide", "rank_small",
+    "ids_count", "ids_scan", "ids_emit"};
 
 int gram_kernel_count(void) { return KID_COUNT; }
 

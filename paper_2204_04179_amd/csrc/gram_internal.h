@@ -24,6 +24,9 @@ constexpr int kSegLongSmall = 32;       // ... or this many when the batch has a
 constexpr int kSegSmallBatch = 65536;
 constexpr int kLightMax = 32;           // items with more positions are gathered by a separate copy kernel
 constexpr int kSlotNew = 1 << 30;       // flag in seg_slot: the buffer row is created by this step
+constexpr int kCountMaxM = 65535;       // the counting dedup: positions per batch, at most
+constexpr int kCountMaxVocab = 131072;  // and IDs
+constexpr int64_t kCountMaxWords = 3 << 20;     // and 32-bit words of its table (12 MiB)
 constexpr int kPseudoRows = 8;          // unique items per block of the pseudo-target kernel
 constexpr int kFixCols4 = 16;           // float4 columns per block of the long-segment combine
 constexpr int kFixLanes = kBlock / kFixCols4;
@@ -68,7 +71,8 @@ enum KernelId {
     KID_SLOT_COUNT, KID_SLOT_EMIT, KID_SEG_REDUCE, KID_SEG_COMBINE, KID_WGRAD_BF16, KID_WGRAD_F32,
     KID_WGRAD_REDUCE, KID_FLUSH_META, KID_FLUSH_ROWS, KID_UNIQUE_SMALL,
     KID_GATHER_HEAVY, KID_PSEUDO_TARGET, KID_PSEUDO_LOSS, KID_CHUNK_IDS, KID_PSEUDO_MISS, KID_MLP_TO_BF16,
-    KID_ENCODE_BF16_WIDE, KID_WGRAD_BF16_WIDE, KID_RANK_SMALL, KID_COUNT
+    KID_ENCODE_BF16_WIDE, KID_WGRAD_BF16_WIDE, KID_RANK_SMALL,
+    KID_IDS_COUNT, KID_IDS_SCAN, KID_IDS_EMIT, KID_COUNT
 };
 
 static_assert(KID_COUNT <= 64, "the profiling mask has 64 bits");
@@ -101,6 +105,11 @@ struct Ctx {
     int* table = nullptr;       // [bins * nw] per-wave digit counts / prefixes
     int* gtot = nullptr;        // [1024] per-digit totals
     int* tile_sums = nullptr;   // [tiles] flag counts per scan tile
+    // counting dedup (vocabularies of at most kCountMaxVocab IDs, contexts for batches beyond the
+    // comparison dedup); NULL: not available
+    uint32_t* cnt_table = nullptr;  // [rows of 1024 positions][IDs] 16-bit counts, then prefixes
+    uint2* id_info = nullptr;       // [IDs] place within the tile of IDs, count
+    int* id_tiles = nullptr;        // [3][tiles of IDs]
     int* offsets = nullptr;     // [cap_u + 1] start row of each segment in sorted order
     int* seg_of_row = nullptr;  // [M_max] segment index of each sorted row
     int* uniq_ws = nullptr;     // [cap_u] copy of uniq of the current batch
@@ -209,6 +218,12 @@ void unique_from_sorted(Ctx* c, int n, int* uniq, int* inverse, int* counts, int
 // Dedup of small batches in one or two launches; returns false if n is too large for it.
 bool unique_small(Ctx* c, const int* ids, int n, int fix_key, int* uniq, int* inverse, int* counts,
                   int* u_out, hipStream_t s, bool prospect = false, int first_step = 0);
+
+// Three-launch dedup for mid-sized batches over small vocabularies; returns false if it does not apply.
+bool unique_by_count(Ctx* c, const int* ids, int n, int fix_key, int* uniq, int* inverse, int* counts,
+                     int* u_out, hipStream_t s, bool prospect = false, int first_step = 0);
+// 32-bit words of the counting dedup's table for a context (0: it does not apply).
+int64_t count_table_words(int64_t vocab_n, int64_t max_positions);
 
 // ---- gram_stream.hip -----------------------------------------------------
 // H has the context's h_dtype (float32, or bf16 rounded to nearest even).

@@ -752,6 +752,295 @@ __global__ __launch_bounds__(kSmallThreads) void k_emit_small(
     }
 }
 
+// ---- mid-sized batches over small vocabularies: counting by ID -------------------------
+//
+// A sort of such a batch is bound by its eight short launches (two radix passes of three, two for the
+// head flags: 33 to 37 us from 12,000 to 65,000 positions whatever the vocabulary).  Where a counter
+// per ID fits in LDS, three launches do it all:
+//   k_ids_count  a block counts the IDs of its 1024 positions in LDS (16-bit counters) and leaves them
+//                as one row of table[block][id];
+//   k_ids_scan   exclusive prefix down every column of the table (a block takes 128 IDs), and per ID
+//                its count and its place among the positions, items and new items of its 128 IDs;
+//   k_ids_emit   position blocks: place of a position = first row of its ID + the column prefix + its
+//                rank among the block's positions of that ID; ID blocks: everything per unique item.
+// Vocabularies beyond kCountIds are cut into parts: a block then takes (1024 positions, one part).
+// 16-bit counts and prefixes hold because a batch has fewer than 65,536 positions.
+constexpr int kCountThreads = 1024;
+constexpr int kCountIds = 65536;             // IDs per part: 128 KiB of 16-bit counters
+constexpr int kCountTile = 128;              // IDs per block of k_ids_scan
+constexpr int kCountTilesMax = kCountMaxVocab / kCountTile;
+static_assert(kCountTilesMax <= kCountThreads, "one thread per tile in the scan of k_ids_emit");
+static_assert(kCountMaxM < 65536, "16-bit prefixes");
+
+int64_t count_table_words(int64_t vocab_n, int64_t max_positions)
+{
+    if (vocab_n > kCountMaxVocab || max_positions <= kSmallMaxN) return 0;
+    const int64_t m = max_positions < kCountMaxM ? max_positions : kCountMaxM;
+    const int64_t rows = (m + kCountThreads - 1) / kCountThreads, pitch = (vocab_n + kCountTile - 1) / kCountTile * kCountTile;
+    int64_t words = rows * pitch / 2;
+    return words > kCountMaxWords ? kCountMaxWords : words;
+}
+
+// ID of position p (checked) and whether it belongs to [lo, hi).
+__device__ __forceinline__ int count_id(int raw, int vocab_n, int fix_key, bool* bad)
+{
+    if (raw < 0 || raw >= vocab_n) {
+        *bad = true;
+        return fix_key;
+    }
+    return raw;
+}
+
+__global__ __launch_bounds__(kCountThreads) void k_ids_count(const int* __restrict__ ids, int n, int vocab_n,
+                                                             int fix_key, int pitch, int* __restrict__ err,
+                                                             uint32_t* __restrict__ table)
+{
+    extern __shared__ __attribute__((aligned(16))) uint32_t cnt[];
+    const int tid = threadIdx.x, lo = blockIdx.y * kCountIds;
+    const int words = (pitch - lo < kCountIds ? pitch - lo : kCountIds) / 2;      // a multiple of 64
+    const int p = blockIdx.x * kCountThreads + tid;
+    const int raw = p < n ? ids[p] : 0;
+    for (int i = tid * 4; i < words; i += kCountThreads * 4) *reinterpret_cast<uint4*>(cnt + i) = make_uint4(0, 0, 0, 0);
+    __syncthreads();
+    bool bad = false;
+    const int id = count_id(raw, vocab_n, fix_key, &bad) - lo;
+    const bool mine = p < n && (unsigned)id < (unsigned)(2 * words);
+    // the ID of the wave's first position (padding, a very popular item) is counted with one atomic
+    // for all lanes that hold it: they would pile up on one LDS word
+    const int id0 = __builtin_amdgcn_readfirstlane(id);
+    const unsigned long long m0 = __ballot(mine && id == id0);
+    if (mine && id != id0) atomicAdd(&cnt[id >> 1], 1u << ((id & 1) * 16));
+    if (lane_id() == 0 && m0) atomicAdd(&cnt[id0 >> 1], (uint32_t)__popcll(m0) << ((id0 & 1) * 16));
+    if (bad && p < n) atomicOr(err, kErrBitRange);
+    __syncthreads();
+    uint32_t* row = table + ((int64_t)blockIdx.x * pitch + lo) / 2;
+    for (int i = tid * 4; i < words; i += kCountThreads * 4)
+        *reinterpret_cast<uint4*>(row + i) = *reinterpret_cast<const uint4*>(cnt + i);
+}
+
+// Per ID: x = first row within the tile (16 bits) | items before it in the tile (8) | new items before
+// it (8); y = its count.  tile_info[t], [T + t], [2 T + t]: positions, items, new items of tile t.
+__global__ __launch_bounds__(kBlock) void k_ids_scan(uint32_t* __restrict__ table, int rows, int pitch,
+                                                     const int* __restrict__ slot_of, int first_step, int vocab_n,
+                                                     uint2* __restrict__ id_info, int* __restrict__ tile_info)
+{
+    constexpr int kGroups = kBlock / (kCountTile / 2);       // 4 groups of threads share the rows of a column
+    constexpr int kRowsMax = (kCountMaxM + kCountThreads - 1) / kCountThreads;
+    constexpr int kPer = (kRowsMax + kGroups - 1) / kGroups;
+    __shared__ uint32_t part[kGroups][kCountTile / 2];
+    const int w = threadIdx.x & (kCountTile / 2 - 1), g = threadIdx.x / (kCountTile / 2);
+    const int word = blockIdx.x * (kCountTile / 2) + w;
+    uint32_t* col = table + word;
+    const int64_t step = pitch / 2;
+    const int per = (rows + kGroups - 1) / kGroups;
+    const int b0 = g * per, b1 = b0 + per < rows ? b0 + per : rows;
+    const int id = 2 * word;
+    int slot0 = -1, slot1 = -1;
+    if (g == 0 && slot_of && !first_step) {
+        if (id < vocab_n) slot0 = slot_of[id];
+        if (id + 1 < vocab_n) slot1 = slot_of[id + 1];
+    }
+    // all of a thread's counts are fetched together; two 16-bit sums per word never carry into each other
+    uint32_t v[kPer], sum = 0;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) v[i] = b0 + i < b1 ? col[(b0 + i) * step] : 0u;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) sum += v[i];
+    part[g][w] = sum;
+    __syncthreads();
+    uint32_t run = 0, tot = 0;
+#pragma unroll
+    for (int i = 0; i < kGroups; ++i) {
+        const uint32_t t = part[i][w];
+        if (i < g) run += t;
+        tot += t;
+    }
+#pragma unroll
+    for (int i = 0; i < kPer; ++i)
+        if (b0 + i < b1) {
+            col[(b0 + i) * step] = run;
+            run += v[i];
+        }
+    if (g != 0) return;
+    // the first wave: 2 IDs per lane
+    static_assert(kCountTile == 2 * kWave, "the tile's IDs sit in one wave");
+    const int c0 = (int)(tot & 0xffffu), c1 = (int)(tot >> 16);
+    const int h0 = c0 > 0, h1 = c1 > 0, n0 = h0 && slot0 < 0, n1 = h1 && slot1 < 0;
+    const int pos = wave_incl_scan(c0 + c1);
+    const int hn = wave_incl_scan((h0 + h1) | (n0 + n1) << 16);
+    const int pos0 = pos - c0 - c1, hd0 = (hn & 0xffff) - h0 - h1, nw0 = (hn >> 16) - n0 - n1;
+    uint2* out = id_info + id;          // two entries as one 16-byte store (id is even)
+    *reinterpret_cast<uint4*>(out) =
+        make_uint4((uint32_t)pos0 | (uint32_t)hd0 << 16 | (uint32_t)nw0 << 24, (uint32_t)c0,
+                   (uint32_t)((pos0 + c0) & 0xffff) | (uint32_t)(hd0 + h0) << 16 | (uint32_t)(nw0 + n0) << 24, (uint32_t)c1);
+    if (w == kWave - 1) {
+        const int T = gridDim.x;
+        tile_info[blockIdx.x] = pos;
+        tile_info[T + blockIdx.x] = hn & 0xffff;
+        tile_info[2 * T + blockIdx.x] = hn >> 16;
+    }
+}
+
+__global__ __launch_bounds__(kCountThreads) void k_ids_emit(
+    const int* __restrict__ ids, int n, int key_bits, int vocab_n, int fix_key, int pitch, int pos_blocks,
+    const uint16_t* __restrict__ table, const uint2* __restrict__ id_info, const int* __restrict__ tile_info, int T,
+    int* __restrict__ perm, int* __restrict__ uniq, int* __restrict__ inverse, int* __restrict__ counts,
+    int* __restrict__ offsets, int* __restrict__ seg_of_row, int* __restrict__ uniq_ws, int* __restrict__ u_out,
+    const int* __restrict__ slot_of, int* __restrict__ seg_slot, int* __restrict__ scal, int first_step,
+    int cap_total)
+{
+    extern __shared__ __attribute__((aligned(16))) uint16_t cnt16[];      // (position blocks) count so far per ID
+    __shared__ int s_pos[kCountTilesMax], s_item[kCountTilesMax], s_new[kCountTilesMax];
+    __shared__ unsigned long long s_wave[kCountThreads / kWave];
+    const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
+    const bool per_id = (int)blockIdx.x >= pos_blocks;
+    const int lo = per_id ? 0 : blockIdx.y * kCountIds;
+    const int words = (pitch - lo < kCountIds ? pitch - lo : kCountIds) / 2;
+    if (per_id && blockIdx.y) return;
+
+    // what does not depend on the scan of the tiles is fetched first
+    const int p = blockIdx.x * kCountThreads + tid;                       // position blocks
+    const int j = ((int)blockIdx.x - pos_blocks) * kCountThreads + tid;   // ID blocks
+    int id = 0;
+    bool mine = false;
+    uint2 info = make_uint2(0, 0);
+    int pre = 0, slot = -1;
+    if (per_id) {
+        if (j < vocab_n) {
+            id = j;
+            info = id_info[j];
+            if (slot_of && !first_step) slot = slot_of[j];
+        }
+    } else {
+        bool bad = false;
+        id = count_id(p < n ? ids[p] : 0, vocab_n, fix_key, &bad);
+        mine = p < n && (unsigned)(id - lo) < (unsigned)(2 * words);
+        if (mine) {
+            info = id_info[id];
+            pre = table[(int64_t)blockIdx.x * pitch + id];
+        }
+    }
+    const int u_base = (slot_of && !first_step) ? scal[kSUTotal] : 0;     // a flush leaves the old count behind
+    // exclusive prefix over the tiles, three figures of at most 17 bits in one 64-bit sum
+    unsigned long long tv = 0;
+    if (tid < T)
+        tv = (unsigned long long)tile_info[tid] | (unsigned long long)tile_info[T + tid] << 20 |
+             (unsigned long long)tile_info[2 * T + tid] << 40;
+    if (!per_id)
+        for (int i = tid * 8; i < 2 * words; i += kCountThreads * 8) *reinterpret_cast<uint4*>(cnt16 + i) = make_uint4(0, 0, 0, 0);
+    unsigned long long incl = tv;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const unsigned long long t = __shfl_up(incl, o);
+        if (lane >= o) incl += t;
+    }
+    if (lane == kWave - 1) s_wave[wave] = incl;
+    __syncthreads();
+    unsigned long long base = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < kCountThreads / kWave; ++w) {
+        const unsigned long long t = s_wave[w];
+        if (w < wave) base += t;
+        all += t;
+    }
+    base += incl - tv;
+    if (tid < T) {
+        s_pos[tid] = (int)(base & 0xfffff);
+        s_item[tid] = (int)(base >> 20 & 0xfffff);
+        s_new[tid] = (int)(base >> 40);
+    }
+    __syncthreads();
+    const int tile = id / kCountTile;
+    const int first_row = s_pos[tile] + (int)(info.x & 0xffff), seg = s_item[tile] + (int)(info.x >> 16 & 0xff);
+
+    if (per_id) {
+        if (info.y > 0) {                                                 // the ID occurs
+            uniq[seg] = id;
+            uniq_ws[seg] = id;
+            offsets[seg] = first_row;
+            counts[seg] = (int)info.y;
+            if (slot_of) {
+                if (slot < 0) {
+                    const int s = u_base + s_new[tile] + (int)(info.x >> 24);
+                    slot = s < cap_total ? (s | kSlotNew) : -1;
+                }
+                seg_slot[seg] = slot;
+            }
+        }
+        if (j == 0) {
+            const int u = (int)(all >> 20 & 0xfffff);
+            scal[kSU] = u;
+            if (u_out) *u_out = u;
+            offsets[u] = n;
+            if (slot_of) {
+                const int nt = u_base + (int)(all >> 40);
+                scal[kSUNext] = nt < cap_total ? nt : cap_total;
+                scal[kSLongCount] = 0;
+            }
+        }
+        return;
+    }
+
+    // rank among the block's positions of the same ID: lanes of the wave find each other by ballots,
+    // the waves take turns at the counters in position order
+    const int rel = id - lo;
+    unsigned long long peers = __ballot(mine);
+    for (int bit = 0; bit < key_bits; ++bit) {
+        const bool one = (id >> bit) & 1;
+        const unsigned long long mm = __ballot(one);
+        peers &= one ? mm : ~mm;
+    }
+    const int below = __popcll(peers & ((1ull << lane) - 1ull));
+    typedef __attribute__((address_space(3))) uint16_t lds_u16;
+    volatile lds_u16* cnt = (volatile lds_u16*)cnt16;
+    int before = 0;
+    for (int w = 0; w < kCountThreads / kWave; ++w) {
+        if (w == wave && mine) {
+            before = cnt[rel];
+            __builtin_amdgcn_wave_barrier();
+            if (below == 0) cnt[rel] = (uint16_t)(before + (int)__popcll(peers));
+        }
+        __syncthreads();
+    }
+    if (mine) {
+        const int pos = first_row + pre + before + below;
+        inverse[p] = seg;
+        if ((unsigned)pos < (unsigned)n) {      // pos < n always holds; the test keeps a logic error from
+            perm[pos] = p;                       // becoming a stray store
+            seg_of_row[pos] = seg;
+        }
+    }
+}
+
+// Returns false where the counting dedup does not apply: a vocabulary or batch beyond its counters, or
+// a table larger than kCountMaxWords (its four trips through memory then cost more than the launches saved).
+bool unique_by_count(Ctx* c, const int* ids, int n, int fix_key, int* uniq, int* inverse, int* counts, int* u_out,
+                     hipStream_t s, bool prospect, int first_step)
+{
+    const int64_t N = c->cfg.vocab_n;
+    if (!c->cnt_table || n > kCountMaxM || N > kCountMaxVocab) return false;
+    const int pitch = (int)((N + kCountTile - 1) / kCountTile * kCountTile);
+    const int rows = (n + kCountThreads - 1) / kCountThreads;
+    if ((int64_t)rows * pitch / 2 > kCountMaxWords) return false;
+    const int parts = (pitch + kCountIds - 1) / kCountIds, T = pitch / kCountTile;
+    const size_t lds = (size_t)(pitch < kCountIds ? pitch : kCountIds) * 2;
+    ensure_dynamic_lds<k_ids_count>(kCountIds * 2);
+    ensure_dynamic_lds<k_ids_emit>(kCountIds * 2);
+    const int* slot_of = prospect ? c->slot_of : nullptr;
+    c->sorted_keys = nullptr;
+    c->perm = c->vals[0];
+    launch_smem(c, KID_IDS_COUNT, k_ids_count, dim3(rows, parts), dim3(kCountThreads), lds, s, ids, n, c->cfg.vocab_n,
+                fix_key, pitch, c->scal + kSErr, c->cnt_table);
+    launch(c, KID_IDS_SCAN, k_ids_scan, dim3(T), dim3(kBlock), s, c->cnt_table, rows, pitch, slot_of, first_step,
+           c->cfg.vocab_n, c->id_info, c->id_tiles);
+    const int id_blocks = (int)((N + kCountThreads - 1) / kCountThreads);
+    launch_smem(c, KID_IDS_EMIT, k_ids_emit, dim3(rows + id_blocks, parts), dim3(kCountThreads), lds, s, ids, n, c->key_bits,
+                c->cfg.vocab_n, fix_key, pitch, rows, reinterpret_cast<const uint16_t*>(c->cnt_table), c->id_info,
+                c->id_tiles, T, c->perm, uniq, inverse, counts, c->offsets, c->seg_of_row, c->uniq_ws, u_out, slot_of,
+                c->seg_slot, c->scal, first_step, (int)c->cap_total);
+    return true;
+}
+
 // prospect: also work out the buffer rows the items would get (slot-table contexts only);
 // first_step: the window's buffer holds nothing yet.
 void unique_from_sorted(Ctx* c, int n, int* uniq, int* inverse, int* counts, int* u_out,

@@ -84,3 +84,30 @@ def test_largest_ids_of_the_type(m):
     np.testing.assert_array_equal(uniq.cpu().numpy()[:ru.size], ru)
     np.testing.assert_array_equal(counts.cpu().numpy()[:ru.size], rc)
     np.testing.assert_array_equal(inverse.cpu().numpy(), ri.reshape(-1))
+
+
+@pytest.mark.parametrize("kind", ["popular", "few"])
+@pytest.mark.parametrize("m,n", [(12289, 100), (20001, 5001), (13000, 127), (13000, 128), (13000, 129), (65535, 20000),
+                                 (65535, 65536), (30000, 65537), (49152, 131072), (16384, 131071),
+                                 # beyond the counting dedup: positions, vocabulary, size of its table
+                                 (65536, 20000), (30000, 131073), (49153, 131072)])
+def test_mid_sized_batches(m, n, kind):
+    check_dedup_window(m, n, kind, m_last=m - 257)
+
+
+def test_mid_sized_batch_of_one_item_and_out_of_range_ids():
+    import torch
+    from paper_2204_04179_amd import gram
+    m, n = 65535, 3000
+    g = gram.Gram(gram.make_config(n, 8, 4, m, 1, 0, 0, gram.F32))
+    uniq, counts = (torch.empty(n, dtype=torch.int32, device="cuda") for _ in range(2))
+    inverse = torch.empty(m, dtype=torch.int32, device="cuda")
+    ids = torch.full((m,), 2999, dtype=torch.int32, device="cuda")      # a count of 65,535: the counters' largest
+    assert g.unique(ids, uniq, inverse, counts, want_host_u=True) == 1
+    assert int(uniq[0]) == 2999 and int(counts[0]) == m and int(inverse.abs().max()) == 0
+    for bad in (n, -1, 2**31 - 1, -2**31):
+        ids[m // 2] = bad
+        with pytest.raises(gram.GramError) as e:
+            g.unique(ids, uniq, inverse, counts, want_host_u=True)
+        assert e.value.status == gram.ERR_RANGE
+    g.close()
