@@ -350,8 +350,8 @@ int gram_unique(gram_ctx* ctx, const int32_t* ids, int64_t m, int32_t* uniq, int
         // slot-table contexts: the dedup kernels also work out the buffer rows of the items
         const bool prospect = !c->dense;
         const int first_step = (c->steps_done == 0 && !c->window_imported) ? 1 : 0;
-        if (!unique_small(c, ids, (int)m, fix, uniq, inverse, counts, u_dev, s, prospect, first_step) &&
-            !unique_by_count(c, ids, (int)m, fix, uniq, inverse, counts, u_dev, s, prospect, first_step)) {
+        if (!unique_by_count(c, ids, (int)m, fix, uniq, inverse, counts, u_dev, s, prospect, first_step) &&
+            !unique_small(c, ids, (int)m, fix, uniq, inverse, counts, u_dev, s, prospect, first_step)) {
             const int r = radix_sort_pairs(c, ids, nullptr, (int)m, nullptr, m, true, fix, s);
             c->sorted_keys = c->keys[r];
             c->perm = c->vals[r];

@@ -24,7 +24,8 @@ constexpr int kSegLongSmall = 32;       // ... or this many when the batch has a
 constexpr int kSegSmallBatch = 65536;
 constexpr int kLightMax = 32;           // items with more positions are gathered by a separate copy kernel
 constexpr int kSlotNew = 1 << 30;       // flag in seg_slot: the buffer row is created by this step
-constexpr int kCountMaxM = 65535;       // the counting dedup: positions per batch, at most
+constexpr int kCountMinM = 8193;        // the counting dedup: positions per batch, at least
+constexpr int kCountMaxM = 65535;       // and at most
 constexpr int kCountMaxVocab = 131072;  // and IDs
 constexpr int64_t kCountMaxWords = 3 << 20;     // and 32-bit words of its table (12 MiB)
 constexpr int kPseudoRows = 8;          // unique items per block of the pseudo-target kernel

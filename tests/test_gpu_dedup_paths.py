@@ -64,7 +64,7 @@ def check_dedup_window(m, n, kind, steps=3, m_last=None):
 @pytest.mark.parametrize("kind", ["popular", "few", "distinct_first"])
 @pytest.mark.parametrize("m", [1, 3, 511, 512, 513, 1024, 1025, 8191, 8192, 8193, 12287, 12288, 12289])
 def test_small_batches(m, kind):
-    check_dedup_window(m, 5001, kind)
+    check_dedup_window(m, 200_001 if m > 8192 else 5001, kind)      # (large vocabulary: not counted by ID)
 
 
 @pytest.mark.parametrize("m", [700, 9000])
@@ -87,7 +87,7 @@ def test_largest_ids_of_the_type(m):
 
 
 @pytest.mark.parametrize("kind", ["popular", "few"])
-@pytest.mark.parametrize("m,n", [(12289, 100), (20001, 5001), (13000, 127), (13000, 128), (13000, 129), (65535, 20000),
+@pytest.mark.parametrize("m,n", [(8450, 9001), (12289, 100), (20001, 5001), (13000, 127), (13000, 128), (13000, 129), (65535, 20000),
                                  (65535, 65536), (30000, 65537), (49152, 131072), (16384, 131071),
                                  # beyond the counting dedup: positions, vocabulary, size of its table
                                  (65536, 20000), (30000, 131073), (49153, 131072)])
