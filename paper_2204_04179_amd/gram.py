@@ -133,10 +133,21 @@ def _ptr(t):
     return t.data_ptr()
 
 
+def _current_stream():
+    """Handle of PyTorch's current stream on the current device.
+
+    `torch.cuda.current_stream()` builds a Stream object, 2.9 us of a call that takes 5 to 8 us
+    altogether (a small step makes five calls and is bound by the host); the handle itself takes 0.2 us.
+    """
+    import torch
+    if torch.cuda.is_initialized():
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
+
+
 def _stream(stream):
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
