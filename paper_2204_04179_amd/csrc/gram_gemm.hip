@@ -894,6 +894,7 @@ constexpr int WOPB = WK * WROWB;             // bytes per operand and stage
 constexpr int WSTAGEB = 2 * WOPB;
 constexpr size_t WSMEM = 2 * (size_t)WSTAGEB;
 constexpr uint32_t kOutOfRange = 0xFFFFFFF0u;
+constexpr int kNonTemporal = 2;              // cache policy bits of a buffer store (nt)
 constexpr int kWgradWaves = 8;
 
 // NW = waves per block: 4 (128x128 each) or 8 (128x64 each, two per SIMD).
@@ -1161,6 +1162,209 @@ __global__ __launch_bounds__(NW * 64) void k_wgrad_tn_bf16(
 #undef GRAM_PARK
 #undef GRAM_ITER
 
+// ---- weight gradient of short windows -------------------------------------------------
+//
+// A window of a few thousand buffer rows over a 768 x 256 matrix is 1 GFLOP: nothing but latency.  The
+// kernel above gives it 24 blocks of 256 x 256 with ten slabs each, one after the other (14 us, 21 with
+// the reduction, at 2,500 rows; this one with its reduction 12).  This one cuts the output into 128 x 64 tiles and the rows twice: over blocks (partials
+// through memory, as above) and inside a block over four groups of four waves, which walk different
+// slabs side by side and add their tiles through LDS at the end.  16 waves per CU with the loads of
+// three slabs each in flight is also what it takes to draw on L2 at 47 instead of 19 B/clk.  Slab i of
+// group g of range z is slab (4 z + g) + 4 S i: which rows a wave starts with does not depend on the row
+// count, so its first loads go out with the load of that count; rows past it are zeroed on their way
+// into LDS (offsets that leave a matrix return zeros).
+// LDS rows of X are 256 bytes (chunk c of row r at c ^ ((r & 3) << 2)), rows of G 128 bytes (chunk c at
+// c ^ ((r & 2) << 1)): either way the 16 pieces of a transposing read cover every bank once.
+constexpr int VM = 128, VN = 64, VGROUPS = 4, VTHREADS = VGROUPS * 256, VDEPTH = 2;
+constexpr int VXB = 32 * VM * 2, VSTAGEB = VXB + 32 * VN * 2;      // bytes per group and stage
+constexpr int VACC_STRIDE = VN + 8;                                 // floats per row of a parked tile
+constexpr size_t VSMEM = (size_t)VGROUPS * VM * VACC_STRIDE * 4;
+static_assert(VSMEM >= 2 * (size_t)VGROUPS * VSTAGEB, "the tiles overlay the stages");
+
+// LISTED: the items of the rows are listed (else row r pairs with item r).
+template <bool EXPORT, bool LISTED>
+__global__ __launch_bounds__(VTHREADS) void k_wgrad_short(
+    const uint16_t* __restrict__ X, uint32_t x_bytes, const int* __restrict__ id_of_slot,
+    const float* __restrict__ G, uint32_t g_bytes, const int* __restrict__ rows_dev, int d_in, int d,
+    int pad_id, int splits, float* __restrict__ partial, int row_begin, int row_end, int accumulate, WgradExport ex)
+{
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    if (EXPORT && ex.meta_blocks > 0 && blockIdx.x >= gridDim.x - ex.meta_blocks) {
+        const int n_ = *rows_dev;
+        const int mb = blockIdx.x - (gridDim.x - ex.meta_blocks);
+        for (int r = mb * VTHREADS + threadIdx.x; r < n_; r += ex.meta_blocks * VTHREADS)
+            flush_meta_row(r, id_of_slot, nullptr, ex.cnt_of_slot, ex.slot_of, ex.uniq_total, ex.counts_total, nullptr);
+        if (mb == 0 && threadIdx.x == 0) {
+            if (ex.u_total_dev) *ex.u_total_dev = n_;
+            ex.scal[kSFlushN] = n_;
+        }
+        return;
+    }
+    // the tiles of one range of rows run on one XCD (or, with fewer than 8 ranges, on 8 / splits of them)
+    // and share the rows through its L2
+    const int tiles_c = (d + VN - 1) / VN, f_tiles = (d_in + VM - 1) / VM, tiles = f_tiles * tiles_c;
+    const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
+    const int z = splits >= 8 ? xcd + 8 * (q / tiles) : xcd % splits;
+    const int tile = splits >= 8 ? q % tiles : q * (8 / splits) + xcd / splits;
+    const int f_idx = tile / tiles_c;
+    const int i0 = f_idx * VM, c0 = (tile % tiles_c) * VN;
+    if (z >= splits || tile >= tiles) return;
+    const int tid = threadIdx.x, grp = __builtin_amdgcn_readfirstlane(tid >> 8), gt = tid & 255;
+    const int lane = tid & 63, wave = (tid >> 6) & 3;
+    const int wm = wave >> 1, wn = wave & 1;
+
+    const __amdgpu_buffer_rsrc_t rsX = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(X), 0, x_bytes, kBufferFlags);
+    const __amdgpu_buffer_rsrc_t rsG = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(G), 0, g_bytes, kBufferFlags);
+
+    // loader: thread gt of a group moves chunk gt & 15 of rows gt >> 4 and (gt >> 4) + 16 of a slab, of
+    // X (16 bytes of bf16) and of G (4 floats)
+    const int lrow = gt >> 4, lpos = gt & 15;
+    const int feat = i0 + ((lpos ^ ((lrow & 3) << 2)) * 8);         // rows lrow and lrow + 16 swizzle alike
+    const bool feat_ok = feat < d_in;
+    const int g_col = c0 + 4 * lpos;
+    const bool g_col_ok = g_col < d;
+    const int first = row_begin / WK + z * VGROUPS + grp, stride = splits * VGROUPS;
+    bool ex_mine[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) ex_mine[t] = EXPORT && (lrow + 16 * t) % f_tiles == f_idx;
+
+    // row_end bounds the rows as allocated: what lies between the rows held and row_end is loaded and
+    // dropped.  Nothing in the loop is conditional (offsets out of range read zeros and store nothing),
+    // so that the loads in flight are known at every wait.
+    const __amdgpu_buffer_rsrc_t rsI = __builtin_amdgcn_make_buffer_rsrc(const_cast<int*>(id_of_slot), 0, LISTED ? row_end * 4 : 0, kBufferFlags);
+    const bool ranked = EXPORT && ex.rank_of_slot;
+    const __amdgpu_buffer_rsrc_t rsR = __builtin_amdgcn_make_buffer_rsrc(const_cast<int*>(ex.rank_of_slot), 0, ranked ? row_end * 4 : 0, kBufferFlags);
+    const __amdgpu_buffer_rsrc_t rsT = __builtin_amdgcn_make_buffer_rsrc(ex.G_total, 0, EXPORT ? g_bytes : 0, kBufferFlags);
+    int ids_next[VDEPTH][2], ids_cur[2], rk[VDEPTH][2];
+    v4i32 rx[VDEPTH][2], rg[VDEPTH][2];
+#define GRAM_SLOT(IT, T_) (((first + (IT) * stride) * WK) + lrow + 16 * (T_))
+#define GRAM_IDS(SET, IT)                                                                           \
+    _Pragma("unroll") for (int t = 0; t < 2; ++t) {                                                 \
+        const int slot = GRAM_SLOT(IT, t);                                                          \
+        ids_next[SET][t] = LISTED ? __builtin_amdgcn_raw_buffer_load_b32(rsI, slot < row_end ? (uint32_t)slot * 4u : kOutOfRange, 0, 0) : slot; \
+    }
+#define GRAM_LOAD(SET, IT)                                                                          \
+    _Pragma("unroll") for (int t = 0; t < 2; ++t) {                                                 \
+        const int slot = GRAM_SLOT(IT, t);                                                          \
+        const bool in_ = slot < row_end;                                                            \
+        if (EXPORT) rk[SET][t] = __builtin_amdgcn_raw_buffer_load_b32(rsR, in_ ? (uint32_t)slot * 4u : kOutOfRange, 0, 0); \
+        const uint32_t ox = in_ && feat_ok && ids_cur[t] != pad_id ? ((uint32_t)ids_cur[t] * (uint32_t)d_in + (uint32_t)feat) * 2u : kOutOfRange; \
+        rx[SET][t] = __builtin_amdgcn_raw_buffer_load_b128(rsX, ox, 0, 0);                          \
+        const uint32_t og = in_ && g_col_ok ? ((uint32_t)slot * (uint32_t)d + (uint32_t)g_col) * 4u : kOutOfRange; \
+        rg[SET][t] = __builtin_amdgcn_raw_buffer_load_b128(rsG, og, 0, 0);                          \
+    }
+#define GRAM_PARK(SET, IT, STAGE)                                                                   \
+    {                                                                                               \
+        unsigned char* s_ = smem + ((STAGE) * VGROUPS + grp) * VSTAGEB;                             \
+        _Pragma("unroll") for (int t = 0; t < 2; ++t) {                                             \
+            const int row = lrow + 16 * t, slot = GRAM_SLOT(IT, t);                                 \
+            const bool held = slot < U && slot >= row_begin;                                        \
+            const v4i32 zero_ = {0, 0, 0, 0};                                                       \
+            *reinterpret_cast<v4i32*>(s_ + row * (VM * 2) + lpos * 16) = held ? rx[SET][t] : zero_; \
+            const v4i32 v = held ? rg[SET][t] : zero_;                                              \
+            const uint32_t lo = pack_bf16x2(__int_as_float(v.x), __int_as_float(v.y));              \
+            const uint32_t hi = pack_bf16x2(__int_as_float(v.z), __int_as_float(v.w));              \
+            *reinterpret_cast<uint2*>(s_ + VXB + row * (VN * 2) + (((lpos >> 1) ^ ((row & 2) << 1)) * 16) + (lpos & 1) * 8) = \
+                make_uint2(lo, hi);                                                                 \
+            if (EXPORT) {                                                                           \
+                const uint32_t to = held && ex_mine[t] && g_col_ok                                  \
+                                        ? ((uint32_t)(ranked ? rk[SET][t] : slot) * (uint32_t)d + (uint32_t)g_col) * 4u : kOutOfRange; \
+                __builtin_amdgcn_raw_buffer_store_b128(v, rsT, to, 0, kNonTemporal);                \
+            }                                                                                       \
+        }                                                                                           \
+    }
+#define GRAM_IDS_TAKE(SET) ids_cur[0] = ids_next[SET][0]; ids_cur[1] = ids_next[SET][1];
+    // The IDs of the first slabs, then the row count, then the slabs.  Memory operations return in
+    // order: the IDs of a slab are fetched two slabs before its data and ahead of them, so that waiting
+    // for them leaves the data of the slabs in between in flight.
+    GRAM_IDS(0, 0)
+    GRAM_IDS(1, 1)
+    const int rows_held = *rows_dev;
+    GRAM_IDS_TAKE(0)
+    GRAM_IDS(0, 2)
+    GRAM_LOAD(0, 0)
+    GRAM_IDS_TAKE(1)
+    GRAM_IDS(1, 3)
+    GRAM_LOAD(1, 1)
+    const int U = rows_held < row_end ? rows_held : row_end;
+    // slabs that hold rows: the trip count of the block's first group, which has the most
+    const int slabs_end = (U + WK - 1) / WK;
+    const int lead = row_begin / WK + z * VGROUPS;
+    const int iters = slabs_end > lead ? (slabs_end - lead + stride - 1) / stride : 0;
+
+    f32x16 acc[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+    // fragment addresses (see k_wgrad_tn_bf16)
+    const int j16 = lane & 15, g16 = lane >> 4;
+    const int f_row = (g16 >> 1) * 8 + (j16 >> 2), f_ch = (g16 & 1) * 2 + ((j16 & 3) >> 1), f_b = (j16 & 1) * 8;
+    int f_offA[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) f_offA[i] = f_row * (VM * 2) + (((wm * 8 + i * 4 + f_ch) ^ ((f_row & 3) << 2)) * 16) + f_b;
+    const int f_offB = VXB + f_row * (VN * 2) + (((wn * 4 + f_ch) ^ ((f_row & 2) << 1)) * 16) + f_b;
+#define GRAM_TR(PTR) __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(PTR))
+#define GRAM_FRAG(P_, ROWB)                                                                         \
+    __builtin_bit_cast(bf16x8, __builtin_shufflevector(GRAM_TR(P_), GRAM_TR((P_) + 4 * (ROWB)), 0, 1, 2, 3, 4, 5, 6, 7))
+#define GRAM_MULTIPLY(STAGE)                                                                        \
+    {                                                                                               \
+        const unsigned char* s_ = smem + ((STAGE) * VGROUPS + grp) * VSTAGEB;                       \
+        _Pragma("unroll") for (int ks = 0; ks < 2; ++ks) {                                          \
+            const bf16x8 fb = GRAM_FRAG(s_ + f_offB + ks * 16 * (VN * 2), VN * 2);                  \
+            _Pragma("unroll") for (int i = 0; i < 2; ++i) {                                         \
+                const bf16x8 fa = GRAM_FRAG(s_ + f_offA[i] + ks * 16 * (VM * 2), VM * 2);           \
+                acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, fb, acc[i], 0, 0, 0);          \
+            }                                                                                       \
+        }                                                                                           \
+    }
+    // slab i sits in register set and LDS stage i % 2, one barrier per slab; a slab past the end parks
+    // zeros
+#define GRAM_ITER(I)                                                                                \
+    GRAM_PARK(I, i + (I), I)                                                                        \
+    GRAM_IDS_TAKE(I)                                                                                \
+    GRAM_IDS(I, i + (I) + 4)                                                                        \
+    GRAM_LOAD(I, i + (I) + 2)                                                                       \
+    __syncthreads();                                                                                \
+    GRAM_MULTIPLY(I)
+    static_assert(VDEPTH == 2, "the set indices of the loop");
+    for (int i = 0; i < iters; i += 2) {
+        GRAM_ITER(0)
+        GRAM_ITER(1)
+    }
+    // the groups' tiles are parked in LDS and added in group order
+    __syncthreads();
+    float* parked = reinterpret_cast<float*>(smem);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            parked[(grp * VM + wm * 64 + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) * VACC_STRIDE + wn * 32 + (lane & 31)] =
+                acc[i][r];
+    __syncthreads();
+    partial += (int64_t)z * d_in * d;
+#pragma unroll
+    for (int h = 0; h < VM * VN / 4 / VTHREADS; ++h) {
+        const int e = tid + h * VTHREADS, row = e / (VN / 4), c4 = e % (VN / 4) * 4;
+        f32x4 s = *reinterpret_cast<const f32x4*>(&parked[row * VACC_STRIDE + c4]);
+#pragma unroll
+        for (int g = 1; g < VGROUPS; ++g) s += *reinterpret_cast<const f32x4*>(&parked[(g * VM + row) * VACC_STRIDE + c4]);
+        if (i0 + row < d_in && c0 + c4 < d) {
+            f32x4* out = reinterpret_cast<f32x4*>(partial + (int64_t)(i0 + row) * d + c0 + c4);
+            *out = accumulate ? *out + s : s;
+        }
+    }
+}
+#undef GRAM_SLOT
+#undef GRAM_IDS
+#undef GRAM_IDS_TAKE
+#undef GRAM_LOAD
+#undef GRAM_PARK
+#undef GRAM_TR
+#undef GRAM_FRAG
+#undef GRAM_MULTIPLY
+#undef GRAM_ITER
+
 __device__ __forceinline__ void split_range(int u_total, int splits, int z, int* kb, int* ke)
 {
     const int chunk = (u_total + splits - 1) / splits;
@@ -1228,7 +1432,7 @@ bool encoder_wgrad(Ctx* c, const void* X, float* dW, hipStream_t s, int64_t firs
                    bool accumulate, const WgradRows* other, float* export_G, const int* rank_of_slot,
                    const WindowMeta* meta)
 {
-    bool exported = false;
+    bool exported = false, direct = false;
     const int d_in = other && other->d_in ? other->d_in : c->cfg.d_in;
     const int d = other && other->d ? other->d : c->cfg.d;
     const int64_t x_rows = other && other->x_rows ? other->x_rows : c->cfg.vocab_n;
@@ -1254,14 +1458,37 @@ bool encoder_wgrad(Ctx* c, const void* X, float* dW, hipStream_t s, int64_t firs
         const int64_t x_bytes = x_rows * d_in * 2, g_bytes = cap * d * 4;
         const int tiles = ((d_in + 255) / 256) * ((d + 255) / 256);
         const WgradExport no_export = {nullptr, nullptr, 0, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-        if (x_bytes < kBufferWindow && g_bytes < kBufferWindow && export_G && !other) {
-            constexpr auto kern = k_wgrad_tn_bf16<kWgradWaves, false, true>;
-            ensure_dynamic_lds<kern>((int)WSMEM);
+        const bool wide = x_bytes >= kBufferWindow || g_bytes >= kBufferWindow;
+        const bool exporting = !wide && export_G && !other;
+        int short_blocks = 0;
+        const int short_tiles = ((d_in + VM - 1) / VM) * ((d + VN - 1) / VN);
+        // Short windows: rows times tiles is the traffic from L2, which is what the short kernel is slower
+        // at.  Kernel and reduction, short against long: 768 x 256 (24 tiles) 12.4 / 20.8 us at 2,500 rows,
+        // 27.4 / 30.6 at 20,000, 45 / 40 at 40,000; 512 x 512 (32) 29.6 / 35.6 at 20,000, 48.9 / 46.6 at
+        // 40,000.  With more than 32 tiles there are fewer than 8 ranges and the line lies lower: 768 x 400
+        // (42) 30.4 / 31.2 at 12,000; 776 x 392 (49) 32.7 / 30.3 at 12,000, 22.9 / 25.7 at 6,400.
+        const bool is_short = !wide && rows_bound * short_tiles <= (short_tiles <= 32 ? 650000 : 450000);
+        if (is_short) {
+            // ranges of rows: about a block per CU; a handful of slabs is one range, whose tiles go
+            // straight to dW (300 rows: 8.4 us against 10.0; at 1,000 the reduction launch pays)
+            int64_t ranges = 256 / short_tiles;
+            if (ranges > slabs_bound / VGROUPS) ranges = slabs_bound / VGROUPS;
+            if (slabs_bound <= 20) ranges = 1;
+            const int most = wgrad_splits_dims(d_in, d, true);      // what the partials have room for
+            if (ranges > most) ranges = most;
+            S = (int)(ranges >= 8 ? ranges / 8 * 8 : ranges >= 4 ? 4 : ranges >= 2 ? 2 : 1);
+            short_blocks = S >= 8 ? short_tiles * S : (short_tiles * S + 7) / 8 * 8;
+        }
+        direct = is_short && S == 1;
+        float* out = direct ? dW : c->wg_partial;
+        const int add_here = direct && accumulate ? 1 : 0;
+        const int waves_threads = is_short ? VTHREADS : kWgradWaves * 64;
+        if (exporting) {
             WgradExport ex = no_export;
             ex.G_total = export_G;
             ex.rank_of_slot = rank_of_slot;
             if (meta) {
-                int64_t mb = (rows_bound + kWgradWaves * 64 - 1) / (kWgradWaves * 64);
+                int64_t mb = (rows_bound + waves_threads - 1) / waves_threads;
                 ex.meta_blocks = (int)(mb < 1 ? 1 : (mb > 64 ? 64 : mb));
                 ex.cnt_of_slot = c->cnt_of_slot;
                 ex.slot_of = c->slot_of;
@@ -1270,11 +1497,29 @@ bool encoder_wgrad(Ctx* c, const void* X, float* dW, hipStream_t s, int64_t firs
                 ex.u_total_dev = meta->u_total_dev;
                 ex.scal = c->scal;
             }
-            launch_smem(c, KID_WGRAD_BF16, kern, dim3((unsigned)(tiles * S + ex.meta_blocks)), dim3(kWgradWaves * 64), WSMEM, s,
-                        static_cast<const uint16_t*>(X), (uint32_t)x_bytes, ids, rows, (uint32_t)g_bytes,
-                        rows_dev, d_in, d, pad_id, S, c->wg_partial, row_begin, row_end, ex);
+            if (is_short) {
+                constexpr auto kern = k_wgrad_short<true, true>;
+                ensure_dynamic_lds<kern>((int)VSMEM);
+                launch_smem(c, KID_WGRAD_BF16, kern, dim3((unsigned)(short_blocks + ex.meta_blocks)), dim3(VTHREADS), VSMEM,
+                            s, static_cast<const uint16_t*>(X), (uint32_t)x_bytes, ids, rows, (uint32_t)g_bytes,
+                            rows_dev, d_in, d, pad_id, S, out, row_begin, row_end, add_here, ex);
+            } else {
+                constexpr auto kern = k_wgrad_tn_bf16<kWgradWaves, false, true>;
+                ensure_dynamic_lds<kern>((int)WSMEM);
+                launch_smem(c, KID_WGRAD_BF16, kern, dim3((unsigned)(tiles * S + ex.meta_blocks)), dim3(kWgradWaves * 64),
+                            WSMEM, s, static_cast<const uint16_t*>(X), (uint32_t)x_bytes, ids, rows, (uint32_t)g_bytes,
+                            rows_dev, d_in, d, pad_id, S, c->wg_partial, row_begin, row_end, ex);
+            }
             exported = true;
-        } else if (x_bytes < kBufferWindow && g_bytes < kBufferWindow) {
+        } else if (is_short) {
+            constexpr auto listed = k_wgrad_short<false, true>;
+            constexpr auto plain = k_wgrad_short<false, false>;
+            ensure_dynamic_lds<listed>((int)VSMEM);
+            ensure_dynamic_lds<plain>((int)VSMEM);
+            launch_smem(c, KID_WGRAD_BF16, ids ? listed : plain, dim3((unsigned)short_blocks), dim3(VTHREADS), VSMEM, s,
+                        static_cast<const uint16_t*>(X), (uint32_t)x_bytes, ids, rows, (uint32_t)g_bytes,
+                        rows_dev, d_in, d, pad_id, S, out, row_begin, row_end, add_here, no_export);
+        } else if (!wide) {
             constexpr auto kern = k_wgrad_tn_bf16<kWgradWaves, false>;
             ensure_dynamic_lds<kern>((int)WSMEM);
             launch_smem(c, KID_WGRAD_BF16, kern, dim3((unsigned)(tiles * S)), dim3(kWgradWaves * 64), WSMEM, s,
@@ -1292,6 +1537,7 @@ bool encoder_wgrad(Ctx* c, const void* X, float* dW, hipStream_t s, int64_t firs
                static_cast<const float*>(X), ids, rows, rows_dev, d_in, d, pad_id, S,
                c->wg_partial, row_begin, row_end);
     }
+    if (direct) return exported;
     const int64_t n4 = (int64_t)d_in * d / 4;
     launch(c, KID_WGRAD_REDUCE, k_wgrad_reduce, dim3((unsigned)((n4 + kBlock - 1) / kBlock)), dim3(kBlock), s,
            reinterpret_cast<const float4*>(c->wg_partial), n4, S, reinterpret_cast<float4*>(dW), accumulate ? 1 : 0);
