@@ -87,7 +87,12 @@ const char* validate(const gram_config* cfg, Derived* dv)
     dv->cap_chunk = dv->cap_u > dv->cap_total ? dv->cap_u : dv->cap_total;
     dv->n_sort_max = cfg->max_positions > dv->cap_total ? cfg->max_positions : dv->cap_total;
     dv->tiles_scan = (cfg->max_positions + kScanTile - 1) / kScanTile + 1;
-    dv->tiles_seg = (cfg->max_positions + kSegRows - 1) / kSegRows;
+    {   // tiles of the segment reduction, over every batch size up to the largest
+        const int64_t small = cfg->max_positions < kSegSmallBatch ? cfg->max_positions : kSegSmallBatch;
+        const int64_t tiles_small = (small + kSegRowsSmall - 1) / kSegRowsSmall;
+        dv->tiles_seg = (cfg->max_positions + kSegRows - 1) / kSegRows;
+        if (dv->tiles_seg < tiles_small) dv->tiles_seg = tiles_small;
+    }
     dv->splits = wgrad_splits_for(*cfg);
     return nullptr;
 }
@@ -109,7 +114,7 @@ int64_t layout(Ctx* c, const gram_config& cfg, const Derived& dv, char* base)
     int* vals1 = (int*)take(dv.n_sort_max * 4);
     int* table = (int*)take(table_elems_for(dv.n_sort_max) * 4);
     int* gtot = (int*)take((1 << kMaxDigitBits) * 4);
-    int* tile_sums = (int*)take(dv.tiles_scan * 3 * 4);     // three figures per scan tile
+    int* tile_sums = (int*)take(dv.tiles_scan * 4 * 4);     // four figures per scan tile
     const int64_t count_words = count_table_words(cfg.vocab_n, cfg.max_positions);
     const int64_t count_ids = count_words ? align_up(cfg.vocab_n, 128) : 0;
     uint32_t* cnt_table = (uint32_t*)take(count_words * 4);
@@ -119,7 +124,7 @@ int64_t layout(Ctx* c, const gram_config& cfg, const Derived& dv, char* base)
     int* seg_of_row = (int*)take(cfg.max_positions * 4);
     int* uniq_ws = (int*)take(dv.cap_u * 4);
     int* seg_slot = (int*)take(dv.cap_u * 4);
-    int* long_list = (int*)take(dv.tiles_seg * 4);
+    int4* long_list = (int4*)take(dv.tiles_seg * 16);
     const bool dense = cfg.buffer_layout == GRAM_BUFFER_DENSE;
     int* slot_of = (int*)take(dense ? 1 : (int64_t)cfg.vocab_n * 4);
     int* id_of_slot = (int*)take(dense ? 1 : dv.cap_total * 4);
@@ -207,7 +212,7 @@ constexpr int64_t kStaticOffVals1 = kStaticOffVals0 + static_align(kStaticMax * 
 constexpr int64_t kStaticOffTable = kStaticOffVals1 + static_align(kStaticMax * 4);
 constexpr int64_t kStaticOffGtot = kStaticOffTable + static_align(kStaticTableElems * 4);
 constexpr int64_t kStaticOffTiles = kStaticOffGtot + static_align((1 << kMaxDigitBits) * 4);
-constexpr int64_t kStaticOffOffsets = kStaticOffTiles + static_align((kStaticMax / kScanTile + 2) * 3 * 4);
+constexpr int64_t kStaticOffOffsets = kStaticOffTiles + static_align((kStaticMax / kScanTile + 2) * 4 * 4);
 constexpr int64_t kStaticOffSegOfRow = kStaticOffOffsets + static_align((kStaticMax + 2) * 4);
 constexpr int64_t kStaticOffUniqWs = kStaticOffSegOfRow + static_align(kStaticMax * 4);
 constexpr int64_t kStaticBytes = kStaticOffUniqWs + static_align(kStaticMax * 4);

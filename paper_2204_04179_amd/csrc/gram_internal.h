@@ -18,10 +18,17 @@ constexpr int kBlock = 256;             // threads of the integer / streaming ke
 constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int kMaxDigitBits = 10;       // radix digit width limit (1024 LDS bins per wave)
 constexpr int kScanTile = 1024;         // rows per block in the flag-scan kernels
-constexpr int kSegRows = 32;            // sorted rows per tile of the segment reduction
-constexpr int kSegLong = 64;            // segments with at least this many rows are reduced tile by tile ...
-constexpr int kSegLongSmall = 32;       // ... or this many when the batch has at most kSegSmallBatch positions
-constexpr int kSegSmallBatch = 65536;
+// Sorted rows per tile of the segment reduction, and the length from which a segment is reduced tile by
+// tile: a tile and the end of a shorter segment that starts in it are at most 2 * rows - 1 <= 63 rows, one
+// per lane of a wave.
+constexpr int kSegRows = 32;
+constexpr int kSegRowsSmall = 16;       // batches of at most kSegSmallBatch positions
+constexpr int kSegSmallBatch = 16384;
+__host__ __device__ constexpr int seg_rows_for(int64_t n) { return n <= kSegSmallBatch ? kSegRowsSmall : kSegRows; }
+// What the dedup leaves per sorted row (seg_of_row): the segment, and two flags.
+constexpr int kRowHead = (int)0x80000000u;   // first row of its segment
+constexpr int kRowLong = 1 << 30;            // segment of at least seg_rows_for(m) rows
+constexpr int kRowSeg = kRowLong - 1;
 constexpr int kLightMax = 32;           // items with more positions are gathered by a separate copy kernel
 constexpr int kSlotNew = 1 << 30;       // flag in seg_slot: the buffer row is created by this step
 constexpr int kCountMinM = 8193;        // the counting dedup: positions per batch, at least
@@ -59,7 +66,7 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
 }
 
 // Device scalars (ctx->scal[...]).
-enum Scalar { kSU = 0, kSUTotal, kSErr, kSUBase, kSLongCount, kSFlushN, kSChunkN, kSUNext, kSCount };
+enum Scalar { kSU = 0, kSUTotal, kSErr, kSUBase, kSLongCount, kSFlushN, kSChunkN, kSUNext, kSPadSeg, kSCount };
 
 // Device-latched error bits (scal[kSErr]).
 constexpr int kErrBitRange = 1;
@@ -112,11 +119,11 @@ struct Ctx {
     uint2* id_info = nullptr;       // [IDs] place within the tile of IDs, count
     int* id_tiles = nullptr;        // [3][tiles of IDs]
     int* offsets = nullptr;     // [cap_u + 1] start row of each segment in sorted order
-    int* seg_of_row = nullptr;  // [M_max] segment index of each sorted row
+    int* seg_of_row = nullptr;  // [M_max] segment of each sorted row, with kRowHead / kRowLong
     int* uniq_ws = nullptr;     // [cap_u] copy of uniq of the current batch
     int* seg_slot = nullptr;    // [cap_u] buffer row of each segment; kSlotNew set = row is new, -1 = dropped
     int* scal = nullptr;        // [kSCount] device scalars, see enum Scalar
-    int* long_list = nullptr;   // [tiles_seg] head tiles of the long segments of the current batch
+    int4* long_list = nullptr;  // [tiles_seg] long segments of the current batch: first tile, parts, row code, padding
     int* slot_of = nullptr;     // [N] buffer row of an ID, -1 = absent
     int* id_of_slot = nullptr;  // [cap_total]
     long long* cnt_of_slot = nullptr; // [cap_total] occurrences of the item of each row in the window

@@ -335,12 +335,13 @@ __device__ __forceinline__ bool is_head(const int* __restrict__ sk, int r)
     return r == 0 || sk[r] != sk[r - 1];
 }
 
-// Two launches over tiles of kScanTile sorted rows.  The first leaves three figures per tile
-// (tile_info[t], [T + t], [2 T + t] with T tiles): the number of segment heads in the tile, how
-// many of those items have no row in the window's buffer yet, and the row of the tile's first
-// head (-1: none).  The second turns them into everything that is known per unique item:
+// Two launches over tiles of kScanTile sorted rows.  The first leaves four figures per tile
+// (tile_info[t], [T + t], [2 T + t], [3 T + t] with T tiles): the number of segment heads in the tile,
+// how many of those items have no row in the window's buffer yet, and the rows of the tile's first and
+// last head (-1: none).  The second turns them into everything that is known per unique item:
 // uniq, offsets, counts (a head's segment ends at the next head, which may lie tiles ahead: the
-// third figure finds it), the inverse index, and - when the context keeps a slot table - the
+// third figure finds it), the inverse index, per sorted row its segment with the flags of the segment
+// reduction (the segment of a tile's first rows may have started tiles before: the fourth figure), and - when the context keeps a slot table - the
 // buffer row each item WOULD get from the next gram_grad_accumulate (seg_slot: its row, or for
 // an item new to the window the next free row with kSlotNew set, in ascending-ID order, or -1
 // when the buffer is full).  Nothing of the slot table is written here: the accumulate step
@@ -365,26 +366,30 @@ constexpr int kNoRow = 0x7fffffff;
 
 __global__ __launch_bounds__(kBlock) void k_heads_count(const int* __restrict__ sk, int n,
                                                         const int* __restrict__ slot_of,
-                                                        int* __restrict__ tile_info, int first_step)
+                                                        int* __restrict__ tile_info, int first_step,
+                                                        int* __restrict__ scal)
 {
     __shared__ int sm[kWavesPerBlock];
     const int r0 = blockIdx.x * kScanTile + threadIdx.x * 4;
-    int s = 0, fresh = 0, first = kNoRow;
+    if (blockIdx.x == 0 && threadIdx.x == 0) scal[kSPadSeg] = -1;      // the emit launch sets it if there is padding
+    int s = 0, fresh = 0, first = kNoRow, last = -1;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
         if (r0 + i < n && is_head(sk, r0 + i)) {
             ++s;
             if (first == kNoRow) first = r0 + i;
+            last = r0 + i;
             // (in the first step of a window the buffer holds nothing: every item is new)
             if (slot_of && (first_step || slot_of[sk[r0 + i]] < 0)) ++fresh;
         }
     const int tot = block_sum(s, sm);
     const int tot_fresh = block_sum(fresh, sm);
-    const int row = block_min(first, sm);
+    const int row = block_min(first, sm), end_row = -block_min(-last, sm);
     if (threadIdx.x == 0) {
         tile_info[blockIdx.x] = tot;
         tile_info[gridDim.x + blockIdx.x] = tot_fresh;
         tile_info[2 * gridDim.x + blockIdx.x] = row == kNoRow ? -1 : row;
+        tile_info[3 * gridDim.x + blockIdx.x] = end_row;
     }
 }
 
@@ -393,7 +398,7 @@ __global__ __launch_bounds__(kBlock) void k_heads_emit(
     int* __restrict__ uniq, int* __restrict__ inverse, int* __restrict__ counts,
     int* __restrict__ offsets, int* __restrict__ seg_of_row, int* __restrict__ uniq_ws,
     int* __restrict__ u_out, const int* __restrict__ slot_of, int* __restrict__ seg_slot,
-    int* __restrict__ scal, int first_step, int cap_total)
+    int* __restrict__ scal, int first_step, int cap_total, int pad_id)
 {
     __shared__ int sm[kWavesPerBlock];
     __shared__ int s_rows[kScanTile + 1];     // rows of the tile's heads, then the next head's row
@@ -420,10 +425,12 @@ __global__ __launch_bounds__(kBlock) void k_heads_emit(
     const int prev = (r0 > 0 && r0 < n) ? sk[r0 - 1] : -1;
     const int u_base = (slot_of && !first_step) ? scal[kSUTotal] : 0;   // a flush leaves the old count behind
     const int ahead0 = (int)blockIdx.x + 1 + (int)threadIdx.x < T ? tile_info[2 * T + blockIdx.x + 1 + threadIdx.x] : -1;
-    int pre = 0, pre_fresh = 0;
+    int pre = 0, pre_fresh = 0, before = -1;
     for (int t = threadIdx.x; t < (int)blockIdx.x; t += kBlock) {
         pre += tile_info[t];
         pre_fresh += tile_info[T + t];
+        const int h = tile_info[3 * T + t];
+        before = h > before ? h : before;
     }
     bool f[4];
     int old[4];
@@ -440,6 +447,8 @@ __global__ __launch_bounds__(kBlock) void k_heads_emit(
     }
     pre = block_sum(pre, sm);
     pre_fresh = block_sum(pre_fresh, sm);
+    before = -block_min(-before, sm);        // the last head before this tile (head rows ascend)
+    const int long_rows = seg_rows_for(n);
     if (threadIdx.x == 0) s_next = kNoRow;
     int total, total_fresh;
     const int local = block_excl_scan(s, &total, sm);
@@ -471,9 +480,14 @@ __global__ __launch_bounds__(kBlock) void k_heads_emit(
         if (r < n) {
             run += f[i] ? 1 : 0;
             const int seg = run - 1;
-            seg_of_row[r] = seg;
+            // li heads of the tile lie before row r: s_rows[li - 1] (this row, if it is one) starts its
+            // segment, s_rows[li] the next one
+            const int li_in = li + (f[i] ? 1 : 0);
+            const int start = li_in > 0 ? s_rows[li_in - 1] : before;
+            seg_of_row[r] = seg | (f[i] ? kRowHead : 0) | (s_rows[li_in] - start >= long_rows ? kRowLong : 0);
             inverse[posn[i]] = seg;
             if (f[i]) {
+                if (key[i] == pad_id) scal[kSPadSeg] = seg;
                 uniq[seg] = key[i];
                 uniq_ws[seg] = key[i];
                 offsets[seg] = r;
@@ -609,14 +623,15 @@ __device__ __forceinline__ int rank_by_comparison(const int* keys, int n, int p0
 }
 
 __global__ __launch_bounds__(kSmallThreads) void k_rank_small(const int* __restrict__ ids, int n, int vocab_n,
-                                                              int fix_key, int* __restrict__ err,
+                                                              int fix_key, int* __restrict__ scal,
                                                               int* __restrict__ sorted_keys, int* __restrict__ perm)
 {
     extern __shared__ __attribute__((aligned(16))) int lds[];
     __shared__ int red[kSmallThreads];
     constexpr int kLog2P = 5;
     static_assert(1 << kLog2P == kRankP, "positions per block");
-    load_small_ids(ids, n, vocab_n, fix_key, err, blockIdx.x == 0, lds);
+    if (blockIdx.x == 0 && threadIdx.x == 0) scal[kSPadSeg] = -1;      // the emit launch sets it if there is padding
+    load_small_ids(ids, n, vocab_n, fix_key, scal + kSErr, blockIdx.x == 0, lds);
     __syncthreads();
     const int p0 = blockIdx.x * kRankP;
     const int rank = rank_by_comparison(lds, n, p0, kLog2P, red);
@@ -635,7 +650,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_emit_small(
     int* __restrict__ inverse, int* __restrict__ counts, int* __restrict__ offsets,
     int* __restrict__ seg_of_row, int* __restrict__ uniq_ws, int* __restrict__ u_ws,
     int* __restrict__ u_out, const int* __restrict__ slot_of, int* __restrict__ seg_slot,
-    int* __restrict__ scal, int first_step, int cap_total)
+    int* __restrict__ scal, int first_step, int cap_total, int pad_id)
 {
     constexpr int NR = kSmallThreads * R;
     // sorted IDs | segment of every row (16-bit) | first row of every segment (16-bit)
@@ -652,6 +667,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_emit_small(
         __shared__ __attribute__((aligned(16))) int kin[kFusedMaxN];
         __shared__ int red[kSmallThreads], pos_of[kFusedMaxN];
         load_small_ids(ids, n, vocab_n, fix_key, err, true, kin);
+        if (tid == 0) scal[kSPadSeg] = -1;
         __syncthreads();
         const int rank = rank_by_comparison(kin, n, 0, log2p, red);
         if (tid < n && (unsigned)rank < (unsigned)n) {
@@ -701,8 +717,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_emit_small(
     }
     __syncthreads();
     if (row < n) {
-        const int seg = lseg[row];
-        seg_of_row[row] = seg;
+        const int seg = lseg[row], start = loff[seg], end = seg + 1 < total ? (int)loff[seg + 1] : n;
+        seg_of_row[row] = seg | (row == start ? kRowHead : 0) | (end - start >= seg_rows_for(n) ? kRowLong : 0);
         inverse[posn] = seg;
     }
     if (row < total) {
@@ -710,6 +726,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_emit_small(
         const int k = sk[r];
         uniq[row] = k;
         uniq_ws[row] = k;
+        if (k == pad_id) scal[kSPadSeg] = row;
         offsets[row] = r;
         counts[row] = (row + 1 < total ? (int)loff[row + 1] : n) - r;
     }
@@ -794,7 +811,7 @@ __device__ __forceinline__ int count_id(int raw, int vocab_n, int fix_key, bool*
 }
 
 __global__ __launch_bounds__(kCountThreads) void k_ids_count(const int* __restrict__ ids, int n, int vocab_n,
-                                                             int fix_key, int pitch, int* __restrict__ err,
+                                                             int fix_key, int pitch, int* __restrict__ scal,
                                                              uint32_t* __restrict__ table)
 {
     extern __shared__ __attribute__((aligned(16))) uint32_t cnt[];
@@ -813,7 +830,8 @@ __global__ __launch_bounds__(kCountThreads) void k_ids_count(const int* __restri
     const unsigned long long m0 = __ballot(mine && id == id0);
     if (mine && id != id0) atomicAdd(&cnt[id >> 1], 1u << ((id & 1) * 16));
     if (lane_id() == 0 && m0) atomicAdd(&cnt[id0 >> 1], (uint32_t)__popcll(m0) << ((id0 & 1) * 16));
-    if (bad && p < n) atomicOr(err, kErrBitRange);
+    if (bad && p < n) atomicOr(scal + kSErr, kErrBitRange);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) scal[kSPadSeg] = -1;    // k_ids_emit sets it if there is padding
     __syncthreads();
     uint32_t* row = table + ((int64_t)blockIdx.x * pitch + lo) / 2;
     for (int i = tid * 4; i < words; i += kCountThreads * 4)
@@ -889,7 +907,7 @@ __global__ __launch_bounds__(kCountThreads) void k_ids_emit(
     int* __restrict__ perm, int* __restrict__ uniq, int* __restrict__ inverse, int* __restrict__ counts,
     int* __restrict__ offsets, int* __restrict__ seg_of_row, int* __restrict__ uniq_ws, int* __restrict__ u_out,
     const int* __restrict__ slot_of, int* __restrict__ seg_slot, int* __restrict__ scal, int first_step,
-    int cap_total)
+    int cap_total, int pad_id)
 {
     extern __shared__ __attribute__((aligned(16))) uint16_t cnt16[];      // (position blocks) count so far per ID
     __shared__ int s_pos[kCountTilesMax], s_item[kCountTilesMax], s_new[kCountTilesMax];
@@ -959,6 +977,7 @@ __global__ __launch_bounds__(kCountThreads) void k_ids_emit(
         if (info.y > 0) {                                                 // the ID occurs
             uniq[seg] = id;
             uniq_ws[seg] = id;
+            if (id == pad_id) scal[kSPadSeg] = seg;
             offsets[seg] = first_row;
             counts[seg] = (int)info.y;
             if (slot_of) {
@@ -1005,11 +1024,11 @@ __global__ __launch_bounds__(kCountThreads) void k_ids_emit(
         __syncthreads();
     }
     if (mine) {
-        const int pos = first_row + pre + before + below;
+        const int at = pre + before + below, pos = first_row + at;
         inverse[p] = seg;
         if ((unsigned)pos < (unsigned)n) {      // pos < n always holds; the test keeps a logic error from
             perm[pos] = p;                       // becoming a stray store
-            seg_of_row[pos] = seg;
+            seg_of_row[pos] = seg | (at == 0 ? kRowHead : 0) | ((int)info.y >= seg_rows_for(n) ? kRowLong : 0);
         }
     }
 }
@@ -1032,14 +1051,14 @@ bool unique_by_count(Ctx* c, const int* ids, int n, int fix_key, int* uniq, int*
     c->sorted_keys = nullptr;
     c->perm = c->vals[0];
     launch_smem(c, KID_IDS_COUNT, k_ids_count, dim3(rows, parts), dim3(kCountThreads), lds, s, ids, n, c->cfg.vocab_n,
-                fix_key, pitch, c->scal + kSErr, c->cnt_table);
+                fix_key, pitch, c->scal, c->cnt_table);
     launch(c, KID_IDS_SCAN, k_ids_scan, dim3(T), dim3(kBlock), s, c->cnt_table, rows, pitch, slot_of, first_step,
            c->cfg.vocab_n, c->id_info, c->id_tiles);
     const int id_blocks = (int)((N + kCountThreads - 1) / kCountThreads);
     launch_smem(c, KID_IDS_EMIT, k_ids_emit, dim3(rows + id_blocks, parts), dim3(kCountThreads), lds, s, ids, n, c->key_bits,
                 c->cfg.vocab_n, fix_key, pitch, rows, reinterpret_cast<const uint16_t*>(c->cnt_table), c->id_info,
                 c->id_tiles, T, c->perm, uniq, inverse, counts, c->offsets, c->seg_of_row, c->uniq_ws, u_out, slot_of,
-                c->seg_slot, c->scal, first_step, (int)c->cap_total);
+                c->seg_slot, c->scal, first_step, (int)c->cap_total, c->cfg.pad_id);
     return true;
 }
 
@@ -1055,10 +1074,10 @@ void unique_from_sorted(Ctx* c, int n, int* uniq, int* inverse, int* counts, int
     const int tiles = (n + kScanTile - 1) / kScanTile;
     const int* slot_of = prospect ? c->slot_of : nullptr;
     launch(c, KID_HEADS_COUNT, k_heads_count, dim3(tiles), dim3(kBlock), s, c->sorted_keys, n, slot_of,
-           c->tile_sums, first_step);
+           c->tile_sums, first_step, c->scal);
     launch(c, KID_HEADS_EMIT, k_heads_emit, dim3(tiles), dim3(kBlock), s, c->sorted_keys, c->perm, n,
            c->tile_sums, uniq, inverse, counts, c->offsets, c->seg_of_row, c->uniq_ws, u_out, slot_of,
-           c->seg_slot, c->scal, first_step, (int)c->cap_total);
+           c->seg_slot, c->scal, first_step, (int)c->cap_total, c->cfg.pad_id);
 }
 
 template <int R, bool FUSED>
@@ -1072,7 +1091,7 @@ static void launch_emit_small(Ctx* c, const int* ids, int n, int log2p, int fix_
     launch_smem(c, KID_UNIQUE_SMALL, kern, dim3(blocks), dim3(kSmallThreads), lds, s, ids, n, log2p, c->cfg.vocab_n,
                 fix_key, c->scal + kSErr, c->sorted_keys, c->perm, uniq, inverse, counts, c->offsets, c->seg_of_row,
                 c->uniq_ws, c->scal + kSU, u_out, prospect ? c->slot_of : nullptr, c->seg_slot, c->scal, first_step,
-                (int)c->cap_total);
+                (int)c->cap_total, c->cfg.pad_id);
 }
 
 bool unique_small(Ctx* c, const int* ids, int n, int fix_key, int* uniq, int* inverse, int* counts,
@@ -1090,7 +1109,7 @@ bool unique_small(Ctx* c, const int* ids, int n, int fix_key, int* uniq, int* in
     const size_t lds = (size_t)((n + 3) & ~3) * sizeof(int);
     ensure_dynamic_lds<k_rank_small>(kSmallMaxN * (int)sizeof(int));
     launch_smem(c, KID_RANK_SMALL, k_rank_small, dim3((unsigned)((n + kRankP - 1) / kRankP)), dim3(kSmallThreads), lds, s,
-                ids, n, c->cfg.vocab_n, fix_key, c->scal + kSErr, c->sorted_keys, c->perm);
+                ids, n, c->cfg.vocab_n, fix_key, c->scal, c->sorted_keys, c->perm);
     if (n <= 8 * kSmallThreads)
         launch_emit_small<8, false>(c, ids, n, 0, fix_key, uniq, inverse, counts, u_out, s, prospect, first_step);
     else

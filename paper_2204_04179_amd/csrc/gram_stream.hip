@@ -193,7 +193,7 @@ __global__ __launch_bounds__(kBlock) void k_gather_heavy(const f32x4* __restrict
     const int rows = (int)(r0 + rows_per_block < m ? rows_per_block : m - r0);
     int heavy = 0;
     if ((int)threadIdx.x < rows) {
-        const int j = seg_of_row[r0 + threadIdx.x];
+        const int j = seg_of_row[r0 + threadIdx.x] & kRowSeg;
         heavy = offsets[j + 1] - offsets[j] > kLightMax;
         s_src[threadIdx.x] = heavy ? j : -1;
         s_dst[threadIdx.x] = perm[r0 + threadIdx.x];
@@ -579,20 +579,28 @@ void assign_slots(Ctx* c, hipStream_t s)
 //
 // Rows of dH are visited in the sorted order of the batch (perm), where the
 // occurrences of one item are adjacent and in ascending position.  The sorted
-// rows are cut into tiles of kSegRows.
-//  * A short segment (< seg_long rows: kSegLong, or kSegLongSmall for small batches) is summed, whole and in order, by the
+// rows are cut into tiles of TR = seg_rows_for(m) rows.
+//  * A short segment (< TR rows) is summed, whole and in order, by the
 //    tile that holds its first row, even where it runs past the tile's end; it
 //    needs no partial result.
 //  * A long segment is summed tile by tile into partial rows (seg_last for the
 //    tile where it starts, seg_first for every later tile), and k_seg_combine
 //    adds the partials in ascending tile order.
-// Destination codes kept per row in LDS:
+//
+// What bounds it: HBM where the batch is large (5.3 TB/s), and on small ones the chain of dependent
+// round trips to memory.  A wave holds one sorted row per lane (a tile and the end of its last segment
+// are at most 2 TR - 1 <= 63 rows): the rows' segments, flags and positions come with one load each, ballots
+// over the flags tell what the tile has to sum, and the rows of dH are requested next.  (Looking the
+// bounds up through seg_of_row, offsets and uniq took three round trips more.)  The rows of the buffer that a step adds to
+// are fetched with the rows of dH they belong to: fetched when a segment ends, each drained all loads in flight.
+// A row is addressed by a descriptor of its own, built from scalars: one of zero length reads zeros and
+// touches no memory, so the loads of a group are unconditional.
 constexpr int kDstNone = -1;    // nothing to write (dropped item)
 constexpr int kDstFirst = -2;   // partial row seg_first[tile]
 constexpr int kDstLast = -3;    // partial row seg_last[tile]
-constexpr int kSegMaxRows = kSegRows + kSegLong;
-constexpr int kSegUnroll = 16;
 constexpr int kSegPlainLoads = 16384;   // batches of at most this many positions read dH with plain loads
+constexpr int kRowDescFlags = 0x00027000;   // raw buffer: 32-bit elements, no swizzle
+typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ void write_final(float4* __restrict__ G, int cols4, int col, int code,
                                             bool is_pad, float4 acc)
@@ -609,124 +617,123 @@ __device__ __forceinline__ void write_final(float4* __restrict__ G, int cols4, i
     }
 }
 
-template <bool PLAIN>      // dH read with plain instead of non-temporal loads
+// Row `row` of a matrix of cols4 float4 columns (row < 0: an empty row), lane's column offset col_off.
+template <bool PLAIN>
+__device__ __forceinline__ f32x4 load_row(const float4* base, int row, int cols4, uint32_t col_off)
+{
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float4*>(base + (int64_t)(row < 0 ? 0 : row) * cols4), 0, row < 0 ? 0 : cols4 * 16, kRowDescFlags);
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, col_off, 0, PLAIN ? 0 : 2));
+}
+
+// TR: rows per tile.  UN: rows in flight.  PLAIN: dH read with plain instead of non-temporal loads (a row is
+// read exactly once; batches of a few thousand positions often still have it in a cache).  OLD: the
+// buffer may hold rows of the batch's items already (not so in the first step of a window).
+template <int TR, int UN, bool PLAIN, bool OLD>
 __global__ __launch_bounds__(kBlock) void k_seg_reduce(
     const float4* __restrict__ dH, const int* __restrict__ perm, const int* __restrict__ seg_of_row,
     const int* __restrict__ offsets, const int* __restrict__ uniq_ws,
-    const int* __restrict__ seg_slot, int n, int cols4, int pad_id, float4* __restrict__ G,
+    const int* __restrict__ seg_slot, int n, int cols4, float4* __restrict__ G,
     float4* __restrict__ seg_first, float4* __restrict__ seg_last, int* __restrict__ scal,
-    int* __restrict__ long_list, int seg_long, int* __restrict__ slot_of, int* __restrict__ id_of_slot,
+    int4* __restrict__ long_list, int* __restrict__ slot_of, int* __restrict__ id_of_slot,
     long long* __restrict__ cnt_of_slot)
 {
-    __shared__ __attribute__((aligned(16))) int s_src[kSegMaxRows];    // dH row of each sorted row, -1 = padding (not read)
-    __shared__ __attribute__((aligned(16))) int s_dst[kSegMaxRows];    // 0 = keep adding; else destination code + 4 (see below)
-    static_assert(kSegMaxRows % kSegUnroll == 0, "a group of rows is read from the tables as whole 16-byte pieces");
-    __shared__ int s_pad[kSegMaxRows];
-
-    const int t = blockIdx.x;
-    const int r0 = t * kSegRows;
-    const int r1 = r0 + kSegRows < n ? r0 + kSegRows : n;
+    static_assert(2 * TR <= kWave, "a tile and the end of its last segment fit the lanes of a wave");
+    const int t = blockIdx.x, lane = lane_id();
+    const int r0 = t * TR, r = r0 + lane;
+    const int info = r < n ? seg_of_row[r] : kRowHead;       // (past the end: closes the last segment)
+    const int p = r < n ? perm[r] : 0;
+    const int pad_seg = scal[kSPadSeg];
     // slot_of given: the buffer rows in seg_slot were worked out by the dedup and are committed
-    // here, each item by the thread that meets the first row of its segment (one tile holds it)
-    const bool commit = slot_of != nullptr && blockIdx.y == 0;
+    // here, each item by the lane that holds the first row of its segment (one tile holds it)
+    const bool commit = slot_of != nullptr && blockIdx.y == 0 && threadIdx.x < kWave;
     if (commit && t == 0 && threadIdx.x == 0) scal[kSUTotal] = scal[kSUNext];
 
-    // first and one-past-last sorted row this tile sums
-    int a, b;
-    {
-        const int sg = seg_of_row[r0];
-        const int o0 = offsets[sg], o1 = offsets[sg + 1];
-        a = (o0 < r0 && o1 - o0 < seg_long) ? o1 : r0;
-        const int sl = seg_of_row[r1 - 1];
-        const int p0 = offsets[sl], p1 = offsets[sl + 1];
-        b = (p1 - p0 < seg_long) ? p1 : r1;
+    const unsigned long long heads = __ballot((info & kRowHead) != 0), longs = __ballot((info & kRowLong) != 0);
+    const int tile_rows = n - r0 < TR ? n - r0 : TR;         // at least 1
+    const unsigned long long in_tile = (1ull << tile_rows) - 1;
+    const unsigned long long starts = (heads | longs) & in_tile;
+    if (starts == 0) return;      // the tile lies inside a short segment owned by an earlier tile
+    // first and one-past-last lane whose row this tile sums
+    const int a = __builtin_ctzll(starts);
+    const int b = (longs >> (tile_rows - 1) & 1) ? tile_rows : __builtin_ctzll(heads & ~in_tile);
+
+    const int seg = info & kRowSeg;
+    const bool mine = lane >= a && lane < b, is_long = (info & kRowLong) != 0;
+    const bool is_pad = seg == pad_seg, ends = lane < kWave - 1 && (heads >> (lane + 1) & 1);
+    const bool begins = (info & kRowHead) != 0;
+    // a long segment's part of the tile ends with the segment or the tile; it is the segment's first
+    // part if the segment starts in the tile
+    const bool part_ends = mine && is_long && (ends || lane == tile_rows - 1);
+    const bool is_first_part = (heads & in_tile & (2ull << lane) - 1) != 0;
+    const bool head_here = begins && lane < tile_rows;
+    const bool need_slot = (mine && !is_long && ends) || (part_ends && is_first_part) || (commit && head_here);
+    const int slot = need_slot ? seg_slot[seg] : 0;
+    int o0 = 0, o1 = 0, id = 0;
+    if ((commit && head_here) || (part_ends && is_first_part)) {
+        o0 = offsets[seg];
+        o1 = offsets[seg + 1];
+        id = uniq_ws[seg];
     }
-    if (a >= r1) return;      // the tile lies inside a short segment owned by an earlier tile
+    // per row: source (-1: padding, not read), and 0 = keep adding, else destination code + 4
+    const int src = mine && !is_pad ? p : -1;
+    const int col = blockIdx.y * blockDim.x + threadIdx.x;
+    const uint32_t col_off = (uint32_t)col * 16u;
     const int rows = b - a;
 
-    for (int i = threadIdx.x; i < rows; i += blockDim.x) {
-        const int r = a + i;
-        const int sg = seg_of_row[r];
-        const int o0 = offsets[sg], o1 = offsets[sg + 1];
-        const bool is_long = o1 - o0 >= seg_long;
-        const bool is_pad = uniq_ws[sg] == pad_id;
-        const bool seg_end = r + 1 == o1;
-        int code = 0;
-        if (is_long) {
-            if (seg_end || r + 1 == r1) code = (o0 < r0 ? kDstFirst : kDstLast) + 4;
-        } else if (seg_end) {
-            code = seg_slot[sg] + 4;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    int code = 0;
+    for (int i0 = 0; i0 < rows; i0 += UN) {
+        f32x4 v[UN], g[OLD ? UN : 1];
+#pragma unroll
+        for (int k = 0; k < UN; ++k)
+            v[k] = load_row<PLAIN>(dH, i0 + k < rows ? __builtin_amdgcn_readlane(src, (a + i0 + k) & (kWave - 1)) : -1, cols4, col_off);
+        // (the rows' codes arrive behind the first group's loads)
+        if (i0 == 0) code = part_ends ? (is_first_part ? kDstLast : kDstFirst) + 4 : (mine && !is_long && ends) ? slot + 4 : 0;
+        if (OLD) {
+#pragma unroll
+            for (int k = 0; k < UN; ++k) {
+                const int c = i0 + k < rows ? __builtin_amdgcn_readlane(code, (a + i0 + k) & (kWave - 1)) - 4 : -1;
+                g[k] = load_row<true>(G, c >= 0 && !(c & kSlotNew) ? c : -1, cols4, col_off);
+            }
         }
-        s_src[i] = is_pad ? -1 : perm[r];
-        s_dst[i] = code;
-        s_pad[i] = is_pad ? 1 : 0;
-        if (commit && r == o0) {
-            const int row = seg_slot[sg];
-            if (row < 0) {
-                atomicOr(&scal[kSErr], kErrBitCapacity);      // dropped: the buffer is full
-            } else if (row & kSlotNew) {
-                const int id = uniq_ws[sg], slot = row & (kSlotNew - 1);
-                slot_of[id] = slot;
-                id_of_slot[slot] = id;
-                cnt_of_slot[slot] = o1 - o0;
-            } else {
-                cnt_of_slot[row] += o1 - o0;
+#pragma unroll
+        for (int k = 0; k < UN; ++k) {
+            const int at = (a + i0 + k) & (kWave - 1);
+            const int cd = i0 + k < rows ? __builtin_amdgcn_readlane(code, at) : 0;
+            acc += v[k];
+            if (cd != 0) {
+                const int dst = cd - 4;
+                const bool pad = __builtin_amdgcn_readlane(is_pad ? 1 : 0, at) != 0;
+                if (col < cols4) {
+                    if (dst == kDstFirst) {
+                        reinterpret_cast<f32x4*>(seg_first)[(int64_t)t * cols4 + col] = acc;
+                    } else if (dst == kDstLast) {
+                        reinterpret_cast<f32x4*>(seg_last)[(int64_t)t * cols4 + col] = acc;
+                    } else if (dst >= 0) {
+                        f32x4* to = reinterpret_cast<f32x4*>(G) + (int64_t)(dst & (kSlotNew - 1)) * cols4 + col;
+                        // a row new to the window is stored past the caches (see write_final)
+                        if (dst & kSlotNew) __builtin_nontemporal_store(acc, to);       // (padding: nothing was added)
+                        else if (OLD && !pad) *to = g[k] + acc;
+                    }
+                }
+                acc = f32x4{0.f, 0.f, 0.f, 0.f};
             }
         }
     }
-    __syncthreads();
-
-    const int col = blockIdx.y * blockDim.x + threadIdx.x;
-    if (col >= cols4) return;
-
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int i0 = 0; i0 < rows; i0 += kSegUnroll) {
-        float4 v[kSegUnroll];
-        // the group's table entries first, as 16-byte LDS reads: fetched one by one, each row's load
-        // would be issued an LDS round trip after the one before it
-        int srcs[kSegUnroll], codes[kSegUnroll];
-#pragma unroll
-        for (int q = 0; q < kSegUnroll / 4; ++q) {
-            const int4 a = *reinterpret_cast<const int4*>(&s_src[i0 + 4 * q]);
-            const int4 b = *reinterpret_cast<const int4*>(&s_dst[i0 + 4 * q]);
-            srcs[4 * q] = a.x; srcs[4 * q + 1] = a.y; srcs[4 * q + 2] = a.z; srcs[4 * q + 3] = a.w;
-            codes[4 * q] = b.x; codes[4 * q + 1] = b.y; codes[4 * q + 2] = b.z; codes[4 * q + 3] = b.w;
-        }
-#pragma unroll
-        for (int k = 0; k < kSegUnroll; ++k) {
-            const int i = i0 + k;
-            const int src = i < rows ? srcs[k] : -1;
-            // every row of dH is read exactly once: stream it past the caches (batches of a few
-            // thousand positions are better off with plain loads: their rows often still sit in a
-            // cache, and what they have to hide is latency; measured 1 to 1.4 us per step).  The
-            // choice is made at compile time: chosen at run time inside this loop it cost the large
-            // shape 10 % of the kernel
-            v[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (src >= 0) {
-                const f32x4* p = reinterpret_cast<const f32x4*>(dH) + (int64_t)src * cols4 + col;
-                const f32x4 t = PLAIN ? *p : __builtin_nontemporal_load(p);
-                v[k] = make_float4(t.x, t.y, t.z, t.w);
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < kSegUnroll; ++k) {
-            const int i = i0 + k;
-            if (i < rows) {
-                acc = f4_add(acc, v[k]);
-                const int code = codes[k];
-                if (code != 0) {
-                    const int dst = code - 4;
-                    if (dst == kDstFirst) {
-                        seg_first[(int64_t)t * cols4 + col] = acc;
-                    } else if (dst == kDstLast) {
-                        seg_last[(int64_t)t * cols4 + col] = acc;
-                        if (col == 0) long_list[atomicAdd(&scal[kSLongCount], 1)] = t;
-                    } else {
-                        write_final(G, cols4, col, dst, s_pad[i] != 0, acc);
-                    }
-                    acc = make_float4(0.f, 0.f, 0.f, 0.f);
-                }
-            }
+    // long segments that start here, for k_seg_combine: everything it would otherwise look up
+    if (blockIdx.y == 0 && threadIdx.x < kWave && part_ends && is_first_part)
+        long_list[atomicAdd(&scal[kSLongCount], 1)] = make_int4(t, 1 + (o1 - 1) / TR - t, slot, is_pad ? 1 : 0);
+    if (commit && head_here) {
+        if (slot < 0) {
+            atomicOr(&scal[kSErr], kErrBitCapacity);      // dropped: the buffer is full
+        } else if (slot & kSlotNew) {
+            const int s = slot & (kSlotNew - 1);
+            slot_of[id] = s;
+            id_of_slot[s] = id;
+            cnt_of_slot[s] = o1 - o0;
+        } else {
+            cnt_of_slot[slot] += o1 - o0;
         }
     }
 }
@@ -735,11 +742,8 @@ __global__ __launch_bounds__(kBlock) void k_seg_reduce(
 // kFixCols4 float4 columns; its kFixLanes row lanes each add every
 // kFixLanes-th partial, then lane sums are added in lane order.
 __global__ __launch_bounds__(kBlock) void k_seg_combine(
-    const int* __restrict__ seg_of_row, const int* __restrict__ offsets,
-    const int* __restrict__ uniq_ws, const int* __restrict__ seg_slot, int n, int cols4, int pad_id,
-    float4* __restrict__ G, const float4* __restrict__ seg_first,
-    const float4* __restrict__ seg_last, const int* __restrict__ scal,
-    const int* __restrict__ long_list)
+    int cols4, float4* __restrict__ G, const float4* __restrict__ seg_first,
+    const float4* __restrict__ seg_last, const int* __restrict__ scal, const int4* __restrict__ long_list)
 {
     __shared__ float4 sm[kFixLanes][kFixCols4];
     const int cl = threadIdx.x % kFixCols4;
@@ -747,14 +751,10 @@ __global__ __launch_bounds__(kBlock) void k_seg_combine(
     const int col = blockIdx.y * kFixCols4 + cl;
     const int count = scal[kSLongCount];
     for (int w = blockIdx.x; w < count; w += gridDim.x) {
-        const int t = long_list[w];
-        int last_row = (t + 1) * kSegRows - 1;
-        if (last_row > n - 1) last_row = n - 1;
-        const int sg = seg_of_row[last_row];
-        const int seg_end = offsets[sg + 1];
-        const bool is_pad = uniq_ws[sg] == pad_id;
-        // partial i: i = 0 -> seg_last[t]; i >= 1 -> seg_first[t + i]
-        const int parts = 1 + (seg_end - 1) / kSegRows - t;
+        // partial i of the segment: i = 0 -> seg_last[t]; i >= 1 -> seg_first[t + i]
+        const int4 entry = long_list[w];
+        const int t = entry.x, parts = entry.y;
+        const bool is_pad = entry.w != 0;
         float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
         if (!is_pad && col < cols4) {
             // the lane's partials are fetched eight at a time (the adds keep their order): one
@@ -780,7 +780,7 @@ __global__ __launch_bounds__(kBlock) void k_seg_combine(
             float4 tot = sm[0][cl];
 #pragma unroll
             for (int k = 1; k < kFixLanes; ++k) tot = f4_add(tot, sm[k][cl]);
-            write_final(G, cols4, col, seg_slot[sg], is_pad, tot);
+            write_final(G, cols4, col, entry.z, is_pad, tot);
         }
         __syncthreads();
     }
@@ -795,31 +795,30 @@ void segment_reduce(Ctx* c, const float* dH, int64_t m, hipStream_t s, bool comm
     int threads = ((cols4 + kWave - 1) / kWave) * kWave;
     if (threads > kBlock) threads = kBlock;
     const int slabs = (cols4 + threads - 1) / threads;
-    // Whole-segment sums are one block's serial chain of row loads: short chains matter most when
-    // the batch has few tiles to hide them behind.
-    const int seg_long = n > kSegSmallBatch ? kSegLong : kSegLongSmall;
-    const int tiles = (n + kSegRows - 1) / kSegRows;
-    if (n > kSegPlainLoads)
-        launch(c, KID_SEG_REDUCE, k_seg_reduce<false>, dim3(tiles, slabs), dim3(threads), s,
-                           reinterpret_cast<const float4*>(dH), c->perm, c->seg_of_row, c->offsets,
-                           c->uniq_ws, c->seg_slot, n, cols4, c->cfg.pad_id,
-                           reinterpret_cast<float4*>(c->G), reinterpret_cast<float4*>(c->seg_first),
-                           reinterpret_cast<float4*>(c->seg_last), c->scal, c->long_list, seg_long,
-                           commit ? c->slot_of : (int*)nullptr, c->id_of_slot, c->cnt_of_slot);
-    else
-        launch(c, KID_SEG_REDUCE, k_seg_reduce<true>, dim3(tiles, slabs), dim3(threads), s,
-                           reinterpret_cast<const float4*>(dH), c->perm, c->seg_of_row, c->offsets,
-                           c->uniq_ws, c->seg_slot, n, cols4, c->cfg.pad_id,
-                           reinterpret_cast<float4*>(c->G), reinterpret_cast<float4*>(c->seg_first),
-                           reinterpret_cast<float4*>(c->seg_last), c->scal, c->long_list, seg_long,
-                           commit ? c->slot_of : (int*)nullptr, c->id_of_slot, c->cnt_of_slot);
-    int fix_blocks = tiles / (seg_long / kSegRows) + 1;   // upper bound of long segments
+    const int tile_rows = seg_rows_for(n);
+    const int tiles = (n + tile_rows - 1) / tile_rows;
+    // in the first step of a window every row is new
+    const bool old = !commit || c->steps_done > 0 || c->window_imported;
+    const dim3 grid(tiles, slabs);
+    auto go = [&](auto kern) {
+        launch(c, KID_SEG_REDUCE, kern, grid, dim3(threads), s, reinterpret_cast<const float4*>(dH), c->perm,
+               c->seg_of_row, c->offsets, c->uniq_ws, c->seg_slot, n, cols4, reinterpret_cast<float4*>(c->G),
+               reinterpret_cast<float4*>(c->seg_first), reinterpret_cast<float4*>(c->seg_last), c->scal, c->long_list,
+               commit ? c->slot_of : (int*)nullptr, c->id_of_slot, c->cnt_of_slot);
+    };
+    static_assert(kSegPlainLoads == kSegSmallBatch, "the two lines of the dispatch below coincide");
+    if (n <= kSegSmallBatch) {
+        if (old) go(k_seg_reduce<kSegRowsSmall, 16, true, true>);
+        else go(k_seg_reduce<kSegRowsSmall, 32, true, false>);
+    } else {
+        if (old) go(k_seg_reduce<kSegRows, 16, false, true>);
+        else go(k_seg_reduce<kSegRows, 16, false, false>);
+    }
+    int fix_blocks = tiles;                          // upper bound of long segments: one starts per tile
     if (fix_blocks > 1024) fix_blocks = 1024;        // a block per long segment for all but extreme batches
     launch(c, KID_SEG_COMBINE, k_seg_combine, dim3(fix_blocks, (cols4 + kFixCols4 - 1) / kFixCols4),
-                       dim3(kBlock), s, c->seg_of_row, c->offsets, c->uniq_ws, c->seg_slot, n,
-                       cols4, c->cfg.pad_id, reinterpret_cast<float4*>(c->G),
-                       reinterpret_cast<const float4*>(c->seg_first),
-                       reinterpret_cast<const float4*>(c->seg_last), c->scal, c->long_list);
+           dim3(kBlock), s, cols4, reinterpret_cast<float4*>(c->G), reinterpret_cast<const float4*>(c->seg_first),
+           reinterpret_cast<const float4*>(c->seg_last), c->scal, c->long_list);
 }
 
 // ---- end of the window: export in ascending ID order, then empty ------------
