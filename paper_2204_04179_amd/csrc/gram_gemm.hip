@@ -22,7 +22,9 @@ namespace gram {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef __attribute__((address_space(3))) void lds_void;
+typedef float f32x4_ __attribute__((ext_vector_type(4)));
+constexpr uint32_t kRawBuffer = 0x00027000;     // descriptor flags: 32-bit elements, no swizzle
+constexpr uint32_t kPastEnd = 0xFFFFFFF0u;      // an offset no descriptor covers: reads zeros
 
 __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f)
 {
@@ -70,7 +72,8 @@ __device__ __forceinline__ void epi_store(float* __restrict__ C, int64_t at, flo
 // ---- small forward kernel: latency first ------------------------------------------
 //
 // Batches whose unique items give the 256x256 kernel fewer tiles than there are CUs (and any
-// d_in that is not a multiple of 32).  Such a launch is bound by the latency of its loads,
+// d_in that is not a multiple of 32), where k_encode_mid below does not apply: the gate epilogue, a width
+// that is not a multiple of 8, a matrix beyond 4 GiB.  Such a launch is bound by the latency of its loads,
 // not by arithmetic: a 64x64 tile per block (one 32x32 MFMA tile per wave) puts a block on
 // nearly every CU, K advances in slabs of 64, and the loads of three slabs are in flight in
 // registers ahead of the one being multiplied.  Two LDS buffers, one barrier per slab.
@@ -235,6 +238,172 @@ __global__ __launch_bounds__(kBlock) void k_encode_bf16(
     for (int r = 0; r < 16; ++r) {
         const int j = m0 + wm * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
         if (j < U && cc < d) epi_store<EPI>(E, (int64_t)j * d + cc, acc[r], av[r], idr[r] == pad_id);
+    }
+}
+
+// ---- the forward of small and mid-sized batches ------------------------------------------
+//
+// What such a launch spends its time on is not arithmetic but the wait for its operands: two dependent
+// round trips (unique list, rows of X) before the first slab, and with the four waves per block of the kernel
+// above a third of K in flight at 19 B/clk per CU.  Here the waves of a block cut K between KG groups,
+// which walk every KG-th slab of 64 side by side and add their tiles through LDS at the end: twice as
+// many waves and bytes in flight per tile.  W is read as the caller holds it; loads go through descriptors
+// (rows of the padding item and everything past an edge read zeros), so the loads in flight are known at
+// every wait.  The unique list is read before the number of items is known: what lies behind its end only
+// selects rows whose products are not stored.  A wave has WR tiles of 32 x 32 below each other.  Four groups
+// (all of K in flight) were slower: the tile then takes longer to add up than its slabs to arrive.
+// LDS: rows of X are 128 bytes (chunk c of row r at c ^ ((r >> 1) & 7)); rows of W as in k_wgrad_short.
+constexpr int SK = 64;
+template <int TM_, int TN, int KG, int WR>
+struct Mid {
+    static constexpr int kGroupThreads = (TM_ / (32 * WR)) * (TN / 32) * 64, kThreads = KG * kGroupThreads;
+    static constexpr size_t kStageB = TM_ * SK * 2 + SK * TN * 2;               // bytes per group
+    static constexpr size_t kTilesB = (size_t)KG * TM_ * (TN + 8) * 4;
+    static constexpr size_t kLds = kTilesB > KG * kStageB ? kTilesB : KG * kStageB;
+};
+
+template <int SM, int TN, int KG, int WR, int DEPTH, int EPI>
+__global__ __launch_bounds__((Mid<SM, TN, KG, WR>::kThreads), 4) void k_encode_mid(
+    const uint16_t* __restrict__ X, uint32_t x_bytes, const uint16_t* __restrict__ W, uint32_t w_bytes,
+    const int* __restrict__ uniq, const int* __restrict__ u_dev, int rows_max, int d_in, int d, int pad_id,
+    float* __restrict__ E, const void* __restrict__ aux)
+{
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    __shared__ int s_ids[SM];
+    constexpr int GT = Mid<SM, TN, KG, WR>::kGroupThreads, STHREADS = KG * GT;
+    constexpr size_t kStageB = Mid<SM, TN, KG, WR>::kStageB;                       // threads per group
+    constexpr int XT = SM * 8 / GT, WT = SK * (TN / 8) / GT; // 16-byte chunks per thread and slab
+    constexpr int WROW = TN * 2;                            // bytes per row of W in LDS
+    constexpr int WM = SM / (32 * WR);                      // waves along the rows
+    // the column tiles of a row tile run on one XCD and share its rows of X
+    const int n_tiles = (d + TN - 1) / TN;
+    const int q = blockIdx.x >> 3;
+    const int m0 = ((q / n_tiles) * 8 + (blockIdx.x & 7)) * SM, n0 = (q % n_tiles) * TN;
+    if (m0 >= rows_max) return;
+    const int tid = threadIdx.x, grp = __builtin_amdgcn_readfirstlane(tid / GT), gt = tid % GT;
+    const int lane = tid & 63, wave = gt >> 6, wm = wave % WM, wn = wave / WM;
+
+    const int xrow = gt >> 3, xpos = gt & 7;                // + (GT / 8) t
+    int id[XT];
+#pragma unroll
+    for (int t = 0; t < XT; ++t) {
+        const int j = m0 + xrow + t * (GT / 8);
+        id[t] = uniq[j < rows_max ? j : rows_max - 1];
+    }
+    const int U = *u_dev;
+    if (m0 >= U) return;
+    const __amdgpu_buffer_rsrc_t rsX = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(X), 0, x_bytes, kRawBuffer);
+    const __amdgpu_buffer_rsrc_t rsW = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(W), 0, w_bytes, kRawBuffer);
+    if (grp == 0 && xpos == 0)
+#pragma unroll
+        for (int t = 0; t < XT; ++t) s_ids[xrow + t * (GT / 8)] = id[t];
+    // rows xrow + (GT / 8) t swizzle alike: GT / 8 is a multiple of 16
+    static_assert(GT / 8 % 16 == 0, "row swizzle");
+    const int xk = (xpos ^ ((xrow >> 1) & 7)) * 8;
+    uint32_t ox[XT];
+#pragma unroll
+    for (int t = 0; t < XT; ++t)
+        ox[t] = id[t] == pad_id ? kPastEnd : ((uint32_t)id[t] * (uint32_t)d_in + (uint32_t)xk) * 2u;
+    constexpr int WC = TN / 8;                              // chunks per row of W
+    const int wrow = gt / WC, wpos = gt % WC;               // + (GT / WC) t
+    const int wcol = n0 + (wpos ^ (WROW == 256 ? (wrow & 3) << 2 : (wrow & 2) << 1)) * 8;
+    static_assert(GT / WC % 4 == 0, "row swizzle");
+    const bool wcol_ok = wcol < d;
+
+    typedef int v4 __attribute__((ext_vector_type(4)));
+    v4 rx[DEPTH][XT], rw[DEPTH][WT];
+#define GRAM_MID_LOAD(SET, IT)                                                                      \
+    {                                                                                               \
+        const int k0_ = (grp + (IT) * KG) * SK;                                                     \
+        _Pragma("unroll") for (int t = 0; t < XT; ++t) {                                            \
+            const uint32_t o_ = k0_ + xk < d_in && ox[t] != kPastEnd ? ox[t] + (uint32_t)k0_ * 2u : kPastEnd; \
+            rx[SET][t] = __builtin_amdgcn_raw_buffer_load_b128(rsX, o_, 0, 0);                      \
+        }                                                                                           \
+        _Pragma("unroll") for (int t = 0; t < WT; ++t) {                                            \
+            const int k_ = k0_ + wrow + t * (GT / WC);                                              \
+            const uint32_t o_ = k_ < d_in && wcol_ok ? ((uint32_t)k_ * (uint32_t)d + (uint32_t)wcol) * 2u : kPastEnd; \
+            rw[SET][t] = __builtin_amdgcn_raw_buffer_load_b128(rsW, o_, 0, 0);                      \
+        }                                                                                           \
+    }
+    const int nslab = (d_in + SK - 1) / SK, iters = (nslab + KG - 1) / KG;
+#pragma unroll
+    for (int s = 0; s < DEPTH; ++s) GRAM_MID_LOAD(s, s)
+
+    f32x16 acc[WR];
+#pragma unroll
+    for (int i = 0; i < WR; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+    unsigned char* stage = smem + grp * kStageB;
+    unsigned char* wstage = stage + SM * SK * 2;
+    const int j16 = lane & 15, g16 = lane >> 4;
+    const int f_row = (g16 >> 1) * 8 + (j16 >> 2), f_ch = wn * 4 + (g16 & 1) * 2 + ((j16 & 3) >> 1);
+    const unsigned char* fw = wstage + f_row * WROW + ((f_ch ^ (WROW == 256 ? (f_row & 3) << 2 : (f_row & 2) << 1)) * 16) + (j16 & 1) * 8;
+    const int a_row = wm * (32 * WR) + (lane & 31), a_x = (a_row >> 1) & 7;      // + 32 i: the same swizzle
+#define GRAM_MID_ITER(SET, IT)                                                                      \
+    {                                                                                               \
+        _Pragma("unroll") for (int t = 0; t < XT; ++t)                                              \
+            *reinterpret_cast<v4*>(stage + (xrow + t * (GT / 8)) * 128 + xpos * 16) = rx[SET][t];   \
+        _Pragma("unroll") for (int t = 0; t < WT; ++t)                                              \
+            *reinterpret_cast<v4*>(wstage + (wrow + t * (GT / WC)) * WROW + wpos * 16) = rw[SET][t]; \
+        GRAM_MID_LOAD(SET, (IT) + DEPTH)                                                            \
+        __syncthreads();                                                                            \
+        _Pragma("unroll") for (int ks = 0; ks < SK / 16; ++ks) {                                    \
+            const unsigned char* b_ = fw + ks * 16 * WROW;                                          \
+            const sv4i16 lo_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_sv4i16*)b_);            \
+            const sv4i16 hi_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_sv4i16*)(b_ + 4 * WROW)); \
+            const bf16x8 fb = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo_, hi_, 0, 1, 2, 3, 4, 5, 6, 7)); \
+            _Pragma("unroll") for (int i = 0; i < WR; ++i) {                                         \
+                const bf16x8 fa = *reinterpret_cast<const bf16x8*>(                                 \
+                    stage + (a_row + i * 32) * 128 + (((ks * 2 + (lane >> 5)) ^ a_x) * 16));        \
+                acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, fb, acc[i], 0, 0, 0);          \
+            }                                                                                       \
+        }                                                                                           \
+        __syncthreads();                                                                            \
+    }
+    for (int it = 0; it < iters; it += DEPTH) {             // (slabs past the end are zeros)
+#pragma unroll
+        for (int s = 0; s < DEPTH; ++s) GRAM_MID_ITER(s, it + s)
+    }
+#undef GRAM_MID_LOAD
+#undef GRAM_MID_ITER
+
+    // the groups' tiles, added in group order; rows of 16-byte pieces to memory
+    constexpr int LD = TN + 8;
+    float* parked = reinterpret_cast<float*>(smem);
+#pragma unroll
+    for (int i = 0; i < WR; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            parked[(grp * SM + wm * (32 * WR) + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) * LD + wn * 32 + (lane & 31)] = acc[i][r];
+    __syncthreads();
+    constexpr int OUT = SM * TN / 4 / STHREADS;
+    f32x4_ av[OUT];
+#pragma unroll
+    for (int h = 0; h < OUT; ++h) {
+        const int e = tid + h * STHREADS, row = e / (TN / 4), c4 = n0 + e % (TN / 4) * 4;
+        av[h] = f32x4_{0.f, 0.f, 0.f, 0.f};
+        if (EPI == kEpiMinus && m0 + row < U && c4 < d)
+            av[h] = *reinterpret_cast<const f32x4_*>(static_cast<const float*>(aux) + (int64_t)(m0 + row) * d + c4);
+    }
+#pragma unroll
+    for (int h = 0; h < OUT; ++h) {
+        const int e = tid + h * STHREADS, row = e / (TN / 4), c = e % (TN / 4) * 4;
+        f32x4_ s = *reinterpret_cast<const f32x4_*>(&parked[row * LD + c]);
+#pragma unroll
+        for (int g = 1; g < KG; ++g) s += *reinterpret_cast<const f32x4_*>(&parked[(g * SM + row) * LD + c]);
+        if (m0 + row < U && n0 + c < d) {
+            const int64_t at = (int64_t)(m0 + row) * d + n0 + c;
+            if (EPI == kEpiReluBf16) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) s[k] = s[k] > 0.f ? s[k] : 0.f;      // (NaN becomes 0, as in epi_store)
+                typedef uint32_t u32x2_ __attribute__((ext_vector_type(2)));
+                *reinterpret_cast<u32x2_*>(reinterpret_cast<uint16_t*>(E) + at) = u32x2_{pack_bf16x2(s[0], s[1]), pack_bf16x2(s[2], s[3])};
+            } else {
+                if (EPI == kEpiMinus) s = s_ids[row] == pad_id ? f32x4_{0.f, 0.f, 0.f, 0.f} : s - av[h];
+                *reinterpret_cast<f32x4_*>(E + at) = s;
+            }
+        }
     }
 }
 
@@ -728,19 +897,33 @@ __global__ __launch_bounds__(kBlock) void k_transpose_w(const uint16_t* __restri
 
 // ---- forward, float32 --------------------------------------------------------
 
+// The operands of 16 products are requested together (one product at a time, each term of the sum waited
+// for a round trip of its own: 10.0 us for 64 terms, now 3.7).
 __global__ __launch_bounds__(kBlock) void k_encode_f32(
     const float* __restrict__ X, const float* __restrict__ W, const int* __restrict__ uniq,
     const int* __restrict__ u_dev, int d_in, int d, int pad_id, float* __restrict__ E)
 {
     const int U = *u_dev;
     const int c = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int j = blockIdx.y * 4 + (threadIdx.x >> 6);
+    const int j = blockIdx.y * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (j >= U || c >= d) return;
     const int id = uniq[j];
     float acc = 0.f;
     if (id != pad_id) {
         const float* x = X + (int64_t)id * d_in;
-        for (int k = 0; k < d_in; ++k) acc = fmaf(x[k], W[(int64_t)k * d + c], acc);
+        const float* w = W + c;
+        int k = 0;
+        for (; k + 16 <= d_in; k += 16) {
+            float xv[16], wv[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                xv[u] = x[k + u];
+                wv[u] = w[(int64_t)(k + u) * d];
+            }
+#pragma unroll
+            for (int u = 0; u < 16; ++u) acc = fmaf(xv[u], wv[u], acc);
+        }
+        for (; k < d_in; ++k) acc = fmaf(x[k], w[(int64_t)k * d], acc);
     }
     E[(int64_t)j * d + c] = acc;
 }
@@ -776,11 +959,18 @@ static bool big_kernel_reads_plain_b(int64_t a_rows, int k, int n_out, int epi)
            (int64_t)k * n_out * 2 < kBufferWindow;
 }
 
+// The kernel for small and mid-sized batches: the second operand untransposed, descriptors for both.
+static bool takes_mid_kernel(int64_t a_rows, int k, int n_out, int epi)
+{
+    return n_out % 8 == 0 && epi != kEpiGate && a_rows * k * 2 < kBufferWindow && (int64_t)k * n_out * 2 < kBufferWindow;
+}
+
 // Whether gemm_rows_bf16 will read B_plain (the [k, n_out] matrix as the caller holds it) instead of
 // the transposed copy Bt for this problem: callers skip the transpose launch then.
 bool gemm_reads_plain_b(const Ctx* c, int64_t rows_max, int64_t a_rows, int k, int n_out, int epi)
 {
     if (takes_big_kernel(c, rows_max, n_out, k, a_rows, epi)) return big_kernel_reads_plain_b(a_rows, k, n_out, epi);
+    if (takes_mid_kernel(a_rows, k, n_out, epi)) return true;
     return n_out % 8 == 0 && (epi == kEpiPlain || epi == kEpiMinus);
 }
 
@@ -804,6 +994,44 @@ bool gemm_rows_bf16(Ctx* c, const void* A, int64_t a_rows, int k, const int* row
                            static_cast<const uint16_t*>(Bt), k, n_out, n_out, k, C, n_out, s, fuse ? &sc : nullptr,
                            pad_id, epi, aux);
         return fuse;
+    }
+    if (B_plain && takes_mid_kernel(a_rows, k, n_out, epi)) {
+        const uint32_t x_bytes = (uint32_t)(a_rows * k * 2), w_bytes = (uint32_t)((int64_t)k * n_out * 2);
+        // The number of items is known on the device only; guessed from the batch: all IDs of a vocabulary
+        // met many times over, 0.6 of one met a few times, else 0.4 of the positions (Zipf laws of the
+        // tests and the benchmark: 0.22 to 0.6).  Measured, event to event with cold operands, in us for
+        // 64 x 64 / 128 x 64 / 128 x 128 tiles (former kernel in brackets): 2,200 items 768 x 256
+        // 11.4 / 13.3 / 17.5 (13.3); 1,600 items 768 x 400 11.7 / 13.8 / 17.2 (13.8); 3,000 items 1024 x 512
+        // 18.6 / 16.0 / 20.6 (21.1); 10,200 items 512 x 128 16.6 / 13.9 / 17.0 (16.3); 11,600 items
+        // 768 x 256 23.3 / 22.9 / 21.2 (25.1); 5,700 items 776 x 392 26.7 / 25.7 / 23.2 (29.5)
+        int64_t guess = rows_max;
+        if (n_dev != c->scal + kSChunkN)
+            guess = c->cur_m >= 8 * (int64_t)c->cfg.vocab_n ? rows_max : c->cur_m >= c->cfg.vocab_n ? rows_max * 3 / 5 : rows_max * 2 / 5;
+        const int64_t tiles64 = (guess + 63) / 64 * ((n_out + 63) / 64);
+        const int shape = tiles64 * 4 <= 5 * (int64_t)c->num_cus ? 0 : tiles64 * 2 <= 5 * (int64_t)c->num_cus ? 1 : 2;
+        auto go = [&](auto kern, int tm, int tn, int threads, size_t lds) {
+            const unsigned blocks = (unsigned)(((rows_max + tm - 1) / tm + 7) / 8 * 8 * ((n_out + tn - 1) / tn));
+            launch_smem(c, KID_ENCODE_BF16, kern, dim3(blocks), dim3(threads), lds, s, static_cast<const uint16_t*>(A),
+                        x_bytes, static_cast<const uint16_t*>(B_plain), w_bytes, row_ids, n_dev, (int)rows_max, k, n_out,
+                        pad_id, C, aux);
+        };
+#define GRAM_MID_(TM_, TN_, KG_, WR_, DEPTH_, EPI_)                                                 \
+    {                                                                                               \
+        constexpr auto kern = k_encode_mid<TM_, TN_, KG_, WR_, DEPTH_, EPI_>;                       \
+        using M_ = Mid<TM_, TN_, KG_, WR_>;                                                         \
+        ensure_dynamic_lds<kern>((int)M_::kLds);                                                    \
+        go(kern, TM_, TN_, M_::kThreads, M_::kLds);                                                 \
+    }
+#define GRAM_GO_MID(EPI_)                                                                           \
+    if (shape == 0) GRAM_MID_(64, 64, 2, 1, 3, EPI_)                                                \
+    else if (shape == 1) GRAM_MID_(128, 64, 2, 2, 2, EPI_)                                          \
+    else GRAM_MID_(128, 128, 2, 2, 2, EPI_)
+        if (epi == kEpiMinus) { GRAM_GO_MID(kEpiMinus) }
+        else if (epi == kEpiReluBf16) { GRAM_GO_MID(kEpiReluBf16) }
+        else { GRAM_GO_MID(kEpiPlain) }
+#undef GRAM_GO_MID
+#undef GRAM_MID_
+        return false;
     }
     const dim3 grid((n_out + BN - 1) / BN, (unsigned)((rows_max + BM - 1) / BM));
     const uint16_t* a16 = static_cast<const uint16_t*>(A);
@@ -1381,7 +1609,7 @@ __global__ __launch_bounds__(kBlock) void k_wgrad_f32(
     float* __restrict__ partial, int row_begin, int row_end)
 {
     const int c = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int i = blockIdx.y * 4 + (threadIdx.x >> 6);
+    const int i = blockIdx.y * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int z = blockIdx.z;
     if (i >= d_in || c >= d) return;
     int kb, ke;
@@ -1391,7 +1619,22 @@ __global__ __launch_bounds__(kBlock) void k_wgrad_f32(
     kb += row_begin;
     ke += row_begin;
     float acc = 0.f;
-    for (int sidx = kb; sidx < ke; ++sidx) {
+    int sidx = kb;
+    for (; sidx + 8 <= ke; sidx += 8) {         // eight rows' IDs, then their operands, requested together
+        int id[8];
+        float xv[8], gv[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) id[u] = id_of_slot ? id_of_slot[sidx + u] : sidx + u;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            xv[u] = X[(int64_t)id[u] * d_in + i];
+            gv[u] = G[(int64_t)(sidx + u) * d + c];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (id[u] != pad_id) acc = fmaf(xv[u], gv[u], acc);
+    }
+    for (; sidx < ke; ++sidx) {
         const int id = id_of_slot ? id_of_slot[sidx] : sidx;
         if (id != pad_id) acc = fmaf(X[(int64_t)id * d_in + i], G[(int64_t)sidx * d + c], acc);
     }

@@ -1,0 +1,80 @@
+"""The forward of small and mid-sized batches (tiles of 64 x 64, 128 x 64 and 128 x 128, K cut between wave
+groups) against a float64 product, at the item counts and widths where tiles, slabs of 64 and the number
+of groups end, and where the tile shape changes.  Bound: float32 sums of K products of bf16 values, a few
+1e-7 of the norm; bf16 results are rounded once (2^-9 per element)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("items,k,d", [(1, 8, 8), (63, 64, 64), (65, 72, 72), (129, 136, 136), (640, 192, 512),
+                                       (1281, 200, 520), (2600, 320, 512), (5200, 264, 264), (9000, 512, 128)])
+@pytest.mark.parametrize("pads", [0, 1])
+def test_every_row_against_float64(items, k, d, pads):
+    import torch
+    from paper_2204_04179_amd import gram
+    torch.manual_seed(items + d)
+    n = 10_000
+    X = torch.randn(n, k, device="cuda", dtype=torch.bfloat16)
+    W = (torch.randn(k, d, device="cuda") * k ** -0.5).to(torch.bfloat16)
+    ids = (torch.randperm(n - 1, device="cuda")[:items] + 1).to(torch.int32)
+    ids[items // 2] = 0 if pads else ids[items // 2]
+    cap = min(2 * items, n)
+    g = gram.Gram(gram.make_config(n, k, d, 2 * items, 1, 0, 0, gram.BF16))
+    both = torch.cat([ids, ids])
+    uniq, counts = (torch.full((cap,), 2**31 - 1, dtype=torch.int32, device="cuda") for _ in range(2))
+    inverse = torch.empty(2 * items, dtype=torch.int32, device="cuda")
+    u = torch.zeros(1, dtype=torch.int32, device="cuda")
+    E = torch.full((cap, d), float("nan"), device="cuda")
+    H = torch.full((2 * items, d), float("nan"), device="cuda")
+    assert g.unique(both, uniq, inverse, counts, u, want_host_u=True) == items
+    # (entries of uniq behind the items stay what they were: the foreign buffers below hold IDs that do not exist)
+    for uq in (uniq, uniq.clone()):
+        E.fill_(float("nan"))
+        g.encode_gather(X, W, uq, inverse, u, 2 * items, E, H)
+        want = X[uniq[:items].long()].double() @ W.double()
+        want[uniq[:items] == 0] = 0
+        err = float((E[:items].double() - want).norm()) / max(float(want.norm()), 1e-30)
+        assert err < 2e-6, err
+        assert bool(torch.isnan(E[items:]).all())
+        assert torch.equal(H, E[inverse.long()])
+        if pads:
+            assert bool((E[0] == 0).all())
+    g.close()
+
+
+@pytest.mark.parametrize("items,k,dh,d", [(70, 72, 136, 72), (3000, 200, 264, 136)])
+def test_rectified_and_subtracting_forms(items, k, dh, d):
+    import torch
+    from paper_2204_04179_amd import gram
+    torch.manual_seed(items)
+    n = 6000
+    X = torch.randn(n, k, device="cuda", dtype=torch.bfloat16)
+    W1 = (torch.randn(k, dh, device="cuda") * k ** -0.5).to(torch.bfloat16)
+    W2 = (torch.randn(dh, d, device="cuda") * dh ** -0.5).to(torch.bfloat16)
+    ids = torch.randperm(n, device="cuda")[:items].to(torch.int32)
+    ids[3] = 0
+    g = gram.Gram(gram.make_config(n, k, d, n, 1, 0, 0, gram.BF16, 0, dh))
+    uniq, counts = (torch.empty(n, dtype=torch.int32, device="cuda") for _ in range(2))
+    inverse, u = torch.empty(items, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+    U = g.unique(ids, uniq, inverse, counts, u, want_host_u=True)
+    A1 = torch.empty(n, dh, device="cuda", dtype=torch.bfloat16)
+    H = torch.empty(items, d, device="cuda")
+    g.mlp_encode_gather(X, W1, W2, uniq, inverse, u, items, A1, None, H)
+    x = X[uniq[:U].long()].double()
+    x[uniq[:U] == 0] = 0
+    a = (x @ W1.double()).clamp(min=0)
+    assert float((A1[:U].double() - a).norm()) <= 3e-3 * float(a.norm())
+    want = A1[:U].double() @ W2.double()
+    assert float((H.double() - want[inverse.long()]).norm()) <= 2e-6 * float(want[inverse.long()].norm())
+    g.close()
+    g = gram.Gram(gram.make_config(n, k, dh, n, 1, 0, 0, gram.BF16))
+    Ht, R, dW = torch.randn(items, dh, device="cuda"), torch.empty(items, dh, device="cuda"), torch.empty(k, dh, device="cuda")
+    g.pseudo_loss_grad(X, W1, ids, Ht, items, R, dW)
+    x = X[ids.long()].double()
+    want = x @ W1.double() - Ht.double()
+    want[ids == 0] = 0
+    assert float((R.double() - want).norm()) <= 2e-6 * float(want.norm())
+    assert bool((R[ids == 0] == 0).all())
+    g.close()
