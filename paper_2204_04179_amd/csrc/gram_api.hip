@@ -133,7 +133,9 @@ int64_t layout(Ctx* c, const gram_config& cfg, const Derived& dv, char* base)
     int* dense_sums = (int*)take(dense ? ((int64_t)cfg.vocab_n / kScanTile + 2) * 4 : 1);
     float* G = (float*)take(dv.cap_total * d * 4);
     float* E_ws = (float*)take(dv.cap_u * d * 4);
-    double* loss_part = (double*)take((dv.cap_chunk / kPseudoRows + 1) * 8);
+    int64_t loss_blocks = epi_loss_blocks_max(dv.cap_chunk, d);
+    if (loss_blocks < dv.cap_chunk / kPseudoRows + 1) loss_blocks = dv.cap_chunk / kPseudoRows + 1;
+    double* loss_part = (double*)take(loss_blocks * 8);
     int* chunk_ids = (int*)take(dv.cap_chunk * 4);
     float* seg_first = (float*)take(dv.tiles_seg * d * 4);
     float* seg_last = (float*)take(dv.tiles_seg * d * 4);
@@ -553,9 +555,12 @@ int gram_pseudo_loss_grad(gram_ctx* ctx, const void* X, const void* W, const int
     hipStream_t s = static_cast<hipStream_t>(stream);
     chunk_ids_prepare(c, ids, n, s);
     if (c->cfg.xw_dtype == GRAM_BF16) {
-        // the contraction subtracts the targets as it stores; only the loss needs another pass
-        encode_forward(c, X, W, c->chunk_ids, c->scal + kSChunkN, n, R, s, nullptr, true, kEpiMinus, Ht);
-        pseudo_miss(c, R, nullptr, n, loss_dev, s);
+        // the contraction subtracts the targets as it stores and sums the squares
+        int parts = 0;
+        const EpiLoss loss = {c->loss_part, &parts};
+        encode_forward(c, X, W, c->chunk_ids, c->scal + kSChunkN, n, R, s, nullptr, true, kEpiMinus, Ht,
+                       loss_dev ? &loss : nullptr);
+        if (loss_dev) pseudo_loss(c, parts, loss_dev, s);
     } else {
         encode_forward(c, X, W, c->chunk_ids, c->scal + kSChunkN, n, R, s, nullptr, true);
         pseudo_miss(c, R, Ht, n, loss_dev, s);

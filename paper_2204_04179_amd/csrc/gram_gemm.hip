@@ -26,46 +26,67 @@ typedef float f32x4_ __attribute__((ext_vector_type(4)));
 constexpr uint32_t kRawBuffer = 0x00027000;     // descriptor flags: 32-bit elements, no swizzle
 constexpr uint32_t kPastEnd = 0xFFFFFFF0u;      // an offset no descriptor covers: reads zeros
 
-__device__ __forceinline__ uint16_t f32_to_bf16_rne(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return 0x7fc0;   // NaN stays NaN
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
-
-// What a contraction kernel does with an output element before storing it (template parameter
-// EPI of the kernels below).  `aux` has the row pitch of C.
+// What a contraction kernel does with its output elements before storing them (template parameter EPI
+// of the kernels below).  `aux` has the row pitch of C.
 //   kEpiPlain      C = v                                   (float32)
 //   kEpiReluBf16   C = bf16(max(v, 0))                     (C is a bf16 matrix)
 //   kEpiMinus      C = v - aux                             (aux float32: stored targets)
-//   kEpiGate       C = v where aux > 0, else 0             (aux bf16: kept activations)
-// A row flagged `zero` (the padding item) is stored as zeros in every mode.
+//   kEpiMinusBf16  C = bf16(v - aux)                       (what the contractions that read it would round)
+//   kEpiGateBf16   C = bf16(v) where aux > 0, else 0       (aux bf16: kept activations)
+// A row flagged `zero` (the padding item) is stored as zeros in every mode.  With the two subtracting modes a
+// kernel can also leave, per block, the sum of the squares of what it stored (before rounding to bf16), in
+// double and in a fixed order: the pseudo-loss without another pass over the matrix.
+__host__ __device__ constexpr bool epi_subtracts(int epi) { return epi == kEpiMinus || epi == kEpiMinusBf16; }
+__host__ __device__ constexpr bool epi_stores_bf16(int epi) { return epi == kEpiReluBf16 || epi == kEpiMinusBf16 || epi == kEpiGateBf16; }
 
-// The aux value of an element is fetched ahead of the stores (epi_load for a group of elements,
-// then epi_store for the group), so that the loads of a group are in flight together.
+// The aux values of 4 consecutive elements (at: a multiple of 4) are fetched ahead of the stores: the
+// targets, or 1 / 0 for an open / closed gate.
 template <int EPI>
-__device__ __forceinline__ float epi_load(const void* __restrict__ aux, int64_t at)
+__device__ __forceinline__ f32x4_ epi_load4(const void* __restrict__ aux, int64_t at)
 {
-    if (EPI == kEpiMinus) return static_cast<const float*>(aux)[at];
-    if (EPI == kEpiGate) {
-        const uint16_t a = static_cast<const uint16_t*>(aux)[at];
-        return ((a & 0x8000u) || !(a & 0x7fffu)) ? 0.f : 1.f;               // positive bf16 only
+    if (epi_subtracts(EPI)) return *reinterpret_cast<const f32x4_*>(static_cast<const float*>(aux) + at);
+    f32x4_ r = {0.f, 0.f, 0.f, 0.f};
+    if (EPI == kEpiGateBf16) {
+        typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
+        const u16x4 a = *reinterpret_cast<const u16x4*>(static_cast<const uint16_t*>(aux) + at);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) r[k] = ((a[k] & 0x8000u) || !(a[k] & 0x7fffu)) ? 0.f : 1.f;   // positive bf16 only
     }
-    return 0.f;
+    return r;
+}
+
+// The value stored (float32, before a rounding to bf16).
+template <int EPI>
+__device__ __forceinline__ float epi_value(float v, float a, bool zero)
+{
+    if (EPI == kEpiReluBf16) return !zero && v > 0.f ? v : 0.f;
+    if (epi_subtracts(EPI)) return zero ? 0.f : v - a;
+    if (EPI == kEpiGateBf16) return zero || a == 0.f ? 0.f : v;
+    return zero ? 0.f : v;
 }
 
 template <int EPI>
-__device__ __forceinline__ void epi_store(float* __restrict__ C, int64_t at, float v, float a, bool zero)
+__device__ __forceinline__ void epi_store4(float* __restrict__ C, int64_t at, f32x4_ v)
 {
-    if (EPI == kEpiReluBf16) {
-        reinterpret_cast<uint16_t*>(C)[at] = (zero || !(v > 0.f)) ? (uint16_t)0 : f32_to_bf16_rne(v);
-    } else if (EPI == kEpiMinus) {
-        C[at] = zero ? 0.f : v - a;
-    } else if (EPI == kEpiGate) {
-        C[at] = (zero || a == 0.f) ? 0.f : v;
+    if (epi_stores_bf16(EPI)) {
+        typedef uint32_t u32x2_ __attribute__((ext_vector_type(2)));
+        *reinterpret_cast<u32x2_*>(reinterpret_cast<uint16_t*>(C) + at) = u32x2_{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
     } else {
-        C[at] = zero ? 0.f : v;
+        *reinterpret_cast<f32x4_*>(C + at) = v;
+    }
+}
+
+// Sum of one double per thread over a block of whole waves, in a fixed order; thread 0 writes it.
+__device__ __forceinline__ void block_sum_double(double v, int threads, double* sm /*[threads / 64]*/, double* out)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o);
+    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double s = 0.0;
+        for (int w = 0; w < threads / 64; ++w) s += sm[w];
+        *out = s;
     }
 }
 
@@ -108,14 +129,18 @@ typedef __attribute__((address_space(3))) sv4i16 lds_sv4i16;
 template <int EPI, bool BDIRECT = false>
 __global__ __launch_bounds__(kBlock) void k_encode_bf16(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ Wt, const int* __restrict__ uniq,
-    const int* __restrict__ u_dev, int d_in, int d, int pad_id, float* __restrict__ E,
-    const void* __restrict__ aux)
+    const int* __restrict__ u_dev, int d_in, int d, const int* __restrict__ zero_ids, int pad_id,
+    float* __restrict__ E, const void* __restrict__ aux, double* __restrict__ loss_part)
 {
     __shared__ __attribute__((aligned(16))) uint16_t sA[2][BM * LDS_STRIDE];
     __shared__ __attribute__((aligned(16))) uint16_t sB[2][BN * LDS_STRIDE];
     const int U = *u_dev;
     const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-    if (m0 >= U) return;
+    if (epi_subtracts(EPI) && loss_part) loss_part += blockIdx.y * gridDim.x + blockIdx.x;
+    if (m0 >= U) {
+        if (epi_subtracts(EPI) && loss_part && threadIdx.x == 0) *loss_part = 0.0;
+        return;
+    }
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
 
@@ -221,24 +246,43 @@ __global__ __launch_bounds__(kBlock) void k_encode_bf16(
 #undef GRAM_PARK_SLAB
 #undef GRAM_SMALL_ITER
 
-    // accumulator element r of a lane sits at (row, col) = ((r / 4) * 8 + (lane / 32) * 4 + r % 4, lane % 32)
-    const int cc = n0 + wn * 32 + (lane & 31);
-    // everything the stores need is fetched first (the aux values and the IDs that tell the padding
-    // row): fetched inside the store loop, each store would wait for its own load and, with it, for
-    // the stores before it
-    float av[16];
-    int idr[16];
+    // accumulator element r of a lane sits at (row, col) = ((r / 4) * 8 + (lane / 32) * 4 + r % 4, lane % 32).
+    // The tile goes through LDS (the slabs are dead), so that a thread stores 4 consecutive columns.
+    // Everything the stores need is fetched first (the aux values and the IDs that tell the padding
+    // row): fetched in the store loop, each store would wait for its own load and, with it, for the
+    // stores before it.
+    constexpr int LD = BN + 4;
+    __shared__ __attribute__((aligned(16))) float s_tile[BM * LD];
+    __shared__ double s_loss[kBlock / 64];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int j = m0 + wm * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-        av[r] = (j < U && cc < d) ? epi_load<EPI>(aux, (int64_t)j * d + cc) : 0.f;
-        idr[r] = j < U ? uniq[j] : 0;
-    }
+    for (int r = 0; r < 16; ++r)
+        s_tile[(wm * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) * LD + wn * 32 + (lane & 31)] = acc[r];
+    f32x4_ av[BM * BN / 4 / kBlock];
+    int idr[BM * BN / 4 / kBlock];
+    const int erow = tid / (BN / 4), ecol = tid % (BN / 4) * 4;
+    const bool col_ok = n0 + ecol < d;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int j = m0 + wm * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-        if (j < U && cc < d) epi_store<EPI>(E, (int64_t)j * d + cc, acc[r], av[r], idr[r] == pad_id);
+    for (int h = 0; h < BM * BN / 4 / kBlock; ++h) {
+        const int j = m0 + erow + h * (kBlock * 4 / BN);
+        av[h] = (j < U && col_ok) ? epi_load4<EPI>(aux, (int64_t)j * d + n0 + ecol) : f32x4_{0.f, 0.f, 0.f, 0.f};
+        idr[h] = j < U ? zero_ids[j] : 0;
     }
+    __syncthreads();
+    double sq = 0.0;
+#pragma unroll
+    for (int h = 0; h < BM * BN / 4 / kBlock; ++h) {
+        const int row = erow + h * (kBlock * 4 / BN), j = m0 + row;
+        f32x4_ v = *reinterpret_cast<const f32x4_*>(&s_tile[row * LD + ecol]);
+        if (j < U && col_ok) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                v[k] = epi_value<EPI>(v[k], av[h][k], idr[h] == pad_id);
+                if (epi_subtracts(EPI)) sq += (double)v[k] * v[k];
+            }
+            epi_store4<EPI>(E, (int64_t)j * d + n0 + ecol, v);
+        }
+    }
+    if (epi_subtracts(EPI) && loss_part) block_sum_double(sq, kBlock, s_loss, loss_part);
 }
 
 // ---- the forward of small and mid-sized batches ------------------------------------------
@@ -265,11 +309,14 @@ struct Mid {
 template <int SM, int TN, int KG, int WR, int DEPTH, int EPI>
 __global__ __launch_bounds__((Mid<SM, TN, KG, WR>::kThreads), 4) void k_encode_mid(
     const uint16_t* __restrict__ X, uint32_t x_bytes, const uint16_t* __restrict__ W, uint32_t w_bytes,
-    const int* __restrict__ uniq, const int* __restrict__ u_dev, int rows_max, int d_in, int d, int pad_id,
-    float* __restrict__ E, const void* __restrict__ aux)
+    const int* __restrict__ uniq, const int* __restrict__ u_dev, int rows_max, int d_in, int d,
+    const int* __restrict__ zero_ids, int pad_id, float* __restrict__ E, const void* __restrict__ aux,
+    double* __restrict__ loss_part)
 {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     __shared__ int s_ids[SM];
+    __shared__ double s_loss[Mid<SM, TN, KG, WR>::kThreads / 64];
+    if (epi_subtracts(EPI) && loss_part) loss_part += blockIdx.x;
     constexpr int GT = Mid<SM, TN, KG, WR>::kGroupThreads, STHREADS = KG * GT;
     constexpr size_t kStageB = Mid<SM, TN, KG, WR>::kStageB;                       // threads per group
     constexpr int XT = SM * 8 / GT, WT = SK * (TN / 8) / GT; // 16-byte chunks per thread and slab
@@ -279,31 +326,38 @@ __global__ __launch_bounds__((Mid<SM, TN, KG, WR>::kThreads), 4) void k_encode_m
     const int n_tiles = (d + TN - 1) / TN;
     const int q = blockIdx.x >> 3;
     const int m0 = ((q / n_tiles) * 8 + (blockIdx.x & 7)) * SM, n0 = (q % n_tiles) * TN;
-    if (m0 >= rows_max) return;
+    if (m0 >= rows_max) {
+        if (epi_subtracts(EPI) && loss_part && threadIdx.x == 0) *loss_part = 0.0;
+        return;
+    }
     const int tid = threadIdx.x, grp = __builtin_amdgcn_readfirstlane(tid / GT), gt = tid % GT;
     const int lane = tid & 63, wave = gt >> 6, wm = wave % WM, wn = wave / WM;
 
     const int xrow = gt >> 3, xpos = gt & 7;                // + (GT / 8) t
-    int id[XT];
+    int id[XT], zid[XT];
 #pragma unroll
     for (int t = 0; t < XT; ++t) {
-        const int j = m0 + xrow + t * (GT / 8);
-        id[t] = uniq[j < rows_max ? j : rows_max - 1];
+        const int j = m0 + xrow + t * (GT / 8), jj = j < rows_max ? j : rows_max - 1;
+        id[t] = uniq[jj];
+        zid[t] = zero_ids[jj];
     }
     const int U = *u_dev;
-    if (m0 >= U) return;
+    if (m0 >= U) {
+        if (epi_subtracts(EPI) && loss_part && threadIdx.x == 0) *loss_part = 0.0;
+        return;
+    }
     const __amdgpu_buffer_rsrc_t rsX = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(X), 0, x_bytes, kRawBuffer);
     const __amdgpu_buffer_rsrc_t rsW = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(W), 0, w_bytes, kRawBuffer);
     if (grp == 0 && xpos == 0)
 #pragma unroll
-        for (int t = 0; t < XT; ++t) s_ids[xrow + t * (GT / 8)] = id[t];
+        for (int t = 0; t < XT; ++t) s_ids[xrow + t * (GT / 8)] = zid[t];
     // rows xrow + (GT / 8) t swizzle alike: GT / 8 is a multiple of 16
     static_assert(GT / 8 % 16 == 0, "row swizzle");
     const int xk = (xpos ^ ((xrow >> 1) & 7)) * 8;
     uint32_t ox[XT];
 #pragma unroll
     for (int t = 0; t < XT; ++t)
-        ox[t] = id[t] == pad_id ? kPastEnd : ((uint32_t)id[t] * (uint32_t)d_in + (uint32_t)xk) * 2u;
+        ox[t] = zid[t] == pad_id ? kPastEnd : ((uint32_t)id[t] * (uint32_t)d_in + (uint32_t)xk) * 2u;
     constexpr int WC = TN / 8;                              // chunks per row of W
     const int wrow = gt / WC, wpos = gt % WC;               // + (GT / WC) t
     const int wcol = n0 + (wpos ^ (WROW == 256 ? (wrow & 3) << 2 : (wrow & 2) << 1)) * 8;
@@ -382,10 +436,9 @@ __global__ __launch_bounds__((Mid<SM, TN, KG, WR>::kThreads), 4) void k_encode_m
 #pragma unroll
     for (int h = 0; h < OUT; ++h) {
         const int e = tid + h * STHREADS, row = e / (TN / 4), c4 = n0 + e % (TN / 4) * 4;
-        av[h] = f32x4_{0.f, 0.f, 0.f, 0.f};
-        if (EPI == kEpiMinus && m0 + row < U && c4 < d)
-            av[h] = *reinterpret_cast<const f32x4_*>(static_cast<const float*>(aux) + (int64_t)(m0 + row) * d + c4);
+        av[h] = m0 + row < U && c4 < d ? epi_load4<EPI>(aux, (int64_t)(m0 + row) * d + c4) : f32x4_{0.f, 0.f, 0.f, 0.f};
     }
+    double sq = 0.0;
 #pragma unroll
     for (int h = 0; h < OUT; ++h) {
         const int e = tid + h * STHREADS, row = e / (TN / 4), c = e % (TN / 4) * 4;
@@ -393,18 +446,17 @@ __global__ __launch_bounds__((Mid<SM, TN, KG, WR>::kThreads), 4) void k_encode_m
 #pragma unroll
         for (int g = 1; g < KG; ++g) s += *reinterpret_cast<const f32x4_*>(&parked[(g * SM + row) * LD + c]);
         if (m0 + row < U && n0 + c < d) {
-            const int64_t at = (int64_t)(m0 + row) * d + n0 + c;
-            if (EPI == kEpiReluBf16) {
+            // (the padding item's product is zero already: only the subtracting modes have to look)
+            const bool zero = epi_subtracts(EPI) && s_ids[row] == pad_id;
 #pragma unroll
-                for (int k = 0; k < 4; ++k) s[k] = s[k] > 0.f ? s[k] : 0.f;      // (NaN becomes 0, as in epi_store)
-                typedef uint32_t u32x2_ __attribute__((ext_vector_type(2)));
-                *reinterpret_cast<u32x2_*>(reinterpret_cast<uint16_t*>(E) + at) = u32x2_{pack_bf16x2(s[0], s[1]), pack_bf16x2(s[2], s[3])};
-            } else {
-                if (EPI == kEpiMinus) s = s_ids[row] == pad_id ? f32x4_{0.f, 0.f, 0.f, 0.f} : s - av[h];
-                *reinterpret_cast<f32x4_*>(E + at) = s;
+            for (int k = 0; k < 4; ++k) {
+                s[k] = epi_value<EPI>(s[k], av[h][k], zero);
+                if (epi_subtracts(EPI)) sq += (double)s[k] * s[k];
             }
+            epi_store4<EPI>(E, (int64_t)(m0 + row) * d + n0 + c, s);
         }
     }
+    if (epi_subtracts(EPI) && loss_part) block_sum_double(sq, STHREADS, s_loss, loss_part);
 }
 
 // ---- C[M,N] = A[M,K] . B[N,K]^T, bf16 in, fp32 out ---------------------------------
@@ -470,8 +522,8 @@ template <bool GATHER, int NW, bool SCATTER, int EPI = kEpiPlain, bool HB = fals
 __global__ __launch_bounds__(NW * 64) void k_gemm_nt_bf16(
     const uint16_t* __restrict__ A, int64_t lda, uint32_t a_bytes, const int* __restrict__ row_ids,
     const int* __restrict__ m_dev, const uint16_t* __restrict__ B, int64_t ldb, uint32_t b_bytes, int n,
-    int ktot, int pad_id, int n_tiles, float* __restrict__ C, int64_t ldc, ScatterArgs sc,
-    const void* __restrict__ aux)
+    int ktot, const int* __restrict__ zero_ids, int pad_id, int n_tiles, float* __restrict__ C, int64_t ldc,
+    ScatterArgs sc, const void* __restrict__ aux, double* __restrict__ loss_part)
 {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     __shared__ int s_pad_row;
@@ -480,7 +532,11 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_nt_bf16(
     const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
     const int m0 = ((q / n_tiles) * 8 + xcd) * TM;
     const int n0 = (q % n_tiles) * TN;
-    if (m0 >= M) return;
+    if (epi_subtracts(EPI) && loss_part) loss_part += blockIdx.x;
+    if (m0 >= M) {
+        if (epi_subtracts(EPI) && loss_part && threadIdx.x == 0) *loss_part = 0.0;
+        return;
+    }
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     constexpr int NT = NW == 4 ? 4 : 2;          // 32-column MFMA tiles per wave
     constexpr int GA = 16 / NW;                  // 16-row groups of A (and of B) a wave loads per slab
@@ -507,7 +563,7 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_nt_bf16(
         int64_t rowA = j;
         if (GATHER) {
             const int id = row_ids[j];
-            if (m0 + r < M && id == pad_id) s_pad_row = r;   // at most one row is the padding item
+            if (m0 + r < M && zero_ids[j] == pad_id) s_pad_row = r;   // at most one row is the padding item
             rowA = id;
         }
         oa[t] = (uint32_t)((rowA * lda + (int64_t)sl_begin * TK + lchunk * 8) * 2);
@@ -736,51 +792,49 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_nt_bf16(
                 }
             }
         }
-    } else if (m0 + TM <= M && n0 + TN <= n) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            float av[16][NT];
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int lr = wm * 128 + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-                const int64_t at = (int64_t)(m0 + lr) * ldc + n0 + wn * (NT * 32) + (lane & 31);
-#pragma unroll
-                for (int jj = 0; jj < NT; ++jj) av[r][jj] = epi_load<EPI>(aux, at + jj * 32);
-            }
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int lr = wm * 128 + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-                const int64_t at = (int64_t)(m0 + lr) * ldc + n0 + wn * (NT * 32) + (lane & 31);
-                const bool zero = lr == pad_row;
-#pragma unroll
-                for (int jj = 0; jj < NT; ++jj) epi_store<EPI>(C, at + jj * 32, acc[i][jj][r], av[r][jj], zero);
-            }
-        }
     } else {
+        // Staged like the fused gather's epilogue, 64 rows at a time: a wave then loads and stores whole row
+        // pieces, 4 columns per lane.  32,768 x 1024 x 1024, element by element and staged: with the
+        // rectifier 85 and 81 us, with the gate 101 and 84 us (half of that from storing bf16), subtracting
+        // 107 us and 23 for the sum of squares in a pass of its own against 112 us for both.
+        const int col = n0 + lane * 4;
+        const bool col_ok = col < n;
+        const int cr0 = (wave / (NW / 2)) * 32 + (wave % (NW / 2)) * RPW;           // first staged row
+        double sq = 0.0;
+        __syncthreads();
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            float av[16][NT];
+            const int row0 = m0 + (cr0 >> 5) * 128 + i * 32 + (cr0 & 31);           // + u
+            f32x4_ av[RPW];
+#pragma unroll
+            for (int u = 0; u < RPW; ++u)
+                av[u] = epi_load4<EPI>(aux, (int64_t)(row0 + u < M ? row0 + u : M - 1) * ldc + (col_ok ? col : 0));
+            unsigned char* stage = smem + (i & 1) * kScatterTileB;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int lr = wm * 128 + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-                const int64_t at = (int64_t)(m0 + lr) * ldc + n0 + wn * (NT * 32) + (lane & 31);
+                const int rr = (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
+                float* dst = reinterpret_cast<float*>(stage + (wm * 32 + rr) * kScatterRowB) + wn * (NT * 32) + (lane & 31);
 #pragma unroll
-                for (int jj = 0; jj < NT; ++jj)
-                    av[r][jj] = (m0 + lr < M && n0 + wn * (NT * 32) + jj * 32 + (lane & 31) < n)
-                                    ? epi_load<EPI>(aux, at + jj * 32) : 0.f;
+                for (int jj = 0; jj < NT; ++jj) dst[jj * 32] = acc[i][jj][r];
             }
+            __syncthreads();
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int lr = wm * 128 + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-                if (m0 + lr < M) {
-                    const int64_t at = (int64_t)(m0 + lr) * ldc + n0 + wn * (NT * 32) + (lane & 31);
-                    const bool zero = lr == pad_row;
+            for (int u = 0; u < RPW; ++u) {
+                f32x4_ v = *reinterpret_cast<const f32x4_*>(stage + (cr0 + u) * kScatterRowB + lane * 16);
+                const bool zero = row0 + u - m0 == pad_row;
 #pragma unroll
-                    for (int jj = 0; jj < NT; ++jj)
-                        if (n0 + wn * (NT * 32) + jj * 32 + (lane & 31) < n)
-                            epi_store<EPI>(C, at + jj * 32, acc[i][jj][r], av[r][jj], zero);
+                for (int k = 0; k < 4; ++k) v[k] = epi_value<EPI>(v[k], av[u][k], zero);
+                if (row0 + u < M && col_ok) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        if (epi_subtracts(EPI)) sq += (double)v[k] * v[k];
+                    epi_store4<EPI>(C, (int64_t)(row0 + u) * ldc + col, v);
                 }
             }
+        }
+        if (epi_subtracts(EPI) && loss_part) {
+            __syncthreads();
+            block_sum_double(sq, NW * 64, reinterpret_cast<double*>(smem), loss_part);
         }
     }
 }
@@ -797,16 +851,16 @@ constexpr int kGemmWaves = 8;
 template <bool SCATTER, int EPI, bool HB, bool WIDE, bool BDIRECT = false>
 static void launch_gemm_variant(Ctx* c, int kid, unsigned blocks, hipStream_t s, const uint16_t* A, int64_t lda,
                                 int64_t a_bytes, const int* row_ids, const int* m_dev, const uint16_t* B,
-                                int64_t ldb, int64_t b_bytes, int n, int k, int pad_id, int n_tiles, float* C,
-                                int64_t ldc, const ScatterArgs& sc, const void* aux)
+                                int64_t ldb, int64_t b_bytes, int n, int k, const int* zero_ids, int pad_id, int n_tiles,
+                                float* C, int64_t ldc, const ScatterArgs& sc, const void* aux, double* loss_part)
 {
     constexpr auto kern = k_gemm_nt_bf16<true, kGemmWaves, SCATTER, EPI, HB, WIDE, BDIRECT>;
-    constexpr size_t smem = SCATTER ? RSMEM_SC : RSMEM;
+    constexpr size_t smem = RSMEM_SC > RSMEM ? RSMEM_SC : RSMEM;
     ensure_dynamic_lds<kern>((int)smem);
     // the descriptor of a WIDE operand is not used; any size that fits its field will do
     launch_smem(c, kid, kern, dim3(blocks), dim3(kGemmWaves * 64), smem, s, A, lda,
-                (uint32_t)(WIDE ? 0 : a_bytes), row_ids, m_dev, B, ldb, (uint32_t)b_bytes, n, k, pad_id, n_tiles, C,
-                ldc, sc, aux);
+                (uint32_t)(WIDE ? 0 : a_bytes), row_ids, m_dev, B, ldb, (uint32_t)b_bytes, n, k, zero_ids, pad_id, n_tiles, C,
+                ldc, sc, aux, loss_part);
 }
 
 // C[j,:] = epi(A[row_ids[j],:k] . B^T) for j < *m_dev <= m_bound with the 256x256 kernel.
@@ -818,29 +872,33 @@ static void launch_gemm_variant(Ctx* c, int kid, unsigned blocks, hipStream_t s,
 static void launch_gemm_nt(Ctx* c, const uint16_t* A, int64_t lda, int64_t a_rows, const int* row_ids,
                            const int* m_dev, int64_t m_bound, const uint16_t* B, int64_t ldb, int64_t b_rows,
                            int n, int k, float* C, int64_t ldc, hipStream_t s, const ScatterArgs* scatter,
-                           int pad_id, int epi, const void* aux, bool b_direct = false)
+                           const int* zero_ids, int pad_id, int epi, const void* aux, const EpiLoss* loss, bool b_direct = false)
 {
     const int n_tiles = (n + TN - 1) / TN;
     const unsigned blocks = (unsigned)((((m_bound + TM - 1) / TM + 7) / 8 * 8) * n_tiles);
     const int64_t a_bytes = a_rows * lda * 2, b_bytes = b_rows * ldb * 2;
     const bool wide = a_bytes >= kBufferWindow;
+    double* loss_part = loss ? loss->part : nullptr;
+    if (loss) *loss->blocks = (int)blocks;
     const int kid = wide ? KID_ENCODE_BF16_WIDE : KID_ENCODE_BF16;
     const ScatterArgs none = {nullptr, nullptr, nullptr, 0, 0, 0};
 #define GRAM_GO(SC, EPI, HB, WIDE, ARGS)                                                            \
     launch_gemm_variant<SC, EPI, HB, WIDE>(c, kid, blocks, s, A, lda, a_bytes, row_ids, m_dev, B, ldb, b_bytes, n, \
-                                           k, pad_id, n_tiles, C, ldc, ARGS, aux)
+                                           k, zero_ids, pad_id, n_tiles, C, ldc, ARGS, aux, loss_part)
 #define GRAM_GO_DIRECT(SC, EPI, HB, ARGS)                                                           \
     launch_gemm_variant<SC, EPI, HB, false, true>(c, kid, blocks, s, A, lda, a_bytes, row_ids, m_dev, B, ldb, b_bytes, n, \
-                                                  k, pad_id, n_tiles, C, ldc, ARGS, aux)
+                                                  k, zero_ids, pad_id, n_tiles, C, ldc, ARGS, aux, loss_part)
     if (b_direct) {
         if (epi == kEpiReluBf16) GRAM_GO_DIRECT(false, kEpiReluBf16, false, none);
         else if (epi == kEpiMinus) GRAM_GO_DIRECT(false, kEpiMinus, false, none);
+        else if (epi == kEpiMinusBf16) GRAM_GO_DIRECT(false, kEpiMinusBf16, false, none);
         else if (scatter && scatter->h_bf16) GRAM_GO_DIRECT(true, kEpiPlain, true, *scatter);
         else if (scatter) GRAM_GO_DIRECT(true, kEpiPlain, false, *scatter);
         else GRAM_GO_DIRECT(false, kEpiPlain, false, none);
     } else if (epi == kEpiReluBf16) GRAM_GO(false, kEpiReluBf16, false, false, none);
     else if (epi == kEpiMinus) GRAM_GO(false, kEpiMinus, false, false, none);
-    else if (epi == kEpiGate) GRAM_GO(false, kEpiGate, false, false, none);
+    else if (epi == kEpiMinusBf16) GRAM_GO(false, kEpiMinusBf16, false, false, none);
+    else if (epi == kEpiGateBf16) GRAM_GO(false, kEpiGateBf16, false, false, none);
     else if (scatter && scatter->h_bf16) {
         if (wide) GRAM_GO(true, kEpiPlain, true, true, *scatter);
         else GRAM_GO(true, kEpiPlain, true, false, *scatter);
@@ -955,14 +1013,20 @@ static bool takes_big_kernel(const Ctx* c, int64_t rows_max, int n_out, int k, i
 // The 256x256 kernel reads the second operand untransposed for these shapes and modes.
 static bool big_kernel_reads_plain_b(int64_t a_rows, int k, int n_out, int epi)
 {
-    return n_out % 8 == 0 && n_out >= 8 && epi != kEpiGate && a_rows * k * 2 < kBufferWindow &&
+    return n_out % 8 == 0 && n_out >= 8 && epi != kEpiGateBf16 && a_rows * k * 2 < kBufferWindow &&
            (int64_t)k * n_out * 2 < kBufferWindow;
+}
+
+// Blocks of the widest grid gemm_rows_bf16 launches for up to `rows` rows.
+int64_t epi_loss_blocks_max(int64_t rows, int64_t n_out)
+{
+    return ((rows + BM - 1) / BM + 7) / 8 * 8 * ((n_out + BN - 1) / BN);
 }
 
 // The kernel for small and mid-sized batches: the second operand untransposed, descriptors for both.
 static bool takes_mid_kernel(int64_t a_rows, int k, int n_out, int epi)
 {
-    return n_out % 8 == 0 && epi != kEpiGate && a_rows * k * 2 < kBufferWindow && (int64_t)k * n_out * 2 < kBufferWindow;
+    return n_out % 8 == 0 && epi != kEpiGateBf16 && a_rows * k * 2 < kBufferWindow && (int64_t)k * n_out * 2 < kBufferWindow;
 }
 
 // Whether gemm_rows_bf16 will read B_plain (the [k, n_out] matrix as the caller holds it) instead of
@@ -976,9 +1040,12 @@ bool gemm_reads_plain_b(const Ctx* c, int64_t rows_max, int64_t a_rows, int k, i
 
 bool gemm_rows_bf16(Ctx* c, const void* A, int64_t a_rows, int k, const int* row_ids, int pad_id,
                     const int* n_dev, int64_t rows_max, const void* Bt, int n_out, float* C, hipStream_t s,
-                    void* H_scatter, bool caller_wants_C, int epi, const void* aux, const void* B_plain)
+                    void* H_scatter, bool caller_wants_C, int epi, const void* aux, const void* B_plain,
+                    const int* zero_ids, const EpiLoss* loss)
 {
     if (rows_max <= 0) return false;
+    if (!zero_ids) zero_ids = row_ids;
+    double* loss_part = loss ? loss->part : nullptr;
     if (takes_big_kernel(c, rows_max, n_out, k, a_rows, epi)) {
         // Fusing the gather pays when there are tiles for every CU: with a handful of tiles the
         // position stores of a tile run on one CU while a separate gather spreads over all.
@@ -988,11 +1055,11 @@ bool gemm_rows_bf16(Ctx* c, const void* A, int64_t a_rows, int k, const int* row
         if (big_kernel_reads_plain_b(a_rows, k, n_out, epi) && B_plain)
             launch_gemm_nt(c, static_cast<const uint16_t*>(A), k, a_rows, row_ids, n_dev, rows_max,
                            static_cast<const uint16_t*>(B_plain), n_out, k, n_out, k, C, n_out, s,
-                           fuse ? &sc : nullptr, pad_id, epi, aux, true);
+                           fuse ? &sc : nullptr, zero_ids, pad_id, epi, aux, loss, true);
         else
             launch_gemm_nt(c, static_cast<const uint16_t*>(A), k, a_rows, row_ids, n_dev, rows_max,
                            static_cast<const uint16_t*>(Bt), k, n_out, n_out, k, C, n_out, s, fuse ? &sc : nullptr,
-                           pad_id, epi, aux);
+                           zero_ids, pad_id, epi, aux, loss);
         return fuse;
     }
     if (B_plain && takes_mid_kernel(a_rows, k, n_out, epi)) {
@@ -1011,9 +1078,10 @@ bool gemm_rows_bf16(Ctx* c, const void* A, int64_t a_rows, int k, const int* row
         const int shape = tiles64 * 4 <= 5 * (int64_t)c->num_cus ? 0 : tiles64 * 2 <= 5 * (int64_t)c->num_cus ? 1 : 2;
         auto go = [&](auto kern, int tm, int tn, int threads, size_t lds) {
             const unsigned blocks = (unsigned)(((rows_max + tm - 1) / tm + 7) / 8 * 8 * ((n_out + tn - 1) / tn));
+            if (loss) *loss->blocks = (int)blocks;
             launch_smem(c, KID_ENCODE_BF16, kern, dim3(blocks), dim3(threads), lds, s, static_cast<const uint16_t*>(A),
                         x_bytes, static_cast<const uint16_t*>(B_plain), w_bytes, row_ids, n_dev, (int)rows_max, k, n_out,
-                        pad_id, C, aux);
+                        zero_ids, pad_id, C, aux, loss_part);
         };
 #define GRAM_MID_(TM_, TN_, KG_, WR_, DEPTH_, EPI_)                                                 \
     {                                                                                               \
@@ -1027,6 +1095,7 @@ bool gemm_rows_bf16(Ctx* c, const void* A, int64_t a_rows, int k, const int* row
     else if (shape == 1) GRAM_MID_(128, 64, 2, 2, 2, EPI_)                                          \
     else GRAM_MID_(128, 128, 2, 2, 2, EPI_)
         if (epi == kEpiMinus) { GRAM_GO_MID(kEpiMinus) }
+        else if (epi == kEpiMinusBf16) { GRAM_GO_MID(kEpiMinusBf16) }
         else if (epi == kEpiReluBf16) { GRAM_GO_MID(kEpiReluBf16) }
         else { GRAM_GO_MID(kEpiPlain) }
 #undef GRAM_GO_MID
@@ -1034,37 +1103,27 @@ bool gemm_rows_bf16(Ctx* c, const void* A, int64_t a_rows, int k, const int* row
         return false;
     }
     const dim3 grid((n_out + BN - 1) / BN, (unsigned)((rows_max + BM - 1) / BM));
-    const uint16_t* a16 = static_cast<const uint16_t*>(A);
-    const uint16_t* b16 = static_cast<const uint16_t*>(Bt);
-    if (B_plain && n_out % 8 == 0 && (epi == kEpiPlain || epi == kEpiMinus)) {
-        // the kernel reads the untransposed operand itself
-        const uint16_t* w16 = static_cast<const uint16_t*>(B_plain);
-        if (epi == kEpiMinus)
-            launch(c, KID_ENCODE_BF16, k_encode_bf16<kEpiMinus, true>, grid, dim3(kBlock), s, a16, w16, row_ids,
-                   n_dev, k, n_out, pad_id, C, aux);
-        else
-            launch(c, KID_ENCODE_BF16, k_encode_bf16<kEpiPlain, true>, grid, dim3(kBlock), s, a16, w16, row_ids,
-                   n_dev, k, n_out, pad_id, C, aux);
-        return false;
-    }
-    if (epi == kEpiReluBf16)
-        launch(c, KID_ENCODE_BF16, k_encode_bf16<kEpiReluBf16>, grid, dim3(kBlock), s, a16, b16, row_ids, n_dev, k,
-               n_out, pad_id, C, aux);
-    else if (epi == kEpiMinus)
-        launch(c, KID_ENCODE_BF16, k_encode_bf16<kEpiMinus>, grid, dim3(kBlock), s, a16, b16, row_ids, n_dev, k,
-               n_out, pad_id, C, aux);
-    else if (epi == kEpiGate)
-        launch(c, KID_ENCODE_BF16, k_encode_bf16<kEpiGate>, grid, dim3(kBlock), s, a16, b16, row_ids, n_dev, k,
-               n_out, pad_id, C, aux);
-    else
-        launch(c, KID_ENCODE_BF16, k_encode_bf16<kEpiPlain>, grid, dim3(kBlock), s, a16, b16, row_ids, n_dev, k,
-               n_out, pad_id, C, aux);
+    if (loss) *loss->blocks = (int)(grid.x * grid.y);
+    // the untransposed second operand, where the kernel reads it itself
+    const bool plain = B_plain && n_out % 8 == 0 && (epi == kEpiPlain || epi == kEpiMinus);
+    const void* B = plain ? B_plain : Bt;
+    auto go = [&](auto kern) {
+        launch(c, KID_ENCODE_BF16, kern, grid, dim3(kBlock), s, static_cast<const uint16_t*>(A),
+               static_cast<const uint16_t*>(B), row_ids, n_dev, k, n_out, zero_ids, pad_id, C, aux, loss_part);
+    };
+    if (plain && epi == kEpiMinus) go(k_encode_bf16<kEpiMinus, true>);
+    else if (plain) go(k_encode_bf16<kEpiPlain, true>);
+    else if (epi == kEpiReluBf16) go(k_encode_bf16<kEpiReluBf16>);
+    else if (epi == kEpiMinus) go(k_encode_bf16<kEpiMinus>);
+    else if (epi == kEpiMinusBf16) go(k_encode_bf16<kEpiMinusBf16>);
+    else if (epi == kEpiGateBf16) go(k_encode_bf16<kEpiGateBf16>);
+    else go(k_encode_bf16<kEpiPlain>);
     return false;
 }
 
 bool encode_forward(Ctx* c, const void* X, const void* W, const int* uniq, const int* u_dev,
                     int64_t rows_max, float* E, hipStream_t s, void* H_scatter, bool caller_wants_E, int epi,
-                    const void* aux)
+                    const void* aux, const EpiLoss* loss)
 {
     if (rows_max <= 0) return false;
     const int d_in = c->cfg.d_in, d = c->cfg.d;
@@ -1073,7 +1132,7 @@ bool encode_forward(Ctx* c, const void* X, const void* W, const int* uniq, const
         const bool direct = gemm_reads_plain_b(c, rows_max, c->cfg.vocab_n, d_in, d, epi);
         if (!direct) transpose_weight(c, W, d_in, d, c->Wt, s);
         return gemm_rows_bf16(c, X, c->cfg.vocab_n, d_in, uniq, c->cfg.pad_id, u_dev, rows_max, c->Wt, d, E, s,
-                              H_scatter, caller_wants_E, epi, aux, direct ? W : nullptr);
+                              H_scatter, caller_wants_E, epi, aux, direct ? W : nullptr, nullptr, loss);
     }
     launch(c, KID_ENCODE_F32, k_encode_f32, dim3((d + 63) / 64, (unsigned)((rows_max + 3) / 4)),
            dim3(kBlock), s, static_cast<const float*>(X), static_cast<const float*>(W), uniq, u_dev,
@@ -1144,7 +1203,8 @@ struct WgradExport {
     int* u_total_dev;          // nullable
     int* scal;
 };
-template <int NW, bool WIDE = false, bool EXPORT = false>
+// GB: the rows are bf16 already (what an earlier contraction stored rounded).
+template <int NW, bool WIDE = false, bool EXPORT = false, bool GB = false>
 __global__ __launch_bounds__(NW * 64) void k_wgrad_tn_bf16(
     const uint16_t* __restrict__ X, uint32_t x_bytes, const int* __restrict__ id_of_slot,
     const float* __restrict__ G, uint32_t g_bytes, const int* __restrict__ rows_dev, int d_in, int d,
@@ -1224,7 +1284,7 @@ __global__ __launch_bounds__(NW * 64) void k_wgrad_tn_bf16(
                     (((wn * (NT * 4) + i * 4 + (grp & 1) * 2 + ((j16 & 3) >> 1)) ^ f_x) * 16) + (j16 & 1) * 8;
 
     bf16x8 fa[2][4], fb[2][NT];
-    v4i32 ra[SETS][RW / 2], rg[SETS][RW];
+    v4i32 ra[SETS][RW / 2], rg[SETS][GB ? RW / 2 : RW];
     // (EXPORT) rk[set]: lane t < RW holds the output row of the t-th buffer row of the slab in that
     // set, -1 if the row is not to be written; fetched BEFORE the slab's data loads (see below)
     int rk[EXPORT ? SETS : 1];
@@ -1295,7 +1355,20 @@ __global__ __launch_bounds__(NW * 64) void k_wgrad_tn_bf16(
                 ra[(SET) % SETS][t] = __builtin_amdgcn_raw_buffer_load_b128(rsX, off, 0, 0);        \
             }                                                                                       \
         }                                                                                           \
-        _Pragma("unroll") for (int t = 0; t < RW; ++t) {                                            \
+        if (GB) _Pragma("unroll") for (int t = 0; t < RW / 2; ++t) {                                \
+            const int slot = sb_ + a_row + 2 * t;                                                   \
+            const int col = c0 + ((a_pos ^ ((slot & 3) << 2)) * 8);                                 \
+            const bool okg = col < d && slot < U && slot >= row_begin;                              \
+            if (WIDE) {                                                                             \
+                v4i32 v_ = {0, 0, 0, 0};                                                            \
+                if (okg) v_ = *reinterpret_cast<const v4i32*>(reinterpret_cast<const uint16_t*>(G) + (int64_t)slot * d + col); \
+                rg[(SET) % SETS][t] = v_;                                                           \
+            } else {                                                                                \
+                const uint32_t off = okg ? (uint32_t)(((int64_t)slot * d + col) * 2) : kOutOfRange; \
+                rg[(SET) % SETS][t] = __builtin_amdgcn_raw_buffer_load_b128(rsG, off, 0, 0);        \
+            }                                                                                       \
+        }                                                                                           \
+        if (!GB) _Pragma("unroll") for (int t = 0; t < RW; ++t) {                                   \
             const int slot = sb_ + wave * RW + t;                                                    \
             const bool okg = g_col_ok && slot < U && slot >= row_begin;                             \
             if (WIDE) {                                                                             \
@@ -1314,7 +1387,9 @@ __global__ __launch_bounds__(NW * 64) void k_wgrad_tn_bf16(
         unsigned char* pg_ = parkG + (STAGE) * WSTAGEB;                                             \
         _Pragma("unroll") for (int t = 0; t < RW / 2; ++t)                                          \
             *reinterpret_cast<v4i32*>(pa_ + t * 1024) = ra[(SET) % SETS][t];                                 \
-        _Pragma("unroll") for (int t = 0; t < RW; ++t) {                                            \
+        if (GB) _Pragma("unroll") for (int t = 0; t < RW / 2; ++t)                                  \
+            *reinterpret_cast<v4i32*>(pa_ + WOPB + t * 1024) = rg[(SET) % SETS][t];                 \
+        if (!GB) _Pragma("unroll") for (int t = 0; t < RW; ++t) {                                   \
             const v4i32 v = rg[(SET) % SETS][t];                                                             \
             const uint32_t lo = pack_bf16x2(__int_as_float(v.x), __int_as_float(v.y));              \
             const uint32_t hi = pack_bf16x2(__int_as_float(v.z), __int_as_float(v.w));              \
@@ -1409,8 +1484,8 @@ constexpr int VACC_STRIDE = VN + 8;                                 // floats pe
 constexpr size_t VSMEM = (size_t)VGROUPS * VM * VACC_STRIDE * 4;
 static_assert(VSMEM >= 2 * (size_t)VGROUPS * VSTAGEB, "the tiles overlay the stages");
 
-// LISTED: the items of the rows are listed (else row r pairs with item r).
-template <bool EXPORT, bool LISTED>
+// LISTED: the items of the rows are listed (else row r pairs with item r).  GB: the rows are bf16 already.
+template <bool EXPORT, bool LISTED, bool GB = false>
 __global__ __launch_bounds__(VTHREADS) void k_wgrad_short(
     const uint16_t* __restrict__ X, uint32_t x_bytes, const int* __restrict__ id_of_slot,
     const float* __restrict__ G, uint32_t g_bytes, const int* __restrict__ rows_dev, int d_in, int d,
@@ -1451,6 +1526,8 @@ __global__ __launch_bounds__(VTHREADS) void k_wgrad_short(
     const bool feat_ok = feat < d_in;
     const int g_col = c0 + 4 * lpos;
     const bool g_col_ok = g_col < d;
+    // (GB: one 16-byte chunk per thread, chunk gt & 7 of row gt >> 3)
+    const int brow = gt >> 3, bcol = c0 + (((gt & 7) ^ ((brow & 2) << 1)) * 8);
     const int first = row_begin / WK + z * VGROUPS + grp, stride = splits * VGROUPS;
     bool ex_mine[2];
 #pragma unroll
@@ -1464,7 +1541,7 @@ __global__ __launch_bounds__(VTHREADS) void k_wgrad_short(
     const __amdgpu_buffer_rsrc_t rsR = __builtin_amdgcn_make_buffer_rsrc(const_cast<int*>(ex.rank_of_slot), 0, ranked ? row_end * 4 : 0, kBufferFlags);
     const __amdgpu_buffer_rsrc_t rsT = __builtin_amdgcn_make_buffer_rsrc(ex.G_total, 0, EXPORT ? g_bytes : 0, kBufferFlags);
     int ids_next[VDEPTH][2], ids_cur[2], rk[VDEPTH][2];
-    v4i32 rx[VDEPTH][2], rg[VDEPTH][2];
+    v4i32 rx[VDEPTH][2], rg[VDEPTH][GB ? 1 : 2];
 #define GRAM_SLOT(IT, T_) (((first + (IT) * stride) * WK) + lrow + 16 * (T_))
 #define GRAM_IDS(SET, IT)                                                                           \
     _Pragma("unroll") for (int t = 0; t < 2; ++t) {                                                 \
@@ -1478,8 +1555,15 @@ __global__ __launch_bounds__(VTHREADS) void k_wgrad_short(
         if (EXPORT) rk[SET][t] = __builtin_amdgcn_raw_buffer_load_b32(rsR, in_ ? (uint32_t)slot * 4u : kOutOfRange, 0, 0); \
         const uint32_t ox = in_ && feat_ok && ids_cur[t] != pad_id ? ((uint32_t)ids_cur[t] * (uint32_t)d_in + (uint32_t)feat) * 2u : kOutOfRange; \
         rx[SET][t] = __builtin_amdgcn_raw_buffer_load_b128(rsX, ox, 0, 0);                          \
-        const uint32_t og = in_ && g_col_ok ? ((uint32_t)slot * (uint32_t)d + (uint32_t)g_col) * 4u : kOutOfRange; \
-        rg[SET][t] = __builtin_amdgcn_raw_buffer_load_b128(rsG, og, 0, 0);                          \
+        if (!GB) {                                                                                  \
+            const uint32_t og = in_ && g_col_ok ? ((uint32_t)slot * (uint32_t)d + (uint32_t)g_col) * 4u : kOutOfRange; \
+            rg[SET][t % (GB ? 1 : 2)] = __builtin_amdgcn_raw_buffer_load_b128(rsG, og, 0, 0);       \
+        }                                                                                           \
+    }                                                                                               \
+    if (GB) {                                                                                       \
+        const int slot = (first + (IT) * stride) * WK + brow;                                       \
+        const uint32_t og = slot < row_end && bcol < d ? ((uint32_t)slot * (uint32_t)d + (uint32_t)bcol) * 2u : kOutOfRange; \
+        rg[SET][0] = __builtin_amdgcn_raw_buffer_load_b128(rsG, og, 0, 0);                          \
     }
 #define GRAM_PARK(SET, IT, STAGE)                                                                   \
     {                                                                                               \
@@ -1489,7 +1573,8 @@ __global__ __launch_bounds__(VTHREADS) void k_wgrad_short(
             const bool held = slot < U && slot >= row_begin;                                        \
             const v4i32 zero_ = {0, 0, 0, 0};                                                       \
             *reinterpret_cast<v4i32*>(s_ + row * (VM * 2) + lpos * 16) = held ? rx[SET][t] : zero_; \
-            const v4i32 v = held ? rg[SET][t] : zero_;                                              \
+            if (GB) continue;                                                                       \
+            const v4i32 v = held ? rg[SET][t % (GB ? 1 : 2)] : zero_;                               \
             const uint32_t lo = pack_bf16x2(__int_as_float(v.x), __int_as_float(v.y));              \
             const uint32_t hi = pack_bf16x2(__int_as_float(v.z), __int_as_float(v.w));              \
             *reinterpret_cast<uint2*>(s_ + VXB + row * (VN * 2) + (((lpos >> 1) ^ ((row & 2) << 1)) * 16) + (lpos & 1) * 8) = \
@@ -1499,6 +1584,11 @@ __global__ __launch_bounds__(VTHREADS) void k_wgrad_short(
                                         ? ((uint32_t)(ranked ? rk[SET][t] : slot) * (uint32_t)d + (uint32_t)g_col) * 4u : kOutOfRange; \
                 __builtin_amdgcn_raw_buffer_store_b128(v, rsT, to, 0, kNonTemporal);                \
             }                                                                                       \
+        }                                                                                           \
+        if (GB) {                                                                                   \
+            const int slot = (first + (IT) * stride) * WK + brow;                                   \
+            const v4i32 zero_ = {0, 0, 0, 0};                                                       \
+            *reinterpret_cast<v4i32*>(s_ + VXB + brow * (VN * 2) + (gt & 7) * 16) = slot < U && slot >= row_begin ? rg[SET][0] : zero_; \
         }                                                                                           \
     }
 #define GRAM_IDS_TAKE(SET) ids_cur[0] = ids_next[SET][0]; ids_cur[1] = ids_next[SET][1];
@@ -1698,7 +1788,8 @@ bool encoder_wgrad(Ctx* c, const void* X, float* dW, hipStream_t s, int64_t firs
         int64_t want = slabs_bound / 8 / 8 * 8;
         if (want < 8) want = 8;
         if (want < S) S = (int)want;
-        const int64_t x_bytes = x_rows * d_in * 2, g_bytes = cap * d * 4;
+        const bool gb = other && other->rows_bf16;
+        const int64_t x_bytes = x_rows * d_in * 2, g_bytes = cap * d * (gb ? 2 : 4);
         const int tiles = ((d_in + 255) / 256) * ((d + 255) / 256);
         const WgradExport no_export = {nullptr, nullptr, 0, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
         const bool wide = x_bytes >= kBufferWindow || g_bytes >= kBufferWindow;
@@ -1755,25 +1846,30 @@ bool encoder_wgrad(Ctx* c, const void* X, float* dW, hipStream_t s, int64_t firs
             }
             exported = true;
         } else if (is_short) {
-            constexpr auto listed = k_wgrad_short<false, true>;
-            constexpr auto plain = k_wgrad_short<false, false>;
-            ensure_dynamic_lds<listed>((int)VSMEM);
-            ensure_dynamic_lds<plain>((int)VSMEM);
-            launch_smem(c, KID_WGRAD_BF16, ids ? listed : plain, dim3((unsigned)short_blocks), dim3(VTHREADS), VSMEM, s,
-                        static_cast<const uint16_t*>(X), (uint32_t)x_bytes, ids, rows, (uint32_t)g_bytes,
-                        rows_dev, d_in, d, pad_id, S, out, row_begin, row_end, add_here, no_export);
-        } else if (!wide) {
-            constexpr auto kern = k_wgrad_tn_bf16<kWgradWaves, false>;
-            ensure_dynamic_lds<kern>((int)WSMEM);
-            launch_smem(c, KID_WGRAD_BF16, kern, dim3((unsigned)(tiles * S)), dim3(kWgradWaves * 64), WSMEM, s,
-                        static_cast<const uint16_t*>(X), (uint32_t)x_bytes, ids, rows, (uint32_t)g_bytes,
-                        rows_dev, d_in, d, pad_id, S, c->wg_partial, row_begin, row_end, no_export);
+            auto go = [&](auto kern) {
+                launch_smem(c, KID_WGRAD_BF16, kern, dim3((unsigned)short_blocks), dim3(VTHREADS), VSMEM, s,
+                            static_cast<const uint16_t*>(X), (uint32_t)x_bytes, ids, rows, (uint32_t)g_bytes,
+                            rows_dev, d_in, d, pad_id, S, out, row_begin, row_end, add_here, no_export);
+            };
+#define GRAM_GO(...) { ensure_dynamic_lds<__VA_ARGS__>((int)VSMEM); go(__VA_ARGS__); }
+            if (gb && ids) GRAM_GO(k_wgrad_short<false, true, true>)
+            else if (gb) GRAM_GO(k_wgrad_short<false, false, true>)
+            else if (ids) GRAM_GO(k_wgrad_short<false, true>)
+            else GRAM_GO(k_wgrad_short<false, false>)
+#undef GRAM_GO
         } else {
-            constexpr auto kern = k_wgrad_tn_bf16<kWgradWaves, true>;
-            ensure_dynamic_lds<kern>((int)WSMEM);
-            launch_smem(c, KID_WGRAD_BF16_WIDE, kern, dim3((unsigned)(tiles * S)), dim3(kWgradWaves * 64), WSMEM, s,
-                        static_cast<const uint16_t*>(X), 0u, ids, rows, 0u, rows_dev, d_in, d, pad_id, S,
-                        c->wg_partial, row_begin, row_end, no_export);
+            auto go = [&](auto kern, int kid, int64_t xb, int64_t gbytes) {
+                launch_smem(c, kid, kern, dim3((unsigned)(tiles * S)), dim3(kWgradWaves * 64), WSMEM, s,
+                            static_cast<const uint16_t*>(X), (uint32_t)xb, ids, rows, (uint32_t)gbytes,
+                            rows_dev, d_in, d, pad_id, S, c->wg_partial, row_begin, row_end, no_export);
+            };
+#define GRAM_GO(KID, XB, GBYTES, ...) { ensure_dynamic_lds<__VA_ARGS__>((int)WSMEM); go(__VA_ARGS__, KID, XB, GBYTES); }
+            // (the descriptors of the WIDE variant are not used)
+            if (wide && gb) GRAM_GO(KID_WGRAD_BF16_WIDE, 0, 0, k_wgrad_tn_bf16<kWgradWaves, true, false, true>)
+            else if (wide) GRAM_GO(KID_WGRAD_BF16_WIDE, 0, 0, k_wgrad_tn_bf16<kWgradWaves, true>)
+            else if (gb) GRAM_GO(KID_WGRAD_BF16, x_bytes, g_bytes, k_wgrad_tn_bf16<kWgradWaves, false, false, true>)
+            else GRAM_GO(KID_WGRAD_BF16, x_bytes, g_bytes, k_wgrad_tn_bf16<kWgradWaves, false>)
+#undef GRAM_GO
         }
     } else {
         launch(c, KID_WGRAD_F32, k_wgrad_f32, dim3((d + 63) / 64, (d_in + 3) / 4, S), dim3(kBlock), s,

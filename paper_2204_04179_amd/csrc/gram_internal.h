@@ -129,7 +129,7 @@ struct Ctx {
     long long* cnt_of_slot = nullptr; // [cap_total] occurrences of the item of each row in the window
     float* G = nullptr;         // [cap_total, d] persistent per-item gradient
     float* E_ws = nullptr;      // [cap_u, d] representations when the caller passes E = NULL
-    double* loss_part = nullptr; // [cap_chunk / kPseudoRows + 1] per-block sums of the pseudo-loss
+    double* loss_part = nullptr; // per-block sums of the pseudo-loss
     long long* cnt64 = nullptr; // [N] occurrences of each ID in the window (dense layout only)
     int* dense_sums = nullptr;  // [N / kScanTile + 1] items per tile of IDs (dense layout only)
     int* chunk_ids = nullptr;   // [cap_chunk] checked copy of a content-encoder batch's item IDs
@@ -240,11 +240,11 @@ void gather_heavy(Ctx* c, const float* E, int64_t m, void* H, hipStream_t s);
 void pseudo_target(Ctx* c, const float* E, float* Ht, double* loss_dev, hipStream_t s);
 // Checked copy of a content-encoder batch's IDs into c->chunk_ids and its size into scal[kSChunkN].
 void chunk_ids_prepare(Ctx* c, const int* ids, int64_t n, hipStream_t s);
-// With Ht: R[j,:] -= Ht[j,:] for the n rows of the batch in c->chunk_ids (zero for the padding
-// item); without: R is taken as it is.  With loss_dev, 1/2 of the sum of the squares of R.
-// R_bf16 (nullable, [n, d] bf16): also receives the miss rounded to bf16.
-void pseudo_miss(Ctx* c, float* R, const float* Ht, int64_t n, double* loss_dev, hipStream_t s,
-                 void* R_bf16 = nullptr);
+// R[j,:] -= Ht[j,:] for the n rows of the batch in c->chunk_ids (zero for the padding item); with
+// loss_dev, 1/2 of the sum of the squares of R.  (float32 contexts)
+void pseudo_miss(Ctx* c, float* R, const float* Ht, int64_t n, double* loss_dev, hipStream_t s);
+// 1/2 of the sum of the `parts` block sums in c->loss_part.
+void pseudo_loss(Ctx* c, int parts, double* loss_dev, hipStream_t s);
 void assign_slots(Ctx* c, hipStream_t s);
 void segment_reduce(Ctx* c, const float* dH, int64_t m, hipStream_t s, bool commit = false);
 void flush_export(Ctx* c, int* uniq_total, int* counts_total, long long* counts64_total, float* G_total,
@@ -266,10 +266,16 @@ void iota_i32(int* p, int64_t n, hipStream_t s);
 // was written (gather_rows must follow).
 // epi (bf16 contexts only; see the enum): what the contraction does with an output element
 // before storing it; a mode other than kEpiPlain excludes the fused gather.
-enum { kEpiPlain = 0, kEpiReluBf16 = 1, kEpiMinus = 2, kEpiGate = 3 };
+enum { kEpiPlain = 0, kEpiReluBf16 = 1, kEpiMinus = 2, kEpiGateBf16 = 3, kEpiMinusBf16 = 4 };
+// Where a subtracting contraction leaves its blocks' sums of squares, and how many there are.
+struct EpiLoss {
+    double* part;
+    int* blocks;
+};
+int64_t epi_loss_blocks_max(int64_t rows, int64_t n_out);
 bool encode_forward(Ctx* c, const void* X, const void* W, const int* uniq, const int* u_dev,
                     int64_t rows_max, float* E, hipStream_t s, void* H_scatter, bool caller_wants_E,
-                    int epi = kEpiPlain, const void* aux = nullptr);
+                    int epi = kEpiPlain, const void* aux = nullptr, const EpiLoss* loss = nullptr);
 // Rows the weight gradient contracts over when they are not the persistent buffer's: row j pairs
 // item ids[j] with rows[j,:] (float32, d columns); *n_dev rows are held, at most n_max.
 // With d_in != 0 the contraction also takes its shape from here instead of the context: the
@@ -282,6 +288,7 @@ struct WgradRows {
     int64_t n_max;
     int64_t x_rows = 0;
     int d_in = 0, d = 0, pad_id = -1;
+    bool rows_bf16 = false;     // rows[] is bf16, rounded by the kernel that wrote it
 };
 // Weight gradient over the buffer rows [first_row, first_row + n_rows) (clipped to the rows held),
 // or over the rows of `other`, written to dW or added to it.
@@ -314,8 +321,8 @@ int wgrad_splits_dims(int d_in, int d, bool bf16);
 // bf16 helpers the two-layer encoder shares with the linear one.
 void transpose_weight(Ctx* c, const void* W, int rows, int cols, void* Wt, hipStream_t s);
 // C[j,:] = epi(A[row_ids[j],:k] . Bt^T) for j < *n_dev (A bf16 [a_rows, k], Bt bf16 [n_out, k], C
-// float32 [., n_out], or bf16 for kEpiReluBf16); a row whose ID equals pad_id is zero.  kEpiMinus
-// subtracts the float32 matrix aux, kEpiGate keeps the value where the bf16 matrix aux is positive
+// float32 [., n_out], or bf16 for the modes named so); a row whose ID in zero_ids (NULL: row_ids) equals
+// pad_id is zero.  kEpiMinus subtracts the float32 matrix aux, kEpiGateBf16 keeps the value where the bf16 matrix aux is positive
 // (both [., n_out]).  B_plain, if given, is the untransposed second operand [k, n_out]: where
 // gemm_reads_plain_b says so, the kernels read it directly and Bt is not touched (the caller need
 // not have filled it).
@@ -324,6 +331,6 @@ bool gemm_reads_plain_b(const Ctx* c, int64_t rows_max, int64_t a_rows, int k, i
 bool gemm_rows_bf16(Ctx* c, const void* A, int64_t a_rows, int k, const int* row_ids, int pad_id,
                     const int* n_dev, int64_t rows_max, const void* Bt, int n_out, float* C, hipStream_t s,
                     void* H_scatter, bool caller_wants_C, int epi = kEpiPlain, const void* aux = nullptr,
-                    const void* B_plain = nullptr);
+                    const void* B_plain = nullptr, const int* zero_ids = nullptr, const EpiLoss* loss = nullptr);
 
 }  // namespace gram

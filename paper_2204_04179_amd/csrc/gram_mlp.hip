@@ -66,9 +66,10 @@ void mlp_backward(Ctx* c, const void* X, const void* W1, const void* W2, const i
     const int d_in = c->cfg.d_in, dh = c->cfg.d_hidden, d = c->cfg.d;
     auto up = [](int64_t v) { return (v + 255) / 256 * 256; };
     char* w = static_cast<char*>(work);
-    float* Z = reinterpret_cast<float*>(w);                  // [n, dh] dL/dz
+    // dL/dz and the rows of dL/dh only ever enter the matrix cores: the kernels that produce them
+    // store them as the bf16 values those would round them to
+    void* Zb = w;                                            // [n, dh] bf16 dL/dz
     void* A1 = w + up(n * dh * 4);                           // [n, dh] bf16 activations
-    float* R = reinterpret_cast<float*>(w + up(n * dh * 4) + up(n * dh * 2));          // [n, d]
     void* Rb = w + up(n * dh * 4) + up(n * dh * 2) + up(n * d * 4);                    // [n, d] bf16
     const int* n_dev = c->scal + kSChunkN;
 
@@ -79,34 +80,33 @@ void mlp_backward(Ctx* c, const void* X, const void* W1, const void* W2, const i
         gemm_rows_bf16(c, X, c->cfg.vocab_n, d_in, c->chunk_ids, c->cfg.pad_id, n_dev, n, c->W1t, dh,
                        static_cast<float*>(A1), s, nullptr, true, kEpiReluBf16, nullptr, plain1 ? W1 : nullptr);
     }
-    const float* Rsrc = rows;
     if (Ht) {
         // Algorithm 1 step 4 as a regression: output at the current weights minus the stored target
+        int parts = 0;
+        const EpiLoss loss = {c->loss_part, &parts};
         if (n > 0) {
-            const bool plain2 = gemm_reads_plain_b(c, n, n, dh, d, kEpiPlain);
+            const bool plain2 = gemm_reads_plain_b(c, n, n, dh, d, kEpiMinusBf16);
             if (!plain2) transpose_weight(c, W2, dh, d, c->W2t, s);
-            gemm_rows_bf16(c, A1, n, dh, c->iota, -1, n_dev, n, c->W2t, d, R, s, nullptr, true, kEpiPlain, nullptr,
-                           plain2 ? W2 : nullptr);
+            gemm_rows_bf16(c, A1, n, dh, c->iota, c->cfg.pad_id, n_dev, n, c->W2t, d, static_cast<float*>(Rb), s, nullptr,
+                           true, kEpiMinusBf16, Ht, plain2 ? W2 : nullptr, c->chunk_ids, loss_dev ? &loss : nullptr);
         }
-        // the miss kernel also leaves the bf16 copy of the miss that the dA contraction reads
-        pseudo_miss(c, R, Ht, n, loss_dev, s, Rb);
-        Rsrc = R;
+        if (loss_dev) pseudo_loss(c, parts, loss_dev, s);
+    } else if (n > 0) {
+        // gradient rows handed in by the caller are rounded to bf16 here
+        launch(c, KID_MLP_TO_BF16, k_to_bf16, dim3(blocks_for(n, d / 4)), dim3(kBlock), s,
+               reinterpret_cast<const f32x4*>(rows), n_dev, d / 4, reinterpret_cast<uint2*>(Rb));
     }
     // dW2 = A1^T R: the kept activations play the part of the features, row j with row j
-    const WgradRows top = {nullptr, Rsrc, n_dev, n, n > 0 ? n : 1, dh, d, -1};
+    const WgradRows top = {nullptr, static_cast<const float*>(Rb), n_dev, n, n > 0 ? n : 1, dh, d, -1, true};
     encoder_wgrad(c, A1, dW2, s, 0, n, accumulate, &top);
-    if (n > 0) {
-        // dA = R . W2^T: W2 [dh, d] is already the K-contiguous second operand of that product; gradient
-        // rows handed in by the caller are rounded to bf16 here (with targets the miss kernel did it)
-        if (!Ht)
-            launch(c, KID_MLP_TO_BF16, k_to_bf16, dim3(blocks_for(n, d / 4)), dim3(kBlock), s,
-                   reinterpret_cast<const f32x4*>(Rsrc), n_dev, d / 4, reinterpret_cast<uint2*>(Rb));
-        // the gate of the rectifier is applied as the product is stored: dZ = dA where the kept
-        // activation is positive, so forward and backward agree on which units are active
-        gemm_rows_bf16(c, Rb, n, d, c->iota, -1, n_dev, n, W2, dh, Z, s, nullptr, true, kEpiGate, A1);
-    }
+    // dA = R . W2^T: W2 [dh, d] is already the K-contiguous second operand of that product; the gate of
+    // the rectifier is applied as it is stored: dZ = dA where the kept activation is positive, so
+    // forward and backward agree on which units are active
+    if (n > 0)
+        gemm_rows_bf16(c, Rb, n, d, c->iota, -1, n_dev, n, W2, dh, static_cast<float*>(Zb), s, nullptr, true,
+                       kEpiGateBf16, A1);
     // dW1 = X[ids]^T dZ
-    const WgradRows bottom = {c->chunk_ids, Z, n_dev, n, c->cfg.vocab_n, d_in, dh, c->cfg.pad_id};
+    const WgradRows bottom = {c->chunk_ids, static_cast<const float*>(Zb), n_dev, n, c->cfg.vocab_n, d_in, dh, c->cfg.pad_id, true};
     encoder_wgrad(c, X, dW1, s, 0, n, accumulate, &bottom);
 }
 

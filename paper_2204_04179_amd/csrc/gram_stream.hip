@@ -272,11 +272,11 @@ __global__ __launch_bounds__(kBlock) void k_pseudo_target(const f32x4* __restric
 }
 
 __global__ __launch_bounds__(kBlock) void k_pseudo_loss(const double* __restrict__ partial,
-                                                        const int* __restrict__ u_ws,
+                                                        const int* __restrict__ u_ws, int parts,
                                                         double* __restrict__ loss)
 {
     __shared__ double s_sum[kBlock];
-    const int n = (*u_ws + kPseudoRows - 1) / kPseudoRows;
+    const int n = u_ws ? (*u_ws + kPseudoRows - 1) / kPseudoRows : parts;
     // thread t adds partials t, t + 256, ... in ascending order, then the fixed tree
     double sum = 0.0;
     for (int i = threadIdx.x; i < n; i += kBlock) sum += partial[i];
@@ -298,8 +298,8 @@ void pseudo_target(Ctx* c, const float* E, float* Ht, double* loss_dev, hipStrea
                reinterpret_cast<const f32x4*>(E), reinterpret_cast<const f32x4*>(c->G), c->seg_slot,
                c->scal + kSU, c->cfg.d / 4, reinterpret_cast<f32x4*>(Ht), c->loss_part);
     if (loss_dev)
-        launch(c, KID_PSEUDO_LOSS, k_pseudo_loss, dim3(1), dim3(kBlock), s, c->loss_part, c->scal + kSU,
-               loss_dev);
+        launch(c, KID_PSEUDO_LOSS, k_pseudo_loss, dim3(1), dim3(kBlock), s, c->loss_part, (const int*)(c->scal + kSU),
+               0, loss_dev);
 }
 
 // ---- one content-encoder batch of the update (Alg. 1 step 4, Eq. 7) ---------
@@ -329,16 +329,14 @@ void chunk_ids_prepare(Ctx* c, const int* ids, int64_t n, hipStream_t s)
            c->cfg.vocab_n, c->cfg.pad_id >= 0 ? c->cfg.pad_id : 0, c->chunk_ids, c->scal);
 }
 
-// With Ht: R[j,:] holds the encoder's output for item j of the batch and becomes the regression
-// miss R[j,:] - Ht[j,:] (zero for the padding item).  Without: R already holds the miss (the
-// contraction subtracted the targets as it stored).  Either way the block's share of sum |miss|^2
-// goes to partial[] exactly as in k_pseudo_target (double per thread, fixed tree, k_pseudo_loss
-// adds the blocks in index order).
+// float32 contexts: R[j,:] holds the encoder's output for item j of the batch and becomes the regression
+// miss R[j,:] - Ht[j,:] (zero for the padding item); the block's share of sum |miss|^2 goes to partial[] as
+// in k_pseudo_target (double per thread, fixed tree, k_pseudo_loss adds the blocks in index order).  (The
+// bf16 contractions subtract as they store, and leave such block sums themselves.)
 __global__ __launch_bounds__(kBlock) void k_pseudo_miss(f32x4* __restrict__ R,
                                                         const f32x4* __restrict__ Ht,
                                                         const int* __restrict__ ids, int n, int pad_id,
-                                                        int cols4, double* __restrict__ partial,
-                                                        uint2* __restrict__ R_bf16)
+                                                        int cols4, double* __restrict__ partial)
 {
     __shared__ double s_sum[kBlock];
     const int j0 = blockIdx.x * kPseudoRows;
@@ -348,16 +346,9 @@ __global__ __launch_bounds__(kBlock) void k_pseudo_miss(f32x4* __restrict__ R,
     for (int e = threadIdx.x; e < total; e += kBlock) {
         const int r = e / cols4, cq = e - r * cols4;
         const int64_t at = (int64_t)(j0 + r) * cols4 + cq;
-        f32x4 m;
-        if (Ht) {
-            m = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (ids[j0 + r] != pad_id) m = R[at] - __builtin_nontemporal_load(&Ht[at]);
-            R[at] = m;
-        } else {
-            m = R[at];
-        }
-        // the copy rounded to bf16 (nearest even) that a following contraction takes as its operand
-        if (R_bf16) R_bf16[at] = make_uint2(pack_bf16x2(m.x, m.y), pack_bf16x2(m.z, m.w));
+        f32x4 m = {0.f, 0.f, 0.f, 0.f};
+        if (ids[j0 + r] != pad_id) m = R[at] - __builtin_nontemporal_load(&Ht[at]);
+        R[at] = m;
         sum += (double)m.x * m.x + (double)m.y * m.y + (double)m.z * m.z + (double)m.w * m.w;
     }
     s_sum[threadIdx.x] = sum;
@@ -369,17 +360,19 @@ __global__ __launch_bounds__(kBlock) void k_pseudo_miss(f32x4* __restrict__ R,
     if (threadIdx.x == 0) partial[blockIdx.x] = s_sum[0];
 }
 
-void pseudo_miss(Ctx* c, float* R, const float* Ht, int64_t n, double* loss_dev, hipStream_t s, void* R_bf16)
+void pseudo_loss(Ctx* c, int parts, double* loss_dev, hipStream_t s)
 {
-    if (!Ht && !loss_dev && !R_bf16) return;       // nothing to subtract, nothing to sum, nothing to round
+    launch(c, KID_PSEUDO_LOSS, k_pseudo_loss, dim3(1), dim3(kBlock), s, c->loss_part, (const int*)nullptr, parts, loss_dev);
+}
+
+void pseudo_miss(Ctx* c, float* R, const float* Ht, int64_t n, double* loss_dev, hipStream_t s)
+{
     const int64_t blocks = (n + kPseudoRows - 1) / kPseudoRows;
     if (blocks > 0)
         launch(c, KID_PSEUDO_MISS, k_pseudo_miss, dim3((unsigned)blocks), dim3(kBlock), s,
                reinterpret_cast<f32x4*>(R), reinterpret_cast<const f32x4*>(Ht), c->chunk_ids, (int)n,
-               c->cfg.pad_id, c->cfg.d / 4, c->loss_part, static_cast<uint2*>(R_bf16));
-    if (loss_dev)
-        launch(c, KID_PSEUDO_LOSS, k_pseudo_loss, dim3(1), dim3(kBlock), s, c->loss_part,
-               c->scal + kSChunkN, loss_dev);
+               c->cfg.pad_id, c->cfg.d / 4, c->loss_part);
+    if (loss_dev) pseudo_loss(c, (int)blocks, loss_dev, s);
 }
 
 // ---- buffer rows for the items of this batch --------------------------------
