@@ -6,7 +6,7 @@
 // passes for a vocabulary of a million items), followed by head-flag scan and
 // compaction.  Each 64-lane wave owns a contiguous chunk of keys; ranks inside
 // a wave come from ballot-based digit matching, ranks across blocks from a
-// per-block digit table that one wave per digit prefix-sums.  Small batches
+// per-block digit table that is prefix-summed down its columns.  Small batches
 // are ranked by counting comparisons instead (k_rank_small).
 // All counters are integer (LDS atomics are order independent), so the result
 // is exact.
@@ -136,7 +136,8 @@ SortPlan make_sort_plan(int key_bits, int64_t n_max)
         GRAM_RUN_BATCH(it0, kb_, vb_, BODY)                                                         \
     }
 
-// Digit histogram of one pass per block.  table[digit * nb + block] = count.
+// Digit histogram of one pass per block.  table[block * bins + digit] = count: a block stores, and in the
+// scatter reads, one row of it (a column cost 1024 separate cache lines each way).
 template <bool CHECK>
 __global__ __launch_bounds__(kBlock) void k_radix_hist(const int* __restrict__ keys_in, int n_host,
                                                        const int* __restrict__ n_dev, int shift,
@@ -159,36 +160,50 @@ __global__ __launch_bounds__(kBlock) void k_radix_hist(const int* __restrict__ k
         })
     if (CHECK && bad) atomicOr(err, kErrBitRange);
     __syncthreads();
-    for (int b = threadIdx.x; b < bins; b += kBlock) table[(int64_t)b * gridDim.x + blockIdx.x] = cnt[b];
+    for (int b = threadIdx.x; b < bins; b += kBlock) table[(int64_t)blockIdx.x * bins + b] = cnt[b];
 }
 
-// One wave per digit: exclusive prefix over the blocks' counts (in place), digit total to gtot.
-__global__ __launch_bounds__(kBlock) void k_radix_scan(int* __restrict__ table, int nb, int bins,
-                                                       int* __restrict__ gtot)
+// Exclusive prefix over the blocks' counts of every digit (in place), digit totals to gtot.  A block
+// takes 64 digits, one per lane; its 16 waves share the rows of the table, and up to 16 rows each are
+// fetched together (256 blocks in all, i.e. batches of up to 4 million keys; beyond that in several turns).
+constexpr int kScanWaves = 16;
+__global__ __launch_bounds__(kScanWaves * kWave) void k_radix_scan(int* __restrict__ table, int nb, int bins,
+                                                                   int* __restrict__ gtot)
 {
-    const int b = blockIdx.x * kWavesPerBlock + wave_id();
-    if (b >= bins) return;
-    const int lane = lane_id();
-    int* row = table + (int64_t)b * nb;
+    __shared__ int part[kScanWaves][kWave];
+    constexpr int kPer = 16;
+    const int lane = lane_id(), g = wave_id();
+    const int b = blockIdx.x * kWave + lane;
+    const bool ok = b < bins;
     int carry = 0;
-    // four chunks of 64 counts are fetched together: the scan of a chunk is short, and one chunk
-    // per round trip would make the launch as long as its number of chunks
-    for (int base = 0; base < nb; base += 4 * kWave) {
-        int v[4];
+    for (int row0 = 0; row0 < nb; row0 += kScanWaves * kPer) {
+        const int rows = nb - row0 < kScanWaves * kPer ? nb - row0 : kScanWaves * kPer;
+        const int per = (rows + kScanWaves - 1) / kScanWaves;
+        const int r0 = g * per, r1 = r0 + per < rows ? r0 + per : rows;
+        int* col = table + (int64_t)row0 * bins + b;
+        int v[kPer], sum = 0;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int i = base + u * kWave + lane;
-            v[u] = i < nb ? row[i] : 0;
+        for (int i = 0; i < kPer; ++i) v[i] = ok && r0 + i < r1 ? col[(int64_t)(r0 + i) * bins] : 0;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) sum += v[i];
+        __syncthreads();
+        part[g][lane] = sum;
+        __syncthreads();
+        int run = carry;
+#pragma unroll
+        for (int w = 0; w < kScanWaves; ++w) {
+            const int s = part[w][lane];
+            if (w < g) run += s;
+            carry += s;
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int i = base + u * kWave + lane;
-            const int incl = wave_incl_scan(v[u]);
-            if (i < nb) row[i] = carry + incl - v[u];
-            carry += __shfl(incl, kWave - 1);
-        }
+        for (int i = 0; i < kPer; ++i)
+            if (ok && r0 + i < r1) {
+                col[(int64_t)(r0 + i) * bins] = run;
+                run += v[i];
+            }
     }
-    if (lane == 0) gtot[b] = carry;
+    if (ok && g == 0) gtot[b] = carry;
 }
 
 // Stable scatter of one pass.  The block recounts its keys per wave, turns the counts into the
@@ -211,7 +226,7 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(
     const int64_t base = ((int64_t)blockIdx.x * kWavesPerBlock + wave) * items * kWave;
 
     // Everything this block reads that does not depend on its own work is fetched first, in one
-    // round trip: the first batch of its keys and values (kept for both walks below), its column
+    // round trip: the first batch of its keys and values (kept for both walks below), its row
     // of the block table and the digit totals.
     int kb0[kSortBatch], vb0[kSortBatch];
     GRAM_LOAD_BATCH(0, kb0, vb0, (vals_in ? vals_in[idx_] : (int)idx_))
@@ -220,7 +235,7 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int b = threadIdx.x + i * kBlock;
-        tb[i] = b < bins ? table[(int64_t)b * gridDim.x + blockIdx.x] : 0;
+        tb[i] = b < bins ? table[(int64_t)blockIdx.x * bins + b] : 0;
     }
 
     for (int b = threadIdx.x; b < bins; b += kBlock)
@@ -310,8 +325,8 @@ int radix_sort_pairs(Ctx* c, const int* keys_in, const int* vals_in, int n_host,
         else
             launch(c, KID_RADIX_HIST, k_radix_hist<false>, dim3(p.blocks), dim3(kBlock), s, kin, n_host,
                                n_dev, shift, db, p.items, c->table, 0, 0, c->scal + kSErr);
-        launch(c, KID_RADIX_SCAN, k_radix_scan, dim3((bins + kWavesPerBlock - 1) / kWavesPerBlock),
-               dim3(kBlock), s, c->table, p.blocks, bins, c->gtot);
+        launch(c, KID_RADIX_SCAN, k_radix_scan, dim3((bins + kWave - 1) / kWave), dim3(kScanWaves * kWave), s, c->table,
+               p.blocks, bins, c->gtot);
         if (chk)
             launch(c, KID_RADIX_SCATTER, k_radix_scatter<true>, dim3(p.blocks), dim3(kBlock), s, kin, vin,
                                n_host, n_dev, shift, db, p.items, c->table, c->gtot,
