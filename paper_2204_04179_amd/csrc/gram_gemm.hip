@@ -1696,7 +1696,7 @@ __device__ __forceinline__ void split_range(int u_total, int splits, int z, int*
 __global__ __launch_bounds__(kBlock) void k_wgrad_f32(
     const float* __restrict__ X, const int* __restrict__ id_of_slot, const float* __restrict__ G,
     const int* __restrict__ rows_dev, int d_in, int d, int pad_id, int splits,
-    float* __restrict__ partial, int row_begin, int row_end)
+    float* __restrict__ partial, int row_begin, int row_end, int accumulate)
 {
     const int c = blockIdx.x * 64 + (threadIdx.x & 63);
     const int i = blockIdx.y * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1710,25 +1710,26 @@ __global__ __launch_bounds__(kBlock) void k_wgrad_f32(
     ke += row_begin;
     float acc = 0.f;
     int sidx = kb;
-    for (; sidx + 8 <= ke; sidx += 8) {         // eight rows' IDs, then their operands, requested together
-        int id[8];
-        float xv[8], gv[8];
+    for (; sidx + 16 <= ke; sidx += 16) {       // sixteen rows' IDs, then their operands, requested together
+        int id[16];
+        float xv[16], gv[16];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) id[u] = id_of_slot ? id_of_slot[sidx + u] : sidx + u;
+        for (int u = 0; u < 16; ++u) id[u] = id_of_slot ? id_of_slot[sidx + u] : sidx + u;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
+        for (int u = 0; u < 16; ++u) {
             xv[u] = X[(int64_t)id[u] * d_in + i];
             gv[u] = G[(int64_t)(sidx + u) * d + c];
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
+        for (int u = 0; u < 16; ++u)
             if (id[u] != pad_id) acc = fmaf(xv[u], gv[u], acc);
     }
     for (; sidx < ke; ++sidx) {
         const int id = id_of_slot ? id_of_slot[sidx] : sidx;
         if (id != pad_id) acc = fmaf(X[(int64_t)id * d_in + i], G[(int64_t)sidx * d + c], acc);
     }
-    partial[((int64_t)z * d_in + i) * d + c] = acc;
+    float* out = partial + ((int64_t)z * d_in + i) * d + c;
+    *out = accumulate ? *out + acc : acc;
 }
 
 __global__ __launch_bounds__(kBlock) void k_wgrad_reduce(const float4* __restrict__ partial,
@@ -1872,9 +1873,14 @@ bool encoder_wgrad(Ctx* c, const void* X, float* dW, hipStream_t s, int64_t firs
 #undef GRAM_GO
         }
     } else {
+        // a few rows are one range that goes straight to dW: the reduction launch costs more than the rows
+        int64_t rows_bound = (other || c->dense) ? cap : (c->window_positions < cap ? c->window_positions : cap);
+        if (rows_bound > row_end - row_begin) rows_bound = row_end - row_begin;
+        direct = rows_bound <= 128;
+        if (direct) S = 1;
         launch(c, KID_WGRAD_F32, k_wgrad_f32, dim3((d + 63) / 64, (d_in + 3) / 4, S), dim3(kBlock), s,
                static_cast<const float*>(X), ids, rows, rows_dev, d_in, d, pad_id, S,
-               c->wg_partial, row_begin, row_end);
+               direct ? dW : c->wg_partial, row_begin, row_end, direct && accumulate ? 1 : 0);
     }
     if (direct) return exported;
     const int64_t n4 = (int64_t)d_in * d / 4;
