@@ -42,6 +42,33 @@ constexpr int kFixLanes = kBlock / kFixCols4;
 // take the kernels' wide-address variants.
 constexpr int64_t kBufferWindow = ((int64_t)1 << 32) - 16;
 
+__device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
+__device__ __forceinline__ int wave_id() { return threadIdx.x >> 6; }
+
+// Scans and reductions over the 64 lanes of a wave with DPP moves (shifts within rows of 16 lanes, then
+// the last lane of a row broadcast to the rows after it).  A shuffle goes through LDS instead, and the
+// dedup's launches are chains of such steps: six at about 100 cycles per scan.
+template <typename Op>
+__device__ __forceinline__ int wave_incl_scan_op(int v, int identity, Op op)
+{
+    v = op(v, __builtin_amdgcn_update_dpp(identity, v, 0x111, 0xf, 0xf, false));    // row_shr:1
+    v = op(v, __builtin_amdgcn_update_dpp(identity, v, 0x112, 0xf, 0xf, false));    // row_shr:2
+    v = op(v, __builtin_amdgcn_update_dpp(identity, v, 0x114, 0xf, 0xf, false));    // row_shr:4
+    v = op(v, __builtin_amdgcn_update_dpp(identity, v, 0x118, 0xf, 0xf, false));    // row_shr:8
+    v = op(v, __builtin_amdgcn_update_dpp(identity, v, 0x142, 0xa, 0xf, false));    // row_bcast:15 to rows 1 and 3
+    v = op(v, __builtin_amdgcn_update_dpp(identity, v, 0x143, 0xc, 0xf, false));    // row_bcast:31 to rows 2 and 3
+    return v;
+}
+__device__ __forceinline__ int wave_incl_scan(int v)
+{
+    return wave_incl_scan_op(v, 0, [](int a, int b) { return a + b; });
+}
+__device__ __forceinline__ int wave_sum(int v) { return __builtin_amdgcn_readlane(wave_incl_scan(v), kWave - 1); }
+__device__ __forceinline__ int wave_min(int v)
+{
+    return __builtin_amdgcn_readlane(wave_incl_scan_op(v, 0x7fffffff, [](int a, int b) { return a < b ? a : b; }), kWave - 1);
+}
+
 // Export of one item at the end of a window: ID and count of the r-th item in ascending-ID order
 // (sorted_slots NULL: buffer row r), its entry of the slot map cleared.
 __device__ __forceinline__ void flush_meta_row(int r, const int* sorted_ids, const int* sorted_slots,

@@ -20,20 +20,6 @@ namespace gram {
 // outstanding memory operation of the wave (its scattered global stores included).
 typedef __attribute__((address_space(3))) int lds_i32;
 
-__device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
-__device__ __forceinline__ int wave_id() { return threadIdx.x >> 6; }
-
-__device__ __forceinline__ int wave_incl_scan(int v)
-{
-    const int lane = lane_id();
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        int t = __shfl_up(v, o);
-        if (lane >= o) v += t;
-    }
-    return v;
-}
-
 // Exclusive scan of one value per thread over a 256-thread block; *total gets the block sum.
 __device__ __forceinline__ int block_excl_scan(int v, int* total, int* sm /*[kWavesPerBlock]*/)
 {
@@ -54,8 +40,7 @@ __device__ __forceinline__ int block_excl_scan(int v, int* total, int* sm /*[kWa
 
 __device__ __forceinline__ int block_sum(int v, int* sm)
 {
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_down(v, o);
+    v = wave_sum(v);
     if (lane_id() == 0) sm[wave_id()] = v;
     __syncthreads();
     int tot = 0;
@@ -363,11 +348,7 @@ __device__ __forceinline__ bool is_head(const int* __restrict__ sk, int r)
 // commits those rows, provided the table has not changed in between.
 __device__ __forceinline__ int block_min(int v, int* sm)
 {
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-        const int t = __shfl_down(v, o);
-        v = t < v ? t : v;
-    }
+    v = wave_min(v);
     if (lane_id() == 0) sm[wave_id()] = v;
     __syncthreads();
     int m = sm[0];
@@ -397,12 +378,11 @@ __global__ __launch_bounds__(kBlock) void k_heads_count(const int* __restrict__ 
             // (in the first step of a window the buffer holds nothing: every item is new)
             if (slot_of && (first_step || slot_of[sk[r0 + i]] < 0)) ++fresh;
         }
-    const int tot = block_sum(s, sm);
-    const int tot_fresh = block_sum(fresh, sm);
+    const int tot = block_sum(s | fresh << 16, sm);        // (at most kScanTile each)
     const int row = block_min(first, sm), end_row = -block_min(-last, sm);
     if (threadIdx.x == 0) {
-        tile_info[blockIdx.x] = tot;
-        tile_info[gridDim.x + blockIdx.x] = tot_fresh;
+        tile_info[blockIdx.x] = tot & 0xffff;
+        tile_info[gridDim.x + blockIdx.x] = tot >> 16;
         tile_info[2 * gridDim.x + blockIdx.x] = row == kNoRow ? -1 : row;
         tile_info[3 * gridDim.x + blockIdx.x] = end_row;
     }
@@ -465,9 +445,11 @@ __global__ __launch_bounds__(kBlock) void k_heads_emit(
     before = -block_min(-before, sm);        // the last head before this tile (head rows ascend)
     const int long_rows = seg_rows_for(n);
     if (threadIdx.x == 0) s_next = kNoRow;
-    int total, total_fresh;
-    const int local = block_excl_scan(s, &total, sm);
-    const int local_fresh = block_excl_scan(fresh, &total_fresh, sm);
+    int total;      // both counts in one scan: at most kScanTile each
+    int local = block_excl_scan(s | fresh << 16, &total, sm);
+    const int local_fresh = local >> 16, total_fresh = total >> 16;
+    local &= 0xffff;
+    total &= 0xffff;
     {
         int li = local;
 #pragma unroll
@@ -963,12 +945,9 @@ __global__ __launch_bounds__(kCountThreads) void k_ids_emit(
              (unsigned long long)tile_info[2 * T + tid] << 40;
     if (!per_id)
         for (int i = tid * 8; i < 2 * words; i += kCountThreads * 8) *reinterpret_cast<uint4*>(cnt16 + i) = make_uint4(0, 0, 0, 0);
-    unsigned long long incl = tv;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const unsigned long long t = __shfl_up(incl, o);
-        if (lane >= o) incl += t;
-    }
+    const unsigned long long incl = (unsigned long long)(unsigned)wave_incl_scan((int)(tv & 0xfffff)) |
+                                    (unsigned long long)(unsigned)wave_incl_scan((int)(tv >> 20 & 0xfffff)) << 20 |
+                                    (unsigned long long)(unsigned)wave_incl_scan((int)(tv >> 40)) << 40;
     if (lane == kWave - 1) s_wave[wave] = incl;
     __syncthreads();
     unsigned long long base = 0, all = 0;

@@ -12,20 +12,6 @@
 
 namespace gram {
 
-__device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
-__device__ __forceinline__ int wave_id() { return threadIdx.x >> 6; }
-
-__device__ __forceinline__ int wave_incl_scan(int v)
-{
-    const int lane = lane_id();
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        int t = __shfl_up(v, o);
-        if (lane >= o) v += t;
-    }
-    return v;
-}
-
 template <int NWAVES = kWavesPerBlock>
 __device__ __forceinline__ int block_excl_scan(int v, int* total, int* sm /*[NWAVES]*/)
 {
@@ -46,8 +32,7 @@ __device__ __forceinline__ int block_excl_scan(int v, int* total, int* sm /*[NWA
 
 __device__ __forceinline__ int block_sum(int v, int* sm)
 {
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_down(v, o);
+    v = wave_sum(v);
     if (lane_id() == 0) sm[wave_id()] = v;
     __syncthreads();
     int tot = 0;
