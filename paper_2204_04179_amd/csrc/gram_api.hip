@@ -554,19 +554,21 @@ int gram_pseudo_loss_grad(gram_ctx* ctx, const void* X, const void* W, const int
         return fail(c, GRAM_ERR_ARG, "gram_pseudo_loss_grad: NULL pointer");
     hipStream_t s = static_cast<hipStream_t>(stream);
     chunk_ids_prepare(c, ids, n, s);
+    LossSum sum = {c->loss_part, 0, nullptr};
     if (c->cfg.xw_dtype == GRAM_BF16) {
         // the contraction subtracts the targets as it stores and sums the squares
         int parts = 0;
         const EpiLoss loss = {c->loss_part, &parts};
         encode_forward(c, X, W, c->chunk_ids, c->scal + kSChunkN, n, R, s, nullptr, true, kEpiMinus, Ht,
                        loss_dev ? &loss : nullptr);
-        if (loss_dev) pseudo_loss(c, parts, loss_dev, s);
+        sum.parts = parts;
+        sum.out = loss_dev;
     } else {
         encode_forward(c, X, W, c->chunk_ids, c->scal + kSChunkN, n, R, s, nullptr, true);
         pseudo_miss(c, R, Ht, n, loss_dev, s);
     }
     const WgradRows rows = {c->chunk_ids, R, c->scal + kSChunkN, n};
-    encoder_wgrad(c, X, dW, s, 0, n, accumulate != 0, &rows);
+    encoder_wgrad(c, X, dW, s, 0, n, accumulate != 0, &rows, nullptr, nullptr, nullptr, sum.out ? &sum : nullptr);
     return launch_status(c, "gram_pseudo_loss_grad");
 }
 

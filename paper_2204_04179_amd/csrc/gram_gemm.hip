@@ -1734,8 +1734,12 @@ __global__ __launch_bounds__(kBlock) void k_wgrad_f32(
 
 __global__ __launch_bounds__(kBlock) void k_wgrad_reduce(const float4* __restrict__ partial,
                                                          int64_t n4, int splits,
-                                                         float4* __restrict__ dW, int accumulate)
+                                                         float4* __restrict__ dW, int accumulate, LossSum loss)
 {
+    if (loss.out && blockIdx.x == gridDim.x - 1) {       // (one more block: the pseudo-loss, a launch less)
+        half_sum_of(loss.part, loss.parts, loss.out);
+        return;
+    }
     const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (e >= n4) return;
     float4 acc = accumulate ? dW[e] : make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1764,7 +1768,7 @@ int wgrad_splits_dims(int d_in, int d, bool bf16)
 
 bool encoder_wgrad(Ctx* c, const void* X, float* dW, hipStream_t s, int64_t first_row, int64_t n_rows,
                    bool accumulate, const WgradRows* other, float* export_G, const int* rank_of_slot,
-                   const WindowMeta* meta)
+                   const WindowMeta* meta, const LossSum* loss)
 {
     bool exported = false, direct = false;
     const int d_in = other && other->d_in ? other->d_in : c->cfg.d_in;
@@ -1882,10 +1886,14 @@ bool encoder_wgrad(Ctx* c, const void* X, float* dW, hipStream_t s, int64_t firs
                static_cast<const float*>(X), ids, rows, rows_dev, d_in, d, pad_id, S,
                direct ? dW : c->wg_partial, row_begin, row_end, direct && accumulate ? 1 : 0);
     }
-    if (direct) return exported;
+    if (direct) {
+        if (loss) pseudo_loss(c, *loss, s);
+        return exported;
+    }
     const int64_t n4 = (int64_t)d_in * d / 4;
-    launch(c, KID_WGRAD_REDUCE, k_wgrad_reduce, dim3((unsigned)((n4 + kBlock - 1) / kBlock)), dim3(kBlock), s,
-           reinterpret_cast<const float4*>(c->wg_partial), n4, S, reinterpret_cast<float4*>(dW), accumulate ? 1 : 0);
+    const LossSum sum = loss ? *loss : LossSum{nullptr, 0, nullptr};
+    launch(c, KID_WGRAD_REDUCE, k_wgrad_reduce, dim3((unsigned)((n4 + kBlock - 1) / kBlock + (loss ? 1 : 0))), dim3(kBlock), s,
+           reinterpret_cast<const float4*>(c->wg_partial), n4, S, reinterpret_cast<float4*>(dW), accumulate ? 1 : 0, sum);
     return exported;
 }
 

@@ -69,6 +69,22 @@ __device__ __forceinline__ int wave_min(int v)
     return __builtin_amdgcn_readlane(wave_incl_scan_op(v, 0x7fffffff, [](int a, int b) { return a < b ? a : b; }), kWave - 1);
 }
 
+// 1/2 of the sum of n doubles by one block of kBlock threads: thread t adds t, t + 256, ... in ascending
+// order, then a fixed tree.
+__device__ __forceinline__ void half_sum_of(const double* __restrict__ partial, int n, double* __restrict__ out)
+{
+    __shared__ double s_sum[kBlock];
+    double sum = 0.0;
+    for (int i = threadIdx.x; i < n; i += kBlock) sum += partial[i];
+    s_sum[threadIdx.x] = sum;
+    __syncthreads();
+    for (int w = kBlock / 2; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w) s_sum[threadIdx.x] += s_sum[threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) *out = 0.5 * s_sum[0];
+}
+
 // Export of one item at the end of a window: ID and count of the r-th item in ascending-ID order
 // (sorted_slots NULL: buffer row r), its entry of the slot map cleared.
 __device__ __forceinline__ void flush_meta_row(int r, const int* sorted_ids, const int* sorted_slots,
@@ -270,8 +286,13 @@ void chunk_ids_prepare(Ctx* c, const int* ids, int64_t n, hipStream_t s);
 // R[j,:] -= Ht[j,:] for the n rows of the batch in c->chunk_ids (zero for the padding item); with
 // loss_dev, 1/2 of the sum of the squares of R.  (float32 contexts)
 void pseudo_miss(Ctx* c, float* R, const float* Ht, int64_t n, double* loss_dev, hipStream_t s);
-// 1/2 of the sum of the `parts` block sums in c->loss_part.
-void pseudo_loss(Ctx* c, int parts, double* loss_dev, hipStream_t s);
+// *out = 1/2 of the sum of `parts` block sums.
+struct LossSum {
+    const double* part;
+    int parts;
+    double* out;
+};
+void pseudo_loss(Ctx* c, const LossSum& loss, hipStream_t s);
 void assign_slots(Ctx* c, hipStream_t s);
 void segment_reduce(Ctx* c, const float* dH, int64_t m, hipStream_t s, bool commit = false);
 void flush_export(Ctx* c, int* uniq_total, int* counts_total, long long* counts64_total, float* G_total,
@@ -330,7 +351,8 @@ struct WindowMeta {
 };
 bool encoder_wgrad(Ctx* c, const void* X, float* dW, hipStream_t s, int64_t first_row, int64_t n_rows,
                    bool accumulate, const WgradRows* other = nullptr, float* export_G = nullptr,
-                   const int* rank_of_slot = nullptr, const WindowMeta* meta = nullptr);
+                   const int* rank_of_slot = nullptr, const WindowMeta* meta = nullptr,
+                   const LossSum* loss = nullptr);      // loss: also sum these (in the reduction's launch, if there is one)
 // ---- gram_mlp.hip --------------------------------------------------------
 // Forward of the two-layer encoder for the unique items of the batch; A1 (nullable) receives the
 // bf16 hidden activations.  Return value as encode_forward.

@@ -80,6 +80,7 @@ void mlp_backward(Ctx* c, const void* X, const void* W1, const void* W2, const i
         gemm_rows_bf16(c, X, c->cfg.vocab_n, d_in, c->chunk_ids, c->cfg.pad_id, n_dev, n, c->W1t, dh,
                        static_cast<float*>(A1), s, nullptr, true, kEpiReluBf16, nullptr, plain1 ? W1 : nullptr);
     }
+    LossSum sum = {c->loss_part, 0, nullptr};
     if (Ht) {
         // Algorithm 1 step 4 as a regression: output at the current weights minus the stored target
         int parts = 0;
@@ -90,7 +91,8 @@ void mlp_backward(Ctx* c, const void* X, const void* W1, const void* W2, const i
             gemm_rows_bf16(c, A1, n, dh, c->iota, c->cfg.pad_id, n_dev, n, c->W2t, d, static_cast<float*>(Rb), s, nullptr,
                            true, kEpiMinusBf16, Ht, plain2 ? W2 : nullptr, c->chunk_ids, loss_dev ? &loss : nullptr);
         }
-        if (loss_dev) pseudo_loss(c, parts, loss_dev, s);
+        sum.parts = parts;
+        sum.out = loss_dev;
     } else if (n > 0) {
         // gradient rows handed in by the caller are rounded to bf16 here
         launch(c, KID_MLP_TO_BF16, k_to_bf16, dim3(blocks_for(n, d / 4)), dim3(kBlock), s,
@@ -98,7 +100,7 @@ void mlp_backward(Ctx* c, const void* X, const void* W1, const void* W2, const i
     }
     // dW2 = A1^T R: the kept activations play the part of the features, row j with row j
     const WgradRows top = {nullptr, static_cast<const float*>(Rb), n_dev, n, n > 0 ? n : 1, dh, d, -1, true};
-    encoder_wgrad(c, A1, dW2, s, 0, n, accumulate, &top);
+    encoder_wgrad(c, A1, dW2, s, 0, n, accumulate, &top, nullptr, nullptr, nullptr, sum.out ? &sum : nullptr);
     // dA = R . W2^T: W2 [dh, d] is already the K-contiguous second operand of that product; the gate of
     // the rectifier is applied as it is stored: dZ = dA where the kept activation is positive, so
     // forward and backward agree on which units are active

@@ -260,18 +260,7 @@ __global__ __launch_bounds__(kBlock) void k_pseudo_loss(const double* __restrict
                                                         const int* __restrict__ u_ws, int parts,
                                                         double* __restrict__ loss)
 {
-    __shared__ double s_sum[kBlock];
-    const int n = u_ws ? (*u_ws + kPseudoRows - 1) / kPseudoRows : parts;
-    // thread t adds partials t, t + 256, ... in ascending order, then the fixed tree
-    double sum = 0.0;
-    for (int i = threadIdx.x; i < n; i += kBlock) sum += partial[i];
-    s_sum[threadIdx.x] = sum;
-    __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) s_sum[threadIdx.x] += s_sum[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *loss = 0.5 * s_sum[0];
+    half_sum_of(partial, u_ws ? (*u_ws + kPseudoRows - 1) / kPseudoRows : parts, loss);
 }
 
 void pseudo_target(Ctx* c, const float* E, float* Ht, double* loss_dev, hipStream_t s)
@@ -345,9 +334,9 @@ __global__ __launch_bounds__(kBlock) void k_pseudo_miss(f32x4* __restrict__ R,
     if (threadIdx.x == 0) partial[blockIdx.x] = s_sum[0];
 }
 
-void pseudo_loss(Ctx* c, int parts, double* loss_dev, hipStream_t s)
+void pseudo_loss(Ctx* c, const LossSum& loss, hipStream_t s)
 {
-    launch(c, KID_PSEUDO_LOSS, k_pseudo_loss, dim3(1), dim3(kBlock), s, c->loss_part, (const int*)nullptr, parts, loss_dev);
+    launch(c, KID_PSEUDO_LOSS, k_pseudo_loss, dim3(1), dim3(kBlock), s, loss.part, (const int*)nullptr, loss.parts, loss.out);
 }
 
 void pseudo_miss(Ctx* c, float* R, const float* Ht, int64_t n, double* loss_dev, hipStream_t s)
@@ -357,7 +346,7 @@ void pseudo_miss(Ctx* c, float* R, const float* Ht, int64_t n, double* loss_dev,
         launch(c, KID_PSEUDO_MISS, k_pseudo_miss, dim3((unsigned)blocks), dim3(kBlock), s,
                reinterpret_cast<f32x4*>(R), reinterpret_cast<const f32x4*>(Ht), c->chunk_ids, (int)n,
                c->cfg.pad_id, c->cfg.d / 4, c->loss_part);
-    if (loss_dev) pseudo_loss(c, (int)blocks, loss_dev, s);
+    if (loss_dev) pseudo_loss(c, {c->loss_part, (int)blocks, loss_dev}, s);
 }
 
 // ---- buffer rows for the items of this batch --------------------------------
