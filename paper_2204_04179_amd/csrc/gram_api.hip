@@ -483,7 +483,8 @@ int gram_grad_accumulate(gram_ctx* ctx, const float* dH, int64_t m, int32_t step
     hipStream_t s = static_cast<hipStream_t>(stream);
     // the rows worked out by gram_unique hold if the slot table is still the one it looked at;
     // the reduction then commits them as it goes, else they are assigned afresh first
-    const bool commit = m > 0 && c->prospect_epoch == c->slot_epoch;
+    // (the dense layout has no rows to work out)
+    const bool commit = m > 0 && (c->dense || c->prospect_epoch == c->slot_epoch);
     if (!commit) assign_slots(c, s);
     segment_reduce(c, dH, m, s, commit);
     c->slot_epoch += 1;

@@ -506,10 +506,10 @@ __global__ __launch_bounds__(kBlock) void k_heads_emit(
         scal[kSU] = u;
         if (u_out) *u_out = u;
         offsets[u] = n;
+        scal[kSLongCount] = 0;
         if (slot_of) {
             const int nt = u_base + pre_fresh + total_fresh;
             scal[kSUNext] = nt < cap_total ? nt : cap_total;
-            scal[kSLongCount] = 0;
         }
     }
 }
@@ -731,6 +731,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_emit_small(
         *u_ws = total;
         if (u_out) *u_out = total;
         offsets[total] = n;
+        scal[kSLongCount] = 0;
     }
     // the buffer rows the items would get from the next gram_grad_accumulate (see k_heads_emit).  In
     // the first step of a window the buffer holds nothing: item j gets row j.  Later thread t looks up
@@ -760,10 +761,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_emit_small(
                 seg_slot[r0 + i] = code;
         }
     }
-    if (blockIdx.x == 0 && tid == 0) {
-        scal[kSUNext] = nt < cap_total ? nt : cap_total;
-        scal[kSLongCount] = 0;
-    }
+    if (blockIdx.x == 0 && tid == 0) scal[kSUNext] = nt < cap_total ? nt : cap_total;
 }
 
 // ---- mid-sized batches over small vocabularies: counting by ID -------------------------
@@ -987,10 +985,10 @@ __global__ __launch_bounds__(kCountThreads) void k_ids_emit(
             scal[kSU] = u;
             if (u_out) *u_out = u;
             offsets[u] = n;
+            scal[kSLongCount] = 0;
             if (slot_of) {
                 const int nt = u_base + (int)(all >> 40);
                 scal[kSUNext] = nt < cap_total ? nt : cap_total;
-                scal[kSLongCount] = 0;
             }
         }
         return;

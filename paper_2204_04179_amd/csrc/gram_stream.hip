@@ -357,8 +357,7 @@ void pseudo_miss(Ctx* c, float* R, const float* Ht, int64_t n, double* loss_dev,
 // summation order of the weight gradient, is a function of the data alone.
 // The dedup kernels normally work these rows out themselves (seg_slot) and the segment
 // reduction commits them; the kernels below do the same job in launches of their own when the
-// slot table has changed since the dedup looked at it, for an empty batch, and for the
-// dense layout.
+// slot table has changed since the dedup looked at it and for an empty batch.
 
 __global__ __launch_bounds__(kBlock) void k_slot_count(const int* __restrict__ uniq_ws,
                                                        const int* __restrict__ slot_of,
@@ -500,23 +499,11 @@ __global__ __launch_bounds__(kSlotSmallThreads) void k_slot_small(
 
 constexpr int64_t kSmallBatch = 8 * kScanTile;   // positions up to which one-block variants are used
 
-// Dense-by-vocabulary buffer: the row of an item is its ID, so there is nothing to hand out; the
-// row is always added to (rows outside a window are zero) and the 64-bit count of the item grows.
-__global__ __launch_bounds__(kBlock) void k_slot_dense(const int* __restrict__ uniq_ws,
-                                                       const int* __restrict__ offsets,
-                                                       int* __restrict__ scal,
-                                                       long long* __restrict__ cnt64,
-                                                       int* __restrict__ seg_slot, int vocab_n)
+// Dense-by-vocabulary buffer: the row of an item is its ID, so there is nothing to hand out (the segment
+// reduction counts the items of a batch as it goes); an empty batch only has to make the rows count.
+__global__ void k_slot_dense(int* __restrict__ scal, int vocab_n)
 {
-    const int j = blockIdx.x * kBlock + threadIdx.x;
-    if (j == 0) {
-        scal[kSLongCount] = 0;
-        scal[kSUTotal] = vocab_n;      // rows the weight gradient contracts over: all of them
-    }
-    if (j >= scal[kSU]) return;
-    const int id = uniq_ws[j];         // distinct within a batch: no two threads meet on a count
-    seg_slot[j] = id;
-    cnt64[id] += offsets[j + 1] - offsets[j];
+    if (threadIdx.x == 0) scal[kSUTotal] = vocab_n;      // rows the weight gradient contracts over: all of them
 }
 
 void assign_slots(Ctx* c, hipStream_t s)
@@ -524,8 +511,7 @@ void assign_slots(Ctx* c, hipStream_t s)
     int64_t bound = c->cur_m < c->cap_u ? c->cur_m : c->cap_u;
     if (bound < 1) bound = 1;
     if (c->dense) {
-        launch(c, KID_SLOT_EMIT, k_slot_dense, dim3((unsigned)((bound + kBlock - 1) / kBlock)), dim3(kBlock), s,
-               c->uniq_ws, c->offsets, c->scal, c->cnt64, c->seg_slot, c->cfg.vocab_n);
+        launch(c, KID_SLOT_EMIT, k_slot_dense, dim3(1), dim3(kWave), s, c->scal, c->cfg.vocab_n);
         return;
     }
     const int first_step = (c->steps_done == 0 && !c->window_imported) ? 1 : 0;
@@ -600,10 +586,10 @@ template <int TR, int UN, bool PLAIN, bool OLD>
 __global__ __launch_bounds__(kBlock) void k_seg_reduce(
     const float4* __restrict__ dH, const int* __restrict__ perm, const int* __restrict__ seg_of_row,
     const int* __restrict__ offsets, const int* __restrict__ uniq_ws,
-    const int* __restrict__ seg_slot, int n, int cols4, float4* __restrict__ G,
+    int* seg_slot, int n, int cols4, float4* __restrict__ G,
     float4* __restrict__ seg_first, float4* __restrict__ seg_last, int* __restrict__ scal,
     int4* __restrict__ long_list, int* __restrict__ slot_of, int* __restrict__ id_of_slot,
-    long long* __restrict__ cnt_of_slot)
+    long long* __restrict__ cnt_of_slot, long long* __restrict__ cnt64, int vocab_n)
 {
     static_assert(2 * TR <= kWave, "a tile and the end of its last segment fit the lanes of a wave");
     const int t = blockIdx.x, lane = lane_id();
@@ -613,8 +599,10 @@ __global__ __launch_bounds__(kBlock) void k_seg_reduce(
     const int pad_seg = scal[kSPadSeg];
     // slot_of given: the buffer rows in seg_slot were worked out by the dedup and are committed
     // here, each item by the lane that holds the first row of its segment (one tile holds it)
-    const bool commit = slot_of != nullptr && blockIdx.y == 0 && threadIdx.x < kWave;
-    if (commit && t == 0 && threadIdx.x == 0) scal[kSUTotal] = scal[kSUNext];
+    // cnt64 given (dense layout): the row of an item is its ID; its count grows here the same way
+    const bool dense = cnt64 != nullptr;
+    const bool commit = (slot_of != nullptr || dense) && blockIdx.y == 0 && threadIdx.x < kWave;
+    if (commit && t == 0 && threadIdx.x == 0) scal[kSUTotal] = dense ? vocab_n : scal[kSUNext];
 
     const unsigned long long heads = __ballot((info & kRowHead) != 0), longs = __ballot((info & kRowLong) != 0);
     const int tile_rows = n - r0 < TR ? n - r0 : TR;         // at least 1
@@ -635,7 +623,7 @@ __global__ __launch_bounds__(kBlock) void k_seg_reduce(
     const bool is_first_part = (heads & in_tile & (2ull << lane) - 1) != 0;
     const bool head_here = begins && lane < tile_rows;
     const bool need_slot = (mine && !is_long && ends) || (part_ends && is_first_part) || (commit && head_here);
-    const int slot = need_slot ? seg_slot[seg] : 0;
+    const int slot = need_slot ? (dense ? uniq_ws : seg_slot)[seg] : 0;
     int o0 = 0, o1 = 0, id = 0;
     if ((commit && head_here) || (part_ends && is_first_part)) {
         o0 = offsets[seg];
@@ -692,7 +680,10 @@ __global__ __launch_bounds__(kBlock) void k_seg_reduce(
     if (blockIdx.y == 0 && threadIdx.x < kWave && part_ends && is_first_part)
         long_list[atomicAdd(&scal[kSLongCount], 1)] = make_int4(t, 1 + (o1 - 1) / TR - t, slot, is_pad ? 1 : 0);
     if (commit && head_here) {
-        if (slot < 0) {
+        if (dense) {
+            seg_slot[seg] = id;
+            cnt64[id] += o1 - o0;            // distinct within a batch: no two threads meet on a count
+        } else if (slot < 0) {
             atomicOr(&scal[kSErr], kErrBitCapacity);      // dropped: the buffer is full
         } else if (slot & kSlotNew) {
             const int s = slot & (kSlotNew - 1);
@@ -765,13 +756,14 @@ void segment_reduce(Ctx* c, const float* dH, int64_t m, hipStream_t s, bool comm
     const int tile_rows = seg_rows_for(n);
     const int tiles = (n + tile_rows - 1) / tile_rows;
     // in the first step of a window every row is new
-    const bool old = !commit || c->steps_done > 0 || c->window_imported;
+    const bool old = c->dense || !commit || c->steps_done > 0 || c->window_imported;
     const dim3 grid(tiles, slabs);
     auto go = [&](auto kern) {
         launch(c, KID_SEG_REDUCE, kern, grid, dim3(threads), s, reinterpret_cast<const float4*>(dH), c->perm,
                c->seg_of_row, c->offsets, c->uniq_ws, c->seg_slot, n, cols4, reinterpret_cast<float4*>(c->G),
                reinterpret_cast<float4*>(c->seg_first), reinterpret_cast<float4*>(c->seg_last), c->scal, c->long_list,
-               commit ? c->slot_of : (int*)nullptr, c->id_of_slot, c->cnt_of_slot);
+               commit && !c->dense ? c->slot_of : (int*)nullptr, c->id_of_slot, c->cnt_of_slot,
+               c->dense ? c->cnt64 : (long long*)nullptr, c->cfg.vocab_n);
     };
     static_assert(kSegPlainLoads == kSegSmallBatch, "the two lines of the dispatch below coincide");
     if (n <= kSegSmallBatch) {
