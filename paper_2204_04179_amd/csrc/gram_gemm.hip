@@ -563,7 +563,8 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_nt_bf16(
         int64_t rowA = j;
         if (GATHER) {
             const int id = row_ids[j];
-            if (m0 + r < M && zero_ids[j] == pad_id) s_pad_row = r;   // at most one row is the padding item
+            // at most one row is the padding item (only the subtracting modes tell it by another list)
+            if (m0 + r < M && (epi_subtracts(EPI) ? zero_ids[j] : id) == pad_id) s_pad_row = r;
             rowA = id;
         }
         oa[t] = (uint32_t)((rowA * lda + (int64_t)sl_begin * TK + lchunk * 8) * 2);
