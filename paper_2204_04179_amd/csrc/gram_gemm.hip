@@ -16,6 +16,8 @@
 //   reads return zero); matrices beyond the 4 GiB a descriptor can address take the
 //   WIDE variants of both kernels, which form 64-bit addresses per lane.
 // The float32 variants are plain FMA code for small problems.
+#include <algorithm>
+
 #include "gram_internal.h"
 
 namespace gram {
@@ -493,7 +495,42 @@ constexpr int kScatterTileB = 64 * kScatterRowB;
 constexpr size_t RSMEM_SC = 2 * (size_t)kScatterTileB;     // two staging buffers (they overlay the dead stages)
 constexpr uint32_t kBufferFlags = 0x00027000;   // raw buffer: 32-bit elements, no swizzle
 
-// NW = waves per block: 4 (each 128x128, one wave per SIMD) or 8 (each 128x64, two per SIMD).
+// How many row tiles of 256 are taken whole.  A block fills its CU (8 waves, over 200 VGPRs), so the tiles
+// go in rounds of num_cus; those left over after the last full round are cut in two where the halves still
+// fit one round, which then takes about 0.6 of a round of whole tiles.  The number of items is known on
+// the device only, so each block works this out, by multiplications: divisions cost the prologue of every
+// block 0.25 us.  (Rounded quotients only move the cut; the grid is made with the same ones.)
+// Measured, all whole / the last ones cut: 56 x 2 tiles (K = 1536, positions stored) 53.5 / 40.5 us, 56 x 6
+// tiles (K = 768) 55.7 / 51.4, the forward of 204,800 positions 1024 x 1024 to bf16 178 / 169.  Nothing left
+// over, or more than half a round (where a round of halves would be followed by another): the same kernel
+// as before, within 1 % of it.
+struct TileCut {
+    uint32_t rounds_per_tile;  // ceil(2^32 n_tiles / num_cus): a row tile in rounds of blocks
+    uint32_t tiles_per_round;  // ceil(2^16 num_cus / n_tiles)
+    int most;                  // row tiles that are cut at most
+
+    TileCut(int n_tiles, int num_cus)
+        : rounds_per_tile((uint32_t)std::min<uint64_t>((((uint64_t)n_tiles << 32) + num_cus - 1) / num_cus, UINT32_MAX)),
+          tiles_per_round((uint32_t)((((uint64_t)num_cus << 16) + n_tiles - 1) / n_tiles)), most(num_cus / (2 * n_tiles)) {}
+    __host__ __device__ int full_rounds(int tiles) const     // in row tiles, a multiple of the 8 XCDs
+    {
+        const uint32_t rounds = (uint32_t)(((uint64_t)(uint32_t)tiles * rounds_per_tile) >> 32);
+        return (int)(((uint64_t)rounds * tiles_per_round) >> 16) & ~7;
+    }
+    __host__ __device__ int whole(int tiles) const
+    {
+        const int f = full_rounds(tiles);
+        return tiles - f <= most ? f : tiles;
+    }
+    int row_tiles_max(int tiles) const       // whole and half ones that up to `tiles` of 256 rows may come to
+    {
+        const int f = full_rounds(tiles);
+        return std::max(tiles, f + 2 * std::min(tiles - f, most));
+    }
+};
+
+// MI = 32-row MFMA tiles per wave: 4 (a tile of 256 rows) or 2 (128 rows).
+// NW = waves per block: 4 (each 32 MI x 128, one wave per SIMD) or 8 (each 32 MI x 64, two per SIMD).
 //
 // SCATTER (forward only): the epilogue is the gather of Section 3.1 as well.  Row j of the
 // product is the representation of unique item j; instead of only storing it to C it is stored
@@ -517,29 +554,17 @@ struct ScatterArgs {
 // of n each (512-byte rows, 16-byte chunk c of row r at position c ^ ((r & 3) << 2)), and the
 // MFMA fragments (8 consecutive k for one n) come from the transposing LDS read, exactly as
 // in k_wgrad_tn_bf16 below.  Saves the transposed copy of the weights and its launch.
-template <bool GATHER, int NW, bool SCATTER, int EPI = kEpiPlain, bool HB = false, bool WIDE = false,
-          bool BDIRECT = false>
-__global__ __launch_bounds__(NW * 64) void k_gemm_nt_bf16(
-    const uint16_t* __restrict__ A, int64_t lda, uint32_t a_bytes, const int* __restrict__ row_ids,
-    const int* __restrict__ m_dev, const uint16_t* __restrict__ B, int64_t ldb, uint32_t b_bytes, int n,
-    int ktot, const int* __restrict__ zero_ids, int pad_id, int n_tiles, float* __restrict__ C, int64_t ldc,
-    ScatterArgs sc, const void* __restrict__ aux, double* __restrict__ loss_part)
+template <int MI, bool GATHER, int NW, bool SCATTER, int EPI, bool HB, bool WIDE, bool BDIRECT>
+__device__ __forceinline__ void gemm_nt_tile(
+    const uint16_t* __restrict__ A, int64_t lda, uint32_t a_bytes, const int* __restrict__ row_ids, int M,
+    const uint16_t* __restrict__ B, int64_t ldb, uint32_t b_bytes, int n, int ktot, const int* __restrict__ zero_ids,
+    int pad_id, int m0, int n0, float* __restrict__ C, int64_t ldc, const ScatterArgs& sc,
+    const void* __restrict__ aux, double* __restrict__ loss_part, unsigned char* smem, int& s_pad_row)
 {
-    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-    __shared__ int s_pad_row;
-    const int M = *m_dev;
-    // row tiles are dealt to the XCDs; the column tiles of a row tile stay together
-    const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
-    const int m0 = ((q / n_tiles) * 8 + xcd) * TM;
-    const int n0 = (q % n_tiles) * TN;
-    if (epi_subtracts(EPI) && loss_part) loss_part += blockIdx.x;
-    if (m0 >= M) {
-        if (epi_subtracts(EPI) && loss_part && threadIdx.x == 0) *loss_part = 0.0;
-        return;
-    }
+    constexpr int TM = MI * 64, TSTAGEB = (TM + TN) * TROWB;   // rows of the tile; bytes per stage
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     constexpr int NT = NW == 4 ? 4 : 2;          // 32-column MFMA tiles per wave
-    constexpr int GA = 16 / NW;                  // 16-row groups of A (and of B) a wave loads per slab
+    constexpr int GA = TM / 16 / NW, GB = TN / 16 / NW;      // 16-row groups of A and of B a wave loads per slab
     const int wm = NW == 4 ? wave >> 1 : wave >> 2, wn = NW == 4 ? wave & 1 : wave & 3;
     if (tid == 0) s_pad_row = -1;
     __syncthreads();
@@ -554,8 +579,9 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_nt_bf16(
     const __amdgpu_buffer_rsrc_t rsB = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(B), 0, b_bytes, kBufferFlags);
     const int lrow = lane >> 2;
     const int lchunk = (lane & 3) ^ ((lane >> 4) & 3);
-    uint32_t oa[GA], ob[GA];
+    uint32_t oa[GA], ob[GB];
     const unsigned char* pa[WIDE ? GA : 1];
+    static_assert(GA >= 1, "a wave loads at least one group");
 #pragma unroll
     for (int t = 0; t < GA; ++t) {
         const int r = (wave * GA + t) * 16 + lrow;
@@ -569,59 +595,63 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_nt_bf16(
         }
         oa[t] = (uint32_t)((rowA * lda + (int64_t)sl_begin * TK + lchunk * 8) * 2);
         if (WIDE) pa[t] = reinterpret_cast<const unsigned char*>(A) + (rowA * lda + (int64_t)sl_begin * TK + lchunk * 8) * 2;
+    }
+#pragma unroll
+    for (int t = 0; t < GB; ++t) {
         if (BDIRECT) {
             // chunk cb of the slab: row cb / 32 of k, position cb % 32 of that row in LDS; columns past
             // n are clamped to the last chunk (their products are never stored)
-            const int cb = (wave * GA + t) * 64 + lane;
+            const int cb = (wave * GB + t) * 64 + lane;
             const int krow = cb >> 5;
             int ncol = n0 + (((cb & 31) ^ ((krow & 3) << 2)) << 3);
             if (ncol > n - 8) ncol = n - 8;
             ob[t] = (uint32_t)(((int64_t)krow * ldb + ncol) * 2);
         } else {
-            const int nn = n0 + r;
+            const int nn = n0 + (wave * GB + t) * 16 + lrow;
             ob[t] = (uint32_t)(((int64_t)(nn < n ? nn : n - 1) * ldb + (int64_t)sl_begin * TK + lchunk * 8) * 2);
         }
     }
     static_assert(!BDIRECT || NW == 8, "the untransposed second operand is wired for 8 waves");
     const uint32_t b_slab_bytes = BDIRECT ? (uint32_t)(TK * ldb * 2) : (uint32_t)(TK * 2);
     unsigned char* park = smem + (wave * GA) * 1024 + lane * 16;
+    unsigned char* park_b = smem + TM * TROWB + (wave * GB) * 1024 + lane * 16;
 
     // (fused gather) position ranges and position lists of the rows this wave will store in the
     // epilogue; fetched here so that their latency hides behind the contraction
     constexpr int RPW = 64 / NW;             // rows per wave and epilogue round
     int seg_o = 0, seg_n = 0;
-    int pv[SCATTER ? 4 * RPW : 1];
+    int pv[SCATTER ? MI * RPW : 1];
     if (SCATTER) {
         {
-            const int k = lane & (4 * RPW - 1);
-            const int lr = (wave / (NW / 2)) * 128 + (k / RPW) * 32 + (wave % (NW / 2)) * RPW + k % RPW;
+            const int k = lane & (MI * RPW - 1);
+            const int lr = (wave / (NW / 2)) * (MI * 32) + (k / RPW) * 32 + (wave % (NW / 2)) * RPW + k % RPW;
             if (m0 + lr < M) {
                 seg_o = sc.seg_off[m0 + lr];
                 seg_n = sc.seg_off[m0 + lr + 1] - seg_o;
             }
         }
 #pragma unroll
-        for (int k = 0; k < 4 * RPW; ++k) {
+        for (int k = 0; k < MI * RPW; ++k) {
             const int cnt = __builtin_amdgcn_readlane(seg_n, k);
             const int o = __builtin_amdgcn_readlane(seg_o, k);
             pv[k] = (cnt <= kLightMax && lane < cnt) ? sc.perm[o + lane] : 0;
         }
     }
 
-    f32x16 acc[4][NT];
+    f32x16 acc[MI][NT];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int j = 0; j < NT; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
     const int ph0 = (lane >> 5) ^ ((lane >> 2) & 3);
-    const int offA = (wm * 128 + (lane & 31)) * TROWB;
+    const int offA = (wm * (MI * 32) + (lane & 31)) * TROWB;
     const int offB = (TM + wn * (NT * 32) + (lane & 31)) * TROWB;
     const int c0 = ph0 * 16, c1 = (ph0 ^ 2) * 16;
-    bf16x8 fa[2][4], fb[2][NT];
-    v4i32 ra[2][GA], rb[2][GA];
+    bf16x8 fa[2][MI], fb[2][NT];
+    v4i32 ra[2][GA], rb[2][GB];
     // (BDIRECT) addresses of the transposing reads: group g = lane / 16, j = lane % 16 (see the header
     // comment of k_wgrad_tn_bf16); the wave's columns start at chunk NT 4 wn of the 512-byte row
     int tr_offB[BDIRECT ? NT : 1];
@@ -637,7 +667,7 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_nt_bf16(
 #define GRAM_FRAGS(FS, STAGE, COFF, KS)                                                             \
     {                                                                                               \
         const unsigned char* sb_ = smem + (STAGE) * TSTAGEB;                                        \
-        _Pragma("unroll") for (int i = 0; i < 4; ++i)                                               \
+        _Pragma("unroll") for (int i = 0; i < MI; ++i)                                              \
             fa[FS][i] = *reinterpret_cast<const bf16x8*>(sb_ + offA + i * 32 * TROWB + (COFF));     \
         _Pragma("unroll") for (int i = 0; i < NT; ++i) {                                            \
             if (BDIRECT) {                                                                          \
@@ -651,7 +681,7 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_nt_bf16(
         }                                                                                           \
     }
 #define GRAM_MMA(FS)                                                                                \
-    _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                   \
+    _Pragma("unroll") for (int i = 0; i < MI; ++i)                                                  \
         _Pragma("unroll") for (int j = 0; j < NT; ++j)                                              \
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[FS][i], fb[FS][j], acc[i][j], 0, 0, 0);
     // Slabs past the end are clamped to the last one (their data is never multiplied).
@@ -662,16 +692,16 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_nt_bf16(
         _Pragma("unroll") for (int t = 0; t < GA; ++t) {                                            \
             if (WIDE) ra[SET][t] = *reinterpret_cast<const v4i32*>(pa[t] + k_);                      \
             else ra[SET][t] = __builtin_amdgcn_raw_buffer_load_b128(rsA, oa[t] + k_, 0, 0);         \
-            rb[SET][t] = __builtin_amdgcn_raw_buffer_load_b128(rsB, ob[t] + kb_, 0, 0);             \
         }                                                                                           \
+        _Pragma("unroll") for (int t = 0; t < GB; ++t)                                              \
+            rb[SET][t] = __builtin_amdgcn_raw_buffer_load_b128(rsB, ob[t] + kb_, 0, 0);             \
     }
 #define GRAM_PARK(SET, STAGE)                                                                       \
     {                                                                                               \
-        unsigned char* p_ = park + (STAGE) * TSTAGEB;                                               \
-        _Pragma("unroll") for (int t = 0; t < GA; ++t) {                                            \
-            *reinterpret_cast<v4i32*>(p_ + t * 1024) = ra[SET][t];                                  \
-            *reinterpret_cast<v4i32*>(p_ + TM * TROWB + t * 1024) = rb[SET][t];                     \
-        }                                                                                           \
+        _Pragma("unroll") for (int t = 0; t < GA; ++t)                                              \
+            *reinterpret_cast<v4i32*>(park + (STAGE) * TSTAGEB + t * 1024) = ra[SET][t];            \
+        _Pragma("unroll") for (int t = 0; t < GB; ++t)                                              \
+            *reinterpret_cast<v4i32*>(park_b + (STAGE) * TSTAGEB + t * 1024) = rb[SET][t];          \
     }
     // first half of a slab: k-step 0 MFMAs with the k-step 1 fragment reads, then the LDS writes
     // of the next slab, one or two LDS instructions between MFMAs (a burst of LDS instructions
@@ -744,18 +774,18 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_nt_bf16(
         // them here once; otherwise every row's store loop would begin with a wait for all vector
         // memory operations, i.e. for the stores of the rows before it.
 #pragma unroll
-        for (int k = 0; k < 4 * RPW; ++k) asm volatile("" : "+v"(pv[k]));
+        for (int k = 0; k < MI * RPW; ++k) asm volatile("" : "+v"(pv[k]));
         __syncthreads();
         // two staging buffers: a wave that has stored its rows of round i stages round i + 1
         // while the others still store, and one barrier per round is enough (round i + 2 reuses
         // the buffer of round i only after the barrier of round i + 1)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < MI; ++i) {
             unsigned char* stage = smem + (i & 1) * kScatterTileB;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int rr = (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-                const bool zero = wm * 128 + i * 32 + rr == pad_row;
+                const bool zero = wm * (MI * 32) + i * 32 + rr == pad_row;
                 float* dst = reinterpret_cast<float*>(stage + (wm * 32 + rr) * kScatterRowB) +
                              wn * (NT * 32) + (lane & 31);
 #pragma unroll
@@ -769,7 +799,7 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_nt_bf16(
                 v[u] = *reinterpret_cast<const f32x4*>(stage + (cr0 + u) * kScatterRowB + lane * 16);
 #pragma unroll
             for (int u = 0; u < RPW; ++u) {
-                const int lr = (cr0 >> 5) * 128 + i * 32 + (cr0 & 31) + u;               // row of the tile
+                const int lr = (cr0 >> 5) * (MI * 32) + i * 32 + (cr0 & 31) + u;         // row of the tile
                 const int cnt = __builtin_amdgcn_readlane(seg_n, i * RPW + u);
                 if (cnt == 0) continue;
                 if (cnt > kLightMax || sc.write_all) {
@@ -804,8 +834,8 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_nt_bf16(
         double sq = 0.0;
         __syncthreads();
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int row0 = m0 + (cr0 >> 5) * 128 + i * 32 + (cr0 & 31);           // + u
+        for (int i = 0; i < MI; ++i) {
+            const int row0 = m0 + (cr0 >> 5) * (MI * 32) + i * 32 + (cr0 & 31);           // + u
             f32x4_ av[RPW];
 #pragma unroll
             for (int u = 0; u < RPW; ++u)
@@ -847,6 +877,36 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_nt_bf16(
 #undef GRAM_SCHED_SECOND
 #undef GRAM_ITER
 
+// One tile per block, of 256 rows or (the last ones, see TileCut) of 128.
+template <bool GATHER, int NW, bool SCATTER, int EPI = kEpiPlain, bool HB = false, bool WIDE = false,
+          bool BDIRECT = false>
+__global__ __launch_bounds__(NW * 64) void k_gemm_nt_bf16(
+    const uint16_t* __restrict__ A, int64_t lda, uint32_t a_bytes, const int* __restrict__ row_ids,
+    const int* __restrict__ m_dev, const uint16_t* __restrict__ B, int64_t ldb, uint32_t b_bytes, int n,
+    int ktot, const int* __restrict__ zero_ids, int pad_id, int n_tiles, TileCut cut, float* __restrict__ C, int64_t ldc,
+    ScatterArgs sc, const void* __restrict__ aux, double* __restrict__ loss_part)
+{
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    __shared__ int s_pad_row;
+    const int M = *m_dev;
+    // row tiles are dealt to the XCDs; the column tiles of a row tile stay together
+    const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
+    const int u = (q / n_tiles) * 8 + xcd, n0 = (q % n_tiles) * TN;
+    const int full = cut.whole((M + TM - 1) / TM);
+    const int m0 = u < full ? u * TM : full * TM + (u - full) * (TM / 2);
+    if (epi_subtracts(EPI) && loss_part) loss_part += blockIdx.x;
+    if (m0 >= M) {
+        if (epi_subtracts(EPI) && loss_part && threadIdx.x == 0) *loss_part = 0.0;
+        return;
+    }
+    if (u < full)
+        gemm_nt_tile<4, GATHER, NW, SCATTER, EPI, HB, WIDE, BDIRECT>(A, lda, a_bytes, row_ids, M, B, ldb, b_bytes, n, ktot, zero_ids,
+                                                                     pad_id, m0, n0, C, ldc, sc, aux, loss_part, smem, s_pad_row);
+    else
+        gemm_nt_tile<2, GATHER, NW, SCATTER, EPI, HB, WIDE, BDIRECT>(A, lda, a_bytes, row_ids, M, B, ldb, b_bytes, n, ktot, zero_ids,
+                                                                     pad_id, m0, n0, C, ldc, sc, aux, loss_part, smem, s_pad_row);
+}
+
 constexpr int kGemmWaves = 8;
 
 template <bool SCATTER, int EPI, bool HB, bool WIDE, bool BDIRECT = false>
@@ -860,7 +920,7 @@ static void launch_gemm_variant(Ctx* c, int kid, unsigned blocks, hipStream_t s,
     ensure_dynamic_lds<kern>((int)smem);
     // the descriptor of a WIDE operand is not used; any size that fits its field will do
     launch_smem(c, kid, kern, dim3(blocks), dim3(kGemmWaves * 64), smem, s, A, lda,
-                (uint32_t)(WIDE ? 0 : a_bytes), row_ids, m_dev, B, ldb, (uint32_t)b_bytes, n, k, zero_ids, pad_id, n_tiles, C,
+                (uint32_t)(WIDE ? 0 : a_bytes), row_ids, m_dev, B, ldb, (uint32_t)b_bytes, n, k, zero_ids, pad_id, n_tiles, TileCut(n_tiles, c->num_cus), C,
                 ldc, sc, aux, loss_part);
 }
 
@@ -876,7 +936,8 @@ static void launch_gemm_nt(Ctx* c, const uint16_t* A, int64_t lda, int64_t a_row
                            const int* zero_ids, int pad_id, int epi, const void* aux, const EpiLoss* loss, bool b_direct = false)
 {
     const int n_tiles = (n + TN - 1) / TN;
-    const unsigned blocks = (unsigned)((((m_bound + TM - 1) / TM + 7) / 8 * 8) * n_tiles);
+    const unsigned blocks =
+        (unsigned)((TileCut(n_tiles, c->num_cus).row_tiles_max((int)((m_bound + TM - 1) / TM)) + 7) / 8 * 8 * n_tiles);
     const int64_t a_bytes = a_rows * lda * 2, b_bytes = b_rows * ldb * 2;
     const bool wide = a_bytes >= kBufferWindow;
     double* loss_part = loss ? loss->part : nullptr;
@@ -1018,7 +1079,9 @@ static bool big_kernel_reads_plain_b(int64_t a_rows, int k, int n_out, int epi)
            (int64_t)k * n_out * 2 < kBufferWindow;
 }
 
-// Blocks of the widest grid gemm_rows_bf16 launches for up to `rows` rows.
+// Blocks of the widest grid gemm_rows_bf16 launches for up to `rows` rows: the 64 x 64 tiles.  (The big kernel
+// has at least num_cus tiles r x t of 256 x 256, so the row tiles that may be cut are at most r / 2 and its
+// blocks at most 8 ceil(1.5 r / 8) t, below the 8 ceil((4 r - 3) / 8) (4 t - 3) of these.)
 int64_t epi_loss_blocks_max(int64_t rows, int64_t n_out)
 {
     return ((rows + BM - 1) / BM + 7) / 8 * 8 * ((n_out + BN - 1) / BN);

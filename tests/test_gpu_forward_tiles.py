@@ -78,3 +78,59 @@ def test_rectified_and_subtracting_forms(items, k, dh, d):
     assert float((R.double() - want).norm()) <= 2e-6 * float(want.norm())
     assert bool((R[ids == 0] == 0).all())
     g.close()
+
+
+# 256-row tiles of which the last ones are cut in two: around the edges of halves, around the most that are
+# cut (64 row tiles with two column tiles on 256 CUs), none left over, one row left over.
+@pytest.mark.parametrize("items", [1, 127, 129, 257, 16_384, 16_385, 32_768, 32_769, 33_025, 49_153])
+@pytest.mark.parametrize("h_bf16", [0, 1])
+def test_large_tiles_cut_at_the_end(items, h_bf16):
+    import torch
+    from paper_2204_04179_amd import gram
+    torch.manual_seed(items)
+    n, k, d, m = 60_000, 64, 504, 50_000
+    X = torch.randn(n, k, device="cuda", dtype=torch.bfloat16)
+    W = (torch.randn(k, d, device="cuda") * k ** -0.5).to(torch.bfloat16)
+    pool = (torch.randperm(n - 1, device="cuda")[:items] + 1).to(torch.int32)
+    pool[items - 1] = 0
+    ids = pool[torch.arange(m, device="cuda") % items]
+    g = gram.Gram(gram.make_config(n, k, d, m, 1, 0, 0, gram.BF16, 0, 0, gram.BF16 if h_bf16 else gram.F32))
+    uniq, counts = (torch.empty(m, dtype=torch.int32, device="cuda") for _ in range(2))
+    inverse, u = torch.empty(m, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+    assert g.unique(ids, uniq, inverse, counts, u, want_host_u=True) == items
+    E = torch.full((m, d), float("nan"), device="cuda")
+    H = torch.full((m, d), float("nan"), device="cuda", dtype=torch.bfloat16 if h_bf16 else torch.float32)
+    g.encode_gather(X, W, uniq, inverse, u, m, E, H)
+    want = X[uniq[:items].long()].double() @ W.double()
+    want[uniq[:items] == 0] = 0
+    err = (E[:items].double() - want).norm(dim=1) / want.norm(dim=1).clamp(min=1e-30)
+    assert float(err.max()) < 2e-6
+    assert bool((E[0] == 0).all()) and bool(torch.isnan(E[items:]).all())
+    assert torch.equal(H, E[inverse.long()].to(H.dtype))
+    E2 = torch.full((m, d), float("nan"), device="cuda", dtype=H.dtype)
+    g.encode_gather(X, W, uniq, inverse, u, m, None, E2)
+    assert torch.equal(H, E2)
+    g.close()
+
+
+@pytest.mark.parametrize("items", [32_769, 40_000, 49_153])
+def test_large_subtracting_tiles_cut_at_the_end(items):
+    import torch
+    from paper_2204_04179_amd import gram
+    torch.manual_seed(items)
+    n, k, d = 60_000, 64, 504
+    X = torch.randn(n, k, device="cuda", dtype=torch.bfloat16)
+    W = (torch.randn(k, d, device="cuda") * k ** -0.5).to(torch.bfloat16)
+    ids = (torch.randperm(n - 1, device="cuda")[:items] + 1).to(torch.int32)
+    ids[items - 1] = 0
+    Ht, R, dW = torch.randn(items, d, device="cuda"), torch.empty(items, d, device="cuda"), torch.empty(k, d, device="cuda")
+    loss = torch.zeros(1, dtype=torch.float64, device="cuda")
+    g = gram.Gram(gram.make_config(n, k, d, items, 1, 0, 0, gram.BF16))
+    g.pseudo_loss_grad(X, W, ids, Ht, items, R, dW, loss_dev=loss)
+    want = X[ids.long()].double() @ W.double() - Ht.double()
+    want[ids == 0] = 0
+    assert float((R.double() - want).norm(dim=1).max()) <= 2e-6 * float(want.norm(dim=1).max())
+    assert bool((R[ids == 0] == 0).all())
+    half_sum = 0.5 * float((R.double() ** 2).sum())
+    assert abs(float(loss) - half_sum) < 1e-9 * half_sum
+    g.close()
