@@ -13,7 +13,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libgram.so")
 SOURCES = ["gram_api.hip", "gram_sort.hip", "gram_stream.hip", "gram_gemm.hip", "gram_mlp.hip"]
-HEADERS = [os.path.join(CSRC, "gram_internal.h"), os.path.join(ROOT, "include", "gram.h")]
+HEADERS = [os.path.join(CSRC, "gram_internal.h"), os.path.join(CSRC, "gram_mid_rows.h"), os.path.join(ROOT, "include", "gram.h")]
 ARCH = "gfx950"
 FLAGS = [
     "-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-fno-gpu-rdc",

@@ -19,6 +19,7 @@
 #include <algorithm>
 
 #include "gram_internal.h"
+#include "gram_mid_rows.h"
 
 namespace gram {
 
@@ -26,7 +27,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4_ __attribute__((ext_vector_type(4)));
 constexpr uint32_t kRawBuffer = 0x00027000;     // descriptor flags: 32-bit elements, no swizzle
-constexpr uint32_t kPastEnd = 0xFFFFFFF0u;      // an offset no descriptor covers: reads zeros
 
 // What a contraction kernel does with its output elements before storing them (template parameter EPI
 // of the kernels below).  `aux` has the row pitch of C.
@@ -295,9 +295,10 @@ __global__ __launch_bounds__(kBlock) void k_encode_bf16(
 // which walk every KG-th slab of 64 side by side and add their tiles through LDS at the end: twice as
 // many waves and bytes in flight per tile.  W is read as the caller holds it; loads go through descriptors
 // (rows of the padding item and everything past an edge read zeros), so the loads in flight are known at
-// every wait.  The unique list is read before the number of items is known: what lies behind its end only
-// selects rows whose products are not stored.  A wave has WR tiles of 32 x 32 below each other.  Four groups
-// (all of K in flight) were slower: the tile then takes longer to add up than its slabs to arrive.
+// every wait.  Neither the list nor A is read behind the U items: both may be the caller's and hold no more
+// than those (reading the list ahead of U saves nothing: the compiler waits for U before it either way).
+// A wave has WR tiles of 32 x 32 below each other.  Four groups (all of K in flight) were slower: the tile
+// then takes longer to add up than its slabs to arrive.
 // LDS: rows of X are 128 bytes (chunk c of row r at c ^ ((r >> 1) & 7)); rows of W as in k_wgrad_short.
 constexpr int SK = 64;
 template <int TM_, int TN, int KG, int WR>
@@ -311,7 +312,7 @@ struct Mid {
 template <int SM, int TN, int KG, int WR, int DEPTH, int EPI>
 __global__ __launch_bounds__((Mid<SM, TN, KG, WR>::kThreads), 4) void k_encode_mid(
     const uint16_t* __restrict__ X, uint32_t x_bytes, const uint16_t* __restrict__ W, uint32_t w_bytes,
-    const int* __restrict__ uniq, const int* __restrict__ u_dev, int rows_max, int d_in, int d,
+    const int* __restrict__ uniq, const int* __restrict__ u_dev, int d_in, int d,
     const int* __restrict__ zero_ids, int pad_id, float* __restrict__ E, const void* __restrict__ aux,
     double* __restrict__ loss_part)
 {
@@ -328,7 +329,8 @@ __global__ __launch_bounds__((Mid<SM, TN, KG, WR>::kThreads), 4) void k_encode_m
     const int n_tiles = (d + TN - 1) / TN;
     const int q = blockIdx.x >> 3;
     const int m0 = ((q / n_tiles) * 8 + (blockIdx.x & 7)) * SM, n0 = (q % n_tiles) * TN;
-    if (m0 >= rows_max) {
+    const int U = *u_dev;
+    if (m0 >= U) {
         if (epi_subtracts(EPI) && loss_part && threadIdx.x == 0) *loss_part = 0.0;
         return;
     }
@@ -339,14 +341,9 @@ __global__ __launch_bounds__((Mid<SM, TN, KG, WR>::kThreads), 4) void k_encode_m
     int id[XT], zid[XT];
 #pragma unroll
     for (int t = 0; t < XT; ++t) {
-        const int j = m0 + xrow + t * (GT / 8), jj = j < rows_max ? j : rows_max - 1;
+        const int jj = mid_list_entry(m0 + xrow + t * (GT / 8), U);
         id[t] = uniq[jj];
         zid[t] = zero_ids[jj];
-    }
-    const int U = *u_dev;
-    if (m0 >= U) {
-        if (epi_subtracts(EPI) && loss_part && threadIdx.x == 0) *loss_part = 0.0;
-        return;
     }
     const __amdgpu_buffer_rsrc_t rsX = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(X), 0, x_bytes, kRawBuffer);
     const __amdgpu_buffer_rsrc_t rsW = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(W), 0, w_bytes, kRawBuffer);
@@ -359,7 +356,7 @@ __global__ __launch_bounds__((Mid<SM, TN, KG, WR>::kThreads), 4) void k_encode_m
     uint32_t ox[XT];
 #pragma unroll
     for (int t = 0; t < XT; ++t)
-        ox[t] = zid[t] == pad_id ? kPastEnd : ((uint32_t)id[t] * (uint32_t)d_in + (uint32_t)xk) * 2u;
+        ox[t] = mid_row_offset(m0 + xrow + t * (GT / 8), U, zid[t] == pad_id, (uint32_t)id[t], (uint32_t)d_in, (uint32_t)xk);
     constexpr int WC = TN / 8;                              // chunks per row of W
     const int wrow = gt / WC, wpos = gt % WC;               // + (GT / WC) t
     const int wcol = n0 + (wpos ^ (WROW == 256 ? (wrow & 3) << 2 : (wrow & 2) << 1)) * 8;
@@ -372,7 +369,7 @@ __global__ __launch_bounds__((Mid<SM, TN, KG, WR>::kThreads), 4) void k_encode_m
     {                                                                                               \
         const int k0_ = (grp + (IT) * KG) * SK;                                                     \
         _Pragma("unroll") for (int t = 0; t < XT; ++t) {                                            \
-            const uint32_t o_ = k0_ + xk < d_in && ox[t] != kPastEnd ? ox[t] + (uint32_t)k0_ * 2u : kPastEnd; \
+            const uint32_t o_ = mid_slab_offset(ox[t], k0_, xk, d_in);                              \
             rx[SET][t] = __builtin_amdgcn_raw_buffer_load_b128(rsX, o_, 0, 0);                      \
         }                                                                                           \
         _Pragma("unroll") for (int t = 0; t < WT; ++t) {                                            \
@@ -1144,7 +1141,7 @@ bool gemm_rows_bf16(Ctx* c, const void* A, int64_t a_rows, int k, const int* row
             const unsigned blocks = (unsigned)(((rows_max + tm - 1) / tm + 7) / 8 * 8 * ((n_out + tn - 1) / tn));
             if (loss) *loss->blocks = (int)blocks;
             launch_smem(c, KID_ENCODE_BF16, kern, dim3(blocks), dim3(threads), lds, s, static_cast<const uint16_t*>(A),
-                        x_bytes, static_cast<const uint16_t*>(B_plain), w_bytes, row_ids, n_dev, (int)rows_max, k, n_out,
+                        x_bytes, static_cast<const uint16_t*>(B_plain), w_bytes, row_ids, n_dev, k, n_out,
                         zero_ids, pad_id, C, aux, loss_part);
         };
 #define GRAM_MID_(TM_, TN_, KG_, WR_, DEPTH_, EPI_)                                                 \

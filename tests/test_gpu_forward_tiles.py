@@ -134,3 +134,35 @@ def test_large_subtracting_tiles_cut_at_the_end(items):
     half_sum = 0.5 * float((R.double() ** 2).sum())
     assert abs(float(loss) - half_sum) < 1e-9 * half_sum
     g.close()
+
+
+# lists trimmed to the items, and hidden activations that end (or turn into NaN) behind their rows: item counts
+# inside a tile, in each of the three tile shapes
+@pytest.mark.parametrize("items,m,dh", [(70, 900, 136), (641, 8000, 520), (2500, 20_000, 520)])
+def test_lists_and_activations_that_end_with_the_items(items, m, dh):
+    import torch
+    from paper_2204_04179_amd import gram
+    torch.manual_seed(items)
+    n, k, d = 50_000, 200, 136
+    X = torch.randn(n, k, device="cuda", dtype=torch.bfloat16)
+    W1 = (torch.randn(k, dh, device="cuda") * k ** -0.5).to(torch.bfloat16)
+    W2 = (torch.randn(dh, d, device="cuda") * dh ** -0.5).to(torch.bfloat16)
+    pool = torch.randperm(n, device="cuda")[:items].to(torch.int32)
+    ids = pool[torch.arange(m, device="cuda") % items]
+    g = gram.Gram(gram.make_config(n, k, d, m, 1, 0, 0, gram.BF16, 0, dh))
+    uniq, counts = (torch.empty(m, dtype=torch.int32, device="cuda") for _ in range(2))
+    inverse, u = torch.empty(m, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+    assert g.unique(ids, uniq, inverse, counts, u, want_host_u=True) == items
+    x = X[uniq[:items].long()].double()
+    x[uniq[:items] == 0] = 0
+    a = (x @ W1.double()).clamp(min=0)
+    for trimmed in (uniq, uniq[:items].clone()):
+        kept = torch.full((items + 300, dh), float("nan"), device="cuda", dtype=torch.bfloat16)
+        H = torch.full((m, d), float("nan"), device="cuda")
+        g.mlp_encode_gather(X, W1, W2, trimmed, inverse if trimmed is uniq else inverse.clone(), u, m, kept[:items], None, H)
+        assert bool(torch.isnan(kept[items:]).all())
+        A1 = kept[:items]
+        assert float((A1.double() - a).norm()) <= 3e-3 * float(a.norm())
+        want = (A1.double() @ W2.double())[inverse.long()]
+        assert float((H.double() - want).norm()) <= 2e-6 * float(want.norm())
+    g.close()
