@@ -556,14 +556,14 @@ __device__ __forceinline__ void gemm_nt_tile(
     const uint16_t* __restrict__ A, int64_t lda, uint32_t a_bytes, const int* __restrict__ row_ids, int M,
     const uint16_t* __restrict__ B, int64_t ldb, uint32_t b_bytes, int n, int ktot, const int* __restrict__ zero_ids,
     int pad_id, int m0, int n0, float* __restrict__ C, int64_t ldc, const ScatterArgs& sc,
-    const void* __restrict__ aux, double* __restrict__ loss_part, unsigned char* smem, int& s_pad_row)
+    const void* __restrict__ aux, double* __restrict__ loss_part, unsigned char* smem, uint32_t* s_pad_rows)
 {
     constexpr int TM = MI * 64, TSTAGEB = (TM + TN) * TROWB;   // rows of the tile; bytes per stage
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     constexpr int NT = NW == 4 ? 4 : 2;          // 32-column MFMA tiles per wave
     constexpr int GA = TM / 16 / NW, GB = TN / 16 / NW;      // 16-row groups of A and of B a wave loads per slab
     const int wm = NW == 4 ? wave >> 1 : wave >> 2, wn = NW == 4 ? wave & 1 : wave & 3;
-    if (tid == 0) s_pad_row = -1;
+    if (tid < TM / 32) s_pad_rows[tid] = 0;      // one bit per row of the tile: the padding item
     __syncthreads();
 
     const int nslab = (ktot + TK - 1) / TK;
@@ -586,8 +586,9 @@ __device__ __forceinline__ void gemm_nt_tile(
         int64_t rowA = j;
         if (GATHER) {
             const int id = row_ids[j];
-            // at most one row is the padding item (only the subtracting modes tell it by another list)
-            if (m0 + r < M && (epi_subtracts(EPI) ? zero_ids[j] : id) == pad_id) s_pad_row = r;
+            // (only the subtracting modes tell the padding item by another list; a batch listed by the
+            // caller may hold it any number of times)
+            if (m0 + r < M && (epi_subtracts(EPI) ? zero_ids[j] : id) == pad_id) atomicOr(&s_pad_rows[r >> 5], 1u << (r & 31));
             rowA = id;
         }
         oa[t] = (uint32_t)((rowA * lda + (int64_t)sl_begin * TK + lchunk * 8) * 2);
@@ -757,7 +758,11 @@ __device__ __forceinline__ void gemm_nt_tile(
     }
 
     // accumulator element r of a lane sits at (row, col) = ((r / 4) * 8 + (lane / 32) * 4 + r % 4, lane % 32)
-    const int pad_row = GATHER ? s_pad_row : -1;
+    // the rows a wave stores are the 32 of MFMA row block i of its wave row: their padding bits
+    const int cr0 = (wave / (NW / 2)) * 32 + (wave % (NW / 2)) * RPW;           // first staged row
+    uint32_t pads[MI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i) pads[i] = GATHER ? __builtin_amdgcn_readfirstlane(s_pad_rows[(cr0 >> 5) * MI + i]) >> (cr0 & 31) & ((1u << RPW) - 1) : 0u;
     if (SCATTER) {
         // The stages are dead.  The tile goes through LDS 64 rows at a time (the 32 rows of MFMA
         // row block i of both wave rows), so that a wave can then store whole 1 KiB row pieces,
@@ -782,18 +787,21 @@ __device__ __forceinline__ void gemm_nt_tile(
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int rr = (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-                const bool zero = wm * (MI * 32) + i * 32 + rr == pad_row;
                 float* dst = reinterpret_cast<float*>(stage + (wm * 32 + rr) * kScatterRowB) +
                              wn * (NT * 32) + (lane & 31);
 #pragma unroll
-                for (int jj = 0; jj < NT; ++jj) dst[jj * 32] = zero ? 0.f : acc[i][jj][r];
+                for (int jj = 0; jj < NT; ++jj) dst[jj * 32] = acc[i][jj][r];
             }
             __syncthreads();
-            const int cr0 = (wave / (NW / 2)) * 32 + (wave % (NW / 2)) * RPW;           // first staged row
             f32x4 v[RPW];
 #pragma unroll
             for (int u = 0; u < RPW; ++u)
                 v[u] = *reinterpret_cast<const f32x4*>(stage + (cr0 + u) * kScatterRowB + lane * 16);
+            if (pads[i] != 0) {
+#pragma unroll
+                for (int u = 0; u < RPW; ++u)
+                    if (pads[i] >> u & 1) v[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
 #pragma unroll
             for (int u = 0; u < RPW; ++u) {
                 const int lr = (cr0 >> 5) * (MI * 32) + i * 32 + (cr0 & 31) + u;         // row of the tile
@@ -827,7 +835,6 @@ __device__ __forceinline__ void gemm_nt_tile(
         // 107 us and 23 for the sum of squares in a pass of its own against 112 us for both.
         const int col = n0 + lane * 4;
         const bool col_ok = col < n;
-        const int cr0 = (wave / (NW / 2)) * 32 + (wave % (NW / 2)) * RPW;           // first staged row
         double sq = 0.0;
         __syncthreads();
 #pragma unroll
@@ -849,7 +856,7 @@ __device__ __forceinline__ void gemm_nt_tile(
 #pragma unroll
             for (int u = 0; u < RPW; ++u) {
                 f32x4_ v = *reinterpret_cast<const f32x4_*>(stage + (cr0 + u) * kScatterRowB + lane * 16);
-                const bool zero = row0 + u - m0 == pad_row;
+                const bool zero = pads[i] >> u & 1;
 #pragma unroll
                 for (int k = 0; k < 4; ++k) v[k] = epi_value<EPI>(v[k], av[u][k], zero);
                 if (row0 + u < M && col_ok) {
@@ -884,7 +891,7 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_nt_bf16(
     ScatterArgs sc, const void* __restrict__ aux, double* __restrict__ loss_part)
 {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-    __shared__ int s_pad_row;
+    __shared__ uint32_t s_pad_rows[TM / 32];
     const int M = *m_dev;
     // row tiles are dealt to the XCDs; the column tiles of a row tile stay together
     const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
@@ -898,10 +905,10 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_nt_bf16(
     }
     if (u < full)
         gemm_nt_tile<4, GATHER, NW, SCATTER, EPI, HB, WIDE, BDIRECT>(A, lda, a_bytes, row_ids, M, B, ldb, b_bytes, n, ktot, zero_ids,
-                                                                     pad_id, m0, n0, C, ldc, sc, aux, loss_part, smem, s_pad_row);
+                                                                     pad_id, m0, n0, C, ldc, sc, aux, loss_part, smem, s_pad_rows);
     else
         gemm_nt_tile<2, GATHER, NW, SCATTER, EPI, HB, WIDE, BDIRECT>(A, lda, a_bytes, row_ids, M, B, ldb, b_bytes, n, ktot, zero_ids,
-                                                                     pad_id, m0, n0, C, ldc, sc, aux, loss_part, smem, s_pad_row);
+                                                                     pad_id, m0, n0, C, ldc, sc, aux, loss_part, smem, s_pad_rows);
 }
 
 constexpr int kGemmWaves = 8;
