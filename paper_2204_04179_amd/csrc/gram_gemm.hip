@@ -445,8 +445,8 @@ __global__ __launch_bounds__((Mid<SM, TN, KG, WR>::kThreads), 4) void k_encode_m
 #pragma unroll
         for (int g = 1; g < KG; ++g) s += *reinterpret_cast<const f32x4_*>(&parked[(g * SM + row) * LD + c]);
         if (m0 + row < U && n0 + c < d) {
-            // (the padding item's product is zero already: only the subtracting modes have to look)
-            const bool zero = epi_subtracts(EPI) && s_ids[row] == pad_id;
+            // (the padding item's product is zero only where the weights are finite)
+            const bool zero = s_ids[row] == pad_id;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 s[k] = epi_value<EPI>(s[k], av[h][k], zero);
