@@ -586,9 +586,9 @@ __device__ __forceinline__ void gemm_nt_tile(
         int64_t rowA = j;
         if (GATHER) {
             const int id = row_ids[j];
-            // (only the subtracting modes tell the padding item by another list; a batch listed by the
-            // caller may hold it any number of times)
-            if (m0 + r < M && (epi_subtracts(EPI) ? zero_ids[j] : id) == pad_id) atomicOr(&s_pad_rows[r >> 5], 1u << (r & 31));
+            // (the two-layer encoder's second contraction tells the padding item by another list than its rows; a
+            // batch listed by the caller may hold it any number of times)
+            if (m0 + r < M && (zero_ids != row_ids ? zero_ids[j] : id) == pad_id) atomicOr(&s_pad_rows[r >> 5], 1u << (r & 31));
             rowA = id;
         }
         oa[t] = (uint32_t)((rowA * lda + (int64_t)sl_begin * TK + lchunk * 8) * 2);

@@ -46,10 +46,10 @@ bool mlp_forward(Ctx* c, const void* X, const void* W1, const void* W2, const in
                    static_cast<float*>(a1), s, nullptr, true, kEpiReluBf16, nullptr, plain1 ? W1 : nullptr);
     const bool plain2 = gemm_reads_plain_b(c, rows_max, rows_max, dh, d, kEpiPlain);
     if (!plain2) transpose_weight(c, W2, dh, d, c->W2t, s);
-    // rows of A1 are in the order of uniq: the identity list stands in for the gather, and no row is
-    // "padding" by its index (the padding item's activation row is zero already)
-    return gemm_rows_bf16(c, a1, rows_max, dh, c->iota, -1, u_dev, rows_max, c->W2t, d, E, s, H_scatter,
-                          caller_wants_E, kEpiPlain, nullptr, plain2 ? W2 : nullptr);
+    // rows of A1 are in the order of uniq: the identity list stands in for the gather, and the padding item is
+    // told by uniq (its activation row is zero, but the product is not where a weight is not finite)
+    return gemm_rows_bf16(c, a1, rows_max, dh, c->iota, c->cfg.pad_id, u_dev, rows_max, c->W2t, d, E, s, H_scatter,
+                          caller_wants_E, kEpiPlain, nullptr, plain2 ? W2 : nullptr, uniq);
 }
 
 int64_t mlp_batch_bytes(const Ctx* c, int64_t n)
