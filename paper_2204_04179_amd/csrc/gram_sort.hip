@@ -770,7 +770,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_emit_small(
 // head flags: 33 to 37 us from 12,000 to 65,000 positions whatever the vocabulary).  Where a counter
 // per ID fits in LDS, three launches do it all:
 //   k_ids_count  a block counts the IDs of its 1024 positions in LDS (16-bit counters) and leaves them
-//                as one row of table[block][id];
+//                as one row of table[block][id], and the checked IDs where k_ids_emit reads them (the caller's
+//                buffer of IDs may be one of the outputs: a launch that writes those does not read it);
 //   k_ids_scan   exclusive prefix down every column of the table (a block takes 128 IDs), and per ID
 //                its count and its place among the positions, items and new items of its 128 IDs;
 //   k_ids_emit   position blocks: place of a position = first row of its ID + the column prefix + its
@@ -795,7 +796,7 @@ int64_t count_table_words(int64_t vocab_n, int64_t max_positions)
     return words > kCountMaxWords ? kCountMaxWords : words;
 }
 
-// ID of position p (checked) and whether it belongs to [lo, hi).
+// A position's ID; one outside [0, vocab_n) is replaced and reported.
 __device__ __forceinline__ int count_id(int raw, int vocab_n, int fix_key, bool* bad)
 {
     if (raw < 0 || raw >= vocab_n) {
@@ -807,7 +808,7 @@ __device__ __forceinline__ int count_id(int raw, int vocab_n, int fix_key, bool*
 
 __global__ __launch_bounds__(kCountThreads) void k_ids_count(const int* __restrict__ ids, int n, int vocab_n,
                                                              int fix_key, int pitch, int* __restrict__ scal,
-                                                             uint32_t* __restrict__ table)
+                                                             uint32_t* __restrict__ table, int* __restrict__ checked)
 {
     extern __shared__ __attribute__((aligned(16))) uint32_t cnt[];
     const int tid = threadIdx.x, lo = blockIdx.y * kCountIds;
@@ -817,7 +818,8 @@ __global__ __launch_bounds__(kCountThreads) void k_ids_count(const int* __restri
     for (int i = tid * 4; i < words; i += kCountThreads * 4) *reinterpret_cast<uint4*>(cnt + i) = make_uint4(0, 0, 0, 0);
     __syncthreads();
     bool bad = false;
-    const int id = count_id(raw, vocab_n, fix_key, &bad) - lo;
+    const int key = count_id(raw, vocab_n, fix_key, &bad), id = key - lo;
+    if (blockIdx.y == 0 && p < n) checked[p] = key;
     const bool mine = p < n && (unsigned)id < (unsigned)(2 * words);
     // the ID of the wave's first position (padding, a very popular item) is counted with one atomic
     // for all lanes that hold it: they would pile up on one LDS word
@@ -897,7 +899,7 @@ __global__ __launch_bounds__(kBlock) void k_ids_scan(uint32_t* __restrict__ tabl
 }
 
 __global__ __launch_bounds__(kCountThreads) void k_ids_emit(
-    const int* __restrict__ ids, int n, int key_bits, int vocab_n, int fix_key, int pitch, int pos_blocks,
+    const int* __restrict__ checked, int n, int key_bits, int vocab_n, int pitch, int pos_blocks,
     const uint16_t* __restrict__ table, const uint2* __restrict__ id_info, const int* __restrict__ tile_info, int T,
     int* __restrict__ perm, int* __restrict__ uniq, int* __restrict__ inverse, int* __restrict__ counts,
     int* __restrict__ offsets, int* __restrict__ seg_of_row, int* __restrict__ uniq_ws, int* __restrict__ u_out,
@@ -927,8 +929,7 @@ __global__ __launch_bounds__(kCountThreads) void k_ids_emit(
             if (slot_of && !first_step) slot = slot_of[j];
         }
     } else {
-        bool bad = false;
-        id = count_id(p < n ? ids[p] : 0, vocab_n, fix_key, &bad);
+        id = p < n ? checked[p] : 0;
         mine = p < n && (unsigned)(id - lo) < (unsigned)(2 * words);
         if (mine) {
             info = id_info[id];
@@ -1043,12 +1044,12 @@ bool unique_by_count(Ctx* c, const int* ids, int n, int fix_key, int* uniq, int*
     c->sorted_keys = nullptr;
     c->perm = c->vals[0];
     launch_smem(c, KID_IDS_COUNT, k_ids_count, dim3(rows, parts), dim3(kCountThreads), lds, s, ids, n, c->cfg.vocab_n,
-                fix_key, pitch, c->scal, c->cnt_table);
+                fix_key, pitch, c->scal, c->cnt_table, c->keys[0]);
     launch(c, KID_IDS_SCAN, k_ids_scan, dim3(T), dim3(kBlock), s, c->cnt_table, rows, pitch, slot_of, first_step,
            c->cfg.vocab_n, c->id_info, c->id_tiles);
     const int id_blocks = (int)((N + kCountThreads - 1) / kCountThreads);
-    launch_smem(c, KID_IDS_EMIT, k_ids_emit, dim3(rows + id_blocks, parts), dim3(kCountThreads), lds, s, ids, n, c->key_bits,
-                c->cfg.vocab_n, fix_key, pitch, rows, reinterpret_cast<const uint16_t*>(c->cnt_table), c->id_info,
+    launch_smem(c, KID_IDS_EMIT, k_ids_emit, dim3(rows + id_blocks, parts), dim3(kCountThreads), lds, s, c->keys[0], n,
+                c->key_bits, c->cfg.vocab_n, pitch, rows, reinterpret_cast<const uint16_t*>(c->cnt_table), c->id_info,
                 c->id_tiles, T, c->perm, uniq, inverse, counts, c->offsets, c->seg_of_row, c->uniq_ws, u_out, slot_of,
                 c->seg_slot, c->scal, first_step, (int)c->cap_total, c->cfg.pad_id);
     return true;

@@ -111,3 +111,32 @@ def test_mid_sized_batch_of_one_item_and_out_of_range_ids():
             g.unique(ids, uniq, inverse, counts, want_host_u=True)
         assert e.value.status == gram.ERR_RANGE
     g.close()
+
+
+@pytest.mark.parametrize("over", ["inverse", "uniq", "counts"])
+@pytest.mark.parametrize("m,n", [(300, 1000), (6000, 1000), (11_000, 200_001), (9000, 5001), (65_535, 20_000), (30_000, 131_072),
+                                 (70_000, 20_000)])
+def test_an_output_in_the_buffer_of_the_ids(m, n, over):
+    """The IDs' own buffer as one of the outputs: one launch, ranks, the counting dedup with one and two parts of the
+    vocabulary, and the sort."""
+    import torch
+    from paper_2204_04179_amd import gram
+    rng = np.random.default_rng(m)
+    ids = _batch(rng, m, n, "popular")
+    ru, ri, rc = np.unique(ids, return_inverse=True, return_counts=True)
+    g = gram.Gram(gram.make_config(n, 8, 4, m, 1, 0, 0, gram.F32))
+    dev = torch.from_numpy(ids).cuda()
+    out = {k: torch.empty(m, dtype=torch.int32, device="cuda") for k in ("uniq", "inverse", "counts")}
+    out[over] = dev
+    assert g.unique(dev, out["uniq"], out["inverse"], out["counts"], want_host_u=True) == ru.size
+    np.testing.assert_array_equal(out["uniq"].cpu().numpy()[:ru.size], ru)
+    np.testing.assert_array_equal(out["counts"].cpu().numpy()[:ru.size], rc)
+    np.testing.assert_array_equal(out["inverse"].cpu().numpy()[:m], ri.reshape(-1))
+    if over != "inverse":               # entries behind the items are untouched
+        np.testing.assert_array_equal(dev.cpu().numpy()[ru.size:], ids[ru.size:])
+    # and the batch's sums: whole numbers
+    g.grad_accumulate(torch.ones(m, 4, device="cuda"), m, 0)
+    Gt = torch.empty(min(m, n), 4, device="cuda")
+    assert g.flush(None, None, Gt, want_host_u=True) == ru.size
+    np.testing.assert_array_equal(Gt.cpu().numpy()[:ru.size, 0], np.where(ru == 0, 0, rc))
+    g.close()
