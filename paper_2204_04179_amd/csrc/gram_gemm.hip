@@ -393,13 +393,13 @@ __global__ __launch_bounds__((Mid<SM, TN, KG, WR>::kThreads), 4) void k_encode_m
     const int f_row = (g16 >> 1) * 8 + (j16 >> 2), f_ch = wn * 4 + (g16 & 1) * 2 + ((j16 & 3) >> 1);
     const unsigned char* fw = wstage + f_row * WROW + ((f_ch ^ (WROW == 256 ? (f_row & 3) << 2 : (f_row & 2) << 1)) * 16) + (j16 & 1) * 8;
     const int a_row = wm * (32 * WR) + (lane & 31), a_x = (a_row >> 1) & 7;      // + 32 i: the same swizzle
-#define GRAM_MID_ITER(SET, IT)                                                                      \
+#define GRAM_MID_ITER(SET, IT, MORE)                                                                \
     {                                                                                               \
         _Pragma("unroll") for (int t = 0; t < XT; ++t)                                              \
             *reinterpret_cast<v4*>(stage + (xrow + t * (GT / 8)) * 128 + xpos * 16) = rx[SET][t];   \
         _Pragma("unroll") for (int t = 0; t < WT; ++t)                                              \
             *reinterpret_cast<v4*>(wstage + (wrow + t * (GT / WC)) * WROW + wpos * 16) = rw[SET][t]; \
-        GRAM_MID_LOAD(SET, (IT) + DEPTH)                                                            \
+        if (MORE) GRAM_MID_LOAD(SET, (IT) + DEPTH)                                                  \
         __syncthreads();                                                                            \
         _Pragma("unroll") for (int ks = 0; ks < SK / 16; ++ks) {                                    \
             const unsigned char* b_ = fw + ks * 16 * WROW;                                          \
@@ -414,9 +414,24 @@ __global__ __launch_bounds__((Mid<SM, TN, KG, WR>::kThreads), 4) void k_encode_m
         }                                                                                           \
         __syncthreads();                                                                            \
     }
-    for (int it = 0; it < iters; it += DEPTH) {             // (slabs past the end are zeros)
-#pragma unroll
-        for (int s = 0; s < DEPTH; ++s) GRAM_MID_ITER(s, it + s)
+    // A trip count rounded up to DEPTH costs whole slabs of zeros (776 features are 7 trips, not 9).
+    static_assert(DEPTH == 2 || DEPTH == 3, "the ends of the loop");
+    if constexpr (DEPTH == 3) {
+        for (int it = 0;; it += DEPTH) {
+            GRAM_MID_ITER(0, it, true)
+            if (it + 1 >= iters) break;
+            GRAM_MID_ITER(1, it + 1, true)
+            if (it + 2 >= iters) break;
+            GRAM_MID_ITER(2, it + 2, true)
+            if (it + 3 >= iters) break;
+        }
+    } else {        // (exits inside the loop cost the two 128-row tiles registers: 27 spilled)
+        int it = 0;
+        for (; it + 1 < iters; it += DEPTH) {
+            GRAM_MID_ITER(0, it, true)
+            GRAM_MID_ITER(1, it + 1, true)
+        }
+        if (it < iters) GRAM_MID_ITER(0, it, false)
     }
 #undef GRAM_MID_LOAD
 #undef GRAM_MID_ITER
