@@ -310,30 +310,17 @@ struct Mid {
 };
 
 template <int SM, int TN, int KG, int WR, int DEPTH, int EPI>
-__global__ __launch_bounds__((Mid<SM, TN, KG, WR>::kThreads), 4) void k_encode_mid(
+__device__ __forceinline__ void encode_mid_tile(
     const uint16_t* __restrict__ X, uint32_t x_bytes, const uint16_t* __restrict__ W, uint32_t w_bytes,
-    const int* __restrict__ uniq, const int* __restrict__ u_dev, int d_in, int d,
-    const int* __restrict__ zero_ids, int pad_id, float* __restrict__ E, const void* __restrict__ aux,
-    double* __restrict__ loss_part)
+    const int* __restrict__ uniq, int U, int d_in, int d, const int* __restrict__ zero_ids, int pad_id,
+    float* __restrict__ E, const void* __restrict__ aux, double* __restrict__ loss_part, int m0, int n0,
+    unsigned char* smem, int* s_ids, double* s_loss)
 {
-    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-    __shared__ int s_ids[SM];
-    __shared__ double s_loss[Mid<SM, TN, KG, WR>::kThreads / 64];
-    if (epi_subtracts(EPI) && loss_part) loss_part += blockIdx.x;
     constexpr int GT = Mid<SM, TN, KG, WR>::kGroupThreads, STHREADS = KG * GT;
     constexpr size_t kStageB = Mid<SM, TN, KG, WR>::kStageB;                       // threads per group
     constexpr int XT = SM * 8 / GT, WT = SK * (TN / 8) / GT; // 16-byte chunks per thread and slab
     constexpr int WROW = TN * 2;                            // bytes per row of W in LDS
     constexpr int WM = SM / (32 * WR);                      // waves along the rows
-    // the column tiles of a row tile run on one XCD and share its rows of X
-    const int n_tiles = (d + TN - 1) / TN;
-    const int q = blockIdx.x >> 3;
-    const int m0 = ((q / n_tiles) * 8 + (blockIdx.x & 7)) * SM, n0 = (q % n_tiles) * TN;
-    const int U = *u_dev;
-    if (m0 >= U) {
-        if (epi_subtracts(EPI) && loss_part && threadIdx.x == 0) *loss_part = 0.0;
-        return;
-    }
     const int tid = threadIdx.x, grp = __builtin_amdgcn_readfirstlane(tid / GT), gt = tid % GT;
     const int lane = tid & 63, wave = gt >> 6, wm = wave % WM, wn = wave / WM;
 
@@ -471,6 +458,49 @@ __global__ __launch_bounds__((Mid<SM, TN, KG, WR>::kThreads), 4) void k_encode_m
         }
     }
     if (epi_subtracts(EPI) && loss_part) block_sum_double(sq, STHREADS, s_loss, loss_part);
+}
+
+// One tile per block; the column tiles of a row tile run on one XCD and share its rows of X.  WIDE: tiles of
+// 128 x 128; else 64 x 64, or 128 x 64 (the same threads) where the items make more than `most_low` of those.
+template <bool WIDE>
+struct MidShape {
+    static constexpr int kCols = WIDE ? 128 : 64;
+    using Low = Mid<64, 64, 2, 1>;
+    using Tall = Mid<128, kCols, 2, 2>;
+    static constexpr int kThreads = Tall::kThreads;
+    static constexpr size_t kLds = Tall::kLds;
+    static_assert(WIDE || (Low::kThreads == kThreads && Low::kLds <= kLds), "either tile by the same block");
+};
+
+template <bool WIDE, int EPI>
+__global__ __launch_bounds__(MidShape<WIDE>::kThreads, 4) void k_encode_mid(
+    const uint16_t* __restrict__ X, uint32_t x_bytes, const uint16_t* __restrict__ W, uint32_t w_bytes,
+    const int* __restrict__ uniq, const int* __restrict__ u_dev, int most_low, int d_in, int d,
+    const int* __restrict__ zero_ids, int pad_id, float* __restrict__ E, const void* __restrict__ aux,
+    double* __restrict__ loss_part)
+{
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    __shared__ int s_ids[128];
+    __shared__ double s_loss[MidShape<WIDE>::kThreads / 64];
+    constexpr int TN = MidShape<WIDE>::kCols;
+    if (epi_subtracts(EPI) && loss_part) loss_part += blockIdx.x;
+    const int n_tiles = (d + TN - 1) / TN, q = blockIdx.x >> 3, qr = q / n_tiles;
+    const int mt = qr * 8 + (blockIdx.x & 7), n0 = (q - qr * n_tiles) * TN;
+    const int U = *u_dev;
+    const bool low = !WIDE && (U + 63) / 64 * n_tiles <= most_low;
+    const int m0 = mt * (low ? 64 : 128);
+    if (m0 >= U) {
+        if (epi_subtracts(EPI) && loss_part && threadIdx.x == 0) *loss_part = 0.0;
+        return;
+    }
+    if constexpr (!WIDE)
+        if (low) {
+            encode_mid_tile<64, 64, 2, 1, 3, EPI>(X, x_bytes, W, w_bytes, uniq, U, d_in, d, zero_ids, pad_id, E, aux, loss_part,
+                                                  m0, n0, smem, s_ids, s_loss);
+            return;
+        }
+    encode_mid_tile<128, TN, 2, 2, 2, EPI>(X, x_bytes, W, w_bytes, uniq, U, d_in, d, zero_ids, pad_id, E, aux, loss_part, m0, n0,
+                                           smem, s_ids, s_loss);
 }
 
 // ---- C[M,N] = A[M,K] . B[N,K]^T, bf16 in, fp32 out ---------------------------------
@@ -1147,36 +1177,42 @@ bool gemm_rows_bf16(Ctx* c, const void* A, int64_t a_rows, int k, const int* row
     }
     if (B_plain && takes_mid_kernel(a_rows, k, n_out, epi)) {
         const uint32_t x_bytes = (uint32_t)(a_rows * k * 2), w_bytes = (uint32_t)((int64_t)k * n_out * 2);
-        // The number of items is known on the device only; guessed from the batch: all IDs of a vocabulary
-        // met many times over, 0.6 of one met a few times, else 0.4 of the positions (Zipf laws of the
-        // tests and the benchmark: 0.22 to 0.6).  Measured, event to event with cold operands, in us for
-        // 64 x 64 / 128 x 64 / 128 x 128 tiles (former kernel in brackets): 2,200 items 768 x 256
-        // 11.4 / 13.3 / 17.5 (13.3); 1,600 items 768 x 400 11.7 / 13.8 / 17.2 (13.8); 3,000 items 1024 x 512
-        // 18.6 / 16.0 / 20.6 (21.1); 10,200 items 512 x 128 16.6 / 13.9 / 17.0 (16.3); 11,600 items
-        // 768 x 256 23.3 / 22.9 / 21.2 (25.1); 5,700 items 776 x 392 26.7 / 25.7 / 23.2 (29.5)
+        // The number of items is known on the device only, and the kernel chooses between tiles of 64 and 128
+        // rows by it: the lower ones up to one per CU.  Only the 128 x 128 tiles (blocks of 1,024 threads) have to be
+        // chosen here, from a guess: all IDs of a vocabulary met many times over, 0.6 of one met a few times, else
+        // 0.4 of the positions (Zipf laws of the tests and the benchmark: 0.22 to 0.6).  They gain where about one of them
+        // falls to a CU, the more the longer K is; up to K = 256 a guess that fails costs more than they gain.
+        // Event to event with cold operands, position copies included, in us for 64 x 64 / 128 x 64 / 128 x 128 tiles (the
+        // 64-row kernel in brackets): 1,200 items 768 x 776 19.5 / 19.4 / 22.1 (18.0); 4,000 items 1544 x 256
+        // 24.9 / 30.5 / 35.8 (25.0); 10,200 items 1544 x 264 57.1 / 53.3 / 44.0 (65.1); 17,300 items 264 x 192
+        // 33.9 / 32.3 / 37.8 (33.0).  Over 4,264 shapes (K 64 to 1,544, widths 8 to 1,024, 2,000 to 51,200 positions, distinct
+        // and Zipf) its time is 0.927 of the 64-row kernel's in the geometric mean; it is slower by more than 3 % at 161, by
+        // up to 19 %.  (All three shapes by the guess: 0.937, 257, 25 %.)
         int64_t guess = rows_max;
         if (n_dev != c->scal + kSChunkN)
             guess = c->cur_m >= 8 * (int64_t)c->cfg.vocab_n ? rows_max : c->cur_m >= c->cfg.vocab_n ? rows_max * 3 / 5 : rows_max * 2 / 5;
-        const int64_t tiles64 = (guess + 63) / 64 * ((n_out + 63) / 64);
-        const int shape = tiles64 * 4 <= 5 * (int64_t)c->num_cus ? 0 : tiles64 * 2 <= 5 * (int64_t)c->num_cus ? 1 : 2;
-        auto go = [&](auto kern, int tm, int tn, int threads, size_t lds) {
-            const unsigned blocks = (unsigned)(((rows_max + tm - 1) / tm + 7) / 8 * 8 * ((n_out + tn - 1) / tn));
-            if (loss) *loss->blocks = (int)blocks;
+        const int64_t tiles_c = (n_out + 63) / 64, tiles64 = (guess + 63) / 64 * tiles_c;
+        const bool wide = k > 256 && tiles64 * 2 > 5 * (int64_t)c->num_cus;
+        // tiles of 64 rows as long as they may be chosen, tiles of 128 rows
+        const int64_t most_low = c->num_cus, low_rows = std::min((rows_max + 63) / 64, most_low / tiles_c);
+        const int64_t tall_rows = (rows_max + 127) / 128;
+        const unsigned blocks = (unsigned)((wide ? tall_rows : std::max(low_rows, tall_rows)) + 7) / 8 * 8 *
+                                (unsigned)(wide ? (n_out + 127) / 128 : tiles_c);
+        if (loss) *loss->blocks = (int)blocks;
+        auto go = [&](auto kern, int threads, size_t lds) {
             launch_smem(c, KID_ENCODE_BF16, kern, dim3(blocks), dim3(threads), lds, s, static_cast<const uint16_t*>(A),
-                        x_bytes, static_cast<const uint16_t*>(B_plain), w_bytes, row_ids, n_dev, k, n_out,
+                        x_bytes, static_cast<const uint16_t*>(B_plain), w_bytes, row_ids, n_dev, (int)most_low, k, n_out,
                         zero_ids, pad_id, C, aux, loss_part);
         };
-#define GRAM_MID_(TM_, TN_, KG_, WR_, DEPTH_, EPI_)                                                 \
+#define GRAM_MID_(WIDE_, EPI_)                                                                      \
     {                                                                                               \
-        constexpr auto kern = k_encode_mid<TM_, TN_, KG_, WR_, DEPTH_, EPI_>;                       \
-        using M_ = Mid<TM_, TN_, KG_, WR_>;                                                         \
-        ensure_dynamic_lds<kern>((int)M_::kLds);                                                    \
-        go(kern, TM_, TN_, M_::kThreads, M_::kLds);                                                 \
+        constexpr auto kern = k_encode_mid<WIDE_, EPI_>;                                            \
+        ensure_dynamic_lds<kern>((int)MidShape<WIDE_>::kLds);                                       \
+        go(kern, MidShape<WIDE_>::kThreads, MidShape<WIDE_>::kLds);                                 \
     }
 #define GRAM_GO_MID(EPI_)                                                                           \
-    if (shape == 0) GRAM_MID_(64, 64, 2, 1, 3, EPI_)                                                \
-    else if (shape == 1) GRAM_MID_(128, 64, 2, 2, 2, EPI_)                                          \
-    else GRAM_MID_(128, 128, 2, 2, 2, EPI_)
+    if (wide) GRAM_MID_(true, EPI_)                                                                 \
+    else GRAM_MID_(false, EPI_)
         if (epi == kEpiMinus) { GRAM_GO_MID(kEpiMinus) }
         else if (epi == kEpiMinusBf16) { GRAM_GO_MID(kEpiMinusBf16) }
         else if (epi == kEpiReluBf16) { GRAM_GO_MID(kEpiReluBf16) }

@@ -166,3 +166,58 @@ def test_lists_and_activations_that_end_with_the_items(items, m, dh):
         want = (A1.double() @ W2.double())[inverse.long()]
         assert float((H.double() - want).norm()) <= 2e-6 * float(want.norm())
     g.close()
+
+
+# The rectified and the two subtracting forms in each tile shape: 64 rows up to one tile per CU (256 of them; five
+# column tiles: 51 row tiles), 128 rows beyond, 128 x 128 for long K and more than 640 of the small tiles.
+@pytest.mark.parametrize("items,k", [(3264, 200), (3265, 200), (7000, 200), (9000, 264), (9000, 392)])
+def test_forms_in_every_tile_shape(items, k):
+    import torch
+    from paper_2204_04179_amd import gram
+    torch.manual_seed(items + k)
+    n, dh, d = 20_000, 264, 264
+    X = torch.randn(n, k, device="cuda", dtype=torch.bfloat16)
+    W1 = (torch.randn(k, dh, device="cuda") * k ** -0.5).to(torch.bfloat16)
+    W2 = (torch.randn(dh, d, device="cuda") * dh ** -0.5).to(torch.bfloat16)
+    ids = torch.randperm(n, device="cuda")[:items].to(torch.int32)
+    ids[items - 1] = ids[70] = 0
+    x = X[ids.long()].double()
+    x[ids == 0] = 0
+    # subtracting, float32 result and the block sums of the pseudo-loss
+    g = gram.Gram(gram.make_config(n, k, dh, n, 1, 0, 0, gram.BF16))
+    Ht, R, dW = torch.randn(items, dh, device="cuda"), torch.empty(items, dh, device="cuda"), torch.empty(k, dh, device="cuda")
+    loss = torch.zeros(1, dtype=torch.float64, device="cuda")
+    g.pseudo_loss_grad(X, W1, ids, Ht, items, R, dW, loss_dev=loss)
+    want = x @ W1.double() - Ht.double()
+    want[ids == 0] = 0
+    assert float((R.double() - want).norm(dim=1).max()) <= 2e-6 * float(want.norm(dim=1).max())
+    half = 0.5 * float((R.double() ** 2).sum())
+    assert abs(float(loss) - half) <= 1e-9 * half
+    g.close()
+    # rectified (bf16), and subtracting with a bf16 result: the two-layer backward.  Activations and misses are
+    # rounded to bf16 once each, 2^-9 per element
+    g = gram.Gram(gram.make_config(n, k, d, n, 1, 0, 0, gram.BF16, 0, dh))
+    work = torch.empty(g.mlp_batch_bytes(items), dtype=torch.uint8, device="cuda")
+    dW1, dW2 = torch.empty(k, dh, device="cuda"), torch.empty(dh, d, device="cuda")
+    g.mlp_backward(X, W1, W2, ids, None, Ht, items, work, dW1, dW2, loss_dev=loss)
+    a = (x @ W1.double()).clamp(min=0).to(torch.bfloat16).double()
+    r = a @ W2.double() - Ht.double()
+    r[ids == 0] = 0
+    half = 0.5 * float((r ** 2).sum())
+    assert abs(float(loss) - half) <= 1e-4 * half
+    assert float((dW2.double() - a.T @ r).norm()) <= 6e-3 * float((a.T @ r).norm())
+    want = x.T @ ((r @ W2.double().T) * (a > 0))
+    assert float((dW1.double() - want).norm()) <= 6e-3 * float(want.norm())
+    # rectified, item order of a dedup
+    uniq, counts, inverse = (torch.empty(n, dtype=torch.int32, device="cuda") for _ in range(3))
+    u = torch.zeros(1, dtype=torch.int32, device="cuda")
+    U = g.unique(ids, uniq, inverse, counts, u, want_host_u=True)
+    A1, H = torch.full((n, dh), float("nan"), device="cuda", dtype=torch.bfloat16), torch.empty(items, d, device="cuda")
+    g.mlp_encode_gather(X, W1, W2, uniq, inverse, u, items, A1, None, H)
+    x = X[uniq[:U].long()].double()
+    x[uniq[:U] == 0] = 0
+    a = (x @ W1.double()).clamp(min=0)
+    assert float((A1[:U].double() - a).norm()) <= 3e-3 * float(a.norm()) and bool(torch.isnan(A1[U:]).all())
+    want = (A1[:U].double() @ W2.double())[inverse[:items].long()]
+    assert float((H.double() - want).norm()) <= 2e-6 * float(want.norm())
+    g.close()

@@ -60,7 +60,7 @@ def test_nothing_behind_the_items_is_read(tmp_path):
 def test_the_kernel_uses_these_functions():
     with open(os.path.join(ROOT, "paper_2204_04179_amd", "csrc", "gram_gemm.hip")) as f:
         src = f.read()
-    body = src[src.index("void k_encode_mid("):src.index("// ---- C[M,N] = A[M,K] . B[N,K]^T")]
+    body = src[src.index("void encode_mid_tile("):src.index("// ---- C[M,N] = A[M,K] . B[N,K]^T")]
     assert "uniq[jj]" in body and "zero_ids[jj]" in body and "jj = mid_list_entry(" in body
     assert body.count("mid_row_offset(") == 1 and body.count("mid_slab_offset(") == 1
     assert "rows_max" not in body          # the only bound is the number of items on the device
