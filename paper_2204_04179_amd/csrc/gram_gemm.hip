@@ -1818,7 +1818,9 @@ __global__ __launch_bounds__(kBlock) void k_wgrad_f32(
     float* __restrict__ partial, int row_begin, int row_end, int accumulate)
 {
     const int c = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int i = blockIdx.y * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // (i is the same in all lanes of a wave, but the wave's loads of X stay vector loads: as scalar ones, 16 rows ahead,
+    // they thrash the scalar cache: 400 rows of 768 x 256 46.5 us, 38.0 like this, 40.0 a row at a time)
+    const int i = blockIdx.y * 4 + (threadIdx.x >> 6);
     const int z = blockIdx.z;
     if (i >= d_in || c >= d) return;
     int kb, ke;
