@@ -762,9 +762,11 @@ int gram_unique_static(const int32_t* ids, int64_t m, int32_t vocab_n, int32_t p
     c.seg_of_row = reinterpret_cast<int*>(base + kStaticOffSegOfRow);
     c.uniq_ws = reinterpret_cast<int*>(base + kStaticOffUniqWs);
 
-    // the array keeps the last call's contents: the error bits must start at zero (a fill kernel,
-    // so that the call can be captured in a HIP graph); everything else is written before it is read
-    fill_i32(c.scal, 64, 0, s);
+    // the array keeps the last call's contents: the error bits must start at zero.  The dedup by comparison writes
+    // them itself; before the others a fill kernel does (so that the call can be captured in a HIP graph).  Everything
+    // else is written before it is read
+    c.fresh_err = m > 0 && m <= kSmallMaxN;
+    if (!c.fresh_err) fill_i32(c.scal, 64, 0, s);
     if (m > 0) {
         const int fix = pad_id >= 0 ? pad_id : 0;
         if (!unique_small(&c, ids, (int)m, fix, uniq, inverse, counts, u_dev, s)) {

@@ -31,6 +31,7 @@ constexpr int kRowLong = 1 << 30;            // segment of at least seg_rows_for
 constexpr int kRowSeg = kRowLong - 1;
 constexpr int kLightMax = 32;           // items with more positions are gathered by a separate copy kernel
 constexpr int kSlotNew = 1 << 30;       // flag in seg_slot: the buffer row is created by this step
+constexpr int kSmallMaxN = 12288;       // the dedup by comparison: positions per batch, at most
 constexpr int kCountMinM = 8193;        // the counting dedup: positions per batch, at least
 constexpr int kCountMaxM = 65535;       // and at most
 constexpr int kCountMaxVocab = 131072;  // and IDs
@@ -137,7 +138,6 @@ struct SortPlan {
     int passes;
     int digit_bits[4];
     int items;   // 64-key rounds per wave
-    int nw;      // waves (chunks) over the host upper bound of n
     int blocks;
 };
 
@@ -153,7 +153,8 @@ struct Ctx {
     char* ws_base = nullptr;
     int64_t ws_bytes = 0;
     int *keys[2] = {nullptr, nullptr}, *vals[2] = {nullptr, nullptr};  // radix ping-pong, [max(M_max, cap_total)]
-    int* table = nullptr;       // [bins * nw] per-wave digit counts / prefixes
+    bool fresh_err = false;     // the dedup by comparison writes the error word instead of adding to it
+    int* table = nullptr;       // [blocks][bins] digit counts / prefixes per block
     int* gtot = nullptr;        // [1024] per-digit totals
     int* tile_sums = nullptr;   // [tiles] flag counts per scan tile
     // counting dedup (vocabularies of at most kCountMaxVocab IDs, contexts for batches beyond the

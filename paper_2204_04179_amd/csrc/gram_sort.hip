@@ -75,7 +75,6 @@ SortPlan make_sort_plan(int key_bits, int64_t n_max)
     int64_t nb = (n_max + kpb - 1) / kpb;
     if (nb < 1) nb = 1;
     p.blocks = (int)nb;
-    p.nw = p.blocks * kWavesPerBlock;
     return p;
 }
 
@@ -543,7 +542,6 @@ __global__ void k_unique_empty(int* u_ws, int* u_out, int* offsets)
 // LDS radix sort took 7.3; at 512 the two launches take as long as the one).
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallWaves = kSmallThreads / kWave;
-constexpr int kSmallMaxN = 12288;
 constexpr int kFusedMaxN = 512;
 constexpr int kRankP = 32;
 
@@ -565,7 +563,9 @@ __device__ __forceinline__ int block1024_excl_scan(int v, int* total, int* wsum 
     return base + incl - v;
 }
 
-// IDs of the batch into LDS (checked; a multiple of 4 entries, the rest larger than any ID).
+// IDs of the batch into LDS (checked; a multiple of 4 entries, the rest larger than any ID).  FRESH: the error
+// word is written, not added to (contains a barrier).
+template <bool FRESH>
 __device__ __forceinline__ void load_small_ids(const int* __restrict__ ids, int n, int vocab_n, int fix_key,
                                                int* __restrict__ err, bool report, int* keys)
 {
@@ -587,7 +587,12 @@ __device__ __forceinline__ void load_small_ids(const int* __restrict__ ids, int 
             keys[i] = k[u];
         }
     }
-    if (report && bad) atomicOr(err, kErrBitRange);
+    if (FRESH) {
+        const int any = __syncthreads_or(bad);
+        if (report && threadIdx.x == 0) *err = any ? kErrBitRange : 0;
+    } else if (report && bad) {
+        atomicOr(err, kErrBitRange);
+    }
 }
 
 // Rank of position p0 + (tid % P) of the n keys in LDS, P = 1 << log2p positions per block; valid in
@@ -619,6 +624,7 @@ __device__ __forceinline__ int rank_by_comparison(const int* keys, int n, int p0
     return rank;
 }
 
+template <bool FRESH>
 __global__ __launch_bounds__(kSmallThreads) void k_rank_small(const int* __restrict__ ids, int n, int vocab_n,
                                                               int fix_key, int* __restrict__ scal,
                                                               int* __restrict__ sorted_keys, int* __restrict__ perm)
@@ -628,7 +634,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_rank_small(const int* __restr
     constexpr int kLog2P = 5;
     static_assert(1 << kLog2P == kRankP, "positions per block");
     if (blockIdx.x == 0 && threadIdx.x == 0) scal[kSPadSeg] = -1;      // the emit launch sets it if there is padding
-    load_small_ids(ids, n, vocab_n, fix_key, scal + kSErr, blockIdx.x == 0, lds);
+    load_small_ids<FRESH>(ids, n, vocab_n, fix_key, scal + kSErr, blockIdx.x == 0, lds);
     __syncthreads();
     const int p0 = blockIdx.x * kRankP;
     const int rank = rank_by_comparison(lds, n, p0, kLog2P, red);
@@ -640,7 +646,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_rank_small(const int* __restr
 }
 
 // R sorted rows per thread (n <= 1024 R).  FUSED: the ranks are worked out here too (one block).
-template <int R, bool FUSED>
+template <int R, bool FUSED, bool FRESH>
 __global__ __launch_bounds__(kSmallThreads) void k_emit_small(
     const int* __restrict__ ids, int n, int log2p, int vocab_n, int fix_key, int* __restrict__ err,
     const int* __restrict__ sorted_keys, int* __restrict__ perm, int* __restrict__ uniq,
@@ -663,7 +669,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_emit_small(
         static_assert(R == 1, "one row per thread");
         __shared__ __attribute__((aligned(16))) int kin[kFusedMaxN];
         __shared__ int red[kSmallThreads], pos_of[kFusedMaxN];
-        load_small_ids(ids, n, vocab_n, fix_key, err, true, kin);
+        load_small_ids<FRESH>(ids, n, vocab_n, fix_key, err, true, kin);
         if (tid == 0) scal[kSPadSeg] = -1;
         __syncthreads();
         const int rank = rank_by_comparison(kin, n, 0, log2p, red);
@@ -1073,12 +1079,12 @@ void unique_from_sorted(Ctx* c, int n, int* uniq, int* inverse, int* counts, int
            c->seg_slot, c->scal, first_step, (int)c->cap_total, c->cfg.pad_id);
 }
 
-template <int R, bool FUSED>
+template <int R, bool FUSED, bool FRESH = false>
 static void launch_emit_small(Ctx* c, const int* ids, int n, int log2p, int fix_key, int* uniq, int* inverse,
                               int* counts, int* u_out, hipStream_t s, bool prospect, int first_step)
 {
     constexpr size_t lds = (size_t)kSmallThreads * R * 8;
-    constexpr auto kern = k_emit_small<R, FUSED>;
+    constexpr auto kern = k_emit_small<R, FUSED, FRESH>;
     ensure_dynamic_lds<kern>((int)lds);
     const unsigned blocks = (unsigned)((n + kSmallThreads - 1) / kSmallThreads);
     launch_smem(c, KID_UNIQUE_SMALL, kern, dim3(blocks), dim3(kSmallThreads), lds, s, ids, n, log2p, c->cfg.vocab_n,
@@ -1096,13 +1102,19 @@ bool unique_small(Ctx* c, const int* ids, int n, int fix_key, int* uniq, int* in
     if (n <= kFusedMaxN) {
         int log2p = 6;
         while ((1 << log2p) < n) ++log2p;
-        launch_emit_small<1, true>(c, ids, n, log2p, fix_key, uniq, inverse, counts, u_out, s, prospect, first_step);
+        if (c->fresh_err) launch_emit_small<1, true, true>(c, ids, n, log2p, fix_key, uniq, inverse, counts, u_out, s, prospect, first_step);
+        else launch_emit_small<1, true>(c, ids, n, log2p, fix_key, uniq, inverse, counts, u_out, s, prospect, first_step);
         return true;
     }
     const size_t lds = (size_t)((n + 3) & ~3) * sizeof(int);
-    ensure_dynamic_lds<k_rank_small>(kSmallMaxN * (int)sizeof(int));
-    launch_smem(c, KID_RANK_SMALL, k_rank_small, dim3((unsigned)((n + kRankP - 1) / kRankP)), dim3(kSmallThreads), lds, s,
-                ids, n, c->cfg.vocab_n, fix_key, c->scal, c->sorted_keys, c->perm);
+    auto rank = [&](auto kern) {
+        launch_smem(c, KID_RANK_SMALL, kern, dim3((unsigned)((n + kRankP - 1) / kRankP)), dim3(kSmallThreads), lds, s,
+                    ids, n, c->cfg.vocab_n, fix_key, c->scal, c->sorted_keys, c->perm);
+    };
+    ensure_dynamic_lds<k_rank_small<false>>(kSmallMaxN * (int)sizeof(int));
+    ensure_dynamic_lds<k_rank_small<true>>(kSmallMaxN * (int)sizeof(int));
+    if (c->fresh_err) rank(k_rank_small<true>);
+    else rank(k_rank_small<false>);
     if (n <= 8 * kSmallThreads)
         launch_emit_small<8, false>(c, ids, n, 0, fix_key, uniq, inverse, counts, u_out, s, prospect, first_step);
     else

@@ -140,3 +140,20 @@ def test_an_output_in_the_buffer_of_the_ids(m, n, over):
     assert g.flush(None, None, Gt, want_host_u=True) == ru.size
     np.testing.assert_array_equal(Gt.cpu().numpy()[:ru.size, 0], np.where(ru == 0, 0, rc))
     g.close()
+
+
+@pytest.mark.parametrize("m", [1, 300, 512, 513, 5000, 12_288, 12_289, 40_000])
+def test_error_word_of_the_call_without_a_context(m):
+    """The scratch array keeps the last call's contents: a bad ID is reported by its own call and not by the next."""
+    import torch
+    from paper_2204_04179_amd import gram
+    n = 1000
+    ids = torch.randint(0, n, (m,), dtype=torch.int32, device="cuda")
+    bad = ids.clone()
+    bad[m - 1] = n
+    uniq, counts, inverse = (torch.empty(m, dtype=torch.int32, device="cuda") for _ in range(3))
+    u, err = torch.zeros(1, dtype=torch.int32, device="cuda"), torch.full((1,), 77, dtype=torch.int32, device="cuda")
+    for batch, want in ((bad, 1), (ids, 0), (bad, 1), (bad, 1), (ids, 0)):
+        gram.unique_static(batch, n, 0, uniq, inverse, counts, u, err)
+        assert int(err) == want
+        assert torch.equal(uniq[inverse.long()], torch.where(batch >= n, 0, batch))
