@@ -187,8 +187,10 @@ int gram_grad_accumulate(gram_ctx* ctx, const float* dH, int64_t m, int32_t step
  *   W1, W2   DEVICE bf16       A1  DEVICE [>= U, d_hidden] bf16, nullable  out: the
  *                              hidden activations of the unique items (zero row for
  *                              the padding ID); other arguments as gram_encode_gather
- * gram_mlp_batch_bytes: bytes of `work` that gram_mlp_backward needs for n items
- *   (n * (6 d_hidden + 6 d), each of four parts rounded up to 256 bytes).
+ * gram_mlp_batch_bytes: bytes of `work` to hand to gram_mlp_backward for n items
+ *   (n * (6 d_hidden + 6 d), each of four parts rounded up to 256 bytes; a fixed layout, so
+ *   that buffers sized by an earlier release stay valid: dL/dz and the misses are kept as bf16
+ *   and 2 d_hidden + 4 d bytes per item of it are not touched).
  * gram_mlp_backward: Algorithm 1 step 4 for one content-encoder batch of items.
  *   The activations are recomputed from the CURRENT weights (W1), so the call
  *   keeps nothing between batches but the caller's `work`.  Exactly one of

@@ -8,7 +8,7 @@
 //            unique-ID list inside the tile loads (the unique items' features are
 //            never copied), B = W^T.  For large batches its epilogue is the gather
 //            as well: every representation is stored straight to the positions of
-//            its item.  Small batches take k_encode_bf16.
+//            its item.  Small and mid-sized batches take k_encode_mid, what that does not take k_encode_bf16.
 //   wgrad:   k_wgrad_tn_bf16 contracts over the rows of the gradient buffer, which
 //            is the slow dimension of both operands in memory, with transposing
 //            LDS reads; split-K over blocks, float32 partials added in split order.
@@ -544,8 +544,9 @@ constexpr uint32_t kBufferFlags = 0x00027000;   // raw buffer: 32-bit elements, 
 // block 0.25 us.  (Rounded quotients only move the cut; the grid is made with the same ones.)
 // Measured, all whole / the last ones cut: 56 x 2 tiles (K = 1536, positions stored) 53.5 / 40.5 us, 56 x 6
 // tiles (K = 768) 55.7 / 51.4, the forward of 204,800 positions 1024 x 1024 to bf16 178 / 169.  Nothing left
-// over, or more than half a round (where a round of halves would be followed by another): the same kernel
-// as before, within 1 % of it.
+// over, or more than half a round (where a round of halves would be followed by another): the same tiles as
+// before; the cut in the prologue costs up to 1 us there (2 to 3.5 % at 24 of 384 shapes of K 32 to 1024, short K
+// above all; the geometric mean over the 384 is 0.93 of the time without it).
 struct TileCut {
     uint32_t rounds_per_tile;  // ceil(2^32 n_tiles / num_cus): a row tile in rounds of blocks
     uint32_t tiles_per_round;  // ceil(2^16 num_cus / n_tiles)
@@ -1112,8 +1113,8 @@ void transpose_weight(Ctx* c, const void* W, int rows, int cols, void* Wt, hipSt
 }
 
 // Batches that give the 256x256 kernel a tile for every CU (and a K that fits its slabs) take it;
-// the rest take the 64x64 latency-oriented kernel, which addresses its operands through plain
-// pointers and therefore also serves the epilogue modes when A lies beyond 4 GiB.
+// the rest take k_encode_mid or, where that does not apply, the 64-row kernel, which addresses its operands
+// through plain pointers and therefore also serves the epilogue modes when A lies beyond 4 GiB.
 static bool takes_big_kernel(const Ctx* c, int64_t rows_max, int n_out, int k, int64_t a_rows, int epi)
 {
     const int64_t tile_bound = ((rows_max + TM - 1) / TM) * ((n_out + TN - 1) / TN);
@@ -1931,7 +1932,7 @@ bool encoder_wgrad(Ctx* c, const void* X, float* dW, hipStream_t s, int64_t firs
         if (is_short) {
             // ranges of rows: about a block per CU; a handful of slabs is one range, whose tiles go
             // straight to dW (300 rows: 8.4 us against 10.0; at 1,000 the reduction launch pays)
-            int64_t ranges = 256 / short_tiles;
+            int64_t ranges = c->num_cus / short_tiles;
             if (ranges > slabs_bound / VGROUPS) ranges = slabs_bound / VGROUPS;
             if (slabs_bound <= 20) ranges = 1;
             const int most = wgrad_splits_dims(d_in, d, true);      // what the partials have room for

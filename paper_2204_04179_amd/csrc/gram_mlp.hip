@@ -67,7 +67,8 @@ void mlp_backward(Ctx* c, const void* X, const void* W1, const void* W2, const i
     auto up = [](int64_t v) { return (v + 255) / 256 * 256; };
     char* w = static_cast<char*>(work);
     // dL/dz and the rows of dL/dh only ever enter the matrix cores: the kernels that produce them
-    // store them as the bf16 values those would round them to
+    // store them as the bf16 values those would round them to (the parts of `work` keep the sizes of a layout
+    // with both in float32: half of the first part and the third are not touched)
     void* Zb = w;                                            // [n, dh] bf16 dL/dz
     void* A1 = w + up(n * dh * 4);                           // [n, dh] bf16 activations
     void* Rb = w + up(n * dh * 4) + up(n * dh * 2) + up(n * d * 4);                    // [n, d] bf16

@@ -524,7 +524,7 @@ __global__ void k_unique_empty(int* u_ws, int* u_out, int* offsets)
 
 // ---- small batches: ranks by comparison ----------------------------------------------
 //
-// Up to kSmallMaxN positions (12,000: 28 us against 32 to 35 us for the radix sort; 16,384: 34 against 32 to
+// Up to kSmallMaxN positions (12,000: 26 us against 32 to 35 us for the radix sort; 16,384: 34 against 32 to
 // 36).  The sorted place of a position is the number of positions whose
 // (id, position) pair is smaller, and that number is counted outright: every position against every
 // other, two VALU instructions per pair.  n^2 comparisons spread over the whole chip are cheaper at

@@ -96,3 +96,22 @@ def test_kernel_names_and_null_context_errors():
     out = C.c_void_p(123)
     assert lib.gram_create(C.byref(out), None) == gram.ERR_ARG and not out.value
     assert b"cfg is NULL" in lib.gram_last_error(None)
+
+
+def test_current_stream_without_the_raw_handle(monkeypatch):
+    """The binding reads the current stream's handle through two functions of torch._C; a release without them
+    falls back to the Stream object."""
+    import torch
+
+    class Stream:
+        cuda_stream = 4711
+
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda dev: 100 + dev, raising=False)
+    assert gram._current_stream() == 103
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    assert gram._current_stream() == 4711
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: False)
+    assert gram._current_stream() == 4711
