@@ -221,3 +221,33 @@ def test_forms_in_every_tile_shape(items, k):
     want = (A1[:U].double() @ W2.double())[inverse[:items].long()]
     assert float((H.double() - want).norm()) <= 2e-6 * float(want.norm())
     g.close()
+
+
+# Around the number of items from which the row tile changes (nine column tiles: 28 row tiles of 64, 1,792 items on 256
+# CUs), with the bound that the grid is made for at the items and far above them.
+@pytest.mark.parametrize("items", [1, 1791, 1792, 1793, 1856, 2048])
+@pytest.mark.parametrize("m", [0, 3584, 9000])
+def test_row_tile_chosen_on_the_device(items, m):
+    import torch
+    from paper_2204_04179_amd import gram
+    torch.manual_seed(items + m)
+    n, k, d = 30_000, 136, 520
+    m = max(m, items)
+    X = torch.randn(n, k, device="cuda", dtype=torch.bfloat16)
+    W = (torch.randn(k, d, device="cuda") * k ** -0.5).to(torch.bfloat16)
+    pool = torch.randperm(n, device="cuda")[:items].to(torch.int32)
+    pool[items // 2] = 0
+    ids = pool[torch.arange(m, device="cuda") % items]
+    items = int(torch.unique(ids).numel())
+    g = gram.Gram(gram.make_config(n, k, d, m, 1, 0, 0, gram.BF16))
+    uniq, counts, inverse = (torch.empty(m, dtype=torch.int32, device="cuda") for _ in range(3))
+    u = torch.zeros(1, dtype=torch.int32, device="cuda")
+    assert g.unique(ids, uniq, inverse, counts, u, want_host_u=True) == items
+    E, H = torch.full((m, d), float("nan"), device="cuda"), torch.full((m, d), float("nan"), device="cuda")
+    g.encode_gather(X, W, uniq, inverse, u, m, E, H)
+    want = X[uniq[:items].long()].double() @ W.double()
+    want[uniq[:items] == 0] = 0
+    err = (E[:items].double() - want).norm(dim=1) / want.norm(dim=1).clamp(min=1e-30)
+    assert float(err.max()) < 2e-6
+    assert bool(torch.isnan(E[items:]).all()) and torch.equal(H, E[inverse.long()])
+    g.close()
