@@ -505,37 +505,75 @@ __global__ __launch_bounds__(MidShape<WIDE>::kThreads, 4) void k_encode_mid(
 
 // ---- C[M,N] = A[M,K] . B[N,K]^T, bf16 in, fp32 out ---------------------------------
 //
-// 256x256 block tile, K in slabs of 32.  LDS rows are 64 bytes (4 chunks of 16); chunk c
-// of row r sits at position c ^ ((r >> 2) & 3), which spreads the 16-byte fragment reads of
-// 16 consecutive rows over all banks; the swizzle is applied by choosing which global chunk
-// each lane fetches.  Block indices are decoded so that the column tiles of one row tile run
-// on the same XCD (consecutive block indices are dealt round-robin to the 8 XCDs) and share
-// the strip of A through that XCD's L2.
-// Row j of A is A[row_ids[j]]; a row whose ID equals pad_id yields zeros.
-constexpr int TM = 256, TN = 256, TK = 32;
-constexpr int TROWB = TK * 2;                          // bytes per LDS row
-constexpr int TSTAGEB = (TM + TN) * TROWB;             // bytes per stage
-
-// Register-staged loads.  Measured on MI355X: a wave that issues direct-to-LDS loads
-// stalls at issue for as long as the memory pipe needs to take them (about 130 cycles
-// per 1 KiB instruction at 4 waves per CU), so load time and MFMA time add up.
-// buffer_load_dwordx4 into registers issues in about 20 cycles and completes in the
-// background.  The kernel therefore loads slab s+3 into one of two register sets, parks
-// slab s+1 in LDS (2 stages) just before the barrier that publishes it, and interleaves
-// the load, LDS-write and fragment-read instructions with the MFMAs of the current slab.
-// Operands are addressed through buffer descriptors (base + 32-bit byte offset); a
-// matrix A beyond the 4 GiB such a descriptor can address takes the WIDE variant, whose
-// lanes keep 64-bit row pointers instead (every address it forms is a valid one: rows
-// past the end are clamped and K is a multiple of the slab).
+// 256x256 block tile, 8 waves (2 x 4, each 128 x 64 as 4 x 2 MFMA tiles of 32 x 32), K in slabs of 64, two LDS
+// stages of 64 KiB.  Block indices are decoded so that the column tiles of one row tile run on the same XCD
+// (consecutive block indices are dealt round-robin to the 8 XCDs) and share the strip of A through that XCD's
+// L2.  Row j of A is A[row_ids[j]]; a row whose ID equals pad_id yields zeros.
+//
+// What bounds the loop is the matrix pipe, and with it the power the chip may draw: a slab takes 2,070 to 2,160
+// cycles, its MFMAs 2,112, at 1.4 GHz where nothing else runs between such launches and above 2 GHz where
+// memory-bound kernels do.  Three things got it there (before: slabs of 32 through registers, one barrier for
+// all waves per slab, 3,400 cycles per 64 of K at 2.0 GHz):
+//   - loads go straight to LDS (buffer_load ... lds), 1 KiB per wave-wide instruction: no registers, no LDS
+//     store instructions.  They are throughput bound (8 rows of 128 bytes: 50 cycles each from HBM, 26 from L2),
+//     so how far ahead they are requested matters little beyond the 4 segments it is here;
+//   - a slab is four segments, each ended by a barrier: read the fragments of B and of the first half of the
+//     wave's rows; multiply; read the second half's; multiply.  The waves of the lower row half are one segment
+//     behind those of the upper: of the two waves on a SIMD one multiplies while the other reads;
+//   - whatever a segment has read is in registers before its barrier, so the part of the stage that is free
+//     afterwards is known, and its refill (two slabs ahead) is issued in the next reading segment.
+// LDS rows: of A (and of a K-contiguous B) 128 bytes, 16-byte chunk c of row r at c ^ ((r >> 1) & 7); of an untransposed B
+// (W [k, n]) 512 bytes, chunk c of row r at c ^ ((r & 3) << 2).  Either way the pieces of a fragment read cover
+// every bank once.  A load writes 64 consecutive chunks, so the swizzle is applied by choosing which global
+// chunk each lane fetches.
+// Operands are addressed through buffer descriptors (base + 32-bit byte offset); a matrix A beyond the 4 GiB such
+// a descriptor can address takes the WIDE variant, whose lanes keep 64-bit row pointers (every address it
+// forms is a valid one: rows past the end are clamped).  K is a multiple of 32; where half a slab is left, the
+// fragments of the other half are cleared.
+constexpr int TM = 256, TN = 256, TK = 64;
+constexpr int kGemmWaves = 8;
+constexpr int TROWB = TK * 2;                          // bytes per LDS row of a K-contiguous operand
+constexpr int TOPB = TM * TROWB;                       // bytes per operand and stage: A 0 and 1, then B 0 and 1
+constexpr size_t TSMEM = 4 * (size_t)TOPB;
 typedef int v4i32 __attribute__((ext_vector_type(4)));
-constexpr int RSTAGES = 2;
-constexpr size_t RSMEM = (size_t)RSTAGES * TSTAGEB;
-// fused-gather epilogue: 64 staged rows of TN floats (+16 bytes against bank conflicts)
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+// fused-gather epilogue: 64 staged rows of TN floats (+16 bytes against bank conflicts)
 constexpr int kScatterRowB = TN * 4 + 16;
 constexpr int kScatterTileB = 64 * kScatterRowB;
-constexpr size_t RSMEM_SC = 2 * (size_t)kScatterTileB;     // two staging buffers (they overlay the dead stages)
+constexpr size_t TSMEM_SC = 2 * (size_t)kScatterTileB;     // two staging buffers (they overlay the dead stages)
 constexpr uint32_t kBufferFlags = 0x00027000;   // raw buffer: 32-bit elements, no swizzle
+constexpr uint32_t kOutOfRange = 0xFFFFFFF0u;
+
+// Loads to LDS: lane l's 16 bytes go to lds + 16 l.  Written in asm because the compiler, which cannot tell the
+// stages apart, puts a wait for all of them in front of every LDS read; there is no result in a register, and the
+// kernel counts the loads itself (wait_loads) before the barrier that publishes them.
+__device__ __forceinline__ void load_to_lds(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds)
+{
+    asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+                 ::"v"(voff), "s"(rsrc), "s"(soff), "s"(lds) : "memory", "m0");
+}
+__device__ __forceinline__ void load_to_lds(const unsigned char* p, uint32_t lds)
+{
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(p), "s"(lds) : "memory", "m0");
+}
+// Waits until at most N of the wave's loads are outstanding.
+template <int N>
+__device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+// A barrier that waits for no memory operation, and that nothing is scheduled across.
+__device__ __forceinline__ void segment_barrier()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+__device__ __forceinline__ u32x4 buffer_words(const void* base, uint32_t bytes)
+{
+    const uint64_t a = (uint64_t)base;
+    return u32x4{(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a), (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32)) & 0xffffu,
+                 (uint32_t)__builtin_amdgcn_readfirstlane((int)bytes), kBufferFlags};
+}
 
 // How many row tiles of 256 are taken whole.  A block fills its CU (8 waves, over 200 VGPRs), so the tiles
 // go in rounds of num_cus; those left over after the last full round are cut in two where the halves still
@@ -573,7 +611,6 @@ struct TileCut {
 };
 
 // MI = 32-row MFMA tiles per wave: 4 (a tile of 256 rows) or 2 (128 rows).
-// NW = waves per block: 4 (each 32 MI x 128, one wave per SIMD) or 8 (each 32 MI x 64, two per SIMD).
 //
 // SCATTER (forward only): the epilogue is the gather of Section 3.1 as well.  Row j of the
 // product is the representation of unique item j; instead of only storing it to C it is stored
@@ -593,72 +630,69 @@ struct ScatterArgs {
 
 // HB (with SCATTER): H holds bf16, values are rounded to nearest even as they are stored.
 // BDIRECT: B is not the K-contiguous [n, k] matrix but its transpose as the caller holds it,
-// W [k, n] (n a multiple of 8, ldb = n): a slab of it is parked as 32 rows of k with 256 values
-// of n each (512-byte rows, 16-byte chunk c of row r at position c ^ ((r & 3) << 2)), and the
+// W [k, n] (n a multiple of 8, ldb = n): a slab of it is 64 rows of k with 256 values of n each, and the
 // MFMA fragments (8 consecutive k for one n) come from the transposing LDS read, exactly as
 // in k_wgrad_tn_bf16 below.  Saves the transposed copy of the weights and its launch.
-template <int MI, bool GATHER, int NW, bool SCATTER, int EPI, bool HB, bool WIDE, bool BDIRECT>
+template <int MI, bool SCATTER, int EPI, bool HB, bool WIDE, bool BDIRECT>
 __device__ __forceinline__ void gemm_nt_tile(
     const uint16_t* __restrict__ A, int64_t lda, uint32_t a_bytes, const int* __restrict__ row_ids, int M,
     const uint16_t* __restrict__ B, int64_t ldb, uint32_t b_bytes, int n, int ktot, const int* __restrict__ zero_ids,
     int pad_id, int m0, int n0, float* __restrict__ C, int64_t ldc, const ScatterArgs& sc,
     const void* __restrict__ aux, double* __restrict__ loss_part, unsigned char* smem, uint32_t* s_pad_rows)
 {
-    constexpr int TM = MI * 64, TSTAGEB = (TM + TN) * TROWB;   // rows of the tile; bytes per stage
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    constexpr int NT = NW == 4 ? 4 : 2;          // 32-column MFMA tiles per wave
-    constexpr int GA = TM / 16 / NW, GB = TN / 16 / NW;      // 16-row groups of A and of B a wave loads per slab
-    const int wm = NW == 4 ? wave >> 1 : wave >> 2, wn = NW == 4 ? wave & 1 : wave & 3;
+    constexpr int TM = MI * 64, NW = kGemmWaves, NT = 2, MH = MI / 2;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 2, wn = wave & 3;
     if (tid < TM / 32) s_pad_rows[tid] = 0;      // one bit per row of the tile: the padding item
     __syncthreads();
 
     const int nslab = (ktot + TK - 1) / TK;
-    constexpr int sl_begin = 0;
 
-    // loader: wave w moves row groups g = GA w + t (16 rows each) of A and of B; lane l moves the
-    // chunk that belongs at position l & 3 of row 16 g + (l >> 2).  Rows past M / past n are
-    // clamped to a valid row: their products are never stored.
-    const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(A), 0, a_bytes, kBufferFlags);
-    const __amdgpu_buffer_rsrc_t rsB = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(B), 0, b_bytes, kBufferFlags);
-    const int lrow = lane >> 2;
-    const int lchunk = (lane & 3) ^ ((lane >> 4) & 3);
-    uint32_t oa[GA], ob[GB];
-    const unsigned char* pa[WIDE ? GA : 1];
-    static_assert(GA >= 1, "a wave loads at least one group");
+    // A load moves 8 rows of A (lane l: position l & 7 of row l >> 3).  Wave w moves groups MH w + t of either half:
+    // half h is the rows h * 16 MI + 0 .. 16 MI - 1 of both wave rows.  Rows past M are clamped to a valid row
+    // (their products are never stored).
+    const u32x4 rsA = buffer_words(A, a_bytes), rsB = buffer_words(B, b_bytes);
+    uint32_t oa[2][MH], la[2][MH];
+    const unsigned char* pa[2][WIDE ? MH : 1];
+    const int a_chunk = (lane & 7) ^ (lane >> 4 & 3);     // of the rows with (row >> 1 & 4) == 0; the others: ^ 4
+    bool a_upper[2][WIDE ? MH : 1];
 #pragma unroll
-    for (int t = 0; t < GA; ++t) {
-        const int r = (wave * GA + t) * 16 + lrow;
-        const int j = m0 + r < M ? m0 + r : M - 1;
-        int64_t rowA = j;
-        if (GATHER) {
-            const int id = row_ids[j];
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int t = 0; t < MH; ++t) {
+            const int g = wave * MH + t, r0 = g / (2 * MI) * (32 * MI) + h * (16 * MI) + g % (2 * MI) * 8;
+            const int r = r0 + (lane >> 3), j = m0 + r < M ? m0 + r : M - 1, id = row_ids[j];
             // (the two-layer encoder's second contraction tells the padding item by another list than its rows; a
             // batch listed by the caller may hold it any number of times)
             if (m0 + r < M && (zero_ids != row_ids ? zero_ids[j] : id) == pad_id) atomicOr(&s_pad_rows[r >> 5], 1u << (r & 31));
-            rowA = id;
+            const int chunk = a_chunk ^ (r0 >> 1 & 4);
+            oa[h][t] = (uint32_t)(((int64_t)id * lda + chunk * 8) * 2);
+            la[h][t] = r0 * TROWB;
+            if (WIDE) {
+                pa[h][t] = reinterpret_cast<const unsigned char*>(A) + ((int64_t)id * lda + chunk * 8) * 2;
+                a_upper[h][t] = chunk >= 4;
+            }
         }
-        oa[t] = (uint32_t)((rowA * lda + (int64_t)sl_begin * TK + lchunk * 8) * 2);
-        if (WIDE) pa[t] = reinterpret_cast<const unsigned char*>(A) + (rowA * lda + (int64_t)sl_begin * TK + lchunk * 8) * 2;
-    }
+    // A load moves 2 rows of W [k, n] (columns past n are clamped to the last chunk: their products are never
+    // stored) or 8 rows of the K-contiguous B.  Wave w moves 4 of them in a row.
+    uint32_t ob[BDIRECT ? 2 : 4];
 #pragma unroll
-    for (int t = 0; t < GB; ++t) {
+    for (int t = 0; t < (BDIRECT ? 2 : 4); ++t) {
         if (BDIRECT) {
-            // chunk cb of the slab: row cb / 32 of k, position cb % 32 of that row in LDS; columns past
-            // n are clamped to the last chunk (their products are never stored)
-            const int cb = (wave * GB + t) * 64 + lane;
-            const int krow = cb >> 5;
-            int ncol = n0 + (((cb & 31) ^ ((krow & 3) << 2)) << 3);
+            const int krow = (wave * 4 + t) * 2 + (lane >> 5);
+            int ncol = n0 + (((lane & 31) ^ ((krow & 3) << 2)) << 3);
             if (ncol > n - 8) ncol = n - 8;
             ob[t] = (uint32_t)(((int64_t)krow * ldb + ncol) * 2);
         } else {
-            const int nn = n0 + (wave * GB + t) * 16 + lrow;
-            ob[t] = (uint32_t)(((int64_t)(nn < n ? nn : n - 1) * ldb + (int64_t)sl_begin * TK + lchunk * 8) * 2);
+            const int r = (wave * 4 + t) * 8 + (lane >> 3), nn = n0 + r < n ? n0 + r : n - 1;
+            ob[t] = (uint32_t)(((int64_t)nn * ldb + ((lane & 7) ^ (r >> 1 & 7)) * 8) * 2);
         }
     }
-    static_assert(!BDIRECT || NW == 8, "the untransposed second operand is wired for 8 waves");
     const uint32_t b_slab_bytes = BDIRECT ? (uint32_t)(TK * ldb * 2) : (uint32_t)(TK * 2);
-    unsigned char* park = smem + (wave * GA) * 1024 + lane * 16;
-    unsigned char* park_b = smem + TM * TROWB + (wave * GB) * 1024 + lane * 16;
+    // (the waves that move the second 32 rows of a slab of W stop a slab earlier where half a slab is left)
+    const int last = nslab - 1, last_b = BDIRECT && wave >= 4 && (ktot & 32) && last > 0 ? last - 1 : last;
+    typedef __attribute__((address_space(3))) unsigned char lds_u8;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)smem, lds_b = lds0 + 2 * TOPB + wave * 4096;
 
     // (fused gather) position ranges and position lists of the rows this wave will store in the
     // epilogue; fetched here so that their latency hides behind the contraction
@@ -690,125 +724,120 @@ __device__ __forceinline__ void gemm_nt_tile(
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-    const int ph0 = (lane >> 5) ^ ((lane >> 2) & 3);
-    const int offA = (wm * (MI * 32) + (lane & 31)) * TROWB;
-    const int offB = (TM + wn * (NT * 32) + (lane & 31)) * TROWB;
-    const int c0 = ph0 * 16, c1 = (ph0 ^ 2) * 16;
-    bf16x8 fa[2][MI], fb[2][NT];
-    v4i32 ra[2][GA], rb[2][GB];
-    // (BDIRECT) addresses of the transposing reads: group g = lane / 16, j = lane % 16 (see the header
-    // comment of k_wgrad_tn_bf16); the wave's columns start at chunk NT 4 wn of the 512-byte row
-    int tr_offB[BDIRECT ? NT : 1];
-    if (BDIRECT) {
-        const int j16 = lane & 15, grp = lane >> 4;
-        const int f_row = (grp >> 1) * 8 + (j16 >> 2);               // + 16 ks + 4 h
-        const int f_x = ((j16 >> 2) & 3) << 2;
+    // fragment addresses: of A per k-step of 16 (+ 32 rows per MFMA tile), of W per MFMA tile (group g = lane / 16,
+    // j = lane % 16, see the header comment of k_wgrad_tn_bf16)
+    bf16x8 fa[MH][4], fb[NT][4];
+    uint32_t ra[4], rb[BDIRECT ? NT : 4];
+    {
+        const int row = wm * (MI * 32) + (lane & 31), x = row >> 1 & 7;
 #pragma unroll
-        for (int i = 0; i < NT; ++i)
-            tr_offB[i] = TM * TROWB + f_row * 512 +
-                         (((wn * (NT * 4) + i * 4 + (grp & 1) * 2 + ((j16 & 3) >> 1)) ^ f_x) * 16) + (j16 & 1) * 8;
+        for (int ks = 0; ks < 4; ++ks) ra[ks] = lds0 + row * TROWB + (((ks * 2 + (lane >> 5)) ^ x) * 16);
+        const int j16 = lane & 15, grp = lane >> 4;
+        const int f_row = (grp >> 1) * 8 + (j16 >> 2), f_x = (j16 >> 2 & 3) << 2;
+        const int brow = wn * 64 + (lane & 31);
+#pragma unroll
+        for (int i = 0; i < (BDIRECT ? NT : 4); ++i)
+            rb[i] = lds0 + 2 * TOPB + (BDIRECT ? f_row * 512 + (((wn * (NT * 4) + i * 4 + (grp & 1) * 2 + ((j16 & 3) >> 1)) ^ f_x) * 16) + (j16 & 1) * 8
+                                               : brow * TROWB + (((i * 2 + (lane >> 5)) ^ (brow >> 1 & 7)) * 16));
     }
-#define GRAM_FRAGS(FS, STAGE, COFF, KS)                                                             \
+    typedef __attribute__((address_space(3))) const bf16x8 lds_frag;
+#define GRAM_LOAD_A(H, SLAB)                                                                        \
     {                                                                                               \
-        const unsigned char* sb_ = smem + (STAGE) * TSTAGEB;                                        \
-        _Pragma("unroll") for (int i = 0; i < MI; ++i)                                              \
-            fa[FS][i] = *reinterpret_cast<const bf16x8*>(sb_ + offA + i * 32 * TROWB + (COFF));     \
-        _Pragma("unroll") for (int i = 0; i < NT; ++i) {                                            \
+        const int s_ = (SLAB) < last ? (SLAB) : last;                                               \
+        const uint32_t to_ = lds0 + ((SLAB) & 1) * TOPB;                                            \
+        _Pragma("unroll") for (int g_ = 0; g_ < MH; ++g_) {                                         \
+            if (WIDE) load_to_lds(pa[H][g_] + (int64_t)s_ * (TK * 2) - (a_upper[H][g_] && s_ * TK + 32 >= ktot ? 64 : 0), to_ + la[H][g_]); \
+            else load_to_lds(rsA, oa[H][g_], (uint32_t)s_ * (TK * 2), to_ + la[H][g_]);             \
+        }                                                                                           \
+    }
+#define GRAM_LOAD_B(SLAB)                                                                           \
+    {                                                                                               \
+        const uint32_t k_ = (uint32_t)((SLAB) < last_b ? (SLAB) : last_b) * b_slab_bytes;           \
+        const uint32_t to_ = lds_b + ((SLAB) & 1) * TOPB;                                           \
+        _Pragma("unroll") for (int g_ = 0; g_ < 4; ++g_)                                            \
+            load_to_lds(rsB, ob[BDIRECT ? g_ & 1 : g_], BDIRECT ? k_ + (uint32_t)(g_ >> 1) * (uint32_t)(8 * ldb) : k_, to_ + g_ * 1024); \
+    }
+#define GRAM_READ_A(H, STAGE)                                                                       \
+    _Pragma("unroll") for (int i = 0; i < MH; ++i)                                                  \
+        _Pragma("unroll") for (int ks = 0; ks < 4; ++ks)                                            \
+            fa[i][ks] = *(lds_frag*)(uintptr_t)(ra[ks] + (STAGE) * TOPB + ((H) * MH + i) * (32 * TROWB));
+#define GRAM_READ_B(STAGE)                                                                          \
+    _Pragma("unroll") for (int j = 0; j < NT; ++j)                                                  \
+        _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) {                                          \
             if (BDIRECT) {                                                                          \
-                const unsigned char* t_ = sb_ + (KS) * 16 * 512 + tr_offB[i];                       \
-                const sv4i16 b0_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_sv4i16*)t_);        \
-                const sv4i16 b1_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_sv4i16*)(t_ + 4 * 512)); \
-                fb[FS][i] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(b0_, b1_, 0, 1, 2, 3, 4, 5, 6, 7)); \
+                const uint32_t at_ = rb[j] + (STAGE) * TOPB + ks * (16 * 512);                      \
+                const sv4i16 lo_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_sv4i16*)(uintptr_t)at_); \
+                const sv4i16 hi_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_sv4i16*)(uintptr_t)(at_ + 4 * 512)); \
+                fb[j][ks] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo_, hi_, 0, 1, 2, 3, 4, 5, 6, 7)); \
             } else {                                                                                \
-                fb[FS][i] = *reinterpret_cast<const bf16x8*>(sb_ + offB + i * 32 * TROWB + (COFF)); \
+                fb[j][ks] = *(lds_frag*)(uintptr_t)(rb[BDIRECT ? 0 : ks] + (STAGE) * TOPB + j * (32 * TROWB)); \
             }                                                                                       \
-        }                                                                                           \
-    }
-#define GRAM_MMA(FS)                                                                                \
-    _Pragma("unroll") for (int i = 0; i < MI; ++i)                                                  \
-        _Pragma("unroll") for (int j = 0; j < NT; ++j)                                              \
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[FS][i], fb[FS][j], acc[i][j], 0, 0, 0);
-    // Slabs past the end are clamped to the last one (their data is never multiplied).
-#define GRAM_LOAD(SET, SLAB)                                                                        \
-    {                                                                                               \
-        const uint32_t k_ = (uint32_t)(((SLAB) < last ? (SLAB) : last) * (TK * 2));                 \
-        const uint32_t kb_ = (uint32_t)((SLAB) < last ? (SLAB) : last) * b_slab_bytes;              \
-        _Pragma("unroll") for (int t = 0; t < GA; ++t) {                                            \
-            if (WIDE) ra[SET][t] = *reinterpret_cast<const v4i32*>(pa[t] + k_);                      \
-            else ra[SET][t] = __builtin_amdgcn_raw_buffer_load_b128(rsA, oa[t] + k_, 0, 0);         \
-        }                                                                                           \
-        _Pragma("unroll") for (int t = 0; t < GB; ++t)                                              \
-            rb[SET][t] = __builtin_amdgcn_raw_buffer_load_b128(rsB, ob[t] + kb_, 0, 0);             \
-    }
-#define GRAM_PARK(SET, STAGE)                                                                       \
-    {                                                                                               \
-        _Pragma("unroll") for (int t = 0; t < GA; ++t)                                              \
-            *reinterpret_cast<v4i32*>(park + (STAGE) * TSTAGEB + t * 1024) = ra[SET][t];            \
-        _Pragma("unroll") for (int t = 0; t < GB; ++t)                                              \
-            *reinterpret_cast<v4i32*>(park_b + (STAGE) * TSTAGEB + t * 1024) = rb[SET][t];          \
-    }
-    // first half of a slab: k-step 0 MFMAs with the k-step 1 fragment reads, then the LDS writes
-    // of the next slab, one or two LDS instructions between MFMAs (a burst of LDS instructions
-    // blocks the wave at issue while the other waves' bursts drain, and the MFMA pipe idles);
-    // second half: k-step 1 MFMAs with the global loads of slab +3 and the fragment reads of the
-    // next slab's k-step 0
-#define GRAM_SCHED_FIRST                                                                            \
-    if (NW == 4) _Pragma("unroll") for (int g = 0; g < 4; ++g) {                                                 \
-        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);                                          \
-        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);                                          \
-    }                                                                                               \
-    if (NW == 4) _Pragma("unroll") for (int g = 0; g < 4; ++g) {                                    \
-        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);                                          \
-        __builtin_amdgcn_sched_group_barrier(0x200, 2, 0);                                          \
-    }
-    // (for the gathered forward the compiler's own order measured 2 % faster, for the streamed
-    // weight gradient the fixed pattern 25 % faster)
-#define GRAM_SCHED_SECOND                                                                           \
-    if (!GATHER && NW == 4) {                                                                       \
-        _Pragma("unroll") for (int g = 0; g < 8; ++g) {                                             \
-            __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);                                      \
-            __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                                      \
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                      \
-        }                                                                                           \
-    }
-#define GRAM_ITER(SL, P)                                                                            \
-    {                                                                                               \
-        GRAM_FRAGS(1, (SL) & 1, c1, 1)                                                              \
-        GRAM_MMA(0)                                                                                 \
-        GRAM_PARK(P, ((SL) + 1) & 1)                                                                \
-        GRAM_SCHED_FIRST                                                                            \
-        __syncthreads();                                                                            \
-        GRAM_LOAD(P, (SL) + 3)                                                                      \
-        GRAM_FRAGS(0, ((SL) + 1) & 1, c0, 0)                                                        \
-        GRAM_MMA(1)                                                                                 \
-        GRAM_SCHED_SECOND                                                                           \
-    }
-
-    if (nslab > 0) {
-        const int last = nslab - 1;
-        GRAM_LOAD(0, 0)
-        GRAM_LOAD(1, 1)
-        GRAM_PARK(0, 0)
-        GRAM_LOAD(0, 2)
-        __syncthreads();
-        GRAM_FRAGS(0, 0, c0, 0)
-        int sl = 0;
-        for (; sl + 1 < last; sl += 2) {
-            GRAM_ITER(sl, 1)          // set 1 holds slab sl+1, set 0 holds slab sl+2
-            GRAM_ITER(sl + 1, 0)      // set 0 holds slab sl+2, set 1 holds slab sl+3
         }
-        if (sl < last) GRAM_ITER(sl, 1)
-        GRAM_FRAGS(1, last & 1, c1, 1)
-        GRAM_MMA(0)
-        GRAM_MMA(1)
+    // (what lies behind K is some other row's, and may be anything: both operands are cleared)
+#define GRAM_CLEAR(F, COUNT)                                                                        \
+    _Pragma("unroll") for (int i = 0; i < (COUNT); ++i)                                             \
+        _Pragma("unroll") for (int ks = 2; ks < 4; ++ks) F[i][ks] = bf16x8{};
+#define GRAM_MMA(H)                                                                                 \
+    __builtin_amdgcn_s_setprio(1);                                                                  \
+    _Pragma("unroll") for (int ks = 0; ks < 4; ++ks)                                                \
+        _Pragma("unroll") for (int i = 0; i < MH; ++i)                                              \
+            _Pragma("unroll") for (int j = 0; j < NT; ++j)                                          \
+                acc[(H) * MH + i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i][ks], fb[j][ks], acc[(H) * MH + i][j], 0, 0, 0); \
+    __builtin_amdgcn_s_setprio(0);
+    // Loads in flight at the end of a reading segment: what its successors wait for was issued before the last
+    // kAhead (a slab's worth).  Slabs past the end reload the last one (never multiplied).
+    constexpr int kAhead = 4 + 2 * MH;
+#define GRAM_SLAB(SL, STAGE)                                                                        \
+    {                                                                                               \
+        GRAM_READ_B(STAGE)                                                                          \
+        GRAM_READ_A(0, STAGE)                                                                       \
+        __builtin_amdgcn_sched_barrier(0);                                                          \
+        GRAM_LOAD_A(1, (SL) + 1)                                                                    \
+        wait_loads<kAhead>();                                                                       \
+        wait_lds();                                                                                 \
+        if ((SL) == half_at) {                                                                      \
+            GRAM_CLEAR(fb, NT)                                                                      \
+            GRAM_CLEAR(fa, MH)                                                                      \
+        }                                                                                           \
+        segment_barrier();                                                                          \
+        GRAM_MMA(0)                                                                                 \
+        segment_barrier();                                                                          \
+        GRAM_READ_A(1, STAGE)                                                                       \
+        __builtin_amdgcn_sched_barrier(0);                                                          \
+        GRAM_LOAD_B((SL) + 2)                                                                       \
+        GRAM_LOAD_A(0, (SL) + 2)                                                                    \
+        wait_loads<kAhead>();                                                                       \
+        wait_lds();                                                                                 \
+        if ((SL) == half_at) { GRAM_CLEAR(fa, MH) }                                                 \
+        segment_barrier();                                                                          \
+        GRAM_MMA(1)                                                                                 \
+        segment_barrier();                                                                          \
     }
+    // slab 0, then B and the first halves of slab 1 (its second halves are requested in slab 0)
+    GRAM_LOAD_B(0)
+    GRAM_LOAD_A(0, 0)
+    GRAM_LOAD_A(1, 0)
+    GRAM_LOAD_B(1)
+    GRAM_LOAD_A(0, 1)
+    wait_loads<kAhead>();
+    segment_barrier();
+    if (wm == 1) segment_barrier();          // the lower row half runs a segment behind
+    const int half_at = ktot & 32 ? last : -1;
+    int sl = 0;
+    for (; sl < last; sl += 2) {
+        GRAM_SLAB(sl, 0)
+        GRAM_SLAB(sl + 1, 1)
+    }
+    if (sl == last) GRAM_SLAB(sl, 0)
+    if (wm == 0) segment_barrier();
+    wait_loads<0>();                         // the stages become the epilogue's (behind its barrier)
 
     // accumulator element r of a lane sits at (row, col) = ((r / 4) * 8 + (lane / 32) * 4 + r % 4, lane % 32)
     // the rows a wave stores are the 32 of MFMA row block i of its wave row: their padding bits
     const int cr0 = (wave / (NW / 2)) * 32 + (wave % (NW / 2)) * RPW;           // first staged row
     uint32_t pads[MI];
 #pragma unroll
-    for (int i = 0; i < MI; ++i) pads[i] = GATHER ? __builtin_amdgcn_readfirstlane(s_pad_rows[(cr0 >> 5) * MI + i]) >> (cr0 & 31) & ((1u << RPW) - 1) : 0u;
+    for (int i = 0; i < MI; ++i) pads[i] = __builtin_amdgcn_readfirstlane(s_pad_rows[(cr0 >> 5) * MI + i]) >> (cr0 & 31) & ((1u << RPW) - 1);
     if (SCATTER) {
         // The stages are dead.  The tile goes through LDS 64 rows at a time (the 32 rows of MFMA
         // row block i of both wave rows), so that a wave can then store whole 1 KiB row pieces,
@@ -874,11 +903,52 @@ __device__ __forceinline__ void gemm_nt_tile(
                 }
             }
         }
+    } else if constexpr (EPI == kEpiReluBf16 || EPI == kEpiGateBf16) {
+        // Straight from the accumulators: neighbouring lanes exchange a value, so that the even one holds two columns of its row
+        // r and the odd one of row r + 1, 4 bytes each, 64 bytes of four rows per store.  What lies behind M or n falls out of
+        // the descriptors.  32,768 x 1024 x 1024 with the rectifier 69 us, 72 through LDS (49,152 rows: 102.5, 106).  The
+        // modes with float32 targets are better off in whole row pieces: subtracting 97 us through LDS, 100 straight.
+        const int rows = M - m0 < TM ? M - m0 : TM, odd = lane & 1;
+        const __amdgpu_buffer_rsrc_t rsC = __builtin_amdgcn_make_buffer_rsrc(
+            reinterpret_cast<uint16_t*>(C) + (int64_t)m0 * ldc, 0, (uint32_t)rows * (uint32_t)ldc * 2u, kBufferFlags);
+        const __amdgpu_buffer_rsrc_t rsX = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<uint16_t*>(static_cast<const uint16_t*>(EPI == kEpiGateBf16 ? aux : C)) + (int64_t)m0 * ldc, 0,
+            (uint32_t)rows * (uint32_t)ldc * 2u, kBufferFlags);
+        uint32_t at[NT];
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            const int col = n0 + wn * 64 + j * 32 + (lane & 31);
+            at[j] = col < n ? ((uint32_t)(wm * (MI * 32) + (lane >> 5) * 4 + odd) * (uint32_t)ldc + (uint32_t)(col - odd)) * 2u : kOutOfRange;
+        }
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+            // register pair r (even): rows i * 32 + (r / 4) * 8 + r % 4 and the next, + 4 (lane / 32)
+            uint32_t av[NT][8];
+            if (EPI == kEpiGateBf16)
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+#pragma unroll
+                    for (int p = 0; p < 8; ++p)
+                        av[j][p] = __builtin_amdgcn_raw_buffer_load_b32(rsX, at[j], (int)((i * 32 + (p >> 1) * 8 + (p & 1) * 2) * (uint32_t)ldc * 2u), 0);
+            const uint32_t pads = s_pad_rows[wm * MI + i] >> ((lane >> 5) * 4);
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int p = 0; p < 8; ++p) {
+                    const int row = (p >> 1) * 8 + (p & 1) * 2;
+                    constexpr int kMode = EPI == kEpiGateBf16 ? kEpiPlain : EPI;
+                    const float lo = epi_value<kMode>(acc[i][j][2 * p], 0.f, pads >> row & 1);
+                    const float hi = epi_value<kMode>(acc[i][j][2 * p + 1], 0.f, pads >> row & 2);
+                    const float got = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(odd ? lo : hi), 0xb1, 0xf, 0xf, false));
+                    uint32_t h = odd ? pack_bf16x2(got, hi) : pack_bf16x2(lo, got);
+                    if (EPI == kEpiGateBf16)        // open where the activation is positive
+                        h &= ((av[j][p] & 0xffffu) - 1u < 0x7fffu ? 0xffffu : 0u) | ((av[j][p] >> 16) - 1u < 0x7fffu ? 0xffff0000u : 0u);
+                    __builtin_amdgcn_raw_buffer_store_b32(h, rsC, at[j], (int)((i * 32 + row) * (uint32_t)ldc * 2u), 0);
+                }
+        }
     } else {
         // Staged like the fused gather's epilogue, 64 rows at a time: a wave then loads and stores whole row
-        // pieces, 4 columns per lane.  32,768 x 1024 x 1024, element by element and staged: with the
-        // rectifier 85 and 81 us, with the gate 101 and 84 us (half of that from storing bf16), subtracting
-        // 107 us and 23 for the sum of squares in a pass of its own against 112 us for both.
+        // pieces, 4 columns per lane.
         const int col = n0 + lane * 4;
         const bool col_ok = col < n;
         double sq = 0.0;
@@ -919,18 +989,17 @@ __device__ __forceinline__ void gemm_nt_tile(
         }
     }
 }
-#undef GRAM_FRAGS
+#undef GRAM_LOAD_A
+#undef GRAM_LOAD_B
+#undef GRAM_READ_A
+#undef GRAM_READ_B
+#undef GRAM_CLEAR
 #undef GRAM_MMA
-#undef GRAM_LOAD
-#undef GRAM_PARK
-#undef GRAM_SCHED_FIRST
-#undef GRAM_SCHED_SECOND
-#undef GRAM_ITER
+#undef GRAM_SLAB
 
 // One tile per block, of 256 rows or (the last ones, see TileCut) of 128.
-template <bool GATHER, int NW, bool SCATTER, int EPI = kEpiPlain, bool HB = false, bool WIDE = false,
-          bool BDIRECT = false>
-__global__ __launch_bounds__(NW * 64) void k_gemm_nt_bf16(
+template <bool SCATTER, int EPI = kEpiPlain, bool HB = false, bool WIDE = false, bool BDIRECT = false>
+__global__ __launch_bounds__(kGemmWaves * 64) void k_gemm_nt_bf16(
     const uint16_t* __restrict__ A, int64_t lda, uint32_t a_bytes, const int* __restrict__ row_ids,
     const int* __restrict__ m_dev, const uint16_t* __restrict__ B, int64_t ldb, uint32_t b_bytes, int n,
     int ktot, const int* __restrict__ zero_ids, int pad_id, int n_tiles, TileCut cut, float* __restrict__ C, int64_t ldc,
@@ -950,14 +1019,12 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_nt_bf16(
         return;
     }
     if (u < full)
-        gemm_nt_tile<4, GATHER, NW, SCATTER, EPI, HB, WIDE, BDIRECT>(A, lda, a_bytes, row_ids, M, B, ldb, b_bytes, n, ktot, zero_ids,
+        gemm_nt_tile<4, SCATTER, EPI, HB, WIDE, BDIRECT>(A, lda, a_bytes, row_ids, M, B, ldb, b_bytes, n, ktot, zero_ids,
                                                                      pad_id, m0, n0, C, ldc, sc, aux, loss_part, smem, s_pad_rows);
     else
-        gemm_nt_tile<2, GATHER, NW, SCATTER, EPI, HB, WIDE, BDIRECT>(A, lda, a_bytes, row_ids, M, B, ldb, b_bytes, n, ktot, zero_ids,
+        gemm_nt_tile<2, SCATTER, EPI, HB, WIDE, BDIRECT>(A, lda, a_bytes, row_ids, M, B, ldb, b_bytes, n, ktot, zero_ids,
                                                                      pad_id, m0, n0, C, ldc, sc, aux, loss_part, smem, s_pad_rows);
 }
-
-constexpr int kGemmWaves = 8;
 
 template <bool SCATTER, int EPI, bool HB, bool WIDE, bool BDIRECT = false>
 static void launch_gemm_variant(Ctx* c, int kid, unsigned blocks, hipStream_t s, const uint16_t* A, int64_t lda,
@@ -965,8 +1032,8 @@ static void launch_gemm_variant(Ctx* c, int kid, unsigned blocks, hipStream_t s,
                                 int64_t ldb, int64_t b_bytes, int n, int k, const int* zero_ids, int pad_id, int n_tiles,
                                 float* C, int64_t ldc, const ScatterArgs& sc, const void* aux, double* loss_part)
 {
-    constexpr auto kern = k_gemm_nt_bf16<true, kGemmWaves, SCATTER, EPI, HB, WIDE, BDIRECT>;
-    constexpr size_t smem = RSMEM_SC > RSMEM ? RSMEM_SC : RSMEM;
+    constexpr auto kern = k_gemm_nt_bf16<SCATTER, EPI, HB, WIDE, BDIRECT>;
+    constexpr size_t smem = TSMEM_SC > TSMEM ? TSMEM_SC : TSMEM;
     ensure_dynamic_lds<kern>((int)smem);
     // the descriptor of a WIDE operand is not used; any size that fits its field will do
     launch_smem(c, kid, kern, dim3(blocks), dim3(kGemmWaves * 64), smem, s, A, lda,
@@ -1119,7 +1186,7 @@ static bool takes_big_kernel(const Ctx* c, int64_t rows_max, int n_out, int k, i
 {
     const int64_t tile_bound = ((rows_max + TM - 1) / TM) * ((n_out + TN - 1) / TN);
     if (epi != kEpiPlain && a_rows * k * 2 >= kBufferWindow) return false;
-    return tile_bound >= c->num_cus && k % TK == 0;
+    return tile_bound >= c->num_cus && k % 32 == 0 && n_out < (1 << 22);     // (32-bit offsets within a tile of C)
 }
 
 // The 256x256 kernel reads the second operand untransposed for these shapes and modes.
@@ -1300,7 +1367,6 @@ constexpr int WROWB = 512;                   // bytes per LDS row (256 bf16)
 constexpr int WOPB = WK * WROWB;             // bytes per operand and stage
 constexpr int WSTAGEB = 2 * WOPB;
 constexpr size_t WSMEM = 2 * (size_t)WSTAGEB;
-constexpr uint32_t kOutOfRange = 0xFFFFFFF0u;
 constexpr int kNonTemporal = 2;              // cache policy bits of a buffer store (nt)
 constexpr int kWgradWaves = 8;
 
@@ -1911,7 +1977,7 @@ bool encoder_wgrad(Ctx* c, const void* X, float* dW, hipStream_t s, int64_t firs
         // (from the host's bound on the rows in the buffer), still a multiple of 8
         int64_t rows_bound = (other || c->dense) ? cap : (c->window_positions < cap ? c->window_positions : cap);
         if (rows_bound > row_end - row_begin) rows_bound = row_end - row_begin;
-        const int64_t slabs_bound = rows_bound / TK + 1;
+        const int64_t slabs_bound = rows_bound / WK + 1;
         int64_t want = slabs_bound / 8 / 8 * 8;
         if (want < 8) want = 8;
         if (want < S) S = (int)want;
