@@ -529,7 +529,7 @@ __global__ __launch_bounds__(MidShape<WIDE>::kThreads, 4) void k_encode_mid(
 // Operands are addressed through buffer descriptors (base + 32-bit byte offset); a matrix A beyond the 4 GiB such
 // a descriptor can address takes the WIDE variant, whose lanes keep 64-bit row pointers (every address it
 // forms is a valid one: rows past the end are clamped).  K is a multiple of 32; where half a slab is left, the
-// fragments of the other half are cleared.
+// other half of its stage holds whatever was loaded and is not multiplied.
 constexpr int TM = 256, TN = 256, TK = 64;
 constexpr int kGemmWaves = 8;
 constexpr int TROWB = TK * 2;                          // bytes per LDS row of a K-contiguous operand
@@ -654,22 +654,27 @@ __device__ __forceinline__ void gemm_nt_tile(
     const u32x4 rsA = buffer_words(A, a_bytes), rsB = buffer_words(B, b_bytes);
     uint32_t oa[2][MH], la[2][MH];
     const unsigned char* pa[2][WIDE ? MH : 1];
+    bool a_upper[2][WIDE ? MH : 1];          // the lane's chunk lies in the upper half of the slab
     const int a_chunk = (lane & 7) ^ (lane >> 4 & 3);     // of the rows with (row >> 1 & 4) == 0; the others: ^ 4
-    bool a_upper[2][WIDE ? MH : 1];
+    int ids[2][MH], zids[2][MH];             // (the two-layer encoder's second contraction tells the padding item by another list than its rows)
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
         for (int t = 0; t < MH; ++t) {
             const int g = wave * MH + t, r0 = g / (2 * MI) * (32 * MI) + h * (16 * MI) + g % (2 * MI) * 8;
-            const int r = r0 + (lane >> 3), j = m0 + r < M ? m0 + r : M - 1, id = row_ids[j];
-            // (the two-layer encoder's second contraction tells the padding item by another list than its rows; a
-            // batch listed by the caller may hold it any number of times)
-            if (m0 + r < M && (zero_ids != row_ids ? zero_ids[j] : id) == pad_id) atomicOr(&s_pad_rows[r >> 5], 1u << (r & 31));
-            const int chunk = a_chunk ^ (r0 >> 1 & 4);
-            oa[h][t] = (uint32_t)(((int64_t)id * lda + chunk * 8) * 2);
+            const int r = m0 + r0 + (lane >> 3);
             la[h][t] = r0 * TROWB;
+            ids[h][t] = row_ids[r < M ? r : M - 1];
+            zids[h][t] = zero_ids[r < M ? r : M - 1];
+        }
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int t = 0; t < MH; ++t) {
+            const int chunk = a_chunk ^ ((wave * MH + t) & 1) * 4;
+            oa[h][t] = (uint32_t)(((int64_t)ids[h][t] * lda + chunk * 8) * 2);
             if (WIDE) {
-                pa[h][t] = reinterpret_cast<const unsigned char*>(A) + ((int64_t)id * lda + chunk * 8) * 2;
+                pa[h][t] = reinterpret_cast<const unsigned char*>(A) + ((int64_t)ids[h][t] * lda + chunk * 8) * 2;
                 a_upper[h][t] = chunk >= 4;
             }
         }
@@ -745,17 +750,22 @@ __device__ __forceinline__ void gemm_nt_tile(
     {                                                                                               \
         const int s_ = (SLAB) < last ? (SLAB) : last;                                               \
         const uint32_t to_ = lds0 + ((SLAB) & 1) * TOPB;                                            \
+        u32x4 rs_ = rsA;                                                                            \
+        rs_.z = (SLAB) <= last ? rs_.z : 0u;                                                        \
+        const uint32_t so_ = (SLAB) <= last ? (uint32_t)s_ * (TK * 2) : 0u;                         \
         _Pragma("unroll") for (int g_ = 0; g_ < MH; ++g_) {                                         \
             if (WIDE) load_to_lds(pa[H][g_] + (int64_t)s_ * (TK * 2) - (a_upper[H][g_] && s_ * TK + 32 >= ktot ? 64 : 0), to_ + la[H][g_]); \
-            else load_to_lds(rsA, oa[H][g_], (uint32_t)s_ * (TK * 2), to_ + la[H][g_]);             \
+            else load_to_lds(rs_, oa[H][g_], so_, to_ + la[H][g_]);                                 \
         }                                                                                           \
     }
 #define GRAM_LOAD_B(SLAB)                                                                           \
     {                                                                                               \
+        u32x4 rs_ = rsB;                                                                            \
+        rs_.z = (SLAB) <= last ? rs_.z : 0u;                                                        \
         const uint32_t k_ = (uint32_t)((SLAB) < last_b ? (SLAB) : last_b) * b_slab_bytes;           \
         const uint32_t to_ = lds_b + ((SLAB) & 1) * TOPB;                                           \
         _Pragma("unroll") for (int g_ = 0; g_ < 4; ++g_)                                            \
-            load_to_lds(rsB, ob[BDIRECT ? g_ & 1 : g_], BDIRECT ? k_ + (uint32_t)(g_ >> 1) * (uint32_t)(8 * ldb) : k_, to_ + g_ * 1024); \
+            load_to_lds(rs_, ob[BDIRECT ? g_ & 1 : g_], (SLAB) <= last ? (BDIRECT ? k_ + (uint32_t)(g_ >> 1) * (uint32_t)(8 * ldb) : k_) : 0u, to_ + g_ * 1024); \
     }
 #define GRAM_READ_A(H, STAGE)                                                                       \
     _Pragma("unroll") for (int i = 0; i < MH; ++i)                                                  \
@@ -773,16 +783,16 @@ __device__ __forceinline__ void gemm_nt_tile(
                 fb[j][ks] = *(lds_frag*)(uintptr_t)(rb[BDIRECT ? 0 : ks] + (STAGE) * TOPB + j * (32 * TROWB)); \
             }                                                                                       \
         }
-    // (what lies behind K is some other row's, and may be anything: both operands are cleared)
-#define GRAM_CLEAR(F, COUNT)                                                                        \
-    _Pragma("unroll") for (int i = 0; i < (COUNT); ++i)                                             \
-        _Pragma("unroll") for (int ks = 2; ks < 4; ++ks) F[i][ks] = bf16x8{};
-#define GRAM_MMA(H)                                                                                 \
-    __builtin_amdgcn_s_setprio(1);                                                                  \
-    _Pragma("unroll") for (int ks = 0; ks < 4; ++ks)                                                \
+    // (of a last half slab, what lies behind K is some other row's and may be anything: it is not multiplied)
+#define GRAM_MMA_STEPS(H, FROM)                                                                     \
+    _Pragma("unroll") for (int ks = (FROM); ks < (FROM) + 2; ++ks)                                  \
         _Pragma("unroll") for (int i = 0; i < MH; ++i)                                              \
             _Pragma("unroll") for (int j = 0; j < NT; ++j)                                          \
-                acc[(H) * MH + i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i][ks], fb[j][ks], acc[(H) * MH + i][j], 0, 0, 0); \
+                acc[(H) * MH + i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i][ks], fb[j][ks], acc[(H) * MH + i][j], 0, 0, 0);
+#define GRAM_MMA(H, SL)                                                                             \
+    __builtin_amdgcn_s_setprio(1);                                                                  \
+    GRAM_MMA_STEPS(H, 0)                                                                            \
+    if ((SL) != half_at) { GRAM_MMA_STEPS(H, 2) }                                                   \
     __builtin_amdgcn_s_setprio(0);
     // Loads in flight at the end of a reading segment: what its successors wait for was issued before the last
     // kAhead (a slab's worth).  Slabs past the end reload the last one (never multiplied).
@@ -795,12 +805,8 @@ __device__ __forceinline__ void gemm_nt_tile(
         GRAM_LOAD_A(1, (SL) + 1)                                                                    \
         wait_loads<kAhead>();                                                                       \
         wait_lds();                                                                                 \
-        if ((SL) == half_at) {                                                                      \
-            GRAM_CLEAR(fb, NT)                                                                      \
-            GRAM_CLEAR(fa, MH)                                                                      \
-        }                                                                                           \
         segment_barrier();                                                                          \
-        GRAM_MMA(0)                                                                                 \
+        GRAM_MMA(0, SL)                                                                             \
         segment_barrier();                                                                          \
         GRAM_READ_A(1, STAGE)                                                                       \
         __builtin_amdgcn_sched_barrier(0);                                                          \
@@ -808,10 +814,17 @@ __device__ __forceinline__ void gemm_nt_tile(
         GRAM_LOAD_A(0, (SL) + 2)                                                                    \
         wait_loads<kAhead>();                                                                       \
         wait_lds();                                                                                 \
-        if ((SL) == half_at) { GRAM_CLEAR(fa, MH) }                                                 \
+        if (epi_subtracts(EPI) && (SL) == last) { GRAM_AUX(0) }                                     \
         segment_barrier();                                                                          \
-        GRAM_MMA(1)                                                                                 \
+        GRAM_MMA(1, SL)                                                                             \
         segment_barrier();                                                                          \
+    }
+    // (subtracting) the targets of the epilogue's first round are requested ahead of the last products
+    f32x4_ av[epi_subtracts(EPI) ? RPW : 1];
+#define GRAM_AUX(I)                                                                                 \
+    _Pragma("unroll") for (int u = 0; u < (epi_subtracts(EPI) ? RPW : 0); ++u) {                    \
+        const int row_ = m0 + (wave >> 2) * (MI * 32) + (I) * 32 + (wave & 3) * RPW + u, col_ = n0 + lane * 4; \
+        av[u] = epi_load4<EPI>(aux, (int64_t)(row_ < M ? row_ : M - 1) * ldc + (col_ < n ? col_ : 0)); \
     }
     // slab 0, then B and the first halves of slab 1 (its second halves are requested in slab 0)
     GRAM_LOAD_B(0)
@@ -819,6 +832,14 @@ __device__ __forceinline__ void gemm_nt_tile(
     GRAM_LOAD_A(1, 0)
     GRAM_LOAD_B(1)
     GRAM_LOAD_A(0, 1)
+    // (a batch listed by the caller may hold the padding item any number of times)
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int t = 0; t < MH; ++t) {
+            const int r = la[h][t] / TROWB + (lane >> 3);
+            if (m0 + r < M && (lane & 7) == 0 && zids[h][t] == pad_id) atomicOr(&s_pad_rows[r >> 5], 1u << (r & 31));
+        }
     wait_loads<kAhead>();
     segment_barrier();
     if (wm == 1) segment_barrier();          // the lower row half runs a segment behind
@@ -830,7 +851,7 @@ __device__ __forceinline__ void gemm_nt_tile(
     }
     if (sl == last) GRAM_SLAB(sl, 0)
     if (wm == 0) segment_barrier();
-    wait_loads<0>();                         // the stages become the epilogue's (behind its barrier)
+    wait_loads<epi_subtracts(EPI) ? RPW : 0>();      // the stages become the epilogue's (behind its barrier)
 
     // accumulator element r of a lane sits at (row, col) = ((r / 4) * 8 + (lane / 32) * 4 + r % 4, lane % 32)
     // the rows a wave stores are the 32 of MFMA row block i of its wave row: their padding bits
@@ -946,6 +967,27 @@ __device__ __forceinline__ void gemm_nt_tile(
                     __builtin_amdgcn_raw_buffer_store_b32(h, rsC, at[j], (int)((i * 32 + row) * (uint32_t)ldc * 2u), 0);
                 }
         }
+    } else if constexpr (EPI == kEpiPlain) {
+        // Straight from the accumulators as well, 128 bytes of two rows per store: 33,000 x 64 x 512 19.6 us, 20.4 through LDS.
+        const int rows = M - m0 < TM ? M - m0 : TM;
+        const __amdgpu_buffer_rsrc_t rsC = __builtin_amdgcn_make_buffer_rsrc(C + (int64_t)m0 * ldc, 0, (uint32_t)rows * (uint32_t)ldc * 4u, kBufferFlags);
+        uint32_t at[NT];
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            const int col = n0 + wn * 64 + j * 32 + (lane & 31);
+            at[j] = col < n ? ((uint32_t)(wm * (MI * 32) + (lane >> 5) * 4) * (uint32_t)ldc + (uint32_t)col) * 4u : kOutOfRange;
+        }
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+            const uint32_t pads = s_pad_rows[wm * MI + i] >> ((lane >> 5) * 4);
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) {
+                    const int row = (r >> 2) * 8 + (r & 3);
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(pads >> row & 1 ? 0.f : acc[i][j][r]), rsC, at[j], (int)((i * 32 + row) * (uint32_t)ldc * 4u), 0);
+                }
+        }
     } else {
         // Staged like the fused gather's epilogue, 64 rows at a time: a wave then loads and stores whole row
         // pieces, 4 columns per lane.
@@ -956,10 +998,7 @@ __device__ __forceinline__ void gemm_nt_tile(
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
             const int row0 = m0 + (cr0 >> 5) * (MI * 32) + i * 32 + (cr0 & 31);           // + u
-            f32x4_ av[RPW];
-#pragma unroll
-            for (int u = 0; u < RPW; ++u)
-                av[u] = epi_load4<EPI>(aux, (int64_t)(row0 + u < M ? row0 + u : M - 1) * ldc + (col_ok ? col : 0));
+            if (i > 0) { GRAM_AUX(i) }
             unsigned char* stage = smem + (i & 1) * kScatterTileB;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
@@ -993,9 +1032,10 @@ __device__ __forceinline__ void gemm_nt_tile(
 #undef GRAM_LOAD_B
 #undef GRAM_READ_A
 #undef GRAM_READ_B
-#undef GRAM_CLEAR
+#undef GRAM_MMA_STEPS
 #undef GRAM_MMA
 #undef GRAM_SLAB
+#undef GRAM_AUX
 
 // One tile per block, of 256 rows or (the last ones, see TileCut) of 128.
 template <bool SCATTER, int EPI = kEpiPlain, bool HB = false, bool WIDE = false, bool BDIRECT = false>
