@@ -357,7 +357,8 @@ int gram_unique(gram_ctx* ctx, const int32_t* ids, int64_t m, int32_t* uniq, int
         // slot-table contexts: the dedup kernels also work out the buffer rows of the items
         const bool prospect = !c->dense;
         const int first_step = (c->steps_done == 0 && !c->window_imported) ? 1 : 0;
-        if (!unique_by_count(c, ids, (int)m, fix, uniq, inverse, counts, u_dev, s, prospect, first_step) &&
+        if (!unique_once(c, ids, (int)m, fix, uniq, inverse, counts, u_dev, s, prospect, first_step) &&
+            !unique_by_count(c, ids, (int)m, fix, uniq, inverse, counts, u_dev, s, prospect, first_step) &&
             !unique_small(c, ids, (int)m, fix, uniq, inverse, counts, u_dev, s, prospect, first_step)) {
             const int r = radix_sort_pairs(c, ids, nullptr, (int)m, nullptr, m, true, fix, s);
             c->sorted_keys = c->keys[r];
@@ -677,7 +678,7 @@ static const char* const kKernelNames[KID_COUNT] = {
     "seg_combine", "wgrad_bf16", "wgrad_f32", "wgrad_reduce", "flush_meta",
     "flush_rows", "unique_small", "gather_heavy", "pseudo_target", "pseudo_loss", "chunk_ids",
     "pseudo_miss", "mlp_to_bf16", "encode_bf16_wide", "wgrad_bf16_wide", "rank_small",
-    "ids_count", "ids_scan", "ids_emit"};
+    "ids_count", "ids_scan", "ids_emit", "ids_once"};
 
 int gram_kernel_count(void) { return KID_COUNT; }
 
@@ -762,21 +763,22 @@ int gram_unique_static(const int32_t* ids, int64_t m, int32_t vocab_n, int32_t p
     c.seg_of_row = reinterpret_cast<int*>(base + kStaticOffSegOfRow);
     c.uniq_ws = reinterpret_cast<int*>(base + kStaticOffUniqWs);
 
-    // the array keeps the last call's contents: the error bits must start at zero.  The dedup by comparison writes
-    // them itself; before the others a fill kernel does (so that the call can be captured in a HIP graph).  Everything
-    // else is written before it is read
-    c.fresh_err = m > 0 && m <= kSmallMaxN;
-    if (!c.fresh_err) fill_i32(c.scal, 64, 0, s);
-    if (m > 0) {
-        const int fix = pad_id >= 0 ? pad_id : 0;
-        if (!unique_small(&c, ids, (int)m, fix, uniq, inverse, counts, u_dev, s)) {
+    // the array keeps the last call's contents: the error bits must start at zero.  The dedup in one launch and the one by
+    // comparison write them themselves; before the others a fill kernel does (so that the call can be captured in a HIP
+    // graph).  Everything else is written before it is read
+    const int fix = pad_id >= 0 ? pad_id : 0;
+    c.fresh_err = true;
+    if (!unique_once(&c, ids, (int)m, fix, uniq, inverse, counts, u_dev, s)) {
+        c.fresh_err = m > 0 && m <= kSmallMaxN;
+        if (!c.fresh_err) fill_i32(c.scal, 64, 0, s);
+        if (m == 0) {
+            unique_from_sorted(&c, 0, uniq, inverse, counts, u_dev, s);
+        } else if (!unique_small(&c, ids, (int)m, fix, uniq, inverse, counts, u_dev, s)) {
             const int r = radix_sort_pairs(&c, ids, nullptr, (int)m, nullptr, m, true, fix, s);
             c.sorted_keys = c.keys[r];
             c.perm = c.vals[r];
             unique_from_sorted(&c, (int)m, uniq, inverse, counts, u_dev, s);
         }
-    } else {
-        unique_from_sorted(&c, 0, uniq, inverse, counts, u_dev, s);
     }
     if (err_dev) hipLaunchKernelGGL(k_copy_scalar, dim3(1), dim3(kWave), 0, s, c.scal + kSErr, err_dev);
     hipError_t e = hipGetLastError();

@@ -124,7 +124,7 @@ enum KernelId {
     KID_WGRAD_REDUCE, KID_FLUSH_META, KID_FLUSH_ROWS, KID_UNIQUE_SMALL,
     KID_GATHER_HEAVY, KID_PSEUDO_TARGET, KID_PSEUDO_LOSS, KID_CHUNK_IDS, KID_PSEUDO_MISS, KID_MLP_TO_BF16,
     KID_ENCODE_BF16_WIDE, KID_WGRAD_BF16_WIDE, KID_RANK_SMALL,
-    KID_IDS_COUNT, KID_IDS_SCAN, KID_IDS_EMIT, KID_COUNT
+    KID_IDS_COUNT, KID_IDS_SCAN, KID_IDS_EMIT, KID_IDS_ONCE, KID_COUNT
 };
 
 static_assert(KID_COUNT <= 64, "the profiling mask has 64 bits");
@@ -271,6 +271,9 @@ void unique_from_sorted(Ctx* c, int n, int* uniq, int* inverse, int* counts, int
 bool unique_small(Ctx* c, const int* ids, int n, int fix_key, int* uniq, int* inverse, int* counts,
                   int* u_out, hipStream_t s, bool prospect = false, int first_step = 0);
 
+// One-launch dedup of small and mid-sized batches; returns false if it does not apply (sizes, or an output that overlaps the IDs).
+bool unique_once(Ctx* c, const int* ids, int n, int fix_key, int* uniq, int* inverse, int* counts, int* u_out,
+                 hipStream_t s, bool prospect = false, int first_step = 0);
 // Three-launch dedup for mid-sized batches over small vocabularies; returns false if it does not apply.
 bool unique_by_count(Ctx* c, const int* ids, int n, int fix_key, int* uniq, int* inverse, int* counts,
                      int* u_out, hipStream_t s, bool prospect = false, int first_step = 0);

@@ -770,6 +770,390 @@ __global__ __launch_bounds__(kSmallThreads) void k_emit_small(
     if (blockIdx.x == 0 && tid == 0) scal[kSUNext] = nt < cap_total ? nt : cap_total;
 }
 
+// ---- small and mid-sized batches: one launch -----------------------------------------------
+//
+// The two launches of the comparison ranks and the three of the counting dedup below are short ones, each a chain of
+// a few round trips.  Up to kOnceMaxM positions one launch does it all, because every block can afford to read all IDs
+// (held in registers): it counts them by key in LDS, those of the positions before its own slice first, then its slice
+// (whose positions' places among their ID's positions are thereby known), then the rest.  A scan over the keys gives
+// every key its first row and its number among the items; each thread of the slice writes what is known of its position
+// and, if it is its ID's first, of the item.  Nothing passes between blocks.
+//   BITS = false: the key is the ID (16-bit counts of all IDs in LDS: up to about 56,000).
+//   BITS = true:  a bitmap of the IDs that occur is made first and the key is the ID's number among them: any
+//                 vocabulary whose bitmap and its prefix fit (0.19 bytes per ID: 524,288), up to kOnceBitsM positions.
+// What bounds it is the LDS atomic per ID, about 30 to 45 cycles per wave (lanes of a wave that meet on a bank): nothing at
+// 6,400 positions, most of the time at 50,000.  Whole call, ranks or counting dedup / one launch: 1,000 positions 8.1 / 6.3 us,
+// 6,400 over 13,000 IDs 13.3 / 6.6, 7,040 over 100,000 14.0 / 9.8, 12,000 over 300,000 26.7 / 12.9, 16,000 over 20,000
+// 12.3 / 10.6, 25,600 12.7 / 14.1 (padded histories 12.9 / 10.8), 51,200 13.8 / 23.3: the line lies at 16,384.
+// The outputs must not overlap the IDs (other blocks still read those): such calls take the ways below.
+constexpr int kOnceThreads = 1024, kOnceWaves = kOnceThreads / kWave;
+constexpr int kOnceMaxM = 16384, kOnceBitsM = 12288;
+constexpr int kOnceSlice = 256;              // positions per block, at most
+constexpr int kOnceRounds = 8;               // groups of 8 keys per thread, at most
+constexpr size_t kOnceLds = 156 * 1024;      // dynamic; beside it 3 KiB
+
+struct OnceLayout {              // byte offsets of the arrays in LDS; groups of 8 keys, words of the bitmap
+    int groups, words, dummy, base, base_f, mask, bits, bits_pre;
+    size_t bytes;
+    __host__ __device__ OnceLayout(bool by_bits, bool slots, int n, int vocab_n)
+    {
+        groups = ((by_bits ? n : vocab_n) + 7) / 8;
+        words = by_bits ? (int)((vocab_n + 127ll) / 128 * 4) : 0;
+        dummy = groups * 16;                                 // [64] words that count padding, one per lane
+        base = dummy + kWave * 4;                            // [groups] first row | items before << 16
+        base_f = base + groups * 4;                          // [groups] new items before
+        mask = base_f + (slots ? (groups * 2 + 3) / 4 * 4 : 0);      // [groups] a bit per key: a new item
+        bits = (mask + (slots ? groups : 0) + 15) / 16 * 16;
+        bits_pre = bits + words * 4;                         // [words] items before
+        bytes = (size_t)bits_pre + (size_t)words * 2;
+    }
+};
+
+// Exclusive scan over rounds of one value per thread (round r before round r + 1, threads in order): v[r] becomes the sum
+// ahead of it; returns the total.  sm: [kOnceRounds * kOnceWaves].  Contains barriers.
+template <int ROUNDS>
+__device__ __forceinline__ uint32_t once_scan(uint32_t (&v)[ROUNDS], uint32_t* sm)
+{
+    static_assert(ROUNDS * kOnceWaves <= 2 * kWave, "two values per lane");
+    const int lane = lane_id(), wave = wave_id();
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const uint32_t incl = (uint32_t)wave_incl_scan((int)v[r]);
+        if (lane == kWave - 1) sm[r * kOnceWaves + wave] = incl;
+        v[r] = incl - v[r];
+    }
+    __syncthreads();
+    const int a = lane < ROUNDS * kOnceWaves ? (int)sm[lane] : 0;
+    const int b = lane + kWave < ROUNDS * kOnceWaves ? (int)sm[lane + kWave] : 0;
+    const int ia = wave_incl_scan(a), ta = __builtin_amdgcn_readlane(ia, kWave - 1), ib = wave_incl_scan(b) + ta;
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const int at = __builtin_amdgcn_readfirstlane(r * kOnceWaves + wave);
+        v[r] += (uint32_t)(at == 0 ? 0 : at <= kWave ? __builtin_amdgcn_readlane(ia, at - 1) : __builtin_amdgcn_readlane(ib, at - 1 - kWave));
+    }
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane(ib, kWave - 1);
+    __syncthreads();
+    return total;
+}
+
+// R: groups of 4 positions per thread.  SLOTS: the buffer may hold items already (slot_of is looked at; else, where it is
+// given, item j gets row j).  fresh_err: the error word is written, not added to.
+template <int R, bool BITS, bool SLOTS>
+__global__ __launch_bounds__(kOnceThreads) void k_ids_once(
+    const int* __restrict__ ids, int n, int slice, int key_bits, int vocab_n, int fix_key, int fresh_err, int* __restrict__ perm, int* __restrict__ uniq,
+    int* __restrict__ inverse, int* __restrict__ counts, int* __restrict__ offsets, int* __restrict__ seg_of_row,
+    int* __restrict__ uniq_ws, int* __restrict__ u_out, const int* __restrict__ slot_of, int* __restrict__ seg_slot,
+    int* __restrict__ scal, int cap_total, int pad_id)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char once_lds[];
+    __shared__ __attribute__((aligned(16))) int own[kOnceSlice];
+    __shared__ uint32_t sm[kOnceRounds * kOnceWaves];
+    typedef int v4a __attribute__((ext_vector_type(4), aligned(4)));
+    const OnceLayout lo(BITS, SLOTS, n, vocab_n);
+    uint32_t* cnt = reinterpret_cast<uint32_t*>(once_lds);
+    uint32_t* base = reinterpret_cast<uint32_t*>(once_lds + lo.base);
+    uint16_t* base_f = reinterpret_cast<uint16_t*>(once_lds + lo.base_f);
+    unsigned char* mask = once_lds + lo.mask;
+    uint32_t* bits = reinterpret_cast<uint32_t*>(once_lds + lo.bits);
+    uint16_t* bits_pre = reinterpret_cast<uint16_t*>(once_lds + lo.bits_pre);
+    const int tid = threadIdx.x, lane = lane_id();
+    const int p_lo = blockIdx.x * slice, p_hi = p_lo + slice < n ? p_lo + slice : n;      // slice: a multiple of 4
+    const int g_lo = p_lo >> 2, g_hi = (p_hi + 3) >> 2;
+
+    // the IDs, checked: thread t holds groups t, t + 1024, ... of 4 positions
+    int k[R][4];
+    bool bad = false;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int p = (tid + r * kOnceThreads) * 4;
+        if (p + 3 < n) {
+            const v4a q = *reinterpret_cast<const v4a*>(ids + p);
+            k[r][0] = q.x; k[r][1] = q.y; k[r][2] = q.z; k[r][3] = q.w;
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) k[r][c] = p + c < n ? ids[p + c] : 0;      // (checked, then marked: -1)
+        }
+    }
+    const int u_base = SLOTS ? scal[kSUTotal] : 0;
+    for (int i = tid; i < lo.base / 16; i += kOnceThreads) reinterpret_cast<uint4*>(cnt)[i] = make_uint4(0, 0, 0, 0);
+    if (BITS) {
+        for (int i = tid; i < lo.words / 4; i += kOnceThreads) reinterpret_cast<uint4*>(bits)[i] = make_uint4(0, 0, 0, 0);
+        if (SLOTS)
+            for (int i = tid; i < (lo.groups + 3) / 4; i += kOnceThreads) reinterpret_cast<uint32_t*>(mask)[i] = 0;
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            if ((unsigned)k[r][c] >= (unsigned)vocab_n) {
+                k[r][c] = fix_key;
+                bad = true;
+            }
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if ((tid + r * kOnceThreads) * 4 + 3 >= n)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if ((tid + r * kOnceThreads) * 4 + c >= n) k[r][c] = -1;       // (no position)
+    if (blockIdx.x == 0) {              // (it has seen all of them)
+        if (fresh_err) {
+            const int any = __syncthreads_or(bad);
+            if (tid == 0) scal[kSErr] = any ? kErrBitRange : 0;
+        } else if (bad) {
+            atomicOr(&scal[kSErr], kErrBitRange);
+        }
+    }
+    if (!BITS && SLOTS) {
+        // which of a group's 8 IDs have no row in the buffer
+        for (int g = tid; g < lo.groups; g += kOnceThreads) {
+            uint32_t m = 0;
+            if (8 * g + 7 < vocab_n) {
+                const int4 a = *reinterpret_cast<const int4*>(slot_of + 8 * g), b = *reinterpret_cast<const int4*>(slot_of + 8 * g + 4);
+                m = (uint32_t)a.x >> 31 | (uint32_t)a.y >> 31 << 1 | (uint32_t)a.z >> 31 << 2 | (uint32_t)a.w >> 31 << 3 |
+                    (uint32_t)b.x >> 31 << 4 | (uint32_t)b.y >> 31 << 5 | (uint32_t)b.z >> 31 << 6 | (uint32_t)b.w >> 31 << 7;
+            } else {
+                for (int i = 0; i < 8; ++i)
+                    if (8 * g + i < vocab_n && slot_of[8 * g + i] < 0) m |= 1u << i;
+            }
+            mask[g] = (unsigned char)m;
+        }
+    }
+    // the slice's IDs (tid < p_hi - p_lo: one position per thread)
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int g = tid + r * kOnceThreads;
+        if (g >= g_lo && g < g_hi) *reinterpret_cast<int4*>(own + 4 * (g - g_lo)) = make_int4(k[r][0], k[r][1], k[r][2], k[r][3]);
+    }
+    __syncthreads();
+    const int p = p_lo + tid;
+    const bool mine = p < p_hi;
+    int id = mine ? own[tid] : 0, key = id, pad_key = pad_id;
+    if (BITS) {
+        // the bitmap, the number of IDs before each of its words, and every ID's number
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int v = k[r][c], first = __builtin_amdgcn_readfirstlane(v);
+                const unsigned long long pads = __ballot(v == pad_id);
+                const bool same = __ballot(v == first) == ~0ull;
+                if (v >= 0 && (v == pad_id ? lane == __builtin_ctzll(pads) : !same || lane == 0)) atomicOr(&bits[v >> 5], 1u << (v & 31));
+            }
+        __syncthreads();
+        constexpr int kWordRounds = 4;
+        uint32_t pre[kWordRounds];
+#pragma unroll
+        for (int r = 0; r < kWordRounds; ++r) {
+            const int w = tid + r * kOnceThreads;
+            uint4 q = make_uint4(0, 0, 0, 0);
+            if (w < lo.words / 4) q = reinterpret_cast<const uint4*>(bits)[w];
+            pre[r] = __popc(q.x) + __popc(q.y) + __popc(q.z) + __popc(q.w);
+        }
+        once_scan(pre, sm);
+#pragma unroll
+        for (int r = 0; r < kWordRounds; ++r) {
+            const int w = tid + r * kOnceThreads;
+            if (w < lo.words / 4) {
+                const uint4 q = reinterpret_cast<const uint4*>(bits)[w];
+                const uint32_t b1 = pre[r] + __popc(q.x), b2 = b1 + __popc(q.y), b3 = b2 + __popc(q.z);
+                reinterpret_cast<uint2*>(bits_pre)[w] = make_uint2(pre[r] | b1 << 16, b2 | b3 << 16);
+            }
+        }
+        __syncthreads();
+        auto number = [&](int v) { return (int)(bits_pre[v >> 5] + __popc(bits[v >> 5] & ((1u << (v & 31)) - 1u))); };
+        if (pad_id >= 0) pad_key = bits[pad_id >> 5] >> (pad_id & 31) & 1 ? number(pad_id) : -1;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int v = k[r][c];
+                if (v < 0) continue;
+                k[r][c] = number(v);
+                if (SLOTS && slot_of[v] < 0) atomicOr(reinterpret_cast<uint32_t*>(mask) + (k[r][c] >> 5), 1u << (k[r][c] & 31));
+            }
+        key = number(id);
+    }
+
+    // Padding, and what is no position, goes to a counter per lane: on one word its many positions would wait for each other.
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            if (k[r][c] == pad_key || k[r][c] < 0) k[r][c] = lo.groups * 8 + lane * 2;
+    auto count_groups = [&](int from, int to) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int g = tid + r * kOnceThreads;
+            if (g >= from && g < to)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) atomicAdd(&cnt[k[r][c] >> 1], 1u << ((uint32_t)k[r][c] << 4 & 31u));
+        }
+    };
+    count_groups(0, g_lo);
+    __syncthreads();
+    // The slice: lanes of a wave with the same key find each other by ballots, the waves take turns at the counters in
+    // position order.
+    typedef __attribute__((address_space(3))) uint16_t lds_u16;
+    volatile lds_u16* cnt16 = (volatile lds_u16*)(lds_u16*)once_lds;
+    unsigned long long peers = __ballot(mine);
+    int at = 0;
+    if (tid < kOnceSlice)
+        for (int bit = 0; bit < key_bits; ++bit) {
+            const bool one = (key >> bit) & 1;
+            const unsigned long long mm = __ballot(one);
+            peers &= one ? mm : ~mm;
+        }
+    const int below = __popcll(peers & ((1ull << lane) - 1ull));
+    const int pads_ahead = wave_sum((int)cnt[lo.dummy / 4 + lane]);
+    if (tid == 0 && pad_key >= 0 && pads_ahead) cnt16[pad_key] = (uint16_t)pads_ahead;
+    for (int w = 0; w * kWave < slice; ++w) {
+        if (w == wave_id() && mine) {
+            at = cnt16[key];
+            __builtin_amdgcn_wave_barrier();
+            if (below == 0) cnt16[key] = (uint16_t)(at + (int)__popcll(peers));
+        }
+        __syncthreads();
+    }
+    at += below;
+    count_groups(g_hi, (n + 3) >> 2);
+    __syncthreads();
+    const int pads_behind = wave_sum((int)cnt[lo.dummy / 4 + lane]) - pads_ahead - (g_hi << 2 < n ? -n & 3 : 0);
+
+    // first row, number among the items and among the new items of every group of 8 keys
+    constexpr int kRounds = BITS ? 2 : kOnceRounds;
+    auto occurring = [](uint4 q) {          // a bit per key of the group that occurs
+        const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+        uint32_t m = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) m |= (w[i] & 0xffffu ? 1u << (2 * i) : 0u) | (w[i] >> 16 ? 2u << (2 * i) : 0u);
+        return m;
+    };
+    uint32_t sum[kRounds], fresh[kRounds];
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        const int g = tid + r * kOnceThreads;
+        sum[r] = fresh[r] = 0;
+        if (g < lo.groups) {
+            uint4 q = reinterpret_cast<const uint4*>(cnt)[g];
+            if (pad_key >= 0 && g == pad_key >> 3) {
+                const uint32_t add = (uint32_t)pads_behind << ((pad_key & 1) * 16);
+                const int w = pad_key >> 1 & 3;
+                q.x += w == 0 ? add : 0u; q.y += w == 1 ? add : 0u; q.z += w == 2 ? add : 0u; q.w += w == 3 ? add : 0u;
+                reinterpret_cast<uint4*>(cnt)[g] = q;
+            }
+            const uint32_t occ = occurring(q), c2 = q.x + q.y + q.z + q.w;      // (two 16-bit sums: at most 65,535 in all)
+            sum[r] = (c2 & 0xffffu) + (c2 >> 16) + ((uint32_t)__popc(occ) << 16);
+            if (SLOTS) fresh[r] = __popc(occ & mask[g]);
+        }
+    }
+    const int items = (int)(once_scan(sum, sm) >> 16);
+    int fresh_all = 0;
+    if (SLOTS) fresh_all = (int)once_scan(fresh, sm);
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        const int g = tid + r * kOnceThreads;
+        if (g < lo.groups) {
+            base[g] = sum[r];
+            if (SLOTS) base_f[g] = (uint16_t)fresh[r];
+        }
+    }
+    __syncthreads();
+
+    if (mine) {
+        const int g = key >> 3, i = key & 7;
+        const uint4 q = reinterpret_cast<const uint4*>(cnt)[g];
+        const uint32_t w[4] = {q.x, q.y, q.z, q.w}, below_i = occurring(q) & ((1u << i) - 1u);
+        int first_row = (int)(base[g] & 0xffffu), count = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int c = (int)(w[j >> 1] >> ((j & 1) * 16) & 0xffffu);
+            first_row += j < i ? c : 0;
+            count = j == i ? c : count;
+        }
+        const int seg = (int)(base[g] >> 16) + __popc(below_i), pos = first_row + at;
+        inverse[p] = seg;
+        if ((unsigned)pos < (unsigned)n) {      // pos < n always holds; the test keeps a logic error from
+            perm[pos] = p;                       // becoming a stray store
+            seg_of_row[pos] = seg | (at == 0 ? kRowHead : 0) | (count >= seg_rows_for(n) ? kRowLong : 0);
+        }
+        if (at == 0) {
+            uniq[seg] = id;
+            uniq_ws[seg] = id;
+            if (id == pad_id) scal[kSPadSeg] = seg;
+            offsets[seg] = first_row;
+            counts[seg] = count;
+            if (slot_of) {
+                int slot = SLOTS ? slot_of[id] : -1;
+                if (slot < 0) {
+                    const int s = SLOTS ? u_base + base_f[g] + __popc(below_i & mask[g]) : seg;
+                    slot = s < cap_total ? (s | kSlotNew) : -1;
+                }
+                seg_slot[seg] = slot;
+            }
+        }
+    }
+    if (blockIdx.x == 0 && tid == 0) {
+        scal[kSU] = items;
+        if (u_out) *u_out = items;
+        offsets[items] = n;
+        scal[kSLongCount] = 0;
+        if (pad_id < 0 || (BITS ? pad_key < 0 : cnt16[pad_id] == 0)) scal[kSPadSeg] = -1;     // (else its first position sets it)
+        if (slot_of) {
+            const int nt = SLOTS ? u_base + fresh_all : items;
+            scal[kSUNext] = nt < cap_total ? nt : cap_total;
+        }
+    }
+}
+
+static bool overlap(const void* a, int64_t a_bytes, const void* b, int64_t b_bytes)
+{
+    const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+    return a && b && x < y + (uintptr_t)b_bytes && y < x + (uintptr_t)a_bytes;
+}
+
+// Returns false where the one-launch dedup does not apply.
+bool unique_once(Ctx* c, const int* ids, int n, int fix_key, int* uniq, int* inverse, int* counts, int* u_out,
+                 hipStream_t s, bool prospect, int first_step)
+{
+    if (n <= kFusedMaxN || n > kOnceMaxM) return false;
+    const int N = c->cfg.vocab_n;
+    const bool slots = prospect && !first_step;
+    const bool by_id = N <= 8 * kOnceRounds * kOnceThreads && OnceLayout(false, slots, n, N).bytes <= kOnceLds;
+    const bool by_bits = !by_id && n <= kOnceBitsM && N <= 128 * 4 * kOnceThreads && OnceLayout(true, slots, n, N).bytes <= kOnceLds;
+    if (!by_id && !by_bits) return false;
+    const int64_t ids_bytes = (int64_t)n * 4, items_bytes = (int64_t)(n < N ? n : N) * 4;
+    if (overlap(ids, ids_bytes, uniq, items_bytes) || overlap(ids, ids_bytes, counts, items_bytes) || overlap(ids, ids_bytes, inverse, ids_bytes) ||
+        overlap(ids, ids_bytes, u_out, 4))
+        return false;
+    c->sorted_keys = nullptr;
+    c->perm = c->vals[0];
+    int slice = ((n + c->num_cus - 1) / c->num_cus + 3) & ~3;
+    slice = slice < kWave ? kWave : slice > kOnceSlice ? kOnceSlice : slice;
+    const OnceLayout lo(by_bits, slots, n, N);
+    int key_bits = 1;
+    while (((by_bits ? n : N) - 1) >> key_bits) ++key_bits;
+    auto go = [&](auto kern) {
+        launch_smem(c, KID_IDS_ONCE, kern, dim3((unsigned)((n + slice - 1) / slice)), dim3(kOnceThreads), lo.bytes, s, ids, n, slice,
+                    key_bits, N, fix_key, c->fresh_err ? 1 : 0, c->perm, uniq, inverse, counts, c->offsets, c->seg_of_row, c->uniq_ws, u_out,
+                    prospect ? c->slot_of : (const int*)nullptr, c->seg_slot, c->scal, (int)c->cap_total, c->cfg.pad_id);
+    };
+#define GRAM_GO(R, BITS)                                                                            \
+    {                                                                                               \
+        ensure_dynamic_lds<k_ids_once<R, BITS, true>>((int)kOnceLds);                               \
+        ensure_dynamic_lds<k_ids_once<R, BITS, false>>((int)kOnceLds);                              \
+        if (slots) go(k_ids_once<R, BITS, true>);                                                   \
+        else go(k_ids_once<R, BITS, false>);                                                        \
+    }
+    constexpr int kPer = 4 * kOnceThreads;
+    static_assert(kOnceBitsM <= 3 * kPer && kOnceMaxM <= 4 * kPer, "positions per thread");
+    if (by_bits && n <= 2 * kPer) GRAM_GO(2, true)
+    else if (by_bits) GRAM_GO(3, true)
+    else if (n <= 2 * kPer) GRAM_GO(2, false)
+    else GRAM_GO(4, false)
+#undef GRAM_GO
+    return true;
+}
+
 // ---- mid-sized batches over small vocabularies: counting by ID -------------------------
 //
 // A sort of such a batch is bound by its eight short launches (two radix passes of three, two for the

@@ -157,3 +157,60 @@ def test_error_word_of_the_call_without_a_context(m):
         gram.unique_static(batch, n, 0, uniq, inverse, counts, u, err)
         assert int(err) == want
         assert torch.equal(uniq[inverse.long()], torch.where(batch >= n, 0, batch))
+
+
+# The one-launch dedup: where its keys change from IDs to numbers in a bitmap (the line depends on whether the buffer may hold
+# items already), the largest vocabulary of either, positions per block and per thread, the last sizes it takes and the next.
+@pytest.mark.parametrize("m,n", [(513, 8), (640, 55_472), (640, 55_473), (700, 63_792), (700, 63_793), (8192, 524_288), (8193, 524_288),
+                                 (8193, 524_289), (12_288, 70_000), (12_289, 55_472), (12_289, 70_000), (16_383, 20_000), (16_384, 20_000),
+                                 (16_385, 20_000)])
+@pytest.mark.parametrize("kind", ["popular", "few", "distinct_first"])
+def test_one_launch(m, n, kind):
+    check_dedup_window(m, n, kind, m_last=m - 3)
+
+
+@pytest.mark.parametrize("m,n", [(700, 1000), (9001, 50_000), (2050, 300_000)])
+@pytest.mark.parametrize("pad", [-1, 0, 17, "last", "absent"])
+def test_one_launch_padding_and_bad_ids(m, n, pad):
+    """The padding ID anywhere in the vocabulary, absent or none at all, over two steps; IDs out of range count as padding (as
+    item 0 where there is none) and are reported."""
+    import torch
+    from paper_2204_04179_amd import gram
+    rng = np.random.default_rng(m)
+    pad_id = n - 1 if pad == "last" else 5 if pad == "absent" else pad
+    g = gram.Gram(gram.make_config(n, 8, 4, m, 2, pad_id, 0, gram.F32))
+    total = np.zeros(n, np.int64)
+    for k in range(2):
+        ids = _batch(rng, m, n, "popular")
+        if pad == "absent":
+            ids[ids == 5] = 6
+        elif pad_id >= 0:
+            ids[rng.random(m) < 0.4] = pad_id
+        if k and pad != "absent":
+            given = ids.copy()
+            given[[0, m // 2, m - 1]] = [n, -1, 2**31 - 1]
+            ids[[0, m // 2, m - 1]] = max(pad_id, 0)
+        else:
+            given = ids
+        uniq, counts = (torch.full((min(m, n),), -7, dtype=torch.int32, device="cuda") for _ in range(2))
+        inverse = torch.empty(m, dtype=torch.int32, device="cuda")
+        g.unique(torch.from_numpy(given).cuda(), uniq, inverse, counts)
+        g.grad_accumulate(torch.ones(m, 4, device="cuda"), m, k)
+        ru, ri, rc = np.unique(ids, return_inverse=True, return_counts=True)
+        np.testing.assert_array_equal(uniq.cpu().numpy()[:ru.size], ru)
+        np.testing.assert_array_equal(counts.cpu().numpy()[:ru.size], rc)
+        np.testing.assert_array_equal(inverse.cpu().numpy(), ri.reshape(-1))
+        assert bool((uniq[ru.size:] == -7).all()) and bool((counts[ru.size:] == -7).all())
+        total += np.bincount(ids, minlength=n)
+    if pad != "absent":
+        with pytest.raises(gram.GramError) as e:
+            g.check()
+        assert e.value.status == gram.ERR_RANGE
+    rows = min(2 * m, n)
+    ut, Gt = torch.empty(rows, dtype=torch.int32, device="cuda"), torch.empty(rows, 4, device="cuda")
+    T = g.flush(ut, None, Gt, want_host_u=True)
+    items = np.flatnonzero(total)
+    np.testing.assert_array_equal(ut.cpu().numpy()[:T], items)
+    want = np.where(items == pad_id, 0, total[items])
+    np.testing.assert_array_equal(Gt.cpu().numpy()[:T, 0], want)
+    g.close()
