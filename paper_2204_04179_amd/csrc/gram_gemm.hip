@@ -1691,6 +1691,162 @@ __global__ __launch_bounds__(NW * 64) void k_wgrad_tn_bf16(
 #undef GRAM_PARK
 #undef GRAM_ITER
 
+// ---- weight gradient of rows that are bf16 already -----------------------------------------
+//
+// Both operands (features through the row list, rows as an earlier contraction stored them) can go straight to LDS, so the loop
+// is the forward's (see k_gemm_nt_bf16): slabs of 32 rows of 512 bytes in a ring of four stages of 32 KiB, two segments per
+// slab (read the fragments and request the slab three ahead; multiply), the lower half of the features a segment behind.  The
+// row list goes through LDS too, 8 slabs' entries at a time: a load into registers would have to be waited for in the queue of
+// the others (scalar loads: 123 us where the list is the identity 82).
+// Padding, rows past the range and features or columns past the edge are offsets out of range, which write zeros to LDS.
+// 32,768 rows, 1024 x 1024, without the reduction: 85 us through registers with one barrier per slab, now 76 (identity) and 80
+// (listed); 13 of it are the partials (64 MiB written).  The same two segments with loads through registers: 92 us, the wait
+// for them then stands between the other waves and the matrix pipe.
+constexpr int PSTAGEB = 2 * WOPB, PSTAGES = 4, kPairLds = PSTAGES * PSTAGEB + 4096;
+
+template <bool LISTED>
+__global__ __launch_bounds__(kWgradWaves * 64) void k_wgrad_rows_bf16(
+    const uint16_t* __restrict__ X, uint32_t x_bytes, const int* __restrict__ row_list, const uint16_t* __restrict__ G,
+    uint32_t g_bytes, const int* __restrict__ rows_dev, int d_in, int d, int pad_id, int splits,
+    float* __restrict__ partial, int row_begin, int row_end)
+{
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const int tiles_c = (d + 255) / 256, tiles = ((d_in + 255) / 256) * tiles_c;
+    const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
+    const int z = xcd + 8 * (q / tiles);
+    const int i0 = ((q % tiles) / tiles_c) * 256, c0 = ((q % tiles) % tiles_c) * 256;
+    if (z >= splits) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 2, wn = wave & 3;
+    // rows [row_begin, U), slabs aligned to multiples of WK rows, a contiguous range of them per block
+    const int rows_held = *rows_dev;
+    const int U = rows_held < row_end ? rows_held : row_end;
+    const int sl0 = row_begin / WK;
+    const int slabs_all = U > row_begin ? (U + WK - 1) / WK - sl0 : 0;
+    const int per = (slabs_all + splits - 1) / splits;
+    const int sl_begin = sl0 + z * per;
+    int nslab = sl0 + slabs_all - sl_begin;
+    if (nslab > per) nslab = per;
+    partial += (int64_t)z * d_in * d;
+
+    const u32x4 rsX = buffer_words(X, x_bytes), rsG = buffer_words(G, g_bytes);
+    // wave w moves rows 4 w + 2 t + lane / 32 of a slab, t = 0, 1, of either operand
+    uint32_t xo[2], go[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int chunk = (lane & 31) ^ ((2 * t + (lane >> 5)) << 2);
+        xo[t] = i0 + chunk * 8 < d_in ? (uint32_t)(i0 + chunk * 8) * 2u : kOutOfRange;
+        go[t] = c0 + chunk * 8 < d ? (uint32_t)(c0 + chunk * 8) * 2u : kOutOfRange;
+    }
+    typedef __attribute__((address_space(3))) unsigned char lds_u8;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)smem, to_w = lds0 + wave * 2048;
+    // entries of the list: ring of 4 pieces of 256, piece k holds those of slabs 8 k .. 8 k + 7 of the block's range
+    const u32x4 rsI = buffer_words(row_list, LISTED ? (uint32_t)row_end * 4u : 0u);
+    const uint32_t list0 = lds0 + PSTAGES * PSTAGEB, list_l = list0 + (uint32_t)(wave * 4 + (lane >> 5)) * 4u;
+    typedef const __attribute__((address_space(3))) int lds_i32;
+#define GRAM_IDS(PIECE)                                                                             \
+    load_to_lds(rsI, (uint32_t)(sl_begin * WK + (PIECE) * 256 + lane * 4) * 4u, 0u, list0 + ((PIECE) & 3) * 1024);
+#define GRAM_LOAD(SL)                                                                               \
+    {                                                                                               \
+        const uint32_t to_ = to_w + ((SL) & (PSTAGES - 1)) * PSTAGEB;                               \
+        const int slot0_ = (sl_begin + (SL)) * WK + wave * 4 + (lane >> 5);                         \
+        _Pragma("unroll") for (int t = 0; t < 2; ++t) {                                             \
+            const int slot_ = slot0_ + 2 * t;                                                       \
+            const bool held_ = (SL) < nslab && slot_ < U && slot_ >= row_begin;                     \
+            const int id_ = LISTED ? *(lds_i32*)(uintptr_t)(list_l + ((uint32_t)(SL) & 31u) * (WK * 4) + t * 8) : slot_; \
+            const uint32_t xr_ = held_ && id_ != pad_id ? (uint32_t)id_ * (uint32_t)(d_in * 2) : kOutOfRange; \
+            const uint32_t gr_ = held_ ? (uint32_t)slot_ * (uint32_t)(d * 2) : kOutOfRange;         \
+            load_to_lds(rsX, __builtin_elementwise_add_sat(xr_, xo[t]), 0u, to_ + t * 1024);        \
+            load_to_lds(rsG, __builtin_elementwise_add_sat(gr_, go[t]), 0u, to_ + WOPB + t * 1024); \
+        }                                                                                           \
+    }
+
+    f32x16 acc[4][2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    const int j16 = lane & 15, grp = lane >> 4;
+    const int f_row = (grp >> 1) * 8 + (j16 >> 2), f_x = (j16 >> 2 & 3) << 2;
+    uint32_t ra[4], rb[2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        ra[i] = lds0 + f_row * WROWB + (((wm * 16 + i * 4 + (grp & 1) * 2 + ((j16 & 3) >> 1)) ^ f_x) * 16) + (j16 & 1) * 8;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+        rb[j] = lds0 + WOPB + f_row * WROWB + (((wn * 8 + j * 4 + (grp & 1) * 2 + ((j16 & 3) >> 1)) ^ f_x) * 16) + (j16 & 1) * 8;
+    bf16x8 fa[2][4], fb[2][2];
+    auto frag = [](uint32_t at) {
+        const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(uintptr_t)at);
+        const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(uintptr_t)(at + 4 * WROWB));
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+
+    if (nslab > 0) {
+        constexpr int kAhead = 2 * 4;        // loads that may be in flight when a slab is published: the next two slabs'
+        if (LISTED) {
+            if (wave == 0) {
+                GRAM_IDS(0)
+                GRAM_IDS(1)
+            }
+            wait_loads<0>();
+            segment_barrier();
+        }
+        GRAM_LOAD(0)
+        GRAM_LOAD(1)
+        GRAM_LOAD(2)
+        wait_loads<kAhead>();
+        segment_barrier();
+        if (wm == 1) segment_barrier();
+        for (int sl = 0; sl < nslab; ++sl) {
+            const uint32_t stage = (uint32_t)(sl & (PSTAGES - 1)) * PSTAGEB;
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+                for (int j = 0; j < 2; ++j) fb[ks][j] = frag(rb[j] + stage + ks * (16 * WROWB));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) fa[ks][i] = frag(ra[i] + stage + ks * (16 * WROWB));
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            // (the piece after next: first read 13 slabs on, what it replaces was last read 12 slabs ago)
+            if (LISTED && wave == 0 && (sl & 7) == 0) { GRAM_IDS((sl >> 3) + 2) }
+            GRAM_LOAD(sl + 3)
+            wait_loads<kAhead>();
+            wait_lds();
+            segment_barrier();
+            __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks][i], fb[ks][j], acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_s_setprio(0);
+            segment_barrier();
+        }
+        if (wm == 0) segment_barrier();
+        wait_loads<0>();
+    }
+#undef GRAM_IDS
+#undef GRAM_LOAD
+    // accumulator element r of a lane sits at (row, col) = ((r / 4) * 8 + (lane / 32) * 4 + r % 4, lane % 32)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int fi = i0 + wm * 128 + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
+            if (fi < d_in) {
+                float* row = partial + (int64_t)fi * d + c0 + wn * 64 + (lane & 31);
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    if (c0 + wn * 64 + j * 32 + (lane & 31) < d) row[j * 32] = acc[i][j][r];
+            }
+        }
+}
+
 // ---- weight gradient of short windows -------------------------------------------------
 //
 // A window of a few thousand buffer rows over a 768 x 256 matrix is 1 GFLOP: nothing but latency.  The
@@ -2100,7 +2256,17 @@ bool encoder_wgrad(Ctx* c, const void* X, float* dW, hipStream_t s, int64_t firs
             // (the descriptors of the WIDE variant are not used)
             if (wide && gb) GRAM_GO(KID_WGRAD_BF16_WIDE, 0, 0, k_wgrad_tn_bf16<kWgradWaves, true, false, true>)
             else if (wide) GRAM_GO(KID_WGRAD_BF16_WIDE, 0, 0, k_wgrad_tn_bf16<kWgradWaves, true>)
-            else if (gb) GRAM_GO(KID_WGRAD_BF16, x_bytes, g_bytes, k_wgrad_tn_bf16<kWgradWaves, false, false, true>)
+            else if (gb) {
+                auto rows_go = [&](auto kern) {
+                    launch_smem(c, KID_WGRAD_BF16, kern, dim3((unsigned)(tiles * S)), dim3(kWgradWaves * 64), kPairLds, s,
+                                static_cast<const uint16_t*>(X), (uint32_t)x_bytes, ids, reinterpret_cast<const uint16_t*>(rows),
+                                (uint32_t)g_bytes, rows_dev, d_in, d, pad_id, S, c->wg_partial, row_begin, row_end);
+                };
+                ensure_dynamic_lds<k_wgrad_rows_bf16<true>>(kPairLds);
+                ensure_dynamic_lds<k_wgrad_rows_bf16<false>>(kPairLds);
+                if (ids) rows_go(k_wgrad_rows_bf16<true>);
+                else rows_go(k_wgrad_rows_bf16<false>);
+            }
             else GRAM_GO(KID_WGRAD_BF16, x_bytes, g_bytes, k_wgrad_tn_bf16<kWgradWaves, false>)
 #undef GRAM_GO
         }
