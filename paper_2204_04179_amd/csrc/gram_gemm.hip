@@ -320,6 +320,7 @@ __device__ __forceinline__ void encode_mid_tile(
     constexpr size_t kStageB = Mid<SM, TN, KG, WR>::kStageB;                       // threads per group
     constexpr int XT = SM * 8 / GT, WT = SK * (TN / 8) / GT; // 16-byte chunks per thread and slab
     constexpr int WROW = TN * 2;                            // bytes per row of W in LDS
+    static_assert(WROW == 128, "the swizzle of its rows");
     constexpr int WM = SM / (32 * WR);                      // waves along the rows
     const int tid = threadIdx.x, grp = __builtin_amdgcn_readfirstlane(tid / GT), gt = tid % GT;
     const int lane = tid & 63, wave = gt >> 6, wm = wave % WM, wn = wave / WM;
@@ -346,7 +347,7 @@ __device__ __forceinline__ void encode_mid_tile(
         ox[t] = mid_row_offset(m0 + xrow + t * (GT / 8), U, zid[t] == pad_id, (uint32_t)id[t], (uint32_t)d_in, (uint32_t)xk);
     constexpr int WC = TN / 8;                              // chunks per row of W
     const int wrow = gt / WC, wpos = gt % WC;               // + (GT / WC) t
-    const int wcol = n0 + (wpos ^ (WROW == 256 ? (wrow & 3) << 2 : (wrow & 2) << 1)) * 8;
+    const int wcol = n0 + (wpos ^ ((wrow & 2) << 1)) * 8;
     static_assert(GT / WC % 4 == 0, "row swizzle");
     const bool wcol_ok = wcol < d;
 
@@ -378,7 +379,7 @@ __device__ __forceinline__ void encode_mid_tile(
     unsigned char* wstage = stage + SM * SK * 2;
     const int j16 = lane & 15, g16 = lane >> 4;
     const int f_row = (g16 >> 1) * 8 + (j16 >> 2), f_ch = wn * 4 + (g16 & 1) * 2 + ((j16 & 3) >> 1);
-    const unsigned char* fw = wstage + f_row * WROW + ((f_ch ^ (WROW == 256 ? (f_row & 3) << 2 : (f_row & 2) << 1)) * 16) + (j16 & 1) * 8;
+    const unsigned char* fw = wstage + f_row * WROW + ((f_ch ^ ((f_row & 2) << 1)) * 16) + (j16 & 1) * 8;
     const int a_row = wm * (32 * WR) + (lane & 31), a_x = (a_row >> 1) & 7;      // + 32 i: the same swizzle
 #define GRAM_MID_ITER(SET, IT, MORE)                                                                \
     {                                                                                               \
@@ -460,20 +461,19 @@ __device__ __forceinline__ void encode_mid_tile(
     if (epi_subtracts(EPI) && loss_part) block_sum_double(sq, STHREADS, s_loss, loss_part);
 }
 
-// One tile per block; the column tiles of a row tile run on one XCD and share its rows of X.  WIDE: tiles of
-// 128 x 128; else 64 x 64, or 128 x 64 (the same threads) where the items make more than `most_low` of those.
-template <bool WIDE>
+// One tile per block; the column tiles of a row tile run on one XCD and share its rows of X.  Tiles of 64 x 64, or
+// 128 x 64 (the same threads) where the items make more than `most_low` of those.
 struct MidShape {
-    static constexpr int kCols = WIDE ? 128 : 64;
-    using Low = Mid<64, 64, 2, 1>;
+    static constexpr int kCols = 64;
+    using Low = Mid<64, kCols, 2, 1>;
     using Tall = Mid<128, kCols, 2, 2>;
     static constexpr int kThreads = Tall::kThreads;
     static constexpr size_t kLds = Tall::kLds;
-    static_assert(WIDE || (Low::kThreads == kThreads && Low::kLds <= kLds), "either tile by the same block");
+    static_assert(Low::kThreads == kThreads && Low::kLds <= kLds, "either tile by the same block");
 };
 
-template <bool WIDE, int EPI>
-__global__ __launch_bounds__(MidShape<WIDE>::kThreads, 4) void k_encode_mid(
+template <int EPI>
+__global__ __launch_bounds__(MidShape::kThreads, 4) void k_encode_mid(
     const uint16_t* __restrict__ X, uint32_t x_bytes, const uint16_t* __restrict__ W, uint32_t w_bytes,
     const int* __restrict__ uniq, const int* __restrict__ u_dev, int most_low, int d_in, int d,
     const int* __restrict__ zero_ids, int pad_id, float* __restrict__ E, const void* __restrict__ aux,
@@ -481,26 +481,24 @@ __global__ __launch_bounds__(MidShape<WIDE>::kThreads, 4) void k_encode_mid(
 {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     __shared__ int s_ids[128];
-    __shared__ double s_loss[MidShape<WIDE>::kThreads / 64];
-    constexpr int TN = MidShape<WIDE>::kCols;
+    __shared__ double s_loss[MidShape::kThreads / 64];
+    constexpr int TN = MidShape::kCols;
     if (epi_subtracts(EPI) && loss_part) loss_part += blockIdx.x;
     const int n_tiles = (d + TN - 1) / TN, q = blockIdx.x >> 3, qr = q / n_tiles;
     const int mt = qr * 8 + (blockIdx.x & 7), n0 = (q - qr * n_tiles) * TN;
     const int U = *u_dev;
-    const bool low = !WIDE && (U + 63) / 64 * n_tiles <= most_low;
+    const bool low = (U + 63) / 64 * n_tiles <= most_low;
     const int m0 = mt * (low ? 64 : 128);
     if (m0 >= U) {
         if (epi_subtracts(EPI) && loss_part && threadIdx.x == 0) *loss_part = 0.0;
         return;
     }
-    if constexpr (!WIDE)
-        if (low) {
-            encode_mid_tile<64, 64, 2, 1, 3, EPI>(X, x_bytes, W, w_bytes, uniq, U, d_in, d, zero_ids, pad_id, E, aux, loss_part,
-                                                  m0, n0, smem, s_ids, s_loss);
-            return;
-        }
-    encode_mid_tile<128, TN, 2, 2, 2, EPI>(X, x_bytes, W, w_bytes, uniq, U, d_in, d, zero_ids, pad_id, E, aux, loss_part, m0, n0,
-                                           smem, s_ids, s_loss);
+    if (low)
+        encode_mid_tile<64, TN, 2, 1, 3, EPI>(X, x_bytes, W, w_bytes, uniq, U, d_in, d, zero_ids, pad_id, E, aux, loss_part, m0, n0,
+                                              smem, s_ids, s_loss);
+    else
+        encode_mid_tile<128, TN, 2, 2, 2, EPI>(X, x_bytes, W, w_bytes, uniq, U, d_in, d, zero_ids, pad_id, E, aux, loss_part, m0, n0,
+                                               smem, s_ids, s_loss);
 }
 
 // ---- C[M,N] = A[M,K] . B[N,K]^T, bf16 in, fp32 out ---------------------------------
@@ -573,6 +571,159 @@ __device__ __forceinline__ u32x4 buffer_words(const void* base, uint32_t bytes)
     const uint64_t a = (uint64_t)base;
     return u32x4{(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a), (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32)) & 0xffffu,
                  (uint32_t)__builtin_amdgcn_readfirstlane((int)bytes), kBufferFlags};
+}
+
+// ---- the forward of mid-sized batches, long K: tiles of 128 x 128 --------------------------------
+//
+// About one such tile falls to a CU, so the launch lasts as long as a tile: 8 waves (2 x 4, each 64 x 32), slabs of 64
+// straight to LDS in a ring of four stages of 32 KiB, requested three slabs ahead (96 KiB on their way: the rows come
+// from HBM), two segments per slab as above.  (Through registers, with K cut between two groups of 8 waves whose tiles
+// are added at the end, LDS stores and the second barrier took as long as the products.)
+// LDS rows of X as above; rows of W are 256 bytes, chunk c of row r at c ^ ((r & 3) << 2).  Offsets out of range (padding item, rows
+// behind the items, K, columns) write zeros.  Neither the list nor A is read behind the items.
+// Whole forward with position copies, us, before / now: 51,200 positions over 20,000 IDs 776 x 392 48.4 / 44.4, 20,000 over
+// 20,000 776 x 256 21.7 / 19.0, 16,000 over 1,000,000 776 x 1024 45.0 / 41.0; over 156 shapes (K 264 to 1,024, widths 128 to 1,024)
+// none slower by more than 2 %, the geometric mean 0.963.
+constexpr int QT = 128, QROWW = QT * 2, QXB = QT * TROWB, QSTAGEB = QXB + TK * QROWW, QSTAGES = 4;
+constexpr int QLD = QT + 8;                             // floats per row of the parked tile
+static_assert(QT * QLD * 4 <= QSTAGES * QSTAGEB, "the tile overlays the stages");
+
+template <int EPI>
+__global__ __launch_bounds__(kGemmWaves * 64) void k_encode_square(
+    const uint16_t* __restrict__ X, uint32_t x_bytes, const uint16_t* __restrict__ W, uint32_t w_bytes,
+    const int* __restrict__ uniq, const int* __restrict__ u_dev, int d_in, int d, const int* __restrict__ zero_ids, int pad_id,
+    float* __restrict__ E, const void* __restrict__ aux, double* __restrict__ loss_part)
+{
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    __shared__ int s_ids[QT];
+    __shared__ double s_loss[kGemmWaves];
+    if (epi_subtracts(EPI) && loss_part) loss_part += blockIdx.x;
+    // the column tiles of a row tile run on one XCD and share its rows of X
+    const int n_tiles = (d + QT - 1) / QT, q = blockIdx.x >> 3, qr = q / n_tiles;
+    const int m0 = (qr * 8 + (blockIdx.x & 7)) * QT, n0 = (q - qr * n_tiles) * QT;
+    const int U = *u_dev;
+    if (m0 >= U) {
+        if (epi_subtracts(EPI) && loss_part && threadIdx.x == 0) *loss_part = 0.0;
+        return;
+    }
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 2, wn = wave & 3;
+    const u32x4 rsX = buffer_words(X, x_bytes), rsW = buffer_words(W, w_bytes);
+
+    // wave w moves rows 16 w + 8 t + lane / 8 of X, and rows 8 w + 4 t + lane / 16 of a slab of W, t = 0, 1
+    uint32_t xo[2], wo[2];
+    int xk[2];
+    int id[2], zid[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int j = mid_list_entry(m0 + wave * 16 + t * 8 + (lane >> 3), U);
+        id[t] = uniq[j];
+        zid[t] = zero_ids[j];
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int r = wave * 16 + t * 8 + (lane >> 3);
+        xk[t] = ((lane & 7) ^ (r >> 1 & 7)) * 8;
+        xo[t] = mid_row_offset(m0 + r, U, zid[t] == pad_id, (uint32_t)id[t], (uint32_t)d_in, (uint32_t)xk[t]);
+        const int k = wave * 8 + t * 4 + (lane >> 4), col = n0 + ((lane & 15) ^ ((k & 3) << 2)) * 8;
+        wo[t] = col < d ? ((uint32_t)k * (uint32_t)d + (uint32_t)col) * 2u : kOutOfRange;
+        if ((lane & 7) == 0) s_ids[r] = zid[t];
+    }
+    typedef __attribute__((address_space(3))) unsigned char lds_u8;
+    typedef __attribute__((address_space(3))) const bf16x8 lds_frag;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)smem, to_w = lds0 + wave * 2048;
+    const int nslab = (d_in + TK - 1) / TK;
+#define GRAM_LOAD(SL)                                                                               \
+    {                                                                                               \
+        const uint32_t to_ = to_w + ((SL) & (QSTAGES - 1)) * QSTAGEB;                               \
+        const uint32_t wk_ = (SL) < nslab ? (uint32_t)(SL) * (uint32_t)(TK * 2) * (uint32_t)d : kOutOfRange; \
+        _Pragma("unroll") for (int t = 0; t < 2; ++t)                                               \
+            load_to_lds(rsX, mid_slab_offset(xo[t], (SL) * TK, xk[t], d_in), 0u, to_ + t * 1024);   \
+        _Pragma("unroll") for (int t = 0; t < 2; ++t)                                               \
+            load_to_lds(rsW, __builtin_elementwise_add_sat(wo[t], wk_), 0u, to_ + QXB + t * 1024);  \
+    }
+    GRAM_LOAD(0)
+    GRAM_LOAD(1)
+    GRAM_LOAD(2)
+
+    f32x16 acc[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+    const int row = wm * 64 + (lane & 31);
+    uint32_t ra[4], rb;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) ra[ks] = lds0 + row * TROWB + (((ks * 2 + (lane >> 5)) ^ (row >> 1 & 7)) * 16);
+    {
+        const int j16 = lane & 15, grp = lane >> 4, f_row = (grp >> 1) * 8 + (j16 >> 2);
+        rb = lds0 + QXB + f_row * QROWW + (((wn * 4 + (grp & 1) * 2 + ((j16 & 3) >> 1)) ^ ((f_row & 3) << 2)) * 16) + (j16 & 1) * 8;
+    }
+    constexpr int kAhead = 2 * 4;            // loads that may be in flight when a slab is published: the next two slabs'
+    wait_loads<kAhead>();
+    segment_barrier();
+    if (wm == 1) segment_barrier();          // the lower row half runs a segment behind
+    for (int sl = 0; sl < nslab; ++sl) {
+        const uint32_t stage = (uint32_t)(sl & (QSTAGES - 1)) * QSTAGEB;
+        bf16x8 fa[2][4], fb[4];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            const sv4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_sv4i16*)(uintptr_t)(rb + stage + ks * (16 * QROWW)));
+            const sv4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_sv4i16*)(uintptr_t)(rb + stage + ks * (16 * QROWW) + 4 * QROWW));
+            fb[ks] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+#pragma unroll
+            for (int i = 0; i < 2; ++i) fa[i][ks] = *(lds_frag*)(uintptr_t)(ra[ks] + stage + i * (32 * TROWB));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        GRAM_LOAD(sl + 3)
+        wait_loads<kAhead>();
+        wait_lds();
+        segment_barrier();
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i][ks], fb[ks], acc[i], 0, 0, 0);
+        __builtin_amdgcn_s_setprio(0);
+        segment_barrier();
+    }
+#undef GRAM_LOAD
+    if (wm == 0) segment_barrier();
+    wait_loads<0>();
+    __syncthreads();
+
+    // the tile through LDS; rows of 16-byte pieces to memory
+    float* parked = reinterpret_cast<float*>(smem);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            parked[(wm * 64 + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) * QLD + wn * 32 + (lane & 31)] = acc[i][r];
+    constexpr int OUT = QT * QT / 4 / (kGemmWaves * 64);
+    f32x4_ av[OUT];
+#pragma unroll
+    for (int h = 0; h < OUT; ++h) {
+        const int e = tid + h * (kGemmWaves * 64), r = e / (QT / 4), c4 = n0 + e % (QT / 4) * 4;
+        av[h] = m0 + r < U && c4 < d ? epi_load4<EPI>(aux, (int64_t)(m0 + r) * d + c4) : f32x4_{0.f, 0.f, 0.f, 0.f};
+    }
+    __syncthreads();
+    double sq = 0.0;
+#pragma unroll
+    for (int h = 0; h < OUT; ++h) {
+        const int e = tid + h * (kGemmWaves * 64), r = e / (QT / 4), c = e % (QT / 4) * 4;
+        f32x4_ s = *reinterpret_cast<const f32x4_*>(&parked[r * QLD + c]);
+        if (m0 + r < U && n0 + c < d) {
+            // (the padding item's product is zero only where the weights are finite)
+            const bool zero = s_ids[r] == pad_id;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                s[k] = epi_value<EPI>(s[k], av[h][k], zero);
+                if (epi_subtracts(EPI)) sq += (double)s[k] * s[k];
+            }
+            epi_store4<EPI>(E, (int64_t)(m0 + r) * d + n0 + c, s);
+        }
+    }
+    if (epi_subtracts(EPI) && loss_part) block_sum_double(sq, kGemmWaves * 64, s_loss, loss_part);
 }
 
 // How many row tiles of 256 are taken whole.  A block fills its CU (8 waves, over 200 VGPRs), so the tiles
@@ -1219,13 +1370,20 @@ void transpose_weight(Ctx* c, const void* W, int rows, int cols, void* Wt, hipSt
     }
 }
 
-// Batches that give the 256x256 kernel a tile for every CU (and a K that fits its slabs) take it;
+static bool takes_mid_kernel(int64_t a_rows, int k, int n_out, int epi);
+
+// Batches that give the 256x256 kernel a tile for every CU (and a K that fits its slabs) take it, but for
+// short K where more than a third of its columns lies behind the matrix: subtracting, 33,000 rows (whole call with the
+// weight gradient, 256x256 / mid-sized kernel) 96 x 264 45.7 / 39.9 us, 160 x 264 49.8 / 47.8, 96 x 400 52.5 / 50.8, 160 x 400
+// 60.6 / 63.0, 96 x 512 60.2 / 61.8;
 // the rest take k_encode_mid or, where that does not apply, the 64-row kernel, which addresses its operands
 // through plain pointers and therefore also serves the epilogue modes when A lies beyond 4 GiB.
 static bool takes_big_kernel(const Ctx* c, int64_t rows_max, int n_out, int k, int64_t a_rows, int epi)
 {
     const int64_t tile_bound = ((rows_max + TM - 1) / TM) * ((n_out + TN - 1) / TN);
     if (epi != kEpiPlain && a_rows * k * 2 >= kBufferWindow) return false;
+    if (k <= 160 && 3 * (int64_t)n_out < 2 * ((n_out + TN - 1) / TN) * TN && epi != kEpiPlain && takes_mid_kernel(a_rows, k, n_out, epi))
+        return false;
     return tile_bound >= c->num_cus && k % 32 == 0 && n_out < (1 << 22);     // (32-bit offsets within a tile of C)
 }
 
@@ -1307,26 +1465,24 @@ bool gemm_rows_bf16(Ctx* c, const void* A, int64_t a_rows, int k, const int* row
         const unsigned blocks = (unsigned)((wide ? tall_rows : std::max(low_rows, tall_rows)) + 7) / 8 * 8 *
                                 (unsigned)(wide ? (n_out + 127) / 128 : tiles_c);
         if (loss) *loss->blocks = (int)blocks;
-        auto go = [&](auto kern, int threads, size_t lds) {
-            launch_smem(c, KID_ENCODE_BF16, kern, dim3(blocks), dim3(threads), lds, s, static_cast<const uint16_t*>(A),
-                        x_bytes, static_cast<const uint16_t*>(B_plain), w_bytes, row_ids, n_dev, (int)most_low, k, n_out,
-                        zero_ids, pad_id, C, aux, loss_part);
-        };
-#define GRAM_MID_(WIDE_, EPI_)                                                                      \
-    {                                                                                               \
-        constexpr auto kern = k_encode_mid<WIDE_, EPI_>;                                            \
-        ensure_dynamic_lds<kern>((int)MidShape<WIDE_>::kLds);                                       \
-        go(kern, MidShape<WIDE_>::kThreads, MidShape<WIDE_>::kLds);                                 \
-    }
 #define GRAM_GO_MID(EPI_)                                                                           \
-    if (wide) GRAM_MID_(true, EPI_)                                                                 \
-    else GRAM_MID_(false, EPI_)
+    if (wide) {                                                                                     \
+        constexpr auto kern = k_encode_square<EPI_>;                                                \
+        ensure_dynamic_lds<kern>(QSTAGES * QSTAGEB);                                                \
+        launch_smem(c, KID_ENCODE_BF16, kern, dim3(blocks), dim3(kGemmWaves * 64), QSTAGES * QSTAGEB, s, static_cast<const uint16_t*>(A), \
+                    x_bytes, static_cast<const uint16_t*>(B_plain), w_bytes, row_ids, n_dev, k, n_out, zero_ids, pad_id, C, aux, loss_part); \
+    } else {                                                                                        \
+        constexpr auto kern = k_encode_mid<EPI_>;                                                   \
+        ensure_dynamic_lds<kern>((int)MidShape::kLds);                                              \
+        launch_smem(c, KID_ENCODE_BF16, kern, dim3(blocks), dim3(MidShape::kThreads), MidShape::kLds, s, static_cast<const uint16_t*>(A), \
+                    x_bytes, static_cast<const uint16_t*>(B_plain), w_bytes, row_ids, n_dev, (int)most_low, k, n_out, \
+                    zero_ids, pad_id, C, aux, loss_part);                                           \
+    }
         if (epi == kEpiMinus) { GRAM_GO_MID(kEpiMinus) }
         else if (epi == kEpiMinusBf16) { GRAM_GO_MID(kEpiMinusBf16) }
         else if (epi == kEpiReluBf16) { GRAM_GO_MID(kEpiReluBf16) }
         else { GRAM_GO_MID(kEpiPlain) }
 #undef GRAM_GO_MID
-#undef GRAM_MID_
         return false;
     }
     const dim3 grid((n_out + BN - 1) / BN, (unsigned)((rows_max + BM - 1) / BM));

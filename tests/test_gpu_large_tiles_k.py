@@ -83,12 +83,13 @@ def test_two_layer_backward(k, dh, d):
     g.close()
 
 
-@pytest.mark.parametrize("k", [32, 96, 128])
-def test_subtracting(k):
+# (up to K = 160, widths up to 336 leave more than a third of the second column tile empty and go to the mid-sized kernel)
+@pytest.mark.parametrize("k,d", [(32, 504), (96, 504), (128, 504), (160, 264), (160, 336), (160, 344), (192, 264)])
+def test_subtracting(k, d):
     import torch
     from paper_2204_04179_amd import gram
     torch.manual_seed(k + 1)
-    n, d = 60_000, 504
+    n = 60_000
     ids = torch.randperm(n, device="cuda")[:ITEMS].to(torch.int32)
     X = _features(n, k, ids, torch)
     ids[5] = ids[ITEMS - 1] = 0
