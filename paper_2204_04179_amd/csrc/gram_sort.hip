@@ -1160,21 +1160,24 @@ bool unique_once(Ctx* c, const int* ids, int n, int fix_key, int* uniq, int* inv
 // head flags: 33 to 37 us from 12,000 to 65,000 positions whatever the vocabulary).  Where a counter
 // per ID fits in LDS, three launches do it all:
 //   k_ids_count  a block counts the IDs of its 1024 positions in LDS (16-bit counters) and leaves them
-//                as one row of table[block][id], and the checked IDs where k_ids_emit reads them (the caller's
-//                buffer of IDs may be one of the outputs: a launch that writes those does not read it);
+//                as one row of table[block][id], every position's rank among its block's positions of the ID, and the
+//                checked IDs where k_ids_emit reads them (the caller's buffer of IDs may be one of the outputs: a launch
+//                that writes those does not read it);
 //   k_ids_scan   exclusive prefix down every column of the table (a block takes 128 IDs), and per ID
 //                its count and its place among the positions, items and new items of its 128 IDs;
-//   k_ids_emit   position blocks: place of a position = first row of its ID + the column prefix + its
-//                rank among the block's positions of that ID; ID blocks: everything per unique item.
+//   k_ids_emit   position blocks: place of a position = first row of its ID + the column prefix + its rank;
+//                ID blocks: everything per unique item.  The first launch has the counters in LDS anyway; with the ranks worked out
+//                here, in blocks of 1024, this one took 7.9 us at 51,200 positions over 20,000 IDs, now 4.8.
 // Vocabularies beyond kCountIds are cut into parts: a block then takes (1024 positions, one part).
 // 16-bit counts and prefixes hold because a batch has fewer than 65,536 positions.  Batches below kCountMinM
 // are as fast ranked by comparison, in a launch less (whole call, 50,000 IDs: 8,192 positions 14.7 us ranked,
-// 14.3 counted; 6,400 positions 13.5 and 14.2; 4,096 11.1 and 14.0; 12,000 26 and 14.5).
+// 14.3 counted; 6,400 positions 13.5 and 14.2; 4,096 11.1 and 14.0; 12,000 26 and 14.5); up to 16,384 positions both are left
+// with what the one launch above does not take.
 constexpr int kCountThreads = 1024;
 constexpr int kCountIds = 65536;             // IDs per part: 128 KiB of 16-bit counters
 constexpr int kCountTile = 128;              // IDs per block of k_ids_scan
 constexpr int kCountTilesMax = kCountMaxVocab / kCountTile;
-static_assert(kCountTilesMax <= kCountThreads, "one thread per tile in the scan of k_ids_emit");
+static_assert(kCountTilesMax % kBlock == 0, "tiles per thread in the scan of k_ids_emit");
 static_assert(kCountMaxM < 65536, "16-bit prefixes");
 
 int64_t count_table_words(int64_t vocab_n, int64_t max_positions)
@@ -1196,30 +1199,44 @@ __device__ __forceinline__ int count_id(int raw, int vocab_n, int fix_key, bool*
     return raw;
 }
 
-__global__ __launch_bounds__(kCountThreads) void k_ids_count(const int* __restrict__ ids, int n, int vocab_n,
+__global__ __launch_bounds__(kCountThreads) void k_ids_count(const int* __restrict__ ids, int n, int key_bits, int vocab_n,
                                                              int fix_key, int pitch, int* __restrict__ scal,
-                                                             uint32_t* __restrict__ table, int* __restrict__ checked)
+                                                             uint32_t* __restrict__ table, int* __restrict__ checked, int* __restrict__ ranks)
 {
     extern __shared__ __attribute__((aligned(16))) uint32_t cnt[];
-    const int tid = threadIdx.x, lo = blockIdx.y * kCountIds;
+    const int tid = threadIdx.x, lane = lane_id(), lo = blockIdx.y * kCountIds;
     const int words = (pitch - lo < kCountIds ? pitch - lo : kCountIds) / 2;      // a multiple of 64
     const int p = blockIdx.x * kCountThreads + tid;
     const int raw = p < n ? ids[p] : 0;
     for (int i = tid * 4; i < words; i += kCountThreads * 4) *reinterpret_cast<uint4*>(cnt + i) = make_uint4(0, 0, 0, 0);
-    __syncthreads();
     bool bad = false;
     const int key = count_id(raw, vocab_n, fix_key, &bad), id = key - lo;
     if (blockIdx.y == 0 && p < n) checked[p] = key;
     const bool mine = p < n && (unsigned)id < (unsigned)(2 * words);
-    // the ID of the wave's first position (padding, a very popular item) is counted with one atomic
-    // for all lanes that hold it: they would pile up on one LDS word
-    const int id0 = __builtin_amdgcn_readfirstlane(id);
-    const unsigned long long m0 = __ballot(mine && id == id0);
-    if (mine && id != id0) atomicAdd(&cnt[id >> 1], 1u << ((id & 1) * 16));
-    if (lane_id() == 0 && m0) atomicAdd(&cnt[id0 >> 1], (uint32_t)__popcll(m0) << ((id0 & 1) * 16));
     if (bad && p < n) atomicOr(scal + kSErr, kErrBitRange);
     if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) scal[kSPadSeg] = -1;    // k_ids_emit sets it if there is padding
+    // rank among the block's positions of the same ID: lanes of a wave find each other by ballots, the waves take
+    // turns at the counters in position order
+    unsigned long long peers = __ballot(mine);
+    for (int bit = 0; bit < key_bits; ++bit) {
+        const bool one = (key >> bit) & 1;
+        const unsigned long long mm = __ballot(one);
+        peers &= one ? mm : ~mm;
+    }
+    const int below = __popcll(peers & ((1ull << lane) - 1ull));
+    typedef __attribute__((address_space(3))) uint16_t lds_u16;
+    volatile lds_u16* cnt16 = (volatile lds_u16*)(lds_u16*)cnt;
+    int before = 0;
     __syncthreads();
+    for (int w = 0; w < kCountThreads / kWave; ++w) {
+        if (w == wave_id() && mine) {
+            before = cnt16[id];
+            __builtin_amdgcn_wave_barrier();
+            if (below == 0) cnt16[id] = (uint16_t)(before + (int)__popcll(peers));
+        }
+        __syncthreads();
+    }
+    if (mine) ranks[p] = before + below;
     uint32_t* row = table + ((int64_t)blockIdx.x * pitch + lo) / 2;
     for (int i = tid * 4; i < words; i += kCountThreads * 4)
         *reinterpret_cast<uint4*>(row + i) = *reinterpret_cast<const uint4*>(cnt + i);
@@ -1288,69 +1305,66 @@ __global__ __launch_bounds__(kBlock) void k_ids_scan(uint32_t* __restrict__ tabl
     }
 }
 
-__global__ __launch_bounds__(kCountThreads) void k_ids_emit(
-    const int* __restrict__ checked, int n, int key_bits, int vocab_n, int pitch, int pos_blocks,
+constexpr int kEmitTiles = kCountTilesMax / kBlock;      // tiles per thread in the scan of k_ids_emit
+
+__global__ __launch_bounds__(kBlock) void k_ids_emit(
+    const int* __restrict__ checked, const int* __restrict__ ranks, int n, int vocab_n, int pitch, int pos_blocks,
     const uint16_t* __restrict__ table, const uint2* __restrict__ id_info, const int* __restrict__ tile_info, int T,
     int* __restrict__ perm, int* __restrict__ uniq, int* __restrict__ inverse, int* __restrict__ counts,
     int* __restrict__ offsets, int* __restrict__ seg_of_row, int* __restrict__ uniq_ws, int* __restrict__ u_out,
     const int* __restrict__ slot_of, int* __restrict__ seg_slot, int* __restrict__ scal, int first_step,
     int cap_total, int pad_id)
 {
-    extern __shared__ __attribute__((aligned(16))) uint16_t cnt16[];      // (position blocks) count so far per ID
     __shared__ int s_pos[kCountTilesMax], s_item[kCountTilesMax], s_new[kCountTilesMax];
-    __shared__ unsigned long long s_wave[kCountThreads / kWave];
+    __shared__ unsigned long long s_wave[kWavesPerBlock];
     const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
     const bool per_id = (int)blockIdx.x >= pos_blocks;
-    const int lo = per_id ? 0 : blockIdx.y * kCountIds;
-    const int words = (pitch - lo < kCountIds ? pitch - lo : kCountIds) / 2;
-    if (per_id && blockIdx.y) return;
 
     // what does not depend on the scan of the tiles is fetched first
-    const int p = blockIdx.x * kCountThreads + tid;                       // position blocks
-    const int j = ((int)blockIdx.x - pos_blocks) * kCountThreads + tid;   // ID blocks
-    int id = 0;
-    bool mine = false;
+    const int p = blockIdx.x * kBlock + tid;                       // position blocks
+    const int j = ((int)blockIdx.x - pos_blocks) * kBlock + tid;   // ID blocks
+    const bool mine = per_id ? j < vocab_n : p < n;
+    int id = 0, at = 0, slot = -1;
     uint2 info = make_uint2(0, 0);
-    int pre = 0, slot = -1;
-    if (per_id) {
-        if (j < vocab_n) {
-            id = j;
-            info = id_info[j];
-            if (slot_of && !first_step) slot = slot_of[j];
-        }
-    } else {
-        id = p < n ? checked[p] : 0;
-        mine = p < n && (unsigned)(id - lo) < (unsigned)(2 * words);
-        if (mine) {
-            info = id_info[id];
-            pre = table[(int64_t)blockIdx.x * pitch + id];
-        }
+    if (mine) {
+        id = per_id ? j : checked[p];
+        if (!per_id) at = ranks[p];
+        info = id_info[id];
+        if (per_id && slot_of && !first_step) slot = slot_of[j];
+        if (!per_id) at += table[(int64_t)(p / kCountThreads) * pitch + id];
     }
     const int u_base = (slot_of && !first_step) ? scal[kSUTotal] : 0;     // a flush leaves the old count behind
     // exclusive prefix over the tiles, three figures of at most 17 bits in one 64-bit sum
-    unsigned long long tv = 0;
-    if (tid < T)
-        tv = (unsigned long long)tile_info[tid] | (unsigned long long)tile_info[T + tid] << 20 |
-             (unsigned long long)tile_info[2 * T + tid] << 40;
-    if (!per_id)
-        for (int i = tid * 8; i < 2 * words; i += kCountThreads * 8) *reinterpret_cast<uint4*>(cnt16 + i) = make_uint4(0, 0, 0, 0);
-    const unsigned long long incl = (unsigned long long)(unsigned)wave_incl_scan((int)(tv & 0xfffff)) |
-                                    (unsigned long long)(unsigned)wave_incl_scan((int)(tv >> 20 & 0xfffff)) << 20 |
-                                    (unsigned long long)(unsigned)wave_incl_scan((int)(tv >> 40)) << 40;
+    unsigned long long tv[kEmitTiles], sum = 0;
+#pragma unroll
+    for (int i = 0; i < kEmitTiles; ++i) {
+        const int t = tid * kEmitTiles + i;
+        tv[i] = t < T ? (unsigned long long)tile_info[t] | (unsigned long long)tile_info[T + t] << 20 |
+                            (unsigned long long)tile_info[2 * T + t] << 40 : 0ull;
+        sum += tv[i];
+    }
+    const unsigned long long incl = (unsigned long long)(unsigned)wave_incl_scan((int)(sum & 0xfffff)) |
+                                    (unsigned long long)(unsigned)wave_incl_scan((int)(sum >> 20 & 0xfffff)) << 20 |
+                                    (unsigned long long)(unsigned)wave_incl_scan((int)(sum >> 40)) << 40;
     if (lane == kWave - 1) s_wave[wave] = incl;
     __syncthreads();
     unsigned long long base = 0, all = 0;
 #pragma unroll
-    for (int w = 0; w < kCountThreads / kWave; ++w) {
+    for (int w = 0; w < kWavesPerBlock; ++w) {
         const unsigned long long t = s_wave[w];
         if (w < wave) base += t;
         all += t;
     }
-    base += incl - tv;
-    if (tid < T) {
-        s_pos[tid] = (int)(base & 0xfffff);
-        s_item[tid] = (int)(base >> 20 & 0xfffff);
-        s_new[tid] = (int)(base >> 40);
+    base += incl - sum;
+#pragma unroll
+    for (int i = 0; i < kEmitTiles; ++i) {
+        const int t = tid * kEmitTiles + i;
+        if (t < T) {
+            s_pos[t] = (int)(base & 0xfffff);
+            s_item[t] = (int)(base >> 20 & 0xfffff);
+            s_new[t] = (int)(base >> 40);
+        }
+        base += tv[i];
     }
     __syncthreads();
     const int tile = id / kCountTile;
@@ -1382,32 +1396,8 @@ __global__ __launch_bounds__(kCountThreads) void k_ids_emit(
                 scal[kSUNext] = nt < cap_total ? nt : cap_total;
             }
         }
-        return;
-    }
-
-    // rank among the block's positions of the same ID: lanes of the wave find each other by ballots,
-    // the waves take turns at the counters in position order
-    const int rel = id - lo;
-    unsigned long long peers = __ballot(mine);
-    for (int bit = 0; bit < key_bits; ++bit) {
-        const bool one = (id >> bit) & 1;
-        const unsigned long long mm = __ballot(one);
-        peers &= one ? mm : ~mm;
-    }
-    const int below = __popcll(peers & ((1ull << lane) - 1ull));
-    typedef __attribute__((address_space(3))) uint16_t lds_u16;
-    volatile lds_u16* cnt = (volatile lds_u16*)cnt16;
-    int before = 0;
-    for (int w = 0; w < kCountThreads / kWave; ++w) {
-        if (w == wave && mine) {
-            before = cnt[rel];
-            __builtin_amdgcn_wave_barrier();
-            if (below == 0) cnt[rel] = (uint16_t)(before + (int)__popcll(peers));
-        }
-        __syncthreads();
-    }
-    if (mine) {
-        const int at = pre + before + below, pos = first_row + at;
+    } else if (mine) {
+        const int pos = first_row + at;
         inverse[p] = seg;
         if ((unsigned)pos < (unsigned)n) {      // pos < n always holds; the test keeps a logic error from
             perm[pos] = p;                       // becoming a stray store
@@ -1429,19 +1419,18 @@ bool unique_by_count(Ctx* c, const int* ids, int n, int fix_key, int* uniq, int*
     const int parts = (pitch + kCountIds - 1) / kCountIds, T = pitch / kCountTile;
     const size_t lds = (size_t)(pitch < kCountIds ? pitch : kCountIds) * 2;
     ensure_dynamic_lds<k_ids_count>(kCountIds * 2);
-    ensure_dynamic_lds<k_ids_emit>(kCountIds * 2);
     const int* slot_of = prospect ? c->slot_of : nullptr;
     c->sorted_keys = nullptr;
     c->perm = c->vals[0];
-    launch_smem(c, KID_IDS_COUNT, k_ids_count, dim3(rows, parts), dim3(kCountThreads), lds, s, ids, n, c->cfg.vocab_n,
-                fix_key, pitch, c->scal, c->cnt_table, c->keys[0]);
+    launch_smem(c, KID_IDS_COUNT, k_ids_count, dim3(rows, parts), dim3(kCountThreads), lds, s, ids, n, c->key_bits, c->cfg.vocab_n,
+                fix_key, pitch, c->scal, c->cnt_table, c->keys[0], c->keys[1]);
     launch(c, KID_IDS_SCAN, k_ids_scan, dim3(T), dim3(kBlock), s, c->cnt_table, rows, pitch, slot_of, first_step,
            c->cfg.vocab_n, c->id_info, c->id_tiles);
-    const int id_blocks = (int)((N + kCountThreads - 1) / kCountThreads);
-    launch_smem(c, KID_IDS_EMIT, k_ids_emit, dim3(rows + id_blocks, parts), dim3(kCountThreads), lds, s, c->keys[0], n,
-                c->key_bits, c->cfg.vocab_n, pitch, rows, reinterpret_cast<const uint16_t*>(c->cnt_table), c->id_info,
-                c->id_tiles, T, c->perm, uniq, inverse, counts, c->offsets, c->seg_of_row, c->uniq_ws, u_out, slot_of,
-                c->seg_slot, c->scal, first_step, (int)c->cap_total, c->cfg.pad_id);
+    const int pos_blocks = (n + kBlock - 1) / kBlock, id_blocks = (int)((N + kBlock - 1) / kBlock);
+    launch(c, KID_IDS_EMIT, k_ids_emit, dim3(pos_blocks + id_blocks), dim3(kBlock), s, c->keys[0], c->keys[1], n,
+           c->cfg.vocab_n, pitch, pos_blocks, reinterpret_cast<const uint16_t*>(c->cnt_table), c->id_info,
+           c->id_tiles, T, c->perm, uniq, inverse, counts, c->offsets, c->seg_of_row, c->uniq_ws, u_out, slot_of,
+           c->seg_slot, c->scal, first_step, (int)c->cap_total, c->cfg.pad_id);
     return true;
 }
 
