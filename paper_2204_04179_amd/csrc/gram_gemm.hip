@@ -8,10 +8,12 @@
 //            unique-ID list inside the tile loads (the unique items' features are
 //            never copied), B = W^T.  For large batches its epilogue is the gather
 //            as well: every representation is stored straight to the positions of
-//            its item.  Small and mid-sized batches take k_encode_mid, what that does not take k_encode_bf16.
+//            its item.  Small and mid-sized batches take k_encode_mid or, with long K and a 128 x 128 tile for
+//            every CU, k_encode_square; what those do not take k_encode_bf16.
 //   wgrad:   k_wgrad_tn_bf16 contracts over the rows of the gradient buffer, which
 //            is the slow dimension of both operands in memory, with transposing
 //            LDS reads; split-K over blocks, float32 partials added in split order.
+//            Rows that are bf16 already take k_wgrad_rows_bf16, short windows k_wgrad_short.
 //   Operands are addressed through buffer descriptors (32-bit offsets, out-of-range
 //   reads return zero); matrices beyond the 4 GiB a descriptor can address take the
 //   WIDE variants of both kernels, which form 64-bit addresses per lane.
@@ -731,7 +733,7 @@ __global__ __launch_bounds__(kGemmWaves * 64) void k_encode_square(
 // fit one round, which then takes about 0.6 of a round of whole tiles.  The number of items is known on
 // the device only, so each block works this out, by multiplications: divisions cost the prologue of every
 // block 0.25 us.  (Rounded quotients only move the cut; the grid is made with the same ones.)
-// Measured, all whole / the last ones cut: 56 x 2 tiles (K = 1536, positions stored) 53.5 / 40.5 us, 56 x 6
+// Measured (with loads through registers and slabs of 32; now about a tenth less on both sides), all whole / the last ones cut: 56 x 2 tiles (K = 1536, positions stored) 53.5 / 40.5 us, 56 x 6
 // tiles (K = 768) 55.7 / 51.4, the forward of 204,800 positions 1024 x 1024 to bf16 178 / 169.  Nothing left
 // over, or more than half a round (where a round of halves would be followed by another): the same tiles as
 // before; the cut in the prologue costs up to 1 us there (2 to 3.5 % at 24 of 384 shapes of K 32 to 1024, short K
@@ -1444,16 +1446,16 @@ bool gemm_rows_bf16(Ctx* c, const void* A, int64_t a_rows, int k, const int* row
     if (B_plain && takes_mid_kernel(a_rows, k, n_out, epi)) {
         const uint32_t x_bytes = (uint32_t)(a_rows * k * 2), w_bytes = (uint32_t)((int64_t)k * n_out * 2);
         // The number of items is known on the device only, and the kernel chooses between tiles of 64 and 128
-        // rows by it: the lower ones up to one per CU.  Only the 128 x 128 tiles (blocks of 1,024 threads) have to be
+        // rows by it: the lower ones up to one per CU.  Only the 128 x 128 tiles (k_encode_square) have to be
         // chosen here, from a guess: all IDs of a vocabulary met many times over, 0.6 of one met a few times, else
         // 0.4 of the positions (Zipf laws of the tests and the benchmark: 0.22 to 0.6).  They gain where about one of them
-        // falls to a CU, the more the longer K is; up to K = 256 a guess that fails costs more than they gain.
-        // Event to event with cold operands, position copies included, in us for 64 x 64 / 128 x 64 / 128 x 128 tiles (the
-        // 64-row kernel in brackets): 1,200 items 768 x 776 19.5 / 19.4 / 22.1 (18.0); 4,000 items 1544 x 256
-        // 24.9 / 30.5 / 35.8 (25.0); 10,200 items 1544 x 264 57.1 / 53.3 / 44.0 (65.1); 17,300 items 264 x 192
-        // 33.9 / 32.3 / 37.8 (33.0).  Over 4,264 shapes (K 64 to 1,544, widths 8 to 1,024, 2,000 to 51,200 positions, distinct
-        // and Zipf) its time is 0.927 of the 64-row kernel's in the geometric mean; it is slower by more than 3 % at 161, by
-        // up to 19 %.  (All three shapes by the guess: 0.937, 257, 25 %.)
+        // falls to a CU, the more the longer K is; up to K = 256 a guess that fails costs more than they gain: chosen from
+        // K > 128 and from fewer tiles they were 3 to 20 % faster where most positions name an item of their own and 5 to 16 %
+        // slower where few do.  (One kernel that holds all three shapes and goes by the number of items: more than 2 % slower at
+        // 79 of 287 shapes, since every block then asks for 128 KiB of LDS and a CU holds one.)
+        // Event to event with cold operands, position copies included, in us for 64 x 64 / 128 x 64 tiles (the
+        // 64-row kernel in brackets): 1,200 items 768 x 776 19.5 / 19.4 (18.0); 4,000 items 1544 x 256
+        // 24.9 / 30.5 (25.0); 17,300 items 264 x 192 33.9 / 32.3 (33.0).
         int64_t guess = rows_max;
         if (n_dev != c->scal + kSChunkN)
             guess = c->cur_m >= 8 * (int64_t)c->cfg.vocab_n ? rows_max : c->cur_m >= c->cfg.vocab_n ? rows_max * 3 / 5 : rows_max * 2 / 5;
@@ -1553,7 +1555,7 @@ bool encode_forward(Ctx* c, const void* X, const void* W, const int* uniq, const
 // padding item or a column past the matrix edge is turned into an out-of-range
 // offset, for which the hardware returns zeros.  WIDE (an operand beyond the 4 GiB
 // of a descriptor): plain 64-bit addresses, and such a load is skipped instead.
-// Same pipeline as k_gemm_nt_bf16: register-staged loads, two LDS stages, one
+// Loads go through registers (the float32 rows are rounded there), two LDS stages, one
 // barrier per slab of 32 buffer rows; split-K with one K range per XCD.
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef short v8i16 __attribute__((ext_vector_type(8)));
@@ -1585,7 +1587,8 @@ struct WgradExport {
     int* u_total_dev;          // nullable
     int* scal;
 };
-// GB: the rows are bf16 already (what an earlier contraction stored rounded).
+// GB: the rows are bf16 already (what an earlier contraction stored rounded); only with WIDE, what a descriptor can
+// address takes k_wgrad_rows_bf16.
 template <int NW, bool WIDE = false, bool EXPORT = false, bool GB = false>
 __global__ __launch_bounds__(NW * 64) void k_wgrad_tn_bf16(
     const uint16_t* __restrict__ X, uint32_t x_bytes, const int* __restrict__ id_of_slot,
