@@ -528,8 +528,8 @@ __global__ __launch_bounds__(MidShape::kThreads, 4) void k_encode_mid(
 // chunk each lane fetches.
 // Operands are addressed through buffer descriptors (base + 32-bit byte offset); a matrix A beyond the 4 GiB such
 // a descriptor can address takes the WIDE variant, whose lanes keep 64-bit row pointers (every address it
-// forms is a valid one: rows past the end are clamped).  K is a multiple of 32; where half a slab is left, the
-// other half of its stage holds whatever was loaded and is not multiplied.
+// forms is a valid one: rows past the end are clamped).  K is a multiple of 32; an odd one is made up by the first slab, of
+// which only the lower half is multiplied, so that no slab reaches behind a row (see gram_mid_rows.h).
 constexpr int TM = 256, TN = 256, TK = 64;
 constexpr int kGemmWaves = 8;
 constexpr int TROWB = TK * 2;                          // bytes per LDS row of a K-contiguous operand
@@ -799,6 +799,7 @@ __device__ __forceinline__ void gemm_nt_tile(
     if (tid < TM / 32) s_pad_rows[tid] = 0;      // one bit per row of the tile: the padding item
     __syncthreads();
 
+    static_assert(TK == kBigSlab, "the slabs of gram_mid_rows.h");
     const int nslab = (ktot + TK - 1) / TK;
 
     // A load moves 8 rows of A (lane l: position l & 7 of row l >> 3).  Wave w moves groups MH w + t of either half:
@@ -807,7 +808,6 @@ __device__ __forceinline__ void gemm_nt_tile(
     const u32x4 rsA = buffer_words(A, a_bytes), rsB = buffer_words(B, b_bytes);
     uint32_t oa[2][MH], la[2][MH];
     const unsigned char* pa[2][WIDE ? MH : 1];
-    bool a_upper[2][WIDE ? MH : 1];          // the lane's chunk lies in the upper half of the slab
     const int a_chunk = (lane & 7) ^ (lane >> 4 & 3);     // of the rows with (row >> 1 & 4) == 0; the others: ^ 4
     int ids[2][MH], zids[2][MH];             // (the two-layer encoder's second contraction tells the padding item by another list than its rows)
 #pragma unroll
@@ -824,12 +824,9 @@ __device__ __forceinline__ void gemm_nt_tile(
     for (int h = 0; h < 2; ++h)
 #pragma unroll
         for (int t = 0; t < MH; ++t) {
-            const int chunk = a_chunk ^ ((wave * MH + t) & 1) * 4;
+            const int chunk = big_slab_part(a_chunk ^ ((wave * MH + t) & 1) * 4, 8, ktot);
             oa[h][t] = (uint32_t)(((int64_t)ids[h][t] * lda + chunk * 8) * 2);
-            if (WIDE) {
-                pa[h][t] = reinterpret_cast<const unsigned char*>(A) + ((int64_t)ids[h][t] * lda + chunk * 8) * 2;
-                a_upper[h][t] = chunk >= 4;
-            }
+            if (WIDE) pa[h][t] = reinterpret_cast<const unsigned char*>(A) + ((int64_t)ids[h][t] * lda + chunk * 8) * 2;
         }
     // A load moves 2 rows of W [k, n] (columns past n are clamped to the last chunk: their products are never
     // stored) or 8 rows of the K-contiguous B.  Wave w moves 4 of them in a row.
@@ -840,15 +837,14 @@ __device__ __forceinline__ void gemm_nt_tile(
             const int krow = (wave * 4 + t) * 2 + (lane >> 5);
             int ncol = n0 + (((lane & 31) ^ ((krow & 3) << 2)) << 3);
             if (ncol > n - 8) ncol = n - 8;
-            ob[t] = (uint32_t)(((int64_t)krow * ldb + ncol) * 2);
+            ob[t] = (uint32_t)(((int64_t)big_slab_part(krow, 1, ktot) * ldb + ncol) * 2);
         } else {
             const int r = (wave * 4 + t) * 8 + (lane >> 3), nn = n0 + r < n ? n0 + r : n - 1;
-            ob[t] = (uint32_t)(((int64_t)nn * ldb + ((lane & 7) ^ (r >> 1 & 7)) * 8) * 2);
+            ob[t] = (uint32_t)(((int64_t)nn * ldb + big_slab_part((lane & 7) ^ (r >> 1 & 7), 8, ktot) * 8) * 2);
         }
     }
-    const uint32_t b_slab_bytes = BDIRECT ? (uint32_t)(TK * ldb * 2) : (uint32_t)(TK * 2);
-    // (the waves that move the second 32 rows of a slab of W stop a slab earlier where half a slab is left)
-    const int last = nslab - 1, last_b = BDIRECT && wave >= 4 && (ktot & 32) && last > 0 ? last - 1 : last;
+    const uint32_t b_k_bytes = BDIRECT ? (uint32_t)(ldb * 2) : 2u;
+    const int last = nslab - 1;
     typedef __attribute__((address_space(3))) unsigned char lds_u8;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)smem, lds_b = lds0 + 2 * TOPB + wave * 4096;
 
@@ -901,13 +897,13 @@ __device__ __forceinline__ void gemm_nt_tile(
     typedef __attribute__((address_space(3))) const bf16x8 lds_frag;
 #define GRAM_LOAD_A(H, SLAB)                                                                        \
     {                                                                                               \
-        const int s_ = (SLAB) < last ? (SLAB) : last;                                               \
+        const uint32_t k_ = (uint32_t)big_slab_start(SLAB, last, ktot) * 2u;                        \
         const uint32_t to_ = lds0 + ((SLAB) & 1) * TOPB;                                            \
         u32x4 rs_ = rsA;                                                                            \
         rs_.z = (SLAB) <= last ? rs_.z : 0u;                                                        \
-        const uint32_t so_ = (SLAB) <= last ? (uint32_t)s_ * (TK * 2) : 0u;                         \
+        const uint32_t so_ = (SLAB) <= last ? k_ : 0u;                                              \
         _Pragma("unroll") for (int g_ = 0; g_ < MH; ++g_) {                                         \
-            if (WIDE) load_to_lds(pa[H][g_] + (int64_t)s_ * (TK * 2) - (a_upper[H][g_] && s_ * TK + 32 >= ktot ? 64 : 0), to_ + la[H][g_]); \
+            if (WIDE) load_to_lds(pa[H][g_] + k_, to_ + la[H][g_]);                                 \
             else load_to_lds(rs_, oa[H][g_], so_, to_ + la[H][g_]);                                 \
         }                                                                                           \
     }
@@ -915,7 +911,7 @@ __device__ __forceinline__ void gemm_nt_tile(
     {                                                                                               \
         u32x4 rs_ = rsB;                                                                            \
         rs_.z = (SLAB) <= last ? rs_.z : 0u;                                                        \
-        const uint32_t k_ = (uint32_t)((SLAB) < last_b ? (SLAB) : last_b) * b_slab_bytes;           \
+        const uint32_t k_ = (uint32_t)big_slab_start(SLAB, last, ktot) * b_k_bytes;                 \
         const uint32_t to_ = lds_b + ((SLAB) & 1) * TOPB;                                           \
         _Pragma("unroll") for (int g_ = 0; g_ < 4; ++g_)                                            \
             load_to_lds(rs_, ob[BDIRECT ? g_ & 1 : g_], (SLAB) <= last ? (BDIRECT ? k_ + (uint32_t)(g_ >> 1) * (uint32_t)(8 * ldb) : k_) : 0u, to_ + g_ * 1024); \
@@ -936,19 +932,19 @@ __device__ __forceinline__ void gemm_nt_tile(
                 fb[j][ks] = *(lds_frag*)(uintptr_t)(rb[BDIRECT ? 0 : ks] + (STAGE) * TOPB + j * (32 * TROWB)); \
             }                                                                                       \
         }
-    // (of a last half slab, what lies behind K is some other row's and may be anything: it is not multiplied)
+    // (of a half slab the upper half is the next slab's: it is not multiplied here)
 #define GRAM_MMA_STEPS(H, FROM)                                                                     \
     _Pragma("unroll") for (int ks = (FROM); ks < (FROM) + 2; ++ks)                                  \
         _Pragma("unroll") for (int i = 0; i < MH; ++i)                                              \
             _Pragma("unroll") for (int j = 0; j < NT; ++j)                                          \
                 acc[(H) * MH + i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i][ks], fb[j][ks], acc[(H) * MH + i][j], 0, 0, 0);
-#define GRAM_MMA(H, SL)                                                                             \
+#define GRAM_MMA(H, SL, STAGE)                                                                      \
     __builtin_amdgcn_s_setprio(1);                                                                  \
     GRAM_MMA_STEPS(H, 0)                                                                            \
-    if ((SL) != half_at) { GRAM_MMA_STEPS(H, 2) }                                                   \
+    if ((STAGE) == 1 || (SL) != half_at) { GRAM_MMA_STEPS(H, 2) }                                   \
     __builtin_amdgcn_s_setprio(0);
     // Loads in flight at the end of a reading segment: what its successors wait for was issued before the last
-    // kAhead (a slab's worth).  Slabs past the end reload the last one (never multiplied).
+    // kAhead (a slab's worth).  Slabs past the end write zeros (WIDE: the last one again) and are never multiplied.
     constexpr int kAhead = 4 + 2 * MH;
 #define GRAM_SLAB(SL, STAGE)                                                                        \
     {                                                                                               \
@@ -959,7 +955,7 @@ __device__ __forceinline__ void gemm_nt_tile(
         wait_loads<kAhead>();                                                                       \
         wait_lds();                                                                                 \
         segment_barrier();                                                                          \
-        GRAM_MMA(0, SL)                                                                             \
+        GRAM_MMA(0, SL, STAGE)                                                                      \
         segment_barrier();                                                                          \
         GRAM_READ_A(1, STAGE)                                                                       \
         __builtin_amdgcn_sched_barrier(0);                                                          \
@@ -969,7 +965,7 @@ __device__ __forceinline__ void gemm_nt_tile(
         wait_lds();                                                                                 \
         if (epi_subtracts(EPI) && (SL) == last) { GRAM_AUX(0) }                                     \
         segment_barrier();                                                                          \
-        GRAM_MMA(1, SL)                                                                             \
+        GRAM_MMA(1, SL, STAGE)                                                                      \
         segment_barrier();                                                                          \
     }
     // (subtracting) the targets of the epilogue's first round are requested ahead of the last products
@@ -996,7 +992,7 @@ __device__ __forceinline__ void gemm_nt_tile(
     wait_loads<kAhead>();
     segment_barrier();
     if (wm == 1) segment_barrier();          // the lower row half runs a segment behind
-    const int half_at = ktot & 32 ? last : -1;
+    const int half_at = big_half_slab(ktot);
     int sl = 0;
     for (; sl < last; sl += 2) {
         GRAM_SLAB(sl, 0)

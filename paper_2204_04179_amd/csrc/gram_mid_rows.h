@@ -1,5 +1,6 @@
-// Which entries of the row list and which rows of A the forward of small and mid-sized batches
-// (k_encode_mid) asks memory for.  Plain C++ as well as device code, so that the limits can be walked on the CPU.
+// Which entries of the row list and which parts of A the forward of small and mid-sized batches (k_encode_mid,
+// k_encode_square) and the 256-row contraction (k_gemm_nt_bf16) ask memory for.  Plain C++ as well as device code, so that
+// the limits can be walked on the CPU.
 #pragma once
 #include <stdint.h>
 
@@ -28,5 +29,25 @@ GRAM_HD uint32_t mid_slab_offset(uint32_t row_offset, int k0, int xk, int d_in)
 {
     return k0 + xk < d_in && row_offset != kPastEnd ? row_offset + (uint32_t)k0 * 2u : kPastEnd;
 }
+
+// ---- the 256-row contraction: slabs of 64 along K (a multiple of 32) -----------------------------
+//
+// An odd multiple leaves half a slab: it is the first, 64 elements of which only the lower 32 are multiplied, and the second
+// starts at 32.  (As the last one, its upper half would lie behind the row, and behind the matrix for the last row.)  For
+// K = 32 both halves of the one slab hold the row.
+constexpr int kBigSlab = 64;
+
+// First element of a slab; slabs past the last are the last one again.
+GRAM_HD int big_slab_start(int slab, int last, int k)
+{
+    const int at = (slab < last ? slab : last) * kBigSlab - (k & 32);
+    return at > 0 ? at : 0;
+}
+
+// The part of a slab (of `size` elements of K each) that a load for part `part` fetches, counted from the slab's start.
+GRAM_HD int big_slab_part(int part, int size, int k) { return k < kBigSlab ? part & (32 / size - 1) : part; }
+
+// The slab whose upper half is not multiplied, -1 if there is none.
+GRAM_HD int big_half_slab(int k) { return k & 32 ? 0 : -1; }
 
 }  // namespace gram
