@@ -959,16 +959,21 @@ __device__ __forceinline__ void gemm_nt_tile(
         segment_barrier();                                                                          \
         GRAM_READ_A(1, STAGE)                                                                       \
         __builtin_amdgcn_sched_barrier(0);                                                          \
-        GRAM_LOAD_B((SL) + 2)                                                                       \
-        GRAM_LOAD_A(0, (SL) + 2)                                                                    \
-        wait_loads<kAhead>();                                                                       \
+        if (epi_subtracts(EPI) && (SL) == last) {                                                   \
+            wait_loads<0>();                                                                        \
+            GRAM_AUX(0)                                                                             \
+        } else {                                                                                    \
+            GRAM_LOAD_B((SL) + 2)                                                                   \
+            GRAM_LOAD_A(0, (SL) + 2)                                                                \
+            wait_loads<kAhead>();                                                                   \
+        }                                                                                           \
         wait_lds();                                                                                 \
-        if (epi_subtracts(EPI) && (SL) == last) { GRAM_AUX(0) }                                     \
         segment_barrier();                                                                          \
         GRAM_MMA(1, SL, STAGE)                                                                      \
         segment_barrier();                                                                          \
     }
-    // (subtracting) the targets of the epilogue's first round are requested ahead of the last products
+    // (subtracting) the targets of the epilogue's first round are requested ahead of the last products, behind the wait for
+    // whatever still lands in the stages: these are loads of the compiler's, which no count of the kernel's may include
     f32x4_ av[epi_subtracts(EPI) ? RPW : 1];
 #define GRAM_AUX(I)                                                                                 \
     _Pragma("unroll") for (int u = 0; u < (epi_subtracts(EPI) ? RPW : 0); ++u) {                    \
@@ -1000,7 +1005,7 @@ __device__ __forceinline__ void gemm_nt_tile(
     }
     if (sl == last) GRAM_SLAB(sl, 0)
     if (wm == 0) segment_barrier();
-    wait_loads<epi_subtracts(EPI) ? RPW : 0>();      // the stages become the epilogue's (behind its barrier)
+    if (!epi_subtracts(EPI)) wait_loads<0>();        // the stages become the epilogue's (behind its barrier)
 
     // accumulator element r of a lane sits at (row, col) = ((r / 4) * 8 + (lane / 32) * 4 + r % 4, lane % 32)
     // the rows a wave stores are the 32 of MFMA row block i of its wave row: their padding bits

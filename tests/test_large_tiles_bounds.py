@@ -66,3 +66,18 @@ def test_the_kernel_uses_these_functions():
     # the offsets of a load: the lane's, which big_slab_part enters, and the slab's start, nothing else along K
     loads = body[body.index("#define GRAM_LOAD_A("):body.index("#define GRAM_READ_A(")]
     assert "TK" not in loads and "load_to_lds(rs_, oa[H][g_], so_," in loads and "load_to_lds(pa[H][g_] + k_," in loads
+
+
+def test_the_epilogue_waits_for_every_load_to_its_stages():
+    """The stages of the main loop become the epilogue's: each wave has waited for all its loads to them before its last
+    barrier of the loop, whatever else it has requested since."""
+    body = _tile_source()
+    slab = body[body.index("#define GRAM_SLAB("):body.index("// (subtracting) the targets")]
+    # subtracting, last slab: wait for all, then the targets, and no load to the stages behind that
+    at = slab.index("if (epi_subtracts(EPI) && (SL) == last) {")
+    end = slab.index("} else {", at)
+    assert slab.index("wait_loads<0>();", at) < slab.index("GRAM_AUX(0)", at) < end
+    assert "GRAM_LOAD" not in slab[at:end] and "GRAM_LOAD" not in slab[slab.index("wait_lds();", end):]
+    # the other forms: wait for all behind the loop
+    tail = body[body.index("if (sl == last) GRAM_SLAB("):]
+    assert tail.index("if (!epi_subtracts(EPI)) wait_loads<0>();") < tail.index("__syncthreads()") and "wait_loads<" not in tail[tail.index("__syncthreads()"):]
