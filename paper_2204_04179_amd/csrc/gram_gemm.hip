@@ -1081,7 +1081,7 @@ __device__ __forceinline__ void gemm_nt_tile(
     } else if constexpr (EPI == kEpiReluBf16 || EPI == kEpiGateBf16) {
         // Straight from the accumulators: neighbouring lanes exchange a value, so that the even one holds two columns of its row
         // r and the odd one of row r + 1, 4 bytes each, 64 bytes of four rows per store.  What lies behind M or n falls out of
-        // the descriptors.  32,768 x 1024 x 1024 with the rectifier 69 us, 72 through LDS (49,152 rows: 102.5, 106).  The
+        // the descriptors: by the lane's own offset, the only one that the range check is sure to cover.  32,768 x 1024 x 1024 with the rectifier 69 us, 72 through LDS (49,152 rows: 102.5, 106).  The
         // modes with float32 targets are better off in whole row pieces: subtracting 97 us through LDS, 100 straight.
         const int rows = M - m0 < TM ? M - m0 : TM, odd = lane & 1;
         const __amdgpu_buffer_rsrc_t rsC = __builtin_amdgcn_make_buffer_rsrc(
@@ -1095,6 +1095,7 @@ __device__ __forceinline__ void gemm_nt_tile(
             const int col = n0 + wn * 64 + j * 32 + (lane & 31);
             at[j] = col < n ? ((uint32_t)(wm * (MI * 32) + (lane >> 5) * 4 + odd) * (uint32_t)ldc + (uint32_t)(col - odd)) * 2u : kOutOfRange;
         }
+        auto below = [&](uint32_t from, int down) { return __builtin_elementwise_add_sat(from, (uint32_t)down * (uint32_t)ldc * 2u); };
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
             // register pair r (even): rows i * 32 + (r / 4) * 8 + r % 4 and the next, + 4 (lane / 32)
@@ -1104,7 +1105,7 @@ __device__ __forceinline__ void gemm_nt_tile(
                 for (int j = 0; j < NT; ++j)
 #pragma unroll
                     for (int p = 0; p < 8; ++p)
-                        av[j][p] = __builtin_amdgcn_raw_buffer_load_b32(rsX, at[j], (int)((i * 32 + (p >> 1) * 8 + (p & 1) * 2) * (uint32_t)ldc * 2u), 0);
+                        av[j][p] = __builtin_amdgcn_raw_buffer_load_b32(rsX, below(at[j], i * 32 + (p >> 1) * 8 + (p & 1) * 2), 0, 0);
             const uint32_t pads = s_pad_rows[wm * MI + i] >> ((lane >> 5) * 4);
 #pragma unroll
             for (int j = 0; j < NT; ++j)
@@ -1118,7 +1119,7 @@ __device__ __forceinline__ void gemm_nt_tile(
                     uint32_t h = odd ? pack_bf16x2(got, hi) : pack_bf16x2(lo, got);
                     if (EPI == kEpiGateBf16)        // open where the activation is positive
                         h &= ((av[j][p] & 0xffffu) - 1u < 0x7fffu ? 0xffffu : 0u) | ((av[j][p] >> 16) - 1u < 0x7fffu ? 0xffff0000u : 0u);
-                    __builtin_amdgcn_raw_buffer_store_b32(h, rsC, at[j], (int)((i * 32 + row) * (uint32_t)ldc * 2u), 0);
+                    __builtin_amdgcn_raw_buffer_store_b32(h, rsC, below(at[j], i * 32 + row), 0, 0);
                 }
         }
     } else if constexpr (EPI == kEpiPlain) {
@@ -1131,6 +1132,7 @@ __device__ __forceinline__ void gemm_nt_tile(
             const int col = n0 + wn * 64 + j * 32 + (lane & 31);
             at[j] = col < n ? ((uint32_t)(wm * (MI * 32) + (lane >> 5) * 4) * (uint32_t)ldc + (uint32_t)col) * 4u : kOutOfRange;
         }
+        auto below = [&](uint32_t from, int down) { return __builtin_elementwise_add_sat(from, (uint32_t)down * (uint32_t)ldc * 4u); };
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
             const uint32_t pads = s_pad_rows[wm * MI + i] >> ((lane >> 5) * 4);
@@ -1139,7 +1141,7 @@ __device__ __forceinline__ void gemm_nt_tile(
 #pragma unroll
                 for (int j = 0; j < NT; ++j) {
                     const int row = (r >> 2) * 8 + (r & 3);
-                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(pads >> row & 1 ? 0.f : acc[i][j][r]), rsC, at[j], (int)((i * 32 + row) * (uint32_t)ldc * 4u), 0);
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(pads >> row & 1 ? 0.f : acc[i][j][r]), rsC, below(at[j], i * 32 + row), 0, 0);
                 }
         }
     } else {

@@ -871,6 +871,7 @@ def test_mlp_encoder_step_with_tiles_for_every_compute_unit():
     U = ref["uniq"].size
     assert U > 65536
     out = run_mlp_step(X, W1, W2, ids, dH, n, [U])
+    assert out["A1_tail_untouched"]
     assert_close(out["E"], ref["E"], TOL[wl.BF16], "E")
     np.testing.assert_array_equal(out["H"], out["E"][out["inverse"]])
     assert_close(out["dW1"], ref["dW1"], TOL[wl.BF16], "dW1")

@@ -81,3 +81,15 @@ def test_the_epilogue_waits_for_every_load_to_its_stages():
     # the other forms: wait for all behind the loop
     tail = body[body.index("if (sl == last) GRAM_SLAB("):]
     assert tail.index("if (!epi_subtracts(EPI)) wait_loads<0>();") < tail.index("__syncthreads()") and "wait_loads<" not in tail[tail.index("__syncthreads()"):]
+
+
+def test_stores_are_bounded_by_their_own_offset():
+    """The range check of a raw buffer access is only sure to cover the lane's offset, so the row of a store or of the
+    activation beside it stands in that, and the scalar offset is zero."""
+    import re
+    body = _tile_source()
+    calls = re.findall(r"raw_buffer_(?:load|store)_b32\((.*)\);", body)
+    assert len(calls) == 3
+    for args in calls:
+        assert re.search(r"rs[CX], below\(at\[j\], .*\), 0, 0$", args), args
+    assert body.count("add_sat(from, ") == 2
