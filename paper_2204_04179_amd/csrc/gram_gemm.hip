@@ -1903,7 +1903,8 @@ __global__ __launch_bounds__(kWgradWaves * 64) void k_wgrad_rows_bf16(
     typedef __attribute__((address_space(3))) unsigned char lds_u8;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)smem, to_w = lds0 + wave * 2048;
     // entries of the list: ring of 4 pieces of 256, piece k holds those of slabs 8 k .. 8 k + 7 of the block's range
-    const u32x4 rsI = buffer_words(row_list, LISTED ? (uint32_t)row_end * 4u : 0u);
+    // (its descriptor ends with a whole load of 4 entries, so that no load is partly out of range: the list has the room)
+    const u32x4 rsI = buffer_words(row_list, LISTED ? ((uint32_t)row_end + 3u & ~3u) * 4u : 0u);
     const uint32_t list0 = lds0 + PSTAGES * PSTAGEB, list_l = list0 + (uint32_t)(wave * 4 + (lane >> 5)) * 4u;
     typedef const __attribute__((address_space(3))) int lds_i32;
 #define GRAM_IDS(PIECE)                                                                             \

@@ -340,7 +340,7 @@ struct WgradRows {
     int64_t n_max;
     int64_t x_rows = 0;
     int d_in = 0, d = 0, pad_id = -1;
-    bool rows_bf16 = false;     // rows[] is bf16, rounded by the kernel that wrote it
+    bool rows_bf16 = false;     // rows[] is bf16, rounded by the kernel that wrote it; ids[] is read to a multiple of 4 entries
 };
 // Weight gradient over the buffer rows [first_row, first_row + n_rows) (clipped to the rows held),
 // or over the rows of `other`, written to dW or added to it.
