@@ -10,6 +10,11 @@ pytestmark = pytest.mark.gpu
 def _batch(rng, m, n, kind):
     if kind == "few":                       # a handful of items: long runs, every slice sees equal IDs
         ids = rng.choice(np.array([0, 1, n // 2, n - 1]), size=m)
+    elif kind == "one":                     # one item that is not padding in every position but the last few
+        ids = np.full(m, n // 2 + 1)
+        ids[m - min(m, 5):] = rng.integers(0, n, size=min(m, 5))
+    elif kind == "runs":                    # sorted: runs that begin anywhere in a thread's four positions
+        ids = np.sort(np.minimum((rng.pareto(0.7, size=m) * 3).astype(np.int64), n - 1))
     elif kind == "distinct_first":          # ascending, then all equal
         ids = np.minimum(np.arange(m), n - 1)
     else:                                   # popular items, padding, the largest ID
@@ -214,3 +219,10 @@ def test_one_launch_padding_and_bad_ids(m, n, pad):
     want = np.where(items == pad_id, 0, total[items])
     np.testing.assert_array_equal(Gt.cpu().numpy()[:T, 0], want)
     g.close()
+
+
+# Four neighbouring positions of one ID are counted at once
+@pytest.mark.parametrize("m,n", [(513, 8), (1001, 300_000), (8190, 20_000), (12_288, 300_000), (16_384, 20_000)])
+@pytest.mark.parametrize("kind", ["one", "runs"])
+def test_one_launch_of_equal_neighbours(m, n, kind):
+    check_dedup_window(m, n, kind, m_last=m - 2)
