@@ -778,19 +778,33 @@ __global__ __launch_bounds__(kSmallThreads) void k_emit_small(
 // (whose positions' places among their ID's positions are thereby known), then the rest.  A scan over the keys gives
 // every key its first row and its number among the items; each thread of the slice writes what is known of its position
 // and, if it is its ID's first, of the item.  Nothing passes between blocks.
-//   BITS = false: the key is the ID (16-bit counts of all IDs in LDS: up to about 56,000).
+//   BITS = false: the key is the ID (16-bit counts of all IDs in LDS: up to about 56,000, less for small batches).
 //   BITS = true:  a bitmap of the IDs that occur is made first and the key is the ID's number among them: any
 //                 vocabulary whose bitmap and its prefix fit (0.19 bytes per ID: 524,288), up to kOnceBitsM positions.
 // What bounds it is the LDS atomic per ID, about 30 to 45 cycles per wave (lanes of a wave that meet on a bank): nothing at
 // 6,400 positions, most of the time at 50,000.  Lanes that meet on one counter wait for each other, about 130 cycles where all 64
 // do: 16,384 positions of one item 20.1 us, so a thread whose four positions hold one ID counts them with one atomic: 10.0 us,
 // sorted IDs 13.2 -> 8.9, Zipf 1.2 10.0 as before.  (Finding such lanes by ballots costs every batch 0.3 to 1 us.)  What is left:
-// half of the positions one item in no order 13.2 us (11.6 in three launches), two items alone 13.7 (11.0).  Whole call, ranks or counting dedup / one launch: 1,000 positions 8.1 / 6.3 us,
-// 6,400 over 13,000 IDs 13.3 / 6.6, 7,040 over 100,000 14.0 / 9.8, 12,000 over 300,000 26.7 / 12.9, 16,000 over 20,000
+// half of the positions one item in no order 13.2 us (11.6 in three launches), two items alone 13.7 (11.0).
+// Whole call, ranks or counting dedup / one launch: 1,000 positions 8.1 / 6.3 us, 6,400 over 13,000 IDs 13.3 / 6.6, 7,040 over 100,000 14.0 / 9.8, 12,000 over 300,000 26.7 / 12.9, 16,000 over 20,000
 // 12.3 / 10.6, 25,600 12.7 / 14.1 (padded histories 12.9 / 10.8), 51,200 13.8 / 23.3: the line lies at 16,384.
+// Small batches over large vocabularies go by the bitmap, which passes over IDs that do not occur sooner, in later steps all
+// the more (by ID, every block looks at every ID's slot): 520 positions over 50,000 IDs, by ID / by bitmap, first step 7.5 / 6.7,
+// later 10.8 / 7.8 (in two launches 8.3); later, 2,048 over 20,000 8.5 / 8.1, 4,000 over 50,000 11.1 / 9.2; 4,000 in a first step
+// 7.9 / 7.8, with many equal IDs 9.1 / 9.6.
+// Later steps of what the counting dedup takes too (from 8,193 positions) are left to it where the look-ups cost more than its two
+// launches: one launch / counting, 10,000 positions over 50,000 IDs Zipf 0.9 to 1.2 12.3 to 13.4 / 12.4, over 100,000 uniform
+// 16.7 / 14.5, 12,000 19.4 / 14.8; over 30,000 10.5 to 11.7 / 11.4, 16,384 over 13,000 9.8 to 11.8 / 11.2.
 // The outputs must not overlap the IDs (other blocks still read those): such calls take the ways below.
+// (constants of the counting dedup)
+constexpr int kCountThreads = 1024;
+constexpr int kCountIds = 65536;             // IDs per part: 128 KiB of 16-bit counters
+constexpr int kCountTile = 128;              // IDs per block of k_ids_scan
+constexpr int kCountTilesMax = kCountMaxVocab / kCountTile;
+
 constexpr int kOnceThreads = 1024, kOnceWaves = kOnceThreads / kWave;
 constexpr int kOnceMaxM = 16384, kOnceBitsM = 12288;
+constexpr int kOnceLaterIds = 40960;         // in later steps, where the counting dedup takes the batch too
 constexpr int kOnceSlice = 256;              // positions per block, at most
 constexpr int kOnceRounds = 8;               // groups of 8 keys per thread, at most
 constexpr size_t kOnceLds = 156 * 1024;      // dynamic; beside it 3 KiB
@@ -1118,6 +1132,14 @@ static bool overlap(const void* a, int64_t a_bytes, const void* b, int64_t b_byt
     return a && b && x < y + (uintptr_t)b_bytes && y < x + (uintptr_t)a_bytes;
 }
 
+static bool counting_takes(const Ctx* c, int n)
+{
+    const int64_t N = c->cfg.vocab_n;
+    if (!c->cnt_table || n < kCountMinM || n > kCountMaxM || N > kCountMaxVocab) return false;
+    const int64_t rows = (n + kCountThreads - 1) / kCountThreads, pitch = (N + kCountTile - 1) / kCountTile * kCountTile;
+    return rows * pitch / 2 <= kCountMaxWords;
+}
+
 // Returns false where the one-launch dedup does not apply.
 bool unique_once(Ctx* c, const int* ids, int n, int fix_key, int* uniq, int* inverse, int* counts, int* u_out,
                  hipStream_t s, bool prospect, int first_step)
@@ -1125,7 +1147,9 @@ bool unique_once(Ctx* c, const int* ids, int n, int fix_key, int* uniq, int* inv
     if (n <= kFusedMaxN || n > kOnceMaxM) return false;
     const int N = c->cfg.vocab_n;
     const bool slots = prospect && !first_step;
-    const bool by_id = N <= 8 * kOnceRounds * kOnceThreads && OnceLayout(false, slots, n, N).bytes <= kOnceLds;
+    if (slots && N > kOnceLaterIds && counting_takes(c, n)) return false;
+    const int most_by_id = n > (slots ? 4096 : 2048) ? 8 * kOnceRounds * kOnceThreads : slots && n <= 2048 ? 16384 : 32768;
+    const bool by_id = N <= most_by_id && OnceLayout(false, slots, n, N).bytes <= kOnceLds;
     const bool by_bits = !by_id && n <= kOnceBitsM && N <= 128 * 4 * kOnceThreads && OnceLayout(true, slots, n, N).bytes <= kOnceLds;
     if (!by_id && !by_bits) return false;
     const int64_t ids_bytes = (int64_t)n * 4, items_bytes = (int64_t)(n < N ? n : N) * 4;
@@ -1180,10 +1204,6 @@ bool unique_once(Ctx* c, const int* ids, int n, int fix_key, int* uniq, int* inv
 // are as fast ranked by comparison, in a launch less (whole call, 50,000 IDs: 8,192 positions 14.7 us ranked,
 // 14.3 counted; 6,400 positions 13.5 and 14.2; 4,096 11.1 and 14.0; 12,000 26 and 14.5); up to 16,384 positions both are left
 // with what the one launch above does not take.
-constexpr int kCountThreads = 1024;
-constexpr int kCountIds = 65536;             // IDs per part: 128 KiB of 16-bit counters
-constexpr int kCountTile = 128;              // IDs per block of k_ids_scan
-constexpr int kCountTilesMax = kCountMaxVocab / kCountTile;
 static_assert(kCountTilesMax % kBlock == 0, "tiles per thread in the scan of k_ids_emit");
 static_assert(kCountMaxM < 65536, "16-bit prefixes");
 
@@ -1418,11 +1438,10 @@ __global__ __launch_bounds__(kBlock) void k_ids_emit(
 bool unique_by_count(Ctx* c, const int* ids, int n, int fix_key, int* uniq, int* inverse, int* counts, int* u_out,
                      hipStream_t s, bool prospect, int first_step)
 {
+    if (!counting_takes(c, n)) return false;
     const int64_t N = c->cfg.vocab_n;
-    if (!c->cnt_table || n < kCountMinM || n > kCountMaxM || N > kCountMaxVocab) return false;
     const int pitch = (int)((N + kCountTile - 1) / kCountTile * kCountTile);
     const int rows = (n + kCountThreads - 1) / kCountThreads;
-    if ((int64_t)rows * pitch / 2 > kCountMaxWords) return false;
     const int parts = (pitch + kCountIds - 1) / kCountIds, T = pitch / kCountTile;
     const size_t lds = (size_t)(pitch < kCountIds ? pitch : kCountIds) * 2;
     ensure_dynamic_lds<k_ids_count>(kCountIds * 2);

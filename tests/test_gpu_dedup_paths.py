@@ -226,3 +226,13 @@ def test_one_launch_padding_and_bad_ids(m, n, pad):
 @pytest.mark.parametrize("kind", ["one", "runs"])
 def test_one_launch_of_equal_neighbours(m, n, kind):
     check_dedup_window(m, n, kind, m_last=m - 2)
+
+
+# Where the one-launch dedup goes from IDs to numbers in a bitmap in small batches, first step and later ones, and where later
+# steps are left to the counting dedup: either side of every line, the last step on another side than those before it
+@pytest.mark.parametrize("m,n,m_last", [(2048, 16_384, 1000), (2048, 16_385, 2047), (2049, 16_385, 2048), (2048, 32_769, 513), (4096, 32_768, 4095),
+                                        (4097, 32_769, 4096), (8193, 40_960, 8192), (8193, 40_961, 8192), (16_384, 40_960, 16_383),
+                                        (16_384, 40_961, 16_383), (16_384, 131_072, 12_288), (12_288, 131_073, 9000)])
+@pytest.mark.parametrize("kind", ["popular", "one"])
+def test_one_launch_lines(m, n, m_last, kind):
+    check_dedup_window(m, n, kind, m_last=m_last)
