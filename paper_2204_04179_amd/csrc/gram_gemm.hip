@@ -1377,18 +1377,28 @@ void transpose_weight(Ctx* c, const void* W, int rows, int cols, void* Wt, hipSt
 
 static bool takes_mid_kernel(int64_t a_rows, int k, int n_out, int epi);
 
-// Batches that give the 256x256 kernel a tile for every CU (and a K that fits its slabs) take it, but for
-// short K where more than a third of its columns lies behind the matrix: subtracting, 33,000 rows (whole call with the
-// weight gradient, 256x256 / mid-sized kernel) 96 x 264 45.7 / 39.9 us, 160 x 264 49.8 / 47.8, 96 x 400 52.5 / 50.8, 160 x 400
-// 60.6 / 63.0, 96 x 512 60.2 / 61.8;
+// Up to K = 160 tiles of 256 columns lose to tiles of 64 where the latter span at most half of the columns (widths to 128) or,
+// in batches that are not too large, 5/8 of them (257 to 320).  Whole content-encoder batch in us, 256 x 256 / mid-sized kernel,
+// subtracting: 66,000 rows K = 96 width 64 44.1 / 34.4, 128 48.7 / 41.3, 168 51.2 / 49.9; 400,000 rows 173 / 127, 300 / 288 and 308 / 345;
+// 33,000 rows K = 160 width 264 50.5 / 48.7, 336 55.7 / 58.9; 100,000 rows K = 128 width 264 105.8 / 99.1, K = 160 136.8 / 142.3;
+// 200,000 rows K = 64 width 304 223.6 / 230.7.  Two-layer backward (the rectified form): 66,000 rows K = 96 hidden width 64 91.4 / 74.4,
+// 264 126.2 / 122.1; 400,000 rows 332 / 263 and 746 / 754.
+static bool narrow_short_k(int64_t rows_max, int n_out, int k)
+{
+    if (k > 160) return false;
+    const int64_t tiles64 = ((int64_t)n_out + 63) / 64, span64 = ((int64_t)n_out + TN - 1) / TN * (TN / 64);
+    return 2 * tiles64 <= span64 || (8 * tiles64 <= 5 * span64 && rows_max <= (k <= 128 ? 131072 : 49152));
+}
+
+// Batches that give the 256x256 kernel a tile for every CU (and a K that fits its slabs) take it, but for narrow ones
+// of short K (not in the plain form, whose 256-row kernel stores the positions too);
 // the rest take k_encode_mid or, where that does not apply, the 64-row kernel, which addresses its operands
 // through plain pointers and therefore also serves the epilogue modes when A lies beyond 4 GiB.
 static bool takes_big_kernel(const Ctx* c, int64_t rows_max, int n_out, int k, int64_t a_rows, int epi)
 {
     const int64_t tile_bound = ((rows_max + TM - 1) / TM) * ((n_out + TN - 1) / TN);
     if (epi != kEpiPlain && a_rows * k * 2 >= kBufferWindow) return false;
-    if (k <= 160 && 3 * (int64_t)n_out < 2 * ((n_out + TN - 1) / TN) * TN && epi != kEpiPlain && takes_mid_kernel(a_rows, k, n_out, epi))
-        return false;
+    if (epi != kEpiPlain && narrow_short_k(rows_max, n_out, k) && takes_mid_kernel(a_rows, k, n_out, epi)) return false;
     return tile_bound >= c->num_cus && k % 32 == 0 && n_out < (1 << 22);     // (32-bit offsets within a tile of C)
 }
 

@@ -83,7 +83,7 @@ def test_two_layer_backward(k, dh, d):
     g.close()
 
 
-# (up to K = 160, widths up to 336 leave more than a third of the second column tile empty and go to the mid-sized kernel)
+# (up to K = 160, widths from 257 to 320 go to the mid-sized kernel)
 @pytest.mark.parametrize("k,d", [(32, 504), (96, 504), (128, 504), (160, 264), (160, 336), (160, 344), (192, 264)])
 def test_subtracting(k, d):
     import torch
