@@ -961,7 +961,7 @@ __device__ __forceinline__ void gemm_nt_tile(
         __builtin_amdgcn_sched_barrier(0);                                                          \
         if (epi_subtracts(EPI) && (SL) == last) {                                                   \
             wait_loads<0>();                                                                        \
-            GRAM_AUX(0)                                                                             \
+            if (BDIRECT) { GRAM_AUX(0) }                                                            \
         } else {                                                                                    \
             GRAM_LOAD_B((SL) + 2)                                                                   \
             GRAM_LOAD_A(0, (SL) + 2)                                                                \
@@ -973,7 +973,9 @@ __device__ __forceinline__ void gemm_nt_tile(
         segment_barrier();                                                                          \
     }
     // (subtracting) the targets of the epilogue's first round are requested ahead of the last products, behind the wait for
-    // whatever still lands in the stages: these are loads of the compiler's, which no count of the kernel's may include
+    // whatever still lands in the stages: these are loads of the compiler's, which no count of the kernel's may include.
+    // (With a K-contiguous B, whose fragments take more addresses, four registers spilled for it: 32,768 x 1024 x 1020 218.0 us with
+    // the weight gradient, 215.5 without either; 33,000 x 64 x 508 61.4 and 62.7.)
     f32x4_ av[epi_subtracts(EPI) ? RPW : 1];
 #define GRAM_AUX(I)                                                                                 \
     _Pragma("unroll") for (int u = 0; u < (epi_subtracts(EPI) ? RPW : 0); ++u) {                    \
@@ -1154,7 +1156,7 @@ __device__ __forceinline__ void gemm_nt_tile(
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
             const int row0 = m0 + (cr0 >> 5) * (MI * 32) + i * 32 + (cr0 & 31);           // + u
-            if (i > 0) { GRAM_AUX(i) }
+            if (i > 0 || !BDIRECT) { GRAM_AUX(i) }
             unsigned char* stage = smem + (i & 1) * kScatterTileB;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {

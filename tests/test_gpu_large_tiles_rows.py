@@ -84,3 +84,29 @@ def test_rectified_and_gated(n):
     for lo, hi in ((n * DH * 2, at[1]), (at[1] + n * DH * 2, at[3]), (at[3] + n * d * 2, work.numel())):
         assert bool((work[lo:hi] == 0x5A).all())
     g.close()
+
+
+# widths that are no multiple of 8: the weights are read from a transposed copy
+@pytest.mark.parametrize("n", [32_769, 32_895, 49_153, 49_407])
+@pytest.mark.parametrize("k,d", [(32, 508), (64, 508), (96, 508), (256, 300)])
+def test_subtracting_from_a_transposed_copy(n, k, d):
+    import torch
+    from paper_2204_04179_amd import gram
+    torch.manual_seed(n + k)
+    X = torch.randn(N, k, device="cuda", dtype=torch.bfloat16)
+    W = (torch.randn(k, d, device="cuda") * k ** -0.5).to(torch.bfloat16)
+    ids = torch.randperm(N, device="cuda")[:n].to(torch.int32)
+    ids[n // 2] = ids[n - 1] = 0
+    Ht, R, dW = torch.randn(n, d, device="cuda"), torch.full((n + 300, d), float("nan"), device="cuda"), torch.empty(k, d, device="cuda")
+    loss = torch.zeros(1, dtype=torch.float64, device="cuda")
+    g = gram.Gram(gram.make_config(N, k, d, n, 1, 0, 0, gram.BF16))
+    g.pseudo_loss_grad(X, W, ids, Ht, n, R[:n], dW, loss_dev=loss)
+    x = X[ids.long()].double()
+    x[ids == 0] = 0
+    want = x @ W.double() - Ht.double()
+    want[ids == 0] = 0
+    _close(R[:n], want, 2e-6)
+    assert bool((R[:n][ids == 0] == 0).all()) and bool(R[n:].isnan().all())
+    half = 0.5 * float((R[:n].double() ** 2).sum())
+    assert abs(float(loss) - half) <= 1e-9 * half
+    g.close()
