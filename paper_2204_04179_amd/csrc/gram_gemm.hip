@@ -1147,6 +1147,7 @@ __device__ __forceinline__ void gemm_nt_tile(
                 }
         }
     } else {
+        static_assert(epi_subtracts(EPI), "what the branches above leave");
         // Staged like the fused gather's epilogue, 64 rows at a time: a wave then loads and stores whole row
         // pieces, 4 columns per lane.
         const int col = n0 + lane * 4;
@@ -1174,13 +1175,12 @@ __device__ __forceinline__ void gemm_nt_tile(
                 for (int k = 0; k < 4; ++k) v[k] = epi_value<EPI>(v[k], av[u][k], zero);
                 if (row0 + u < M && col_ok) {
 #pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        if (epi_subtracts(EPI)) sq += (double)v[k] * v[k];
+                    for (int k = 0; k < 4; ++k) sq += (double)v[k] * v[k];
                     epi_store4<EPI>(C, (int64_t)(row0 + u) * ldc + col, v);
                 }
             }
         }
-        if (epi_subtracts(EPI) && loss_part) {
+        if (loss_part) {
             __syncthreads();
             block_sum_double(sq, NW * 64, reinterpret_cast<double*>(smem), loss_part);
         }
@@ -1583,7 +1583,7 @@ constexpr size_t WSMEM = 2 * (size_t)WSTAGEB;
 constexpr int kNonTemporal = 2;              // cache policy bits of a buffer store (nt)
 constexpr int kWgradWaves = 8;
 
-// NW = waves per block: 4 (128x128 each) or 8 (128x64 each, two per SIMD).
+// 8 waves per block (128x64 each, two per SIMD).
 // EXPORT: the end of a window also copies the buffer rows out in ascending-ID order
 // (gram_flush); this kernel has every row of G in registers anyway, so it writes row s to
 // G_total[rank_of_slot[s]] (rank_of_slot NULL: the buffer is in that order already) and the
@@ -1604,8 +1604,8 @@ struct WgradExport {
 };
 // GB: the rows are bf16 already (what an earlier contraction stored rounded); only with WIDE, what a descriptor can
 // address takes k_wgrad_rows_bf16.
-template <int NW, bool WIDE = false, bool EXPORT = false, bool GB = false>
-__global__ __launch_bounds__(NW * 64) void k_wgrad_tn_bf16(
+template <bool WIDE = false, bool EXPORT = false, bool GB = false>
+__global__ __launch_bounds__(kWgradWaves * 64) void k_wgrad_tn_bf16(
     const uint16_t* __restrict__ X, uint32_t x_bytes, const int* __restrict__ id_of_slot,
     const float* __restrict__ G, uint32_t g_bytes, const int* __restrict__ rows_dev, int d_in, int d,
     int pad_id, int splits, float* __restrict__ partial, int row_begin, int row_end, WgradExport ex)
@@ -1614,7 +1614,7 @@ __global__ __launch_bounds__(NW * 64) void k_wgrad_tn_bf16(
     if (EXPORT && ex.meta_blocks > 0 && blockIdx.x >= gridDim.x - ex.meta_blocks) {
         const int n_ = *rows_dev;
         const int mb = blockIdx.x - (gridDim.x - ex.meta_blocks);
-        for (int r = mb * (NW * 64) + threadIdx.x; r < n_; r += ex.meta_blocks * (NW * 64))
+        for (int r = mb * (kWgradWaves * 64) + threadIdx.x; r < n_; r += ex.meta_blocks * (kWgradWaves * 64))
             flush_meta_row(r, id_of_slot, nullptr, ex.cnt_of_slot, ex.slot_of, ex.uniq_total, ex.counts_total, nullptr);
         if (mb == 0 && threadIdx.x == 0) {
             if (ex.u_total_dev) *ex.u_total_dev = n_;
@@ -1628,12 +1628,13 @@ __global__ __launch_bounds__(NW * 64) void k_wgrad_tn_bf16(
     const int i0 = ((q % tiles) / tiles_c) * 256, c0 = ((q % tiles) % tiles_c) * 256;
     if (z >= splits) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    constexpr int NT = NW == 4 ? 4 : 2;          // 32-column MFMA tiles per wave
-    constexpr int RW = 32 / NW;                  // buffer rows of a slab this wave loads
+    static_assert(!GB || WIDE, "bf16 rows that a descriptor can address have a kernel of their own");
+    constexpr int NT = 2;                        // 32-column MFMA tiles per wave
+    constexpr int RW = WK / kWgradWaves;         // buffer rows of a slab this wave loads
     // two register sets for loads in flight: a load has two slabs of MFMAs to land (246 VGPRs
     // with 8 waves, so two waves per SIMD still fit)
     constexpr int SETS = 2;
-    const int wm = NW == 4 ? wave >> 1 : wave >> 2, wn = NW == 4 ? wave & 1 : wave & 3;
+    const int wm = wave >> 2, wn = wave & 3;
 
     // buffer rows [row_begin, U) take part (row_end clips U: the chunked call); slabs stay aligned
     // to multiples of WK rows, rows outside the range are loaded as zeros
@@ -1759,14 +1760,9 @@ __global__ __launch_bounds__(NW * 64) void k_wgrad_tn_bf16(
             const int slot = sb_ + a_row + 2 * t;                                                   \
             const int col = c0 + ((a_pos ^ ((slot & 3) << 2)) * 8);                                 \
             const bool okg = col < d && slot < U && slot >= row_begin;                              \
-            if (WIDE) {                                                                             \
-                v4i32 v_ = {0, 0, 0, 0};                                                            \
-                if (okg) v_ = *reinterpret_cast<const v4i32*>(reinterpret_cast<const uint16_t*>(G) + (int64_t)slot * d + col); \
-                rg[(SET) % SETS][t] = v_;                                                           \
-            } else {                                                                                \
-                const uint32_t off = okg ? (uint32_t)(((int64_t)slot * d + col) * 2) : kOutOfRange; \
-                rg[(SET) % SETS][t] = __builtin_amdgcn_raw_buffer_load_b128(rsG, off, 0, 0);        \
-            }                                                                                       \
+            v4i32 v_ = {0, 0, 0, 0};                                                                \
+            if (okg) v_ = *reinterpret_cast<const v4i32*>(reinterpret_cast<const uint16_t*>(G) + (int64_t)slot * d + col); \
+            rg[(SET) % SETS][t] = v_;                                                               \
         }                                                                                           \
         if (!GB) _Pragma("unroll") for (int t = 0; t < RW; ++t) {                                   \
             const int slot = sb_ + wave * RW + t;                                                    \
@@ -2402,7 +2398,7 @@ bool encoder_wgrad(Ctx* c, const void* X, float* dW, hipStream_t s, int64_t firs
                             s, static_cast<const uint16_t*>(X), (uint32_t)x_bytes, ids, rows, (uint32_t)g_bytes,
                             rows_dev, d_in, d, pad_id, S, out, row_begin, row_end, add_here, ex);
             } else {
-                constexpr auto kern = k_wgrad_tn_bf16<kWgradWaves, false, true>;
+                constexpr auto kern = k_wgrad_tn_bf16<false, true>;
                 ensure_dynamic_lds<kern>((int)WSMEM);
                 launch_smem(c, KID_WGRAD_BF16, kern, dim3((unsigned)(tiles * S + ex.meta_blocks)), dim3(kWgradWaves * 64),
                             WSMEM, s, static_cast<const uint16_t*>(X), (uint32_t)x_bytes, ids, rows, (uint32_t)g_bytes,
@@ -2429,8 +2425,8 @@ bool encoder_wgrad(Ctx* c, const void* X, float* dW, hipStream_t s, int64_t firs
             };
 #define GRAM_GO(KID, XB, GBYTES, ...) { ensure_dynamic_lds<__VA_ARGS__>((int)WSMEM); go(__VA_ARGS__, KID, XB, GBYTES); }
             // (the descriptors of the WIDE variant are not used)
-            if (wide && gb) GRAM_GO(KID_WGRAD_BF16_WIDE, 0, 0, k_wgrad_tn_bf16<kWgradWaves, true, false, true>)
-            else if (wide) GRAM_GO(KID_WGRAD_BF16_WIDE, 0, 0, k_wgrad_tn_bf16<kWgradWaves, true>)
+            if (wide && gb) GRAM_GO(KID_WGRAD_BF16_WIDE, 0, 0, k_wgrad_tn_bf16<true, false, true>)
+            else if (wide) GRAM_GO(KID_WGRAD_BF16_WIDE, 0, 0, k_wgrad_tn_bf16<true>)
             else if (gb) {
                 auto rows_go = [&](auto kern) {
                     launch_smem(c, KID_WGRAD_BF16, kern, dim3((unsigned)(tiles * S)), dim3(kWgradWaves * 64), kPairLds, s,
@@ -2442,7 +2438,7 @@ bool encoder_wgrad(Ctx* c, const void* X, float* dW, hipStream_t s, int64_t firs
                 if (ids) rows_go(k_wgrad_rows_bf16<true>);
                 else rows_go(k_wgrad_rows_bf16<false>);
             }
-            else GRAM_GO(KID_WGRAD_BF16, x_bytes, g_bytes, k_wgrad_tn_bf16<kWgradWaves, false>)
+            else GRAM_GO(KID_WGRAD_BF16, x_bytes, g_bytes, k_wgrad_tn_bf16<false>)
 #undef GRAM_GO
         }
     } else {
