@@ -1,6 +1,6 @@
-"""The forward of small and mid-sized batches (tiles of 64 x 64, 128 x 64 and 128 x 128, K cut between wave
-groups) against a float64 product, at the item counts and widths where tiles, slabs of 64 and the number
-of groups end, and where the tile shape changes.  Bound: float32 sums of K products of bf16 values, a few
+"""The forward of small and mid-sized batches (tiles of 64 x 64 and 128 x 64, K cut between two wave groups; tiles of 128 x 128
+for long K) and of large ones (tiles of 256 x 256) against a float64 product, at the item counts and widths where tiles, slabs
+of 64 and the number of groups end, and where the tile shape changes.  Bound: float32 sums of K products of bf16 values, a few
 1e-7 of the norm; bf16 results are rounded once (2^-9 per element)."""
 import numpy as np
 import pytest
@@ -137,7 +137,7 @@ def test_large_subtracting_tiles_cut_at_the_end(items):
 
 
 # lists trimmed to the items, and hidden activations that end (or turn into NaN) behind their rows: item counts
-# inside a tile, in each of the three tile shapes
+# inside a tile, in the tiles of 64 columns (those of 128 x 128: below)
 @pytest.mark.parametrize("items,m,dh", [(70, 900, 136), (641, 8000, 520), (2500, 20_000, 520)])
 def test_lists_and_activations_that_end_with_the_items(items, m, dh):
     import torch
@@ -250,4 +250,43 @@ def test_row_tile_chosen_on_the_device(items, m):
     err = (E[:items].double() - want).norm(dim=1) / want.norm(dim=1).clamp(min=1e-30)
     assert float(err.max()) < 2e-6
     assert bool(torch.isnan(E[items:]).all()) and torch.equal(H, E[inverse.long()])
+    g.close()
+
+
+# 128 x 128 tiles (K above 256 and more than 640 tiles of 64 x 64 by the host's guess of the items, here 0.6 of the rows there is
+# room for) with far fewer items than that, inside and around the edges of a tile: lists and activations that end with the items,
+# nothing stored behind them
+@pytest.mark.parametrize("items", [1, 127, 128, 129, 2500, 19_999])
+def test_square_tiles_with_few_items(items):
+    import torch
+    from paper_2204_04179_amd import gram
+    torch.manual_seed(items)
+    n, m, k, dh, d = 20_000, 51_200, 264, 776, 392
+    guess = min(m, n) * 3 // 5
+    assert n <= m < 8 * n and all(kk > 256 and (guess + 63) // 64 * ((c + 63) // 64) * 2 > 5 * 256 for kk, c in ((k, dh), (dh, d)))
+    X = torch.randn(n, k, device="cuda", dtype=torch.bfloat16)
+    W1 = (torch.randn(k, dh, device="cuda") * k ** -0.5).to(torch.bfloat16)
+    W2 = (torch.randn(dh, d, device="cuda") * dh ** -0.5).to(torch.bfloat16)
+    pool = torch.randperm(n, device="cuda")[:items].to(torch.int32)
+    if items > 2:
+        pool[0] = 0
+    ids = pool[torch.arange(m, device="cuda") % items]
+    items = int(torch.unique(ids).numel())
+    g = gram.Gram(gram.make_config(n, k, d, m, 1, 0, 0, gram.BF16, 0, dh))
+    uniq, counts = (torch.empty(n, dtype=torch.int32, device="cuda") for _ in range(2))
+    inverse, u = torch.empty(m, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+    assert g.unique(ids, uniq, inverse, counts, u, want_host_u=True) == items
+    x = X[uniq[:items].long()].double()
+    x[uniq[:items] == 0] = 0
+    a = (x @ W1.double()).clamp(min=0)
+    for trimmed in (uniq, uniq[:items].clone()):
+        kept = torch.full((items + 300, dh), float("nan"), device="cuda", dtype=torch.bfloat16)
+        E, H = torch.full((n, d), float("nan"), device="cuda"), torch.full((m, d), float("nan"), device="cuda")
+        g.mlp_encode_gather(X, W1, W2, trimmed, inverse if trimmed is uniq else inverse.clone(), u, m, kept[:items], E, H)
+        assert bool(torch.isnan(kept[items:]).all()) and bool(torch.isnan(E[items:]).all())
+        A1 = kept[:items]
+        assert float((A1.double() - a).norm(dim=1).max()) <= 3e-3 * float(a.norm(dim=1).max())
+        want = A1.double() @ W2.double()
+        assert float((E[:items].double() - want).norm(dim=1).max()) <= 2e-6 * float(want.norm(dim=1).max())
+        assert torch.equal(H, E[inverse.long()])
     g.close()

@@ -64,3 +64,15 @@ def test_the_kernel_uses_these_functions():
     assert "uniq[jj]" in body and "zero_ids[jj]" in body and "jj = mid_list_entry(" in body
     assert body.count("mid_row_offset(") == 1 and body.count("mid_slab_offset(") == 1
     assert "rows_max" not in body          # the only bound is the number of items on the device
+
+
+def test_the_kernel_of_square_tiles_uses_them_too():
+    with open(os.path.join(ROOT, "paper_2204_04179_amd", "csrc", "gram_gemm.hip")) as f:
+        src = f.read()
+    body = src[src.index("void k_encode_square("):src.index("// How many row tiles of 256 are taken whole.")]
+    assert "uniq[j]" in body and "zero_ids[j]" in body and "j = mid_list_entry(" in body
+    assert body.count("mid_row_offset(") == 1 and body.count("mid_slab_offset(") == 1
+    assert "rows_max" not in body
+    # every load's offset is the lane's own, which the range check covers
+    loads = [line for line in body.splitlines() if "load_to_lds(" in line]
+    assert len(loads) == 2 and all(", 0u, to_" in line for line in loads)
