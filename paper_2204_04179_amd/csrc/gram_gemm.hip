@@ -897,7 +897,7 @@ __device__ __forceinline__ void gemm_nt_tile(
     typedef __attribute__((address_space(3))) const bf16x8 lds_frag;
 #define GRAM_LOAD_A(H, SLAB)                                                                        \
     {                                                                                               \
-        const uint32_t k_ = (uint32_t)big_slab_start(SLAB, last, ktot) * 2u;                        \
+        const uint32_t k_ = (uint32_t)big_slab_start(WIDE && (SLAB) > last ? last : (SLAB), ktot) * 2u;\
         const uint32_t to_ = lds0 + ((SLAB) & 1) * TOPB;                                            \
         u32x4 rs_ = rsA;                                                                            \
         rs_.z = (SLAB) <= last ? rs_.z : 0u;                                                        \
@@ -911,7 +911,7 @@ __device__ __forceinline__ void gemm_nt_tile(
     {                                                                                               \
         u32x4 rs_ = rsB;                                                                            \
         rs_.z = (SLAB) <= last ? rs_.z : 0u;                                                        \
-        const uint32_t k_ = (uint32_t)big_slab_start(SLAB, last, ktot) * b_k_bytes;                 \
+        const uint32_t k_ = (uint32_t)big_slab_start(SLAB, ktot) * b_k_bytes;                       \
         const uint32_t to_ = lds_b + ((SLAB) & 1) * TOPB;                                           \
         _Pragma("unroll") for (int g_ = 0; g_ < 4; ++g_)                                            \
             load_to_lds(rs_, ob[BDIRECT ? g_ & 1 : g_], (SLAB) <= last ? (BDIRECT ? k_ + (uint32_t)(g_ >> 1) * (uint32_t)(8 * ldb) : k_) : 0u, to_ + g_ * 1024); \

@@ -37,12 +37,8 @@ GRAM_HD uint32_t mid_slab_offset(uint32_t row_offset, int k0, int xk, int d_in)
 // K = 32 both halves of the one slab hold the row.
 constexpr int kBigSlab = 64;
 
-// First element of a slab; slabs past the last are the last one again.
-GRAM_HD int big_slab_start(int slab, int last, int k)
-{
-    const int at = (slab < last ? slab : last) * kBigSlab - (k & 32);
-    return at > 0 ? at : 0;
-}
+// First element of slab 0 .. last (loads for slabs past the last fetch nothing, or the last one again).
+GRAM_HD int big_slab_start(int slab, int k) { return slab ? slab * kBigSlab - (k & 32) : 0; }
 
 // The part of a slab (of `size` elements of K each) that a load for part `part` fetches, counted from the slab's start.
 GRAM_HD int big_slab_part(int part, int size, int k) { return k < kBigSlab ? part & (32 / size - 1) : part; }

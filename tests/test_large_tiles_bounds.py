@@ -18,7 +18,7 @@ int main()
         const int slabs = (k + kBigSlab - 1) / kBigSlab;
         int next = 0;                                   // element of K that is to be multiplied next
         for (int slab = 0; slab < slabs + 3; ++slab) {  // and the slabs past the end
-            const int k0 = big_slab_start(slab, slabs - 1, k);
+            const int k0 = big_slab_start(slab < slabs ? slab : slabs - 1, k);
             for (int chunk = 0; chunk < 8; ++chunk) {   // chunks of 8 elements: rows of A, and of a K-contiguous B
                 const int at = k0 + big_slab_part(chunk, 8, k) * 8;
                 if (at < 0 || at + 8 > k) return std::printf("K %d slab %d chunk %d: element %d\n", k, slab, chunk, at), 1;
