@@ -1,6 +1,6 @@
-"""The 256-row contraction where K ends inside its slabs of 64: one slab, half a slab, odd and even numbers of slabs with and
-without half a slab behind them, in every form it stores.  Every row of the features that the batch does not name is NaN: what
-a slab fetches behind K belongs to such a row and must not reach a result.  Against float64.  Bounds: float32 sums of K products
+"""The 256-row contraction where K is no multiple of its slabs of 64: one slab, half a slab, odd and even numbers of slabs with and
+without half a slab before them, in every form it stores.  Every row of the features that the batch does not name is NaN: a slab
+that took a part of such a row for K would show.  Against float64.  Bounds: float32 sums of K products
 of bf16 values, a few 1e-7 of the norm; activations and misses that are stored as bf16 are rounded once (2^-9 per element, 6e-3
 of the norm of a product of two such)."""
 import pytest
