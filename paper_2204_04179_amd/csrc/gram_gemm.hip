@@ -510,9 +510,9 @@ __global__ __launch_bounds__(MidShape::kThreads, 4) void k_encode_mid(
 // (consecutive block indices are dealt round-robin to the 8 XCDs) and share the strip of A through that XCD's
 // L2.  Row j of A is A[row_ids[j]]; a row whose ID equals pad_id yields zeros.
 //
-// What bounds the loop is the matrix pipe, and with it the power the chip may draw: a slab takes 2,070 to 2,160
-// cycles, its MFMAs 2,112, at 1.4 GHz where nothing else runs between such launches and above 2 GHz where
-// memory-bound kernels do.  Three things got it there (before: slabs of 32 through registers, one barrier for
+// What bounds the loop is the matrix pipe, and with it the power the chip may draw: a slab takes 2,070 to 2,200
+// cycles, its MFMAs 2,112, at 1.4 to 1.65 GHz; the epilogues of the same launch run at 2.36 (clock reads per tile).
+// Three things got it there (before: slabs of 32 through registers, one barrier for
 // all waves per slab, 3,400 cycles per 64 of K at 2.0 GHz):
 //   - loads go straight to LDS (buffer_load ... lds), 1 KiB per wave-wide instruction: no registers, no LDS
 //     store instructions.  They are throughput bound (8 rows of 128 bytes: 50 cycles each from HBM, 26 from L2),
