@@ -783,9 +783,10 @@ __global__ __launch_bounds__(kSmallThreads) void k_emit_small(
 //                 vocabulary whose bitmap and its prefix fit (0.19 bytes per ID: 524,288), up to kOnceBitsM positions.
 // What bounds it is the LDS atomic per ID, about 30 to 45 cycles per wave (lanes of a wave that meet on a bank): nothing at
 // 6,400 positions, most of the time at 50,000.  Lanes that meet on one counter wait for each other, about 130 cycles where all 64
-// do: 16,384 positions of one item 20.1 us, so a thread whose four positions hold one ID counts them with one atomic: 10.0 us,
-// sorted IDs 13.2 -> 8.9, Zipf 1.2 10.0 as before.  (Finding such lanes by ballots costs every batch 0.3 to 1 us.)  What is left:
-// half of the positions one item in no order 13.2 us (11.6 in three launches), two items alone 13.7 (11.0).
+// do, so the first of a thread's four positions that hold one ID counts them all.  16,384 positions over 13,000 IDs, first step, an
+// atomic per position / four equal ones together / any equal ones together (three launches): one item 20.1 / 10.0 / 9.9 us (10.9),
+// half of them one item 13.7 / 13.1 / 10.2 (11.5), two items 14.3 / 13.6 / 10.4 (11.0), Zipf 1.2 10.0 / 9.9 / 9.4 (11.6), uniform 7.9 / 8.1 / 8.5
+// (12.7).  (Finding equal lanes of a wave by ballots costs every batch 0.3 to 1 us.)
 // Whole call, ranks or counting dedup / one launch: 1,000 positions 8.1 / 6.3 us, 6,400 over 13,000 IDs 13.3 / 6.6, 7,040 over 100,000 14.0 / 9.8, 12,000 over 300,000 26.7 / 12.9, 16,000 over 20,000
 // 12.3 / 10.6, 25,600 12.7 / 14.1 (padded histories 12.9 / 10.8), 51,200 13.8 / 23.3: the line lies at 16,384.
 // Small batches over large vocabularies go by the bitmap, which passes over IDs that do not occur sooner, in later steps all
@@ -1002,12 +1003,13 @@ __global__ __launch_bounds__(kOnceThreads) void k_ids_once(
         for (int r = 0; r < R; ++r) {
             const int g = tid + r * kOnceThreads;
             if (g < from || g >= to) continue;
-            if (k[r][0] == k[r][1] && k[r][0] == k[r][2] && k[r][0] == k[r][3]) {
-                atomicAdd(&cnt[k[r][0] >> 1], 4u << ((uint32_t)k[r][0] << 4 & 31u));
-                continue;
-            }
+            // (the first of a thread's equal keys adds for all of them)
+            const int k0 = k[r][0], k1 = k[r][1], k2 = k[r][2], k3 = k[r][3];
+            const bool e01 = k0 == k1, e02 = k0 == k2, e03 = k0 == k3, e12 = k1 == k2, e13 = k1 == k3, e23 = k2 == k3;
+            const uint32_t add[4] = {1u + e01 + e02 + e03, e01 ? 0u : 1u + e12 + e13, e02 || e12 ? 0u : 1u + e23, e03 || e13 || e23 ? 0u : 1u};
 #pragma unroll
-            for (int c = 0; c < 4; ++c) atomicAdd(&cnt[k[r][c] >> 1], 1u << ((uint32_t)k[r][c] << 4 & 31u));
+            for (int c = 0; c < 4; ++c)
+                if (add[c]) atomicAdd(&cnt[k[r][c] >> 1], add[c] << ((uint32_t)k[r][c] << 4 & 31u));
         }
     };
     count_groups(0, g_lo);

@@ -221,9 +221,9 @@ def test_one_launch_padding_and_bad_ids(m, n, pad):
     g.close()
 
 
-# Four neighbouring positions of one ID are counted at once
+# A thread's four neighbouring positions are counted together where they are equal: all of them, any of them
 @pytest.mark.parametrize("m,n", [(513, 8), (1001, 300_000), (8190, 20_000), (12_288, 300_000), (16_384, 20_000)])
-@pytest.mark.parametrize("kind", ["one", "runs"])
+@pytest.mark.parametrize("kind", ["one", "runs", "few"])
 def test_one_launch_of_equal_neighbours(m, n, kind):
     check_dedup_window(m, n, kind, m_last=m - 2)
 
